@@ -19,7 +19,7 @@ struct BatchLayerArgs {
     float *x;                     // residual stream [T, d], updated in place
     float *q;                     // rotated queries, row stride q_stride
     int q_stride;
-    uint16_t *xs;                 // split operand image (hi then lo), capacity 2 * T * max(d, H hd, ffn)
+    uint16_t *xs;                 // split operand image (hi then lo, each [K / 8][T][8]), capacity 2 * T * max(d, H hd, ffn)
     float *partial;               // split-K partial sums, capacity ks_max * T * max(nqkv, d, 2 ffn)
     float *ss_part;               // [2][T][d / 1024] partial sums of squares (attention norm, FFN norm)
     // cache

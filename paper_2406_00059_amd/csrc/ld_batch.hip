@@ -9,6 +9,7 @@
 //   k_red_add_split    : residual += sums; operand for the next product = split(residual * gain);
 //                        per-workgroup partial sums of squares of the new residual
 //   k_red_swiglu_split : silu(gate) * up from the gate/up sums -> split operand of the down projection
+// Operand images are laid out [part][K / 8][T][8] (octet_index), which the product reads in long runs.
 // RMSNorm: the gain is applied to the operand, the scalar 1/rms is applied to the finished sums by the
 // consumer, which adds the few partial sums of squares in fixed order (deterministic).
 #include "ld_batch.h"
@@ -49,8 +50,9 @@ __global__ __launch_bounds__(256) void k_red_add_split(const float *__restrict__
     const float f[4] = {v.x * gv.x, v.y * gv.y, v.z * gv.z, v.w * gv.w};
     uint2 hi, lo;
     split4(f, hi, lo);
-    *reinterpret_cast<uint2 *>(xs + (int64_t)t * d + n) = hi;
-    *reinterpret_cast<uint2 *>(xs + (int64_t)(T + t) * d + n) = lo;
+    bf16_t *dst = xs + octet_index(t, n, T);
+    *reinterpret_cast<uint2 *>(dst) = hi;
+    *reinterpret_cast<uint2 *>(dst + (int64_t)T * d) = lo;
     float ss = wave_sum(v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
     __syncthreads();
@@ -117,8 +119,9 @@ __global__ __launch_bounds__(256) void k_red_swiglu_split(const float *__restric
     for (int e = 0; e < 4; e++) act[e] = gg[e] / (1.0f + __expf(-gg[e])) * uu[e];
     uint2 hi, lo;
     split4(act, hi, lo);
-    *reinterpret_cast<uint2 *>(xs + (int64_t)t * F + n) = hi;
-    *reinterpret_cast<uint2 *>(xs + (int64_t)(T + t) * F + n) = lo;
+    bf16_t *dst = xs + octet_index(t, n, T);
+    *reinterpret_cast<uint2 *>(dst) = hi;
+    *reinterpret_cast<uint2 *>(dst + (int64_t)T * F) = lo;
 }
 
 }  // namespace
@@ -133,10 +136,10 @@ size_t batch_layer_xs_bytes(int T, int d, int H, int hd, int ffn) {
 }
 size_t batch_layer_partial_bytes(int T, int d, int H, int Hkv, int hd, int ffn) {
     const size_t nqkv = (size_t)(H + 2 * Hkv) * hd, nq = (size_t)H * hd;
-    size_t m = skinny_slabs(d) * nqkv;                       // q/k/v: K = d
-    m = std::max(m, (size_t)skinny_slabs((int)nq) * d);      // wo: K = nq
-    m = std::max(m, (size_t)skinny_slabs(d) * 2 * ffn);      // gate/up: K = d
-    m = std::max(m, (size_t)skinny_slabs(ffn) * d);          // down: K = ffn
+    size_t m = skinny_slabs(T, d) * nqkv;                       // q/k/v: K = d
+    m = std::max(m, (size_t)skinny_slabs(T, (int)nq) * d);      // wo: K = nq
+    m = std::max(m, (size_t)skinny_slabs(T, d) * 2 * ffn);      // gate/up: K = d
+    m = std::max(m, (size_t)skinny_slabs(T, ffn) * d);          // down: K = ffn
     return m * T * sizeof(float);
 }
 size_t batch_layer_ss_bytes(int T, int d) { return (size_t)2 * T * (d / RB) * sizeof(float); }
@@ -148,9 +151,9 @@ void launch_batch_prepare(const float *x, const float *g, int T, int d, uint16_t
 
 void launch_batch_qkv(const BatchLayerArgs &a, hipStream_t s) {
     const int nqkv = (a.H + 2 * a.Hkv) * a.hd, nssp = a.d / RB;
-    launch_gemm_skinny(a.wqkv, a.xs, a.xs + (size_t)a.T * a.d, a.T, nqkv, a.d, a.partial, s);
+    launch_gemm_skinny(a.wqkv, a.xs, a.xs + (size_t)a.T * a.d, a.T, nqkv, a.d, a.partial, s, true);
     const int n = a.T * (a.H + 2 * a.Hkv) * 64;
-    LD_LAUNCH(k_red_rope, dim3((n + 255) / 256), dim3(256), 0, s, a.partial, skinny_slabs(a.d), a.ss_part, nssp,
+    LD_LAUNCH(k_red_rope, dim3((n + 255) / 256), dim3(256), 0, s, a.partial, skinny_slabs(a.T, a.d), a.ss_part, nssp,
                        a.eps, a.d, a.T, a.H, a.Hkv, (const float2 *)a.cos_sin, a.pos, a.seq_slot, a.table, a.table_stride,
                        a.q, a.q_stride, a.pool);
 }
@@ -158,25 +161,25 @@ void launch_batch_qkv(const BatchLayerArgs &a, hipStream_t s) {
 void launch_batch_wo(const BatchLayerArgs &a, hipStream_t s) {
     // output projection; residual; operand + statistics of the FFN norm
     const int nq = a.H * a.hd, nssp = a.d / RB;
-    launch_gemm_skinny(a.wo, a.xs, a.xs + (size_t)a.T * nq, a.T, a.d, nq, a.partial, s);
-    LD_LAUNCH(k_red_add_split, dim3(nssp, a.T), dim3(256), 0, s, a.partial, skinny_slabs(nq), a.x, a.ffn_norm, a.T,
+    launch_gemm_skinny(a.wo, a.xs, a.xs + (size_t)a.T * nq, a.T, a.d, nq, a.partial, s, true);
+    LD_LAUNCH(k_red_add_split, dim3(nssp, a.T), dim3(256), 0, s, a.partial, skinny_slabs(a.T, nq), a.x, a.ffn_norm, a.T,
                        a.d, a.xs, a.ss_part + (size_t)a.T * nssp);
 }
 
 void launch_batch_gate_up(const BatchLayerArgs &a, hipStream_t s) {
     // gate/up; SwiGLU; operand of the down projection
     const int nssp = a.d / RB;
-    launch_gemm_skinny(a.wgate_up, a.xs, a.xs + (size_t)a.T * a.d, a.T, 2 * a.ffn, a.d, a.partial, s);
+    launch_gemm_skinny(a.wgate_up, a.xs, a.xs + (size_t)a.T * a.d, a.T, 2 * a.ffn, a.d, a.partial, s, true);
     const int64_t n = (int64_t)a.T * (a.ffn / 4);
-    LD_LAUNCH(k_red_swiglu_split, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.partial, skinny_slabs(a.d),
+    LD_LAUNCH(k_red_swiglu_split, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.partial, skinny_slabs(a.T, a.d),
                        a.ss_part + (size_t)a.T * nssp, nssp, a.eps, a.d, a.T, a.ffn, a.xs);
 }
 
 void launch_batch_down(const BatchLayerArgs &a, hipStream_t s) {
     // down; residual; operand + statistics of the next layer's attention norm
     const int nssp = a.d / RB;
-    launch_gemm_skinny(a.wdown, a.xs, a.xs + (size_t)a.T * a.ffn, a.T, a.d, a.ffn, a.partial, s);
-    LD_LAUNCH(k_red_add_split, dim3(nssp, a.T), dim3(256), 0, s, a.partial, skinny_slabs(a.ffn), a.x, a.next_norm,
+    launch_gemm_skinny(a.wdown, a.xs, a.xs + (size_t)a.T * a.ffn, a.T, a.d, a.ffn, a.partial, s, true);
+    LD_LAUNCH(k_red_add_split, dim3(nssp, a.T), dim3(256), 0, s, a.partial, skinny_slabs(a.T, a.ffn), a.x, a.next_norm,
                        a.T, a.d, a.xs, a.ss_part);
 }
 

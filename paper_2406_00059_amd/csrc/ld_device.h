@@ -36,6 +36,8 @@ __device__ __forceinline__ void store_split(bf16_t *__restrict__ hi, bf16_t *__r
     hi[idx] = (bf16_t)h;
     lo[idx] = (bf16_t)l;
 }
+// Index of entry (row t, column k) of an operand image of T rows laid out [K / 8][T][8].
+__device__ __forceinline__ int64_t octet_index(int t, int k, int T) { return ((int64_t)(k >> 3) * T + t) * 8 + (k & 7); }
 // Rotation of the pair (a, b) by the angle whose (cos, sin) is c, every product rounded: the kernels that rotate
 // a row's q and k heads must agree bit for bit.
 __device__ __forceinline__ float2 rope_rotate(float a, float b, float2 c) {

@@ -17,8 +17,10 @@ size_t gemm_split_bytes(int T, int K);
 size_t gemm_scratch_bytes(int T, int N, int K, int epi);
 
 // xs <- split(x * rsqrt(mean x^2 + eps) * g)  (g == nullptr: plain split), row by row:
-// hi = bf16(v), lo = bf16(v - hi), stored as two [T, K] bf16 matrices (hi first).
-void launch_norm_split(const float *x, const float *g, float eps, int T, int K, uint16_t *xs, hipStream_t s);
+// hi = bf16(v), lo = bf16(v - hi), stored as two [T, K] bf16 matrices (hi first); octets: each as [K / 8][T][8]
+// instead, the layout the small-batch kernel reads faster (gemm_takes_octets(T); launch_gemm has to be told).
+bool gemm_takes_octets(int T);
+void launch_norm_split(const float *x, const float *g, float eps, int T, int K, uint16_t *xs, hipStream_t s, bool octets = false);
 
 // y = epilogue(X W^T) with X given by its split image at the start of the scratch area xs
 // (gemm_scratch_bytes bytes); W bf16 [N, K] ([2N, K] for GEMM_SWIGLU).
@@ -40,17 +42,17 @@ void launch_norm_split(const float *x, const float *g, float eps, int T, int K, 
 // weight fragment into fp16 on its way to the matrix cores; same values either way, bit-equal results.
 struct GemmNext { const float *g; float eps; uint16_t *xs; const RopeKvArgs *rope = nullptr; };
 void launch_gemm(const uint16_t *W, uint16_t *xs, int T, int N, int K, int epi, float *y, hipStream_t s,
-                 const GemmNext *next = nullptr, int *f16_flag = nullptr, const uint16_t *W16 = nullptr);
+                 const GemmNext *next = nullptr, int *f16_flag = nullptr, const uint16_t *W16 = nullptr, bool octets = false);
 bool gemm_f16_rows(int T, int N, int K, int epi);
 // *flag (device memory) = 1 if the bf16 matrix W (n elements, a multiple of 8) holds a value beyond +-65504 or not a number.
 void launch_weight_range_check(const uint16_t *W, int64_t n, int *flag, hipStream_t s);
 // The same check, and out[n] = W as fp16 (exact where the flag stays clear, values below 2^-14 in magnitude aside).
 void launch_weight_to_f16(const uint16_t *W, int64_t n, uint16_t *out, int *flag, hipStream_t s);
 
-// Skinny product alone (T <= 32 rows, K a multiple of 128): partial[z][t][row] for the skinny_slabs(K)
-// 512-wide K slabs z; the caller adds the slabs in order.
-int skinny_slabs(int K);
+// Skinny product alone (T <= 64 rows, K a multiple of 128): partial[z][t][row] for the skinny_slabs(T, K) K slabs z;
+// the caller adds the slabs in order.  octets: the layout of the images, see launch_norm_split.
+int skinny_slabs(int T, int K);
 void launch_gemm_skinny(const uint16_t *W, const uint16_t *xhi, const uint16_t *xlo, int T, int n_rows, int K,
-                        float *partial, hipStream_t s);
+                        float *partial, hipStream_t s, bool octets);
 
 }  // namespace ld

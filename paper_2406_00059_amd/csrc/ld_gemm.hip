@@ -5,17 +5,11 @@
 // product carries ~16 significant bits of the activation instead of 8.  In the decode regime the
 // kernel is bound by the weight stream from HBM, where the second MFMA pass is free.
 //
-// Three kernels by row count, all with the token index on the MFMA row side (an accumulator register
-// then holds 32 consecutive output columns of one token and stores are 128-byte contiguous), all fed
-// by the (hi, lo) bf16 images of the activations, which k_norm_split writes in a pass of its own or a
-// producer writes directly (k_reduce_add_norm_split and the SwiGLU epilogues here, the attention kernels,
-// the fused reducers of ld_batch.hip):
-//  - k_gemm_skinny (2..48 rows): weight-stream bound; slab-resident, see its comment.
-//  - k_gemm_mfma (49..64 rows): W streamed from global memory straight into B-operand registers
-//    (lane (n = lane % 32, h = lane / 32) loads 16 bytes of row n; the contraction order over k is
-//    permuted so that the four loads of a 64-wide k-group give a row 128 contiguous bytes), X staged
-//    through padded LDS, loads issued one chunk ahead.
-//  - k_gemm_big (> 64 rows): MFMA-bound; both operands through LDS, see its comment.
+// Two kinds of kernel by row count, fed by the (hi, lo) bf16 images of the activations, which k_norm_split
+// writes in a pass of its own or a producer writes directly (k_reduce_add_norm_split and the SwiGLU epilogues
+// here, the attention kernels, the fused reducers of ld_batch.hip):
+//  - k_gemm_skinny (2..64 rows): weight-stream bound, see its comment.
+//  - k_gemm_dma / k_gemm_big (> 64 rows): MFMA-bound; both operands through LDS, see their comments.
 // Workgroups that share a W panel (same columns, different token tiles) are mapped to the same XCD so
 // that the panel is fetched into one L2 only.  Split-K partial sums are added in fixed slab order.
 #include "ld_gemm.h"
@@ -32,6 +26,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(2))) __fp16 fp16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;   // native 16-byte vector (keeps arrays of it in registers)
 
 constexpr float F16_LIMIT = 65504.f;   // largest finite fp16
@@ -47,8 +42,6 @@ __device__ __forceinline__ f16x8 bf16x8_to_f16x8(const __attribute__((ext_vector
 }
 
 constexpr int KC = 128;          // K granularity the launcher requires (largest chunk any variant stages)
-constexpr int XPAD = 8;          // bf16 elements of row padding in LDS
-constexpr int NW = 4;            // waves per workgroup
 
 // SwiGLU of one (gate, up) pair with the last product rounded to float, as a store to memory would: where the
 // value goes straight into the bf16 split, a product fused into the split's subtraction would change the low part.
@@ -72,39 +65,55 @@ __device__ __forceinline__ float4 scale4(const float4 &v, float rstd, const floa
     return make_float4(v.x * rstd * g.x, v.y * rstd * g.y, v.z * rstd * g.z, v.w * rstd * g.w);
 }
 
+// One workgroup per row.  ROW_REGS > 0: the row (at most 1024 * ROW_REGS long) is read once and kept in registers, all
+// loads in flight together.  OCT: the images are written as [K / 8][T][8] (see k_gemm_skinny), else row-major.
+template <int ROW_REGS, bool OCT>
 __global__ __launch_bounds__(256) void k_norm_split(const float *__restrict__ x, const float *__restrict__ g,
                                                     float eps, int K, bf16_t *__restrict__ hi,
                                                     bf16_t *__restrict__ lo) {
     __shared__ float red[4];
     const int t = blockIdx.x;
     const float *row = x + (int64_t)t * K;
+    float4 keep[ROW_REGS > 0 ? ROW_REGS : 1];
+    if constexpr (ROW_REGS > 0) {
+#pragma unroll
+        for (int u = 0; u < ROW_REGS; u++) {
+            const int i = threadIdx.x * 4 + u * 1024;
+            if (i < K) keep[u] = *reinterpret_cast<const float4 *>(row + i);
+        }
+    }
     float rstd = 1.f;
     if (g) {
         float ss = 0.f;
-        for (int i = threadIdx.x * 4; i < K; i += 1024) {
-            const float4 v = *reinterpret_cast<const float4 *>(row + i);
-            ss = add_squares(ss, v);
+        if constexpr (ROW_REGS > 0) {
+#pragma unroll
+            for (int u = 0; u < ROW_REGS; u++)
+                if (threadIdx.x * 4 + u * 1024 < K) ss = add_squares(ss, keep[u]);
+        } else {
+            for (int i = threadIdx.x * 4; i < K; i += 1024) ss = add_squares(ss, *reinterpret_cast<const float4 *>(row + i));
         }
         ss = wave_sum(ss);
         if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
         __syncthreads();
         rstd = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / K + eps);
     }
-    for (int i = threadIdx.x * 4; i < K; i += 1024) {
-        float4 v = *reinterpret_cast<const float4 *>(row + i);
-        if (g) {
-            const float4 gv = *reinterpret_cast<const float4 *>(g + i);
-            v = scale4(v, rstd, gv);
-        }
+    auto store = [&](int i, float4 v) {
+        if (g) v = scale4(v, rstd, *reinterpret_cast<const float4 *>(g + i));
         uint32_t l0, l1;
         const uint32_t h0 = split2_bf16(v.x, v.y, l0), h1 = split2_bf16(v.z, v.w, l1);
-        *reinterpret_cast<uint2 *>(hi + (int64_t)t * K + i) = make_uint2(h0, h1);
-        *reinterpret_cast<uint2 *>(lo + (int64_t)t * K + i) = make_uint2(l0, l1);
+        const int64_t at = OCT ? octet_index(t, i, gridDim.x) : (int64_t)t * K + i;
+        *reinterpret_cast<uint2 *>(hi + at) = make_uint2(h0, h1);
+        *reinterpret_cast<uint2 *>(lo + at) = make_uint2(l0, l1);
+    };
+    if constexpr (ROW_REGS > 0) {
+#pragma unroll
+        for (int u = 0; u < ROW_REGS; u++)
+            if (threadIdx.x * 4 + u * 1024 < K) store(threadIdx.x * 4 + u * 1024, keep[u]);
+    } else {
+        for (int i = threadIdx.x * 4; i < K; i += 1024) store(i, *reinterpret_cast<const float4 *>(row + i));
     }
 }
 
-// TT: token tiles of 32 rows per workgroup.  WC: 32-column tiles per wave.  KCH: K chunk staged in LDS.
-// A wave multiplies TT x WF accumulator tiles per k-step, WF = WC (x 2 for SwiGLU: gate and up rows).
 // The (hi, lo) images of n8 * 8 activations become one fp16 image in place of the high one (hi + lo is exact in
 // float32; one rounding to fp16).  *flag is set when a value does not fit into fp16.
 __global__ __launch_bounds__(256) void k_split_to_f16(bf16_t *__restrict__ hi, const bf16_t *__restrict__ lo, int64_t n8,
@@ -153,287 +162,172 @@ __global__ __launch_bounds__(256) void k_weight_to_f16(const bf16_t *__restrict_
     if (big) *flag = 1;
 }
 
-template <int TT, int WC, int KCH, int EPI>
-__global__ __launch_bounds__(256) void k_gemm_mfma(const bf16_t *__restrict__ W, const bf16_t *__restrict__ xhi,
-                                                   const bf16_t *__restrict__ xlo, int T, int N, int K,
-                                                   float *__restrict__ y, int n_ttiles, int ks,
-                                                   float *__restrict__ partial, bf16_t *__restrict__ hi_out,
-                                                   bf16_t *__restrict__ lo_out) {
-    constexpr int WR = (EPI == ld::GEMM_SWIGLU) ? 2 : 1;
-    constexpr int WF = WC * WR;                          // W fragments per wave per k-step
-    constexpr int TROWS = TT * 32;
-    constexpr int NT = 32 * WC * NW;                     // output columns per workgroup
-    constexpr int XLD = KCH + XPAD;                      // LDS row stride in elements
-    constexpr int XV = TROWS * (KCH / 8) * 2 / 256;      // 16-byte pieces per thread to stage one chunk (hi + lo)
-    constexpr int KG = KCH / 64;                         // 64-wide k-groups per chunk
-    __shared__ __attribute__((aligned(16))) bf16_t xs[2][TROWS][XLD];
+// Up to 64 rows (decode batches, short chunks): the weight stream is everything, so the kernel is built around never
+// interrupting it and around asking for it in long runs.  One workgroup of eight waves per CU stays for the whole
+// launch and owns a range of W rows and a slab of K (2048 wide, 1024 for more than 32 rows); its waves split the slab
+// and keep the (hi, lo) X fragments of their share in registers for good.  W arrives 16 rows at a time, each row's
+// whole slab (4 KB in a row) by one wave, copied straight into LDS (global_load_lds, non-temporal): 128 KB per CU are
+// in flight and no register waits for them.  The access shape is what the rate depends on: streaming the 7B gate/up
+// (down) matrix alone takes 28.7 (17.4) us in runs of 4 KB per wave, 31.6 (20.7) us with 512 bytes of two rows per
+// instruction and 32.7 (21.8) us with 128 bytes of eight.
+// Per 16-row tile: wait for the own copies, barrier, read fragments (lane = row), barrier, request the tile that takes
+// this one's place, add up the tile before, multiply.  The sum over the eight waves goes through LDS in wave order; one partial sum per K slab goes to scratch and a reduction kernel adds the slabs in order (for
+// SwiGLU the gate and up rows are plain rows here and are paired by the reduce kernel).
+// LDS: piece p (16 bytes) of a row's slab sits in slot p ^ row: the 16 rows that a fragment read touches at one p then
+// lie in 16 different bank groups, and a lane of a copy may fetch any piece into its fixed slot.
+constexpr int SK_WAVES = 8;
+constexpr int sk_steps(int tt) { return tt > 2 ? 4 : 8; }                       // 32-wide k-steps of a wave, at most
+constexpr int sk_slab(int tt) { return SK_WAVES * sk_steps(tt) * 32; }          // K slab of a workgroup, at most
 
-    // XCD-aware decode of the linear block id: blocks b, b+8, b+16, ... run on the same XCD
-    const int b = blockIdx.x, xcd = b & 7, s = b >> 3;
-    const int kz = s % ks, tt_idx = (s / ks) % n_ttiles, nb = (s / (ks * n_ttiles)) * 8 + xcd;
-    const int n_nblocks = (N + NT - 1) / NT;
-    if (nb >= n_nblocks) return;
-    const int t0 = tt_idx * TROWS;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int l32 = lane & 31, half = lane >> 5;
-    const int n0 = nb * NT + wave * (32 * WC);
-
-    // W rows of this lane (clamped in range; out-of-range columns are never stored); fragment f = c * WR + r
-    const bf16_t *wrow[WF];
-#pragma unroll
-    for (int c = 0; c < WC; c++)
-#pragma unroll
-        for (int r = 0; r < WR; r++) {
-            const int n = min(n0 + c * 32 + l32, N - 1);
-            wrow[c * WR + r] = W + ((int64_t)r * N + n) * K + half * 32;
-        }
-    // staging assignment: piece v -> (part, row, col16)
-    int st_row[XV], st_c16[XV], st_part[XV];
-    const bf16_t *st_src[XV];
-#pragma unroll
-    for (int v = 0; v < XV; v++) {
-        const int idx = threadIdx.x + 256 * v;
-        st_part[v] = idx / (TROWS * (KCH / 8));
-        const int rem = idx % (TROWS * (KCH / 8));
-        st_row[v] = rem / (KCH / 8);
-        st_c16[v] = rem % (KCH / 8);
-        const int t = min(t0 + st_row[v], T - 1);        // rows past T are staged from row T-1 and never stored
-        st_src[v] = (st_part[v] ? xlo : xhi) + (int64_t)t * K + st_c16[v] * 8;
-    }
-
-    f32x16 acc[WF][TT];
-#pragma unroll
-    for (int f = 0; f < WF; f++)
-#pragma unroll
-        for (int tt = 0; tt < TT; tt++)
-#pragma unroll
-            for (int i = 0; i < 16; i++) acc[f][tt][i] = 0.f;
-
-    u32x4 wA[WF][KG * 4], wB[WF][KG * 4], xr[XV];
-    auto load_w = [&](u32x4 (&w)[WF][KG * 4], int kc) {
-#pragma unroll
-        for (int f = 0; f < WF; f++)
-#pragma unroll
-            for (int kg = 0; kg < KG; kg++)
-#pragma unroll
-                for (int j = 0; j < 4; j++)
-                    w[f][kg * 4 + j] = *reinterpret_cast<const u32x4 *>(wrow[f] + kc * KCH + kg * 64 + j * 8);
-    };
-    auto load_x = [&](u32x4 (&xv)[XV], int kc) {
-#pragma unroll
-        for (int v = 0; v < XV; v++) xv[v] = *reinterpret_cast<const u32x4 *>(st_src[v] + kc * KCH);
-    };
-    auto compute = [&](u32x4 (&w)[WF][KG * 4]) {
-#pragma unroll
-        for (int kg = 0; kg < KG; kg++)
-#pragma unroll
-            for (int j = 0; j < 4; j++) {
-                const int k = kg * 64 + half * 32 + j * 8;
-                bf16x8 ah[TT], al[TT];
-#pragma unroll
-                for (int tt = 0; tt < TT; tt++) {
-                    ah[tt] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(&xs[0][tt * 32 + l32][k]));
-                    al[tt] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(&xs[1][tt * 32 + l32][k]));
-                }
-                // all high parts, then all low parts: consecutive MFMAs never share an accumulator
-#pragma unroll
-                for (int f = 0; f < WF; f++) {
-                    const bf16x8 bw = __builtin_bit_cast(bf16x8, w[f][kg * 4 + j]);
-#pragma unroll
-                    for (int tt = 0; tt < TT; tt++)
-                        acc[f][tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[tt], bw, acc[f][tt], 0, 0, 0);
-                }
-#pragma unroll
-                for (int f = 0; f < WF; f++) {
-                    const bf16x8 bw = __builtin_bit_cast(bf16x8, w[f][kg * 4 + j]);
-#pragma unroll
-                    for (int tt = 0; tt < TT; tt++)
-                        acc[f][tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[tt], bw, acc[f][tt], 0, 0, 0);
-                }
-            }
-    };
-    auto stage = [&](const u32x4 (&xv)[XV]) {
-#pragma unroll
-        for (int v = 0; v < XV; v++)
-            *reinterpret_cast<u32x4 *>(&xs[st_part[v]][st_row[v]][st_c16[v] * 8]) = xv[v];
-    };
-
-    // this workgroup's K slab: chunks [c_begin, n_chunks) of K / KCH, split evenly over ks workgroups
-    const int c_begin = (int)((int64_t)kz * (K / KCH) / ks), n_chunks = (int)((int64_t)(kz + 1) * (K / KCH) / ks);
-    load_x(xr, c_begin);
-    load_w(wA, c_begin);
-    for (int kc = c_begin; kc < n_chunks; kc += 2) {
-        lds_barrier();                 // everyone finished reading the previous chunk from LDS
-        stage(xr);
-        lds_barrier();
-        if (kc + 1 < n_chunks) { load_x(xr, kc + 1); load_w(wB, kc + 1); }
-        compute(wA);
-        if (kc + 1 < n_chunks) {
-            lds_barrier();
-            stage(xr);
-            lds_barrier();
-            if (kc + 2 < n_chunks) { load_x(xr, kc + 2); load_w(wA, kc + 2); }
-            compute(wB);
-        }
-    }
-
-    // accumulator element i of lane (l32, half): token t0 + tt*32 + 8*(i/4) + 4*half + i%4, column n0 + 32c + l32
-#pragma unroll
-    for (int c = 0; c < WC; c++) {
-        const int n = n0 + c * 32 + l32;
-        if (n >= N) continue;
-#pragma unroll
-        for (int tt = 0; tt < TT; tt++)
-#pragma unroll
-            for (int i = 0; i < 16; i++) {
-                const int t = t0 + tt * 32 + 8 * (i / 4) + 4 * half + (i % 4);
-                if (t >= T) continue;
-                if (ks > 1) {
-                    // split-K: raw partial sums, [kz][t][r * N + n]; a second kernel adds the slabs in fixed order
-#pragma unroll
-                    for (int r = 0; r < WR; r++)
-                        partial[((int64_t)kz * T + t) * (WR * N) + r * N + n] = acc[c * WR + r][tt][i];
-                } else {
-                    float *dst = y + (int64_t)t * N + n;
-                    if constexpr (EPI == ld::GEMM_STORE) *dst = acc[c][tt][i];
-                    else if constexpr (EPI == ld::GEMM_ADD) *dst += acc[c][tt][i];
-                    else {
-                        const float a = swiglu(acc[c * WR][tt][i], acc[c * WR + 1][tt][i]);
-                        if (hi_out) store_split(hi_out, lo_out, (int64_t)t * N + n, a);
-                        else *dst = a;
-                    }
-                }
-            }
-    }
+// LDS accesses of this kernel are written in assembly (reads with their wait in the same block): the compiler cannot
+// tell which copies in flight they have nothing to do with and would wait for all of them first.
+__device__ __forceinline__ uint32_t lds_address(const void *p) {
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)p;
+}
+__device__ __forceinline__ void ds_read_b128xn(u32x4 (&w)[8], const uint32_t (&a)[8]) {
+    asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
+                 "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(w[4]), "=&v"(w[5]), "=&v"(w[6]), "=&v"(w[7])
+                 : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7])
+                 : "memory");
+}
+__device__ __forceinline__ void ds_read_b128xn(u32x4 (&w)[4], const uint32_t (&a)[4]) {
+    asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3])
+                 : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3])
+                 : "memory");
 }
 
-// Up to 32 rows (decode batches; up to 48 in two groups of rows): the weight stream is everything, so a workgroup
-// takes 128 rows of W and a 512-wide K slab, requests its whole W slab at once (32 independent 16-byte loads per
-// lane), stages the matching X slab (hi and lo) in LDS meanwhile, and multiplies as the loads land: one memory
-// round trip per workgroup, no barrier inside the product loop.  Every (slab, row) partial sum goes to scratch and
-// a reduction kernel adds the slabs in fixed order (for SwiGLU the gate and up rows are plain rows here and are
-// paired by the reduce kernel).
-//
-// W is fetched in the layout the memory system likes, not in the one the matrix cores want: a load instruction
-// covers 8 rows x 128 contiguous bytes (8 lanes per row), so every 128-byte line is touched by one instruction
-// (with lane = row, the B-operand layout, an instruction touches 32 lines and each line takes part in eight
-// instructions: 37.6 against 30.9 us for the loads alone of the 7B gate/up matrix).  Each 64-wide k-group then
-// passes through 4 KB of LDS private to the wave (written as fetched, read back with lane = row).
-// LDS: X slab [part][row][64 pieces of 16 bytes], piece c of row r in slot c ^ (r & 15) (rows are 1 KB apart, so
-// the 16 rows that a fragment read touches at one c land in 16 different bank groups without padding); per wave
-// 32 rows x 128 bytes for the W k-group, piece p of row r in slot p ^ ((r >> 1) & 7).  80 KB: two workgroups per CU.
-constexpr int SL = 512;   // K slab per workgroup
+// TT: 16-row tiles of X.  OCT: X comes as [part][K / 8][T][8] (the layout the producers of a decode batch write: a
+// fragment load is then four runs of 256 bytes instead of sixteen of 64, 2 us less per launch at 32 rows and 4 us at
+// 64), else row-major.  grid: ks * row groups, block b takes K slab b % ks of row group b / ks.
+template <int TT, bool OCT>
+__global__ __launch_bounds__(64 * SK_WAVES, 2) void k_gemm_skinny(const bf16_t *__restrict__ W, const bf16_t *__restrict__ xhi,
+                                                                  const bf16_t *__restrict__ xlo, int T, int n_rows, int K,
+                                                                  int ks, float *__restrict__ partial) {
+    constexpr int STEPS = sk_steps(TT), ROWB = sk_slab(TT) * 2;      // ROWB: bytes of LDS per row of a stage
+    constexpr int STAGE = 16 * ROWB, S = TT > 2 ? 3 : 2;             // 2 stages of 64 KB, or 3 of 32 KB
+    constexpr int IPR = ROWB / 1024, P = 2 * IPR;                    // copy instructions per row; per wave and stage
+    __shared__ __attribute__((aligned(1024))) char ring[S * STAGE];
+    __shared__ __attribute__((aligned(1024))) char red[2][SK_WAVES * TT * 1024];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, kg = lane >> 4;
+    const int kz = blockIdx.x % ks, grp = blockIdx.x / ks, n_grp = gridDim.x / ks;
+    // rows [row0, row1) of W, in units of four; the slab [k0, k0 + 32 steps) in units of 128; this wave's k-steps of it
+    const int64_t units = (n_rows + 3) / 4, n128 = K / 128;
+    const int row0 = (int)(units * grp / n_grp) * 4, row1 = min((int)(units * (grp + 1) / n_grp) * 4, n_rows);
+    const int k0 = (int)(n128 * kz / ks) * 128, steps = (int)((n128 * (kz + 1) / ks) * 128 - k0) / 32;
+    const int s0 = steps * wave / SK_WAVES, ns = steps * (wave + 1) / SK_WAVES - s0;      // ns <= STEPS
+    const int n_tiles = (row1 - row0 + 15) / 16;
+    const int last_piece = steps * 4 - 1;
+    const uint32_t red_base = lds_address(red), ring_base = lds_address(ring);
 
-// FULL: K is a multiple of the slab width, every slab is whole and every load unconditional.
-template <bool FULL>
-__global__ __launch_bounds__(256, 2) void k_gemm_skinny(const bf16_t *__restrict__ W, const bf16_t *__restrict__ xhi,
-                                                        const bf16_t *__restrict__ xlo, int T, int n_rows, int K,
-                                                        int ks, float *__restrict__ partial) {
-    __shared__ __attribute__((aligned(16))) char xs[2 * 32 * SL * 2];
-    __shared__ __attribute__((aligned(16))) char tp[NW][32 * 128];
-    const int b = blockIdx.x;
-    const int kz = b % ks, nb = b / ks;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int l32 = lane & 31, half = lane >> 5;
-    const int r8 = lane >> 3, p8 = lane & 7;
-    const int k0 = kz * SL;
-    const int slab = FULL ? SL : min(SL, K - k0);          // multiple of 128
-    const int n_kg = FULL ? 8 : slab / 64;
-    const int n = nb * 128 + wave * 32 + l32;
-
-    // X slab of a group of 32 rows: 64 rows of 1 KB (2 parts x 32), 16 per wave, one load instruction per row; lane
-    // l fills slot l of the row, so it fetches piece l ^ (row & 15).  Requested before W and staged while W is in flight.
-    u32x4 xv[16];
-    auto x_request = [&](int t0) {
+    auto request = [&](int tile) {
 #pragma unroll
-        for (int v = 0; v < 16; v++) {
-            const int prow = wave * 16 + v, part = prow >> 5, row = prow & 31;
-            int c = lane ^ (row & 15);
-            if (!FULL && c * 8 >= slab) c = 0;      // slots beyond a short slab are never read
-            const int t = min(t0 + row, T - 1);
-            xv[v] = *reinterpret_cast<const u32x4 *>((part ? xlo : xhi) + (int64_t)t * K + k0 + c * 8);
-        }
-    };
-    auto x_stage = [&]() {
+        for (int r = 0; r < 2; r++) {
+            const int tr = 2 * wave + r;                                     // this wave's rows of the tile
+            const int row = min(row0 + tile * 16 + tr, row1 - 1);            // past the range: the last row again
+            const bf16_t *src = W + (int64_t)row * K + k0;
 #pragma unroll
-        for (int v = 0; v < 16; v++) *reinterpret_cast<u32x4 *>(xs + (wave * 16 + v) * 1024 + lane * 16) = xv[v];
-    };
-    x_request(0);
-    __builtin_amdgcn_sched_barrier(0);     // X first: its waits then leave the W loads in flight
-    u32x4 w[32];
-#pragma unroll
-    for (int kg = 0; kg < 8; kg++) {
-        if (FULL || kg < n_kg) {
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const int row = min(nb * 128 + wave * 32 + i * 8 + r8, n_rows - 1);
-                w[kg * 4 + i] = __builtin_nontemporal_load(
-                    reinterpret_cast<const u32x4 *>(W + (int64_t)row * K + k0 + kg * 64 + p8 * 8));
+            for (int j = 0; j < IPR; j++) {
+                const int piece = min((j * 64 + lane) ^ tr, last_piece);
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + piece * 8),
+                                                 (__attribute__((address_space(3))) void *)(ring + (tile % S) * STAGE + tr * ROWB + j * 1024),
+                                                 16, 0, 2);
             }
         }
-    }
+    };
+    // X fragments: lane (row l16, k group kg) holds 8 consecutive k of each 32-wide step; rows past T are never stored.
+    // Requested ahead of W (loads return in order: behind it they cost 5 us more)
+    bf16x8 xf[TT][2][STEPS];
+#pragma unroll
+    for (int tt = 0; tt < TT; tt++)
+#pragma unroll
+        for (int part = 0; part < 2; part++)
+#pragma unroll
+            for (int s = 0; s < STEPS; s++) {
+                const int t = min(tt * 16 + l16, T - 1), k = k0 + (s0 + min(s, max(ns - 1, 0))) * 32 + kg * 8;
+                const bf16_t *src = (part ? xlo : xhi) + (OCT ? ((int64_t)(k >> 3) * T + t) * 8 : (int64_t)t * K + k);
+                xf[tt][part][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(src));
+            }
+
     __builtin_amdgcn_sched_barrier(0);
-    // LDS addresses: what depends on the lane sits in a few registers, the rest are immediates
-    const char *xf[2][4];       // X fragment of piece (k1 * 8 + half * 4 + j) of row l32; + (kg >> 1) * 256, + 32 KB for the low part
 #pragma unroll
-    for (int k1 = 0; k1 < 2; k1++)
+    for (int i = 0; i < S; i++)
+        if (i < n_tiles) request(i);
+    __builtin_amdgcn_sched_barrier(0);
+    // waited for here, once: left to their first use, inside the loop, the wait would cover every copy in flight there
 #pragma unroll
-        for (int j = 0; j < 4; j++) xf[k1][j] = xs + (l32 * 64 + ((k1 * 8 + half * 4 + j) ^ (l32 & 15))) * 16;
-    char *tw = tp[wave];
-    char *tw_st[2];             // where this lane's piece of row i * 8 + r8 goes: + (i >> 1) * 2048 for the row pair
+    for (int tt = 0; tt < TT; tt++)
 #pragma unroll
-    for (int i1 = 0; i1 < 2; i1++) tw_st[i1] = tw + (i1 * 8 + r8) * 128 + ((p8 ^ (((i1 * 8 + r8) >> 1) & 7)) * 16);
-    const char *tw_ld[4];
+        for (int part = 0; part < 2; part++)
 #pragma unroll
-    for (int j = 0; j < 4; j++) tw_ld[j] = tw + l32 * 128 + (((half * 4 + j) ^ ((l32 >> 1) & 7)) * 16);
+            for (int s = 0; s < STEPS; s++) asm volatile("" : "+v"(xf[tt][part][s]));
 
-    // Rows are taken 32 at a time against the same weight registers (one group for a decode batch, two for
-    // up to 64 rows): the X slab of a group is staged, multiplied and its partial sums written before the next
-    // group's slab replaces it in LDS.  The first group is spelled out ahead of the loop: there the W loads are
-    // still in flight and each k-group waits for its own four only.
-    auto group = [&](int t0) {
-        f32x16 acc_h, acc_l;
+    // adds the eight waves' sums of a tile (in LDS since the barrier before) and stores them
+    auto finish = [&](int tile) {
 #pragma unroll
-        for (int i = 0; i < 16; i++) acc_h[i] = acc_l[i] = 0.f;
+        for (int u = 0; u < (TT + 1) / 2; u++) {
+            const int t = u * 32 + (threadIdx.x >> 4), r = threadIdx.x & 15, row = row0 + tile * 16 + r;
+            if (t < T && row < row1) {
+                const uint32_t src = red_base + (tile & 1) * (SK_WAVES * TT * 1024) + t * 64 + r * 4;
+                float v[SK_WAVES];
+                static_assert(SK_WAVES == 8, "one read per wave below");
+                constexpr int O = TT * 1024;
+                asm volatile("ds_read_b32 %0, %8\n\tds_read_b32 %1, %8 offset:%9\n\tds_read_b32 %2, %8 offset:%10\n\t"
+                             "ds_read_b32 %3, %8 offset:%11\n\tds_read_b32 %4, %8 offset:%12\n\tds_read_b32 %5, %8 offset:%13\n\t"
+                             "ds_read_b32 %6, %8 offset:%14\n\tds_read_b32 %7, %8 offset:%15\n\ts_waitcnt lgkmcnt(0)"
+                             : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
+                             : "v"(src), "n"(O), "n"(2 * O), "n"(3 * O), "n"(4 * O), "n"(5 * O), "n"(6 * O), "n"(7 * O)
+                             : "memory");
 #pragma unroll
-        for (int kg = 0; kg < 8; kg++) {
-            if (FULL || kg < n_kg) {
-                // the k-group through the wave's own LDS rows (a wave's LDS operations execute in order)
-#pragma unroll
-                for (int i = 0; i < 4; i++) *reinterpret_cast<u32x4 *>(tw_st[i & 1] + (i >> 1) * 2048) = w[kg * 4 + i];
-                __builtin_amdgcn_wave_barrier();
-                u32x4 bw[4];
-#pragma unroll
-                for (int j = 0; j < 4; j++) bw[j] = *reinterpret_cast<const u32x4 *>(tw_ld[j]);
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int j = 0; j < 4; j++) {      // k = kg * 64 + half * 32 + j * 8
-                    const char *xa = xf[kg & 1][j] + (kg >> 1) * 256;
-                    const bf16x8 ah = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(xa));
-                    const bf16x8 al = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(xa + 32 * 1024));
-                    acc_h = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, __builtin_bit_cast(bf16x8, bw[j]), acc_h, 0, 0, 0);
-                    acc_l = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, __builtin_bit_cast(bf16x8, bw[j]), acc_l, 0, 0, 0);
-                }
-            }
-        }
-        if (n < n_rows) {
-#pragma unroll
-            for (int i = 0; i < 16; i++) {
-                const int t = t0 + 8 * (i / 4) + 4 * half + (i % 4);
-                if (t < T) partial[((int64_t)kz * T + t) * n_rows + n] = acc_h[i] + acc_l[i];
+                for (int w = 1; w < SK_WAVES; w++) v[0] += v[w];
+                partial[((int64_t)kz * T + t) * n_rows + row] = v[0];
             }
         }
     };
-    x_stage();
-    lds_barrier();
-    group(0);
-    for (int t0 = 32; t0 < T; t0 += 32) {
-        lds_barrier();      // every wave has finished reading the previous group's slab
-        x_request(t0);
-        x_stage();
+
+    for (int tile = 0; tile < n_tiles; tile++) {
+        // the own copies of this tile have landed once no more than the younger tiles' are outstanding (copies return in
+        // order; stores of partial sums among them only make the wait stricter)
+        const int younger = min(n_tiles - 1 - tile, S - 1);
+        if (younger == S - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 1) * P) : "memory");
+        else if (S > 2 && younger == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * P) : "memory");
+        else if (S > 2 && younger == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(P) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         lds_barrier();
-        group(t0);
+        const uint32_t st = ring_base + (tile % S) * STAGE + l16 * ROWB;
+        u32x4 wf[STEPS];
+        uint32_t at[STEPS];
+#pragma unroll
+        for (int s = 0; s < STEPS; s++)      // a step past ns reads the last one's fragment again: not used
+            at[s] = st + ((((s0 + min(s, max(ns - 1, 0))) * 4 + kg) ^ l16) * 16);
+        ds_read_b128xn(wf, at);
+        lds_barrier();
+        if (tile + S < n_tiles) request(tile + S);
+        if (tile) finish(tile - 1);      // the other half of red is written below
+        f32x4 acc[TT][2];
+#pragma unroll
+        for (int tt = 0; tt < TT; tt++)
+#pragma unroll
+            for (int part = 0; part < 2; part++) acc[tt][part] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < STEPS; s++)
+            if (s < ns)      // uniform over the wave
+#pragma unroll
+                for (int tt = 0; tt < TT; tt++)
+#pragma unroll
+                    for (int part = 0; part < 2; part++)
+                        acc[tt][part] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[s]), xf[tt][part][s], acc[tt][part], 0, 0, 0);
+        // lane (l16, kg) holds W rows 4 kg .. + 4 of the tile for X row l16
+#pragma unroll
+        for (int tt = 0; tt < TT; tt++) {
+            const f32x4 v = acc[tt][0] + acc[tt][1];
+            asm volatile("ds_write_b128 %0, %1" ::"v"(red_base + (tile & 1) * (SK_WAVES * TT * 1024) + wave * (TT * 1024) + (tt * 16 + l16) * 64 + kg * 16), "v"(v) : "memory");
+        }
     }
+    lds_barrier();
+    finish(n_tiles - 1);
 }
 
 // More than 64 rows (prefill chunks, mixed steps): MFMA-bound.  64*WM tokens x BN weight rows per
@@ -935,13 +829,15 @@ __global__ __launch_bounds__(64) void k_reduce_rope_kv(const float *__restrict__
     blk[kv_v_offset(rk.Hkv, hd, j, slot, i + half)] = f32_to_bf16(vb);
 }
 
-// Kernel by row count: up to 48 rows -> k_gemm_skinny; 49..64 rows -> k_gemm_mfma with 64 x 128 tiles and
-// 128-wide K chunks; more -> k_gemm_big.
-struct Shape { int tt, wc, kch; };
-
 int env_int(const char *name, int dflt) {
     const char *v = getenv(name);
     return v ? atoi(v) : dflt;
+}
+int cu_count() {
+    hipDeviceProp_t p;
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&p, dev) == hipSuccess) n = p.multiProcessorCount;
+    return n > 0 ? n : 256;
 }
 // Tile, workgroup count and split-K factor of the big-tile kernel for a row count: the candidate with the
 // smallest estimated time.  A candidate runs ceil(workgroups / 256) rounds of one workgroup per CU (two for
@@ -998,53 +894,19 @@ BigPlan plan_big(int T, int N, int K, int epi, bool f16 = false) {
     }
     return best;
 }
-Shape pick_shape(int T, int epi) {
-    (void)T; (void)epi;
-    return {2, 1, 128};   // up to 64 rows: 64 x 128 tiles, 128-wide K chunks
-}
-
-// Most rows the skinny kernel takes (measured on the 7B and 13B layer shapes: two groups of rows beat the
-// 64-row kernel up to 48 rows by 7 %, are level with it at 64 rows on the former and 0.5 % behind on the
-// latter).  LD_GEMM_SKINNY_MAX: tuning knob, 32 .. 64.
-int skinny_max_rows() {
-    static const int v = env_int("LD_GEMM_SKINNY_MAX", 48);
-    return std::min(std::max(v, 32), 64);
-}
+// Most rows the small-batch kernel takes: four 16-row tiles of X fit a wave's registers beside its fragments.  Feed-
+// forward of the 7B shape at 33 / 48 / 49 / 64 rows against the kernels that took these rows before it (a 512-wide
+// slab kernel in two groups of rows, then one with X staged chunk by chunk): 105 -> 79, 111 -> 84, 129 -> 88,
+// 128 -> 91 us; at 2 / 16 / 32 rows 68 -> 64, 76 -> 68, 84 -> 74 us.
+constexpr int SKINNY_MAX_ROWS = 64;
+int skinny_tiles(int T) { return T <= 16 ? 1 : T <= 32 ? 2 : T <= 48 ? 3 : 4; }      // 16-row tiles of X
+// K slabs: what the eight waves of a workgroup hold of X in registers
+int skinny_split(int T, int K) { return (K + sk_slab(skinny_tiles(T)) - 1) / sk_slab(skinny_tiles(T)); }
 
 int split_factor(int T, int N, int K, int epi, bool f16 = false) {
-    if (T <= skinny_max_rows()) return (K + SL - 1) / SL;   // skinny kernel: one 512-wide slab per workgroup
-    if (T > 64) { const BigPlan p = plan_big(T, N, K, epi, f16); return std::max(p.ks, p.ks_b); }
-    const Shape sh = pick_shape(T, epi);
-    const int n_ttiles = (T + sh.tt * 32 - 1) / (sh.tt * 32), n_nblocks = (N + 128 * sh.wc - 1) / (128 * sh.wc);
-    const int wgs = n_ttiles * n_nblocks;
-    int ks = (768 + wgs - 1) / wgs;               // aim at ~3 workgroups per CU
-    ks = std::min(ks, K / sh.kch / 2);            // at least two chunks per slab
-    ks = std::min(ks, K / (8 * T));               // partial sums: at most a quarter of the matrix bytes
-    ks = std::min(ks, 32);
-    static const int forced = env_int("LD_GEMM_KS", 0);   // tuning knob
-    if (forced > 0) ks = std::min(forced, K / sh.kch);
-    return std::max(ks, 1);
-}
-
-template <int TT, int WC, int KCH>
-void launch_shape(const bf16_t *W, const bf16_t *hi, const bf16_t *lo, int T, int N, int K, int epi, float *y,
-                  float *partial, hipStream_t s, bool reduce = true, bf16_t *hi_out = nullptr, bf16_t *lo_out = nullptr) {
-    const int n_ttiles = (T + TT * 32 - 1) / (TT * 32);
-    const int n_nblocks = (N + 128 * WC - 1) / (128 * WC);
-    const int ks = split_factor(T, N, K, epi);
-    const int grid = ((n_nblocks + 7) / 8) * 8 * n_ttiles * ks;
-    const int rgrid = (int)(((int64_t)T * N + 255) / 256);
-#define LD_GEMM(EPI_)                                                                                                  \
-    do {                                                                                                               \
-        LD_LAUNCH((k_gemm_mfma<TT, WC, KCH, EPI_>), dim3(grid), dim3(256), 0, s, W, hi, lo, T, N, K, y, n_ttiles, \
-                           ks, partial, hi_out, lo_out);                                                               \
-        if (ks > 1 && reduce)                                                                                          \
-            LD_LAUNCH((k_splitk_reduce<EPI_>), dim3(rgrid), dim3(256), 0, s, partial, T, N, ks, y, 0, N, hi_out, lo_out); \
-    } while (0)
-    if (epi == ld::GEMM_STORE) LD_GEMM(ld::GEMM_STORE);
-    else if (epi == ld::GEMM_ADD) LD_GEMM(ld::GEMM_ADD);
-    else if constexpr (WC == 1) LD_GEMM(ld::GEMM_SWIGLU);   // SwiGLU always runs with one column tile per wave
-#undef LD_GEMM
+    if (T <= SKINNY_MAX_ROWS) return skinny_split(T, K);
+    const BigPlan p = plan_big(T, N, K, epi, f16);
+    return std::max(p.ks, p.ks_b);
 }
 
 }  // namespace
@@ -1070,7 +932,7 @@ int tail_rows(int T, int N, int K, int epi, bool f16) {
 
 static size_t partial_bytes(int T, int N, int K, int epi, bool f16 = false) {
     const int ks = split_factor(T, N, K, epi, f16);
-    return (ks > 1 || T <= skinny_max_rows()) ? (size_t)ks * T * N * (epi == GEMM_SWIGLU ? 2 : 1) * sizeof(float) : 0;
+    return (ks > 1 || T <= SKINNY_MAX_ROWS) ? (size_t)ks * T * N * (epi == GEMM_SWIGLU ? 2 : 1) * sizeof(float) : 0;
 }
 
 size_t gemm_scratch_bytes(int T, int N, int K, int epi) {
@@ -1084,25 +946,42 @@ size_t gemm_scratch_bytes(int T, int N, int K, int epi) {
     return gemm_split_bytes(T, K) + part;
 }
 
-void launch_norm_split(const float *x, const float *g, float eps, int T, int K, uint16_t *xs, hipStream_t s) {
-    LD_LAUNCH(k_norm_split, dim3(T), dim3(256), 0, s, x, g, eps, K, xs, xs + (size_t)T * K);
+bool gemm_takes_octets(int T) { return T >= 2 && T <= SKINNY_MAX_ROWS; }
+
+void launch_norm_split(const float *x, const float *g, float eps, int T, int K, uint16_t *xs, hipStream_t s, bool octets) {
+    bf16_t *lo = xs + (size_t)T * K;
+#define LD_NS(R_)                                                                                                      \
+    do {                                                                                                               \
+        if (octets) LD_LAUNCH((k_norm_split<R_, true>), dim3(T), dim3(256), 0, s, x, g, eps, K, xs, lo);               \
+        else LD_LAUNCH((k_norm_split<R_, false>), dim3(T), dim3(256), 0, s, x, g, eps, K, xs, lo);                     \
+    } while (0)
+    if (K <= 5 * 1024) LD_NS(5);
+    else if (K <= 14 * 1024) LD_NS(14);
+    else LD_NS(0);
+#undef LD_NS
 }
 
-int skinny_slabs(int K) { return (K + SL - 1) / SL; }
-
-// K a multiple of the slab width: every workgroup's slab is whole and its loads are unconditional (the compiler
-// can then count how many loads may stay in flight at each use)
-static void skinny_launch(const uint16_t *W, const uint16_t *xhi, const uint16_t *xlo, int T, int n_rows, int K, int ks,
-                          float *partial, hipStream_t s) {
-    const dim3 grid(((n_rows + 127) / 128) * ks);
-    if (K % SL == 0) LD_LAUNCH(k_gemm_skinny<true>, grid, dim3(256), 0, s, W, xhi, xlo, T, n_rows, K, ks, partial);
-    else LD_LAUNCH(k_gemm_skinny<false>, grid, dim3(256), 0, s, W, xhi, xlo, T, n_rows, K, ks, partial);
-}
+int skinny_slabs(int T, int K) { return skinny_split(T, K); }
 
 void launch_gemm_skinny(const uint16_t *W, const uint16_t *xhi, const uint16_t *xlo, int T, int n_rows, int K,
-                        float *partial, hipStream_t s) {
-    const int ks = skinny_slabs(K);
-    skinny_launch(W, xhi, xlo, T, n_rows, K, ks, partial, s);
+                        float *partial, hipStream_t s, bool octets) {
+    const int ks = skinny_split(T, K);
+    static const int n_cu = cu_count();
+    // one workgroup per CU; fewer where a row group would get less than a tile
+    const int n_grp = std::max(1, std::min(n_cu / ks, (n_rows + 15) / 16));
+    const dim3 grid(n_grp * ks), block(64 * SK_WAVES);
+#define LD_SKINNY(TT_)                                                                                                 \
+    do {                                                                                                               \
+        if (octets) LD_LAUNCH((k_gemm_skinny<TT_, true>), grid, block, 0, s, W, xhi, xlo, T, n_rows, K, ks, partial);  \
+        else LD_LAUNCH((k_gemm_skinny<TT_, false>), grid, block, 0, s, W, xhi, xlo, T, n_rows, K, ks, partial);        \
+    } while (0)
+    switch (skinny_tiles(T)) {
+        case 1: LD_SKINNY(1); break;
+        case 2: LD_SKINNY(2); break;
+        case 3: LD_SKINNY(3); break;
+        default: LD_SKINNY(4);
+    }
+#undef LD_SKINNY
 }
 
 // The direct-to-LDS kernel addresses its operands with 32-bit byte offsets from the start of each matrix.
@@ -1199,7 +1078,7 @@ bool gemm_f16_rows(int T, int N, int K, int epi) {
 // image where the caller keeps one (the kernel then reads it in W's place and converts nothing), else nullptr.
 static void gemm_rows(const uint16_t *W, bf16_t *hi, const bf16_t *lo, int T, int N, int K, int epi, float *y,
                       float *partial, hipStream_t s, const RowsNext *nx = nullptr, int *f16_flag = nullptr,
-                      const uint16_t *W16 = nullptr) {
+                      const uint16_t *W16 = nullptr, bool octets = false) {
     const bool chain_rope = nx && epi == GEMM_STORE && nx->rope;
     const bool chain_add = (nx && epi == GEMM_ADD) || chain_rope;      // a finishing kernel replaces the split-K reduction
     bf16_t *ho = nx && epi == GEMM_SWIGLU ? nx->hi : nullptr, *lo_o = nx && epi == GEMM_SWIGLU ? nx->lo : nullptr;
@@ -1213,9 +1092,9 @@ static void gemm_rows(const uint16_t *W, bf16_t *hi, const bf16_t *lo, int T, in
             LD_LAUNCH(k_reduce_add_norm_split, dim3(T), dim3(256), 0, s, partial, T, N, ks, col0, col1, y, nx->g, nx->eps,
                       nx->hi, nx->lo);
     };
-    if (T <= skinny_max_rows()) {
+    if (T <= SKINNY_MAX_ROWS) {
         const int ks = split_factor(T, N, K, epi), n_rows = N * (epi == GEMM_SWIGLU ? 2 : 1);
-        skinny_launch(W, hi, lo, T, n_rows, K, ks, partial, s);
+        launch_gemm_skinny(W, hi, lo, T, n_rows, K, partial, s, octets);
         const int rgrid = (int)(((int64_t)T * N + 255) / 256);
         bf16_t *none = nullptr;
         if (chain_add) finish(ks, 0, N, true);     // the skinny kernel writes partial sums even for one slab
@@ -1224,32 +1103,27 @@ static void gemm_rows(const uint16_t *W, bf16_t *hi, const bf16_t *lo, int T, in
         else LD_LAUNCH((k_splitk_reduce<GEMM_SWIGLU>), dim3(rgrid), dim3(256), 0, s, partial, T, N, ks, y, 0, N, ho, lo_o);
         return;
     }
-    if (T > 64) {
-        const int f16 = f16_flag ? (W16 ? 2 : 1) : 0;
-        const BigPlan p = plan_big(T, N, K, epi, f16 != 0);
-        if (f16 == 2) W = W16;
-        if (f16) {
-            const int64_t n8 = (int64_t)T * K / 8;
-            LD_LAUNCH(k_split_to_f16, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, s, hi, lo, n8, f16_flag);
-        }
-        if (p.nb_a > 0) {
-            // two phases: whole rounds of unsplit tiles, then the remaining column blocks with a split K
-            const int nout = (epi == GEMM_SWIGLU ? p.bn / 2 : p.bn), mid = p.nb_a * nout;
-            launch_big_cols(W, hi, lo, T, N, K, epi, y, partial, p.wm, p.bn, p.n_ttiles, 1, 0, mid, s, true, ho, lo_o, f16);
-            launch_big_cols(W, hi, lo, T, N, K, epi, y, partial, p.wm, p.bn, p.n_ttiles, p.ks_b, mid, N, s, !chain_add, ho, lo_o, f16);
-            if (chain_add) finish(p.ks_b, mid, N);
-        } else {
-            launch_big_cols(W, hi, lo, T, N, K, epi, y, partial, p.wm, p.bn, p.n_ttiles, p.ks, 0, N, s, !chain_add, ho, lo_o, f16);
-            if (chain_add) finish(p.ks, 0, N);
-        }
-        return;
+    const int f16 = f16_flag ? (W16 ? 2 : 1) : 0;
+    const BigPlan p = plan_big(T, N, K, epi, f16 != 0);
+    if (f16 == 2) W = W16;
+    if (f16) {
+        const int64_t n8 = (int64_t)T * K / 8;
+        LD_LAUNCH(k_split_to_f16, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, s, hi, lo, n8, f16_flag);
     }
-    launch_shape<2, 1, 128>(W, hi, lo, T, N, K, epi, y, partial, s, !chain_add, ho, lo_o);   // 49..64 rows
-    if (chain_add) finish(split_factor(T, N, K, epi), 0, N);
+    if (p.nb_a > 0) {
+        // two phases: whole rounds of unsplit tiles, then the remaining column blocks with a split K
+        const int nout = (epi == GEMM_SWIGLU ? p.bn / 2 : p.bn), mid = p.nb_a * nout;
+        launch_big_cols(W, hi, lo, T, N, K, epi, y, partial, p.wm, p.bn, p.n_ttiles, 1, 0, mid, s, true, ho, lo_o, f16);
+        launch_big_cols(W, hi, lo, T, N, K, epi, y, partial, p.wm, p.bn, p.n_ttiles, p.ks_b, mid, N, s, !chain_add, ho, lo_o, f16);
+        if (chain_add) finish(p.ks_b, mid, N);
+    } else {
+        launch_big_cols(W, hi, lo, T, N, K, epi, y, partial, p.wm, p.bn, p.n_ttiles, p.ks, 0, N, s, !chain_add, ho, lo_o, f16);
+        if (chain_add) finish(p.ks, 0, N);
+    }
 }
 
 void launch_gemm(const uint16_t *W, uint16_t *xs, int T, int N, int K, int epi, float *y, hipStream_t s,
-                 const GemmNext *next, int *f16_flag, const uint16_t *W16) {
+                 const GemmNext *next, int *f16_flag, const uint16_t *W16, bool octets) {
     float *partial = (float *)((char *)xs + gemm_split_bytes(T, K));
     bf16_t *hi = xs, *lo = xs + (size_t)T * K;
     // the rows beyond a multiple of 256 that the cost model sends through the small-batch kernels keep both terms
@@ -1265,7 +1139,7 @@ void launch_gemm(const uint16_t *W, uint16_t *xs, int T, int N, int K, int epi, 
         b = {next->g, next->eps, next->xs ? a.hi + (size_t)(T - r) * N : nullptr, next->xs ? a.lo + (size_t)(T - r) * N : nullptr,
              next->rope, T - r};
     }
-    gemm_rows(W, hi, lo, T - r, N, K, epi, y, partial, s, next ? &a : nullptr, f16_flag, W16);
+    gemm_rows(W, hi, lo, T - r, N, K, epi, y, partial, s, next ? &a : nullptr, f16_flag, W16, octets);
     // the tail reuses the partial-sum scratch: the stream orders it behind the main part's reduction
     if (r) gemm_rows(W, hi + (size_t)(T - r) * K, lo + (size_t)(T - r) * K, r, N, K, epi, y + (size_t)(T - r) * N, partial, s,
                      next ? &b : nullptr);

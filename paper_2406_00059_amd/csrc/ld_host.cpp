@@ -362,7 +362,7 @@ ld_status enqueue_pass(ld_kv *kv, const std::vector<Row> &rows, int n_single, co
             LD_TIMED(LD_PROF_QKV, timed_void([&] { ld::launch_batch_qkv(a, st); }));
             LD_TIMED(LD_PROF_ATTENTION, ld::paged_attention_split(w.qkv, nqkv, pool_l, c.dtype, w.table, kv->max_blocks, d_slot,
                                                                   d_ctx, max_ctx_dec, T, H, Hkv, hd, c.window, w.b_xs,
-                                                                  w.att_scratch, w.att_scratch_bytes, st));
+                                                                  w.att_scratch, w.att_scratch_bytes, st, 0, true));
             LD_TIMED(LD_PROF_WO, timed_void([&] { ld::launch_batch_wo(a, st); }));
             LD_TIMED(LD_PROF_GATE_UP, timed_void([&] { ld::launch_batch_gate_up(a, st); }));
             LD_TIMED(LD_PROF_DOWN, timed_void([&] { ld::launch_batch_down(a, st); }));
