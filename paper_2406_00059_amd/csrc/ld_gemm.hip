@@ -9,7 +9,7 @@
 // writes in a pass of its own or a producer writes directly (k_reduce_add_norm_split and the SwiGLU epilogues
 // here, the attention kernels, the fused reducers of ld_batch.hip):
 //  - k_gemm_skinny (2..64 rows): weight-stream bound, see its comment.
-//  - k_gemm_dma / k_gemm_big (> 64 rows): MFMA-bound; both operands through LDS, see their comments.
+//  - k_gemm_tile (> 64 rows): MFMA-bound; both operands through LDS, see its comment.
 // Workgroups that share a W panel (same columns, different token tiles) are mapped to the same XCD so
 // that the panel is fetched into one L2 only.  Split-K partial sums are added in fixed slab order.
 #include "ld_gemm.h"
@@ -330,400 +330,223 @@ __global__ __launch_bounds__(64 * SK_WAVES, 2) void k_gemm_skinny(const bf16_t *
     finish(n_tiles - 1);
 }
 
-// More than 64 rows (prefill chunks, mixed steps): MFMA-bound.  64*WM tokens x BN weight rows per
-// workgroup, 2*WM waves as WM (tokens) x 2 (columns), both operands through LDS.  What limits this kernel is
-// the operand traffic from L2 per flop (the split doubles the X side), so the tile is as large as the
-// accumulators allow: 256 x 256 with eight waves from 512 rows on, 128 x 256 (or x 128) below.  K advances
-// in chunks of 32; the global loads of a chunk are issued D chunks before their data is written to LDS, in
-// a ring of register sets; LDS is double buffered, one barrier per chunk.  LDS holds 16-byte pieces
-// segment-major ([k-segment][row], segment stride padded by 64 bytes): the operand reads of 16 consecutive
-// lanes are 256 contiguous bytes and the staging writes of a 16-lane group (4 rows x 4 segments) cover all
-// 64 banks once.
-template <int WM, int BN, int D, int EPI>
-__global__ __launch_bounds__(128 * WM) void k_gemm_big(const bf16_t *__restrict__ W, const bf16_t *__restrict__ xhi,
-                                                       const bf16_t *__restrict__ xlo, int T, int N, int K,
-                                                       float *__restrict__ y, int n_ttiles, int ks,
-                                                       float *__restrict__ partial, int col0, int col1,
-                                                       bf16_t *__restrict__ hi_out, bf16_t *__restrict__ lo_out) {
-    constexpr bool SWI = (EPI == ld::GEMM_SWIGLU);
-    constexpr int NT = 128 * WM;                  // threads
-    constexpr int BM = 64 * WM, BK = 32, SEGS = BK / 8;
-    constexpr int WCT = BN / 2 / 32;              // 32-column accumulator tiles per wave
-    constexpr int NOUT = SWI ? BN / 2 : BN;       // output columns per workgroup
-    constexpr int XSEG = BM * 16 + 64, WSEG = BN * 16 + 64;   // bytes per k-segment of a stage
-    constexpr int NVX = 2 * BM * SEGS / NT, NVW = BN * SEGS / NT;   // 16-byte pieces per thread per chunk
-    __shared__ __attribute__((aligned(16))) char xs[2][2][SEGS][XSEG];
-    __shared__ __attribute__((aligned(16))) char ws[2][SEGS][WSEG];
-
-    const int b = blockIdx.x, xcd = b & 7, s = b >> 3;
-    const int kz = s % ks, tt_idx = (s / ks) % n_ttiles, nb = (s / (ks * n_ttiles)) * 8 + xcd;
-    const int n_nblocks = (col1 - col0 + NOUT - 1) / NOUT;   // this launch covers output columns [col0, col1)
-    if (nb >= n_nblocks) return;
-    const int t0 = tt_idx * BM, n0 = col0 + nb * NOUT;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int l32 = lane & 31, half = lane >> 5;
-    const int wm = wave >> 1, wn = wave & 1;
-
-    // global source of every piece this thread stages (rows clamped; clamped rows are never stored)
-    const bf16_t *xsrc[NVX], *wsrc[NVW];
-    int xdst[NVX], wdst[NVW];
-#pragma unroll
-    for (int v = 0; v < NVX; v++) {
-        const int p = threadIdx.x + NT * v, part = p / (BM * SEGS), r = (p % (BM * SEGS)) >> 2, seg = p & 3;
-        xsrc[v] = (part ? xlo : xhi) + (int64_t)min(t0 + r, T - 1) * K + seg * 8;
-        xdst[v] = (part * SEGS + seg) * XSEG + r * 16;
-    }
-#pragma unroll
-    for (int v = 0; v < NVW; v++) {
-        const int p = threadIdx.x + NT * v, wr = p >> 2, seg = p & 3;
-        int grow;
-        if (SWI) {   // local rows of a wave column: gate tiles, then the up tiles of the same columns
-            const int wcol = wr / (BN / 2), within = wr % (BN / 2);
-            const int col = n0 + wcol * (BN / 4) + (within % (BN / 4));
-            grow = min(col, N - 1) + (within >= BN / 4 ? N : 0);
-        } else {
-            grow = min(n0 + wr, N - 1);
-        }
-        wsrc[v] = W + (int64_t)grow * K + seg * 8;
-        wdst[v] = seg * WSEG + wr * 16;
-    }
-
-    f32x16 acc[2][WCT];
-#pragma unroll
-    for (int tt = 0; tt < 2; tt++)
-#pragma unroll
-        for (int wc = 0; wc < WCT; wc++)
-#pragma unroll
-            for (int i = 0; i < 16; i++) acc[tt][wc][i] = 0.f;
-
-    u32x4 ring[D][NVX + NVW];
-    auto issue = [&](u32x4 (&r)[NVX + NVW], int kc) {
-#pragma unroll
-        for (int v = 0; v < NVX; v++) r[v] = *reinterpret_cast<const u32x4 *>(xsrc[v] + kc * BK);
-#pragma unroll
-        for (int v = 0; v < NVW; v++) r[NVX + v] = *reinterpret_cast<const u32x4 *>(wsrc[v] + kc * BK);
-    };
-    auto stage = [&](const u32x4 (&r)[NVX + NVW], int st) {
-#pragma unroll
-        for (int v = 0; v < NVX; v++) *reinterpret_cast<u32x4 *>(&xs[st][0][0][0] + xdst[v]) = r[v];
-#pragma unroll
-        for (int v = 0; v < NVW; v++) *reinterpret_cast<u32x4 *>(&ws[st][0][0] + wdst[v]) = r[NVX + v];
-    };
-    auto compute = [&](int st) {
-#pragma unroll
-        for (int kstep = 0; kstep < BK / 16; kstep++) {
-            const int seg = kstep * 2 + half;
-            bf16x8 a[2][2], bw[WCT];
-#pragma unroll
-            for (int part = 0; part < 2; part++)
-#pragma unroll
-                for (int tt = 0; tt < 2; tt++)
-                    a[part][tt] = __builtin_bit_cast(
-                        bf16x8, *reinterpret_cast<const u32x4 *>(&xs[st][part][seg][(wm * 64 + tt * 32 + l32) * 16]));
-#pragma unroll
-            for (int wc = 0; wc < WCT; wc++)
-                bw[wc] = __builtin_bit_cast(
-                    bf16x8, *reinterpret_cast<const u32x4 *>(&ws[st][seg][(wn * (BN / 2) + wc * 32 + l32) * 16]));
-#pragma unroll
-            for (int part = 0; part < 2; part++)
-#pragma unroll
-                for (int tt = 0; tt < 2; tt++)
-#pragma unroll
-                    for (int wc = 0; wc < WCT; wc++)
-                        acc[tt][wc] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[part][tt], bw[wc], acc[tt][wc], 0, 0, 0);
-        }
-    };
-
-    const int c_begin = (int)((int64_t)kz * (K / BK) / ks), c_end = (int)((int64_t)(kz + 1) * (K / BK) / ks);
-#pragma unroll
-    for (int d = 0; d < D; d++)
-        if (c_begin + d < c_end) issue(ring[d], c_begin + d);
-    for (int c = c_begin; c < c_end; c += D) {
-#pragma unroll
-        for (int d = 0; d < D; d++) {
-            const int cc = c + d;
-            if (cc < c_end) {
-                const int st = (D % 2 == 0) ? (d & 1) : ((cc - c_begin) & 1);   // LDS stage alternates per chunk
-                stage(ring[d], st);
-                lds_barrier();
-                if (cc + D < c_end) issue(ring[d], cc + D);
-                compute(st);
-            }
-        }
-    }
-
-    // accumulator element i of lane (l32, half): token t0 + wm*64 + tt*32 + 8*(i/4) + 4*half + i%4
-    constexpr int WOUT = SWI ? WCT / 2 : WCT;     // output column tiles per wave
-    const int ncols = SWI ? 2 * N : N;            // row length of the partial-sum buffer
-#pragma unroll
-    for (int wc = 0; wc < WOUT; wc++) {
-        const int n = n0 + wn * (NOUT / 2) + wc * 32 + l32;
-        if (n >= col1) continue;
-#pragma unroll
-        for (int tt = 0; tt < 2; tt++)
-#pragma unroll
-            for (int i = 0; i < 16; i++) {
-                const int t = t0 + wm * 64 + tt * 32 + 8 * (i / 4) + 4 * half + (i % 4);
-                if (t >= T) continue;
-                if (ks > 1) {
-                    float *dst = partial + ((int64_t)kz * T + t) * ncols + n;
-                    dst[0] = acc[tt][wc][i];
-                    if constexpr (SWI) dst[N] = acc[tt][wc + WCT / 2][i];
-                } else {
-                    float *dst = y + (int64_t)t * N + n;
-                    if constexpr (EPI == ld::GEMM_STORE) *dst = acc[tt][wc][i];
-                    else if constexpr (EPI == ld::GEMM_ADD) *dst += acc[tt][wc][i];
-                    else {
-                        const float a = swiglu(acc[tt][wc][i], acc[tt][wc + WCT / 2][i]);
-                        if (hi_out) store_split(hi_out, lo_out, (int64_t)t * N + n, a);
-                        else *dst = a;
-                    }
-                }
-            }
-    }
-}
-
-// The same tile scheme with the operands copied from global memory straight into LDS
-// (global_load_lds_dwordx4: lane l of a wave writes its 16 bytes at the wave's LDS base + 16 l), so that no
-// operand byte passes through registers on its way to LDS and the registers of the prefetch ring are free.
-// A stage holds the tile's rows row-major, 64 bytes (one K chunk of 32) per row: X hi rows, X lo rows, W
-// rows.  One copy instruction of a wave covers 16 rows x 4 sixteen-byte pieces (1 KB of LDS, 64 contiguous
-// bytes of 16 rows in memory).  Piece `seg` of row r sits in slot seg ^ ((r >> 2) & 3) of the row, which
-// makes the operand reads of 16 consecutive rows hit 16 different bank groups; the swizzle costs nothing
-// because a lane may fetch any global piece into its fixed slot.  S stages; the copies of chunk c + S - 1
-// are issued right after the barrier of chunk c, when every wave has finished reading the stage they
-// overwrite; before the barrier of chunk c a wave waits until its own copies of chunk c have landed
-// (s_waitcnt vmcnt with the number of younger copies still allowed in flight).
-// WM x WN waves; a wave owns 64 rows x BN / WN columns of the tile.  Both shapes in use run eight waves, two
-// per SIMD, so that one wave's operand reads and barrier waits sit under the other's MFMAs: 256 x 256 as
-// 4 x 2 waves of 64 x 128, 128 x 256 as 2 x 4 waves of 64 x 64 (measured against four waves of 64 x 128 on
-// the same tile: layer GEMMs at 128 - 512 rows 4 - 7 % faster, the full-grid rate 410 -> 440 TFLOP/s; sixteen
-// waves of 64 x 64 on the 256 x 256 tile fit in 109 registers and change nothing).
+// The big-tile kernel.  Four waves, one per SIMD (512 registers each), WM x WN of them, a wave owning AT x BT accumulator
+// tiles of 32 x 32: the fewest operand bytes out of LDS per MFMA that the registers allow.  K advances in chunks of 64
+// (rows of 128 bytes: whole cache lines), two stages, copied straight into LDS (buffer loads with the lds bit: a
+// scalar base, a lane offset that never changes and a scalar step along K, so that a copy costs no vector
+// arithmetic).  What decides the rate is how the copies are issued.  A copy whose turn comes while the CU's address
+// unit is busy holds up the MFMAs behind it, and two stages leave a copy less than a chunk's time to arrive; so
+//  - the operands of a chunk are all in registers before its last two k-steps (112 - 128 registers), its stage is free
+//    from then on, and
+//  - the copies of the chunk after next are spread over a whole chunk's MFMAs, a few per k-step, none in a row.
+// A product of 2048 x 8192 x 13824 in fp16 runs at 1245 TFLOP/s so, 1118 with the copies in two k-steps, 1454 without
+// any copies; the eight-wave kernel with 32-wide chunks before this one at 1178.
+// One copy instruction covers 8 rows x 128 bytes; piece p (16 bytes) of row r sits in slot p ^ ((r >> 1) & 7) of its row:
+// 16 consecutive rows at one p lie in 16 bank groups.
 //
-// F16 != 0 (rows that nobody reads at full precision, see launch_gemm): one operand image instead of two, the
-// activations rounded to fp16 (11 significant bits; xhi then points at a [T, K] fp16 matrix): half the matrix-core
-// work and two thirds of the operand traffic of the two-term form.  F16 == 1: W is the bf16 matrix and every wave
-// turns the fragments it reads from LDS into fp16 on their way to the matrix cores (exact for 2^-14 <= |w| < 65520,
-// which the launcher has checked on the whole matrix).  F16 == 2: W is the matrix's fp16 image (k_weight_to_f16),
-// used as it is; same values, same sums.
-template <int WM, int BN, int S, int EPI, int WN, int F16>
-__global__ __launch_bounds__(64 * WM * WN) void k_gemm_dma(const bf16_t *__restrict__ W, const bf16_t *__restrict__ xhi,
-                                                       const bf16_t *__restrict__ xlo, int T, int N, int K,
-                                                       float *__restrict__ y, int n_ttiles, int ks,
-                                                       float *__restrict__ partial, int col0, int col1,
-                                                       bf16_t *__restrict__ hi_out, bf16_t *__restrict__ lo_out) {
+// TERMS 2: (hi, lo) bf16 images of the activations against the bf16 matrix, both into the same accumulators.
+// TERMS 1 (rows that nobody reads at full precision, see launch_gemm): the activations as one fp16 image (xhi); WF 1: W
+// is the bf16 matrix and a wave turns its fragments into fp16 on their way to the matrix cores (exact for 2^-14 <= |w| <
+// 65520, which the launcher has checked on the whole matrix); WF 2: W is the matrix's fp16 image (k_weight_to_f16).
+// Same values, same sums either way.
+#if defined(__HIP_DEVICE_COMPILE__)
+struct BufferCopy {      // 16 bytes per lane from base + lane offset + scalar offset into LDS, 1 KB in a row per wave
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ BufferCopy(const void *base)
+        : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, -1, 0x00020000)) {}
+    __device__ __forceinline__ void operator()(char *dst, uint32_t lane_off, uint32_t off) const {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)dst, 16, lane_off, off, 0, 0);
+    }
+};
+#else
+struct BufferCopy {
+    __device__ BufferCopy(const void *) {}
+    __device__ void operator()(char *, uint32_t, uint32_t) const {}
+};
+#endif
+
+constexpr int tile_lds(int terms, int bm, int bn) { return 2 * (terms * bm + bn) * 128; }
+
+template <int TERMS, int WF, int AT, int BT, int WM, int WN, int EPI>
+__global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16_t *__restrict__ W, const bf16_t *__restrict__ xhi,
+                                                      const bf16_t *__restrict__ xlo, int T, int N, int K,
+                                                      float *__restrict__ y, int n_ttiles, int ks,
+                                                      float *__restrict__ partial, bf16_t *__restrict__ hi_out, bf16_t *__restrict__ lo_out) {
     constexpr bool SWI = (EPI == ld::GEMM_SWIGLU);
-    constexpr int NW = WM * WN;                   // waves: WM along the rows (64 each) x WN along the columns
-    constexpr int BM = 64 * WM, BK = 32;
-    constexpr int WCOLS = BN / WN;                // W rows of the tile that one wave column multiplies
-    constexpr int WCT = WCOLS / 32;               // 32-column accumulator tiles per wave
-    constexpr int NOUT = SWI ? BN / 2 : BN;       // output columns per workgroup
-    constexpr int TERMS = F16 ? 1 : 2;
-    constexpr int XR = TERMS * BM;                // X rows of a stage: hi and lo images (one fp16 image)
-    constexpr int ROWS = XR + BN;                 // rows of a stage: X hi, X lo, W
-    constexpr int STAGE = ROWS * 64;              // bytes
-    constexpr int P = ROWS / 16 / NW;             // copy instructions per wave per chunk
-    static_assert(ROWS % (16 * NW) == 0, "rows must split evenly over the waves");
+    static_assert(WM * WN == 4 && (!SWI || BT % 2 == 0), "four waves; a wave column holds gate and up tiles");
+    constexpr int BM = WM * AT * 32, BN = WN * BT * 32, NOUT = SWI ? BN / 2 : BN;
+    constexpr int ROWS = TERMS * BM + BN, STAGE = ROWS * 128, WC = BT * 32;
+    constexpr int P = ROWS / 32;                      // copies per wave and chunk: copy j of wave w covers rows (4 j + w) 8 .. + 8
+    constexpr int NA = TERMS * AT, NM = NA * BT, NR = NA + BT;      // A tiles, MFMAs and operand reads of a k-step
+    // copies (for the chunk after next) issued in k-steps 2 and 3 of a chunk, then in 0 and in 1 of the chunk that follows
+    constexpr int PRE = (P * 10 + 15) / 16, C0 = (P * 14 + 15) / 16 - PRE, C1 = P - PRE - C0;
+    constexpr int NH = NA / 2;                        // A tiles of the last k-step that are multiplied before the next chunk is looked at
     extern __shared__ __attribute__((aligned(1024))) char lds[];
 
-    const int b = blockIdx.x, xcd = b & 7, s = b >> 3;
-    const int kz = s % ks, tt_idx = (s / ks) % n_ttiles, nb = (s / (ks * n_ttiles)) * 8 + xcd;
-    const int n_nblocks = (col1 - col0 + NOUT - 1) / NOUT;   // this launch covers output columns [col0, col1)
-    if (nb >= n_nblocks) return;
-    const int t0 = tt_idx * BM, n0 = col0 + nb * NOUT;
-    // the wave index as a scalar: what depends on it alone (which rows a copy covers, its LDS address) stays in SGPRs
+    // Blocks b, b + 8, ... run on one XCD.  Each XCD takes an equal run of the work items (K slab fastest, then row tile,
+    // then column block), so that its workgroups share W panels in its L2 and no XCD gets an item more than another
+    const int xcd = blockIdx.x & 7, n_items = n_ttiles * ks * ((N + NOUT - 1) / NOUT);
+    const int item = (int)((int64_t)n_items * xcd / 8) + (blockIdx.x >> 3);
+    if (item >= (int)((int64_t)n_items * (xcd + 1) / 8)) return;
+    const int kz = item % ks, tt_idx = item / ks % n_ttiles, nb = item / (ks * n_ttiles);
+    const int t0 = tt_idx * BM, n0 = nb * NOUT;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l32 = lane & 31, half = lane >> 5;
     const int wm = wave / WN, wn = wave % WN;
 
-    // Global source of the piece this lane fetches in copy j of a chunk: a base pointer that is the same for the
-    // whole wave (the 16 rows of a copy lie in one of the three matrices) plus a 32-bit byte offset per lane, the
-    // form in which the copy instruction takes a scalar base and advancing along K is scalar arithmetic (the
-    // launcher keeps matrices of 4 GB or more away).  Rows are clamped; clamped rows are never stored.
-    const char *cbase[P];
+    // lane offsets of the copies from the tile's first row of each matrix (rows clamped: clamped rows are never stored)
     uint32_t coff[P];
 #pragma unroll
     for (int j = 0; j < P; j++) {
-        const int vr0 = (wave * P + j) * 16;                       // first row of the copy (scalar)
-        const int vr = vr0 + (lane >> 2);                          // row of the stage
-        const int slot = lane & 3;
-        const int seg = slot ^ ((vr >> 2) & 3);
-        if (vr0 < XR) {
-            const int r = vr % BM;
-            cbase[j] = reinterpret_cast<const char *>(vr0 < BM ? xhi : xlo);
-            coff[j] = ((uint32_t)min(t0 + r, T - 1) * (uint32_t)K + seg * 8) * 2u;
+        const int vr = (4 * j + wave) * 8 + (lane >> 3);                       // row of the stage
+        int row;
+        if (32 * j < TERMS * BM) {
+            row = min(vr % BM, T - 1 - t0);
         } else {
-            const int wr = vr - XR;
-            int grow;
-            if (SWI) {   // local rows of a wave column: gate tiles, then the up tiles of the same columns
-                const int wcol = wr / WCOLS, within = wr % WCOLS;
-                const int col = n0 + wcol * (WCOLS / 2) + (within % (WCOLS / 2));
-                grow = min(col, N - 1) + (within >= WCOLS / 2 ? N : 0);
-            } else {
-                grow = min(n0 + wr, N - 1);
-            }
-            cbase[j] = reinterpret_cast<const char *>(W);
-            coff[j] = ((uint32_t)grow * (uint32_t)K + seg * 8) * 2u;
+            const int wr = vr - TERMS * BM;      // SwiGLU: a wave column's gate tiles, then the up tiles of the same columns
+            row = min(SWI ? (wr / WC) * (WC / 2) + wr % (WC / 2) : wr, N - 1 - n0);
         }
+        coff[j] = ((uint32_t)row * (uint32_t)K + ((lane & 7) ^ ((vr >> 1) & 7)) * 8) * 2u;
     }
-    auto copy_chunk = [&](int kc, int st) {
+    const BufferCopy from_hi(xhi + (int64_t)t0 * K), from_lo((TERMS == 2 ? xlo : xhi) + (int64_t)t0 * K), from_w(W + (int64_t)n0 * K),
+        from_up(W + (int64_t)(SWI ? N + n0 : n0) * K);
+    const int c_begin = (int)((int64_t)kz * (K / 64) / ks), n = (int)((int64_t)(kz + 1) * (K / 64) / ks) - c_begin;      // >= 2 chunks
+    auto copies = [&](int c, int lo, int hi) {      // copies [lo, hi) of chunk c into its stage
 #pragma unroll
-        for (int j = 0; j < P; j++)
-            __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void *)(cbase[j] + (size_t)kc * (BK * 2) + (size_t)coff[j]),
-                (__attribute__((address_space(3))) void *)(lds + st * STAGE + (wave * P + j) * 1024), 16, 0, 0);
+        for (int j = lo; j < hi; j++) {
+            char *dst = lds + (c & 1) * STAGE + (4 * j + wave) * 1024;
+            const uint32_t off = (uint32_t)(c_begin + c) * 128u;
+            if (32 * j < BM) from_hi(dst, coff[j], off);
+            else if (32 * j < TERMS * BM) from_lo(dst, coff[j], off);
+            else if (SWI && (32 * j - TERMS * BM) % WC >= WC / 2) from_up(dst, coff[j], off);
+            else from_w(dst, coff[j], off);
+        }
     };
 
-    f32x16 acc[2][WCT];
+    f32x16 acc[AT][BT];
 #pragma unroll
-    for (int tt = 0; tt < 2; tt++)
+    for (int i = 0; i < AT; i++)
 #pragma unroll
-        for (int wc = 0; wc < WCT; wc++)
+        for (int j = 0; j < BT; j++)
 #pragma unroll
-            for (int i = 0; i < 16; i++) acc[tt][wc][i] = 0.f;
-
-    struct Frags { u32x4 a[TERMS][2], bw[WCT]; };
-    auto load_frags = [&](Frags &f, int st, int kstep) {
-        const char *base = lds + st * STAGE;
-        const int seg = kstep * 2 + half;
+            for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
+    struct Frags { u32x4 a[NA], w[BT]; };
+    const int sw = (l32 >> 1) & 7;
+    auto load = [&](Frags &f, int st, int kstep) {
+        const char *base = lds + st * STAGE + l32 * 128 + (((kstep * 2 + half) ^ sw) * 16);
 #pragma unroll
-        for (int part = 0; part < TERMS; part++)
+        for (int i = 0; i < NA; i++) f.a[i] = *reinterpret_cast<const u32x4 *>(base + ((i / AT) * BM + (wm * AT + i % AT) * 32) * 128);
 #pragma unroll
-            for (int tt = 0; tt < 2; tt++) {
-                const int r = wm * 64 + tt * 32 + l32;       // BM is a multiple of 16: (r >> 2) & 3 is the stage row's
-                f.a[part][tt] = *reinterpret_cast<const u32x4 *>(base + (part * BM + r) * 64 + ((seg ^ ((r >> 2) & 3)) * 16));
+        for (int j = 0; j < BT; j++) f.w[j] = *reinterpret_cast<const u32x4 *>(base + (TERMS * BM + (wn * BT + j) * 32) * 128);
+    };
+    auto mfmas = [&](const Frags &f, int lo, int hi) {      // A tiles [lo, hi)
+#pragma unroll
+        for (int i = lo; i < hi; i++)
+#pragma unroll
+            for (int j = 0; j < BT; j++) {
+                f32x16 &c = acc[i % AT][j];
+                if constexpr (WF == 0) {
+                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.a[i]), __builtin_bit_cast(bf16x8, f.w[j]), c, 0, 0, 0);
+                } else {
+                    const f16x8 wv = WF == 2 ? __builtin_bit_cast(f16x8, f.w[j]) : bf16x8_to_f16x8(f.w[j]);
+                    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, f.a[i]), wv, c, 0, 0, 0);
+                }
             }
-#pragma unroll
-        for (int wc = 0; wc < WCT; wc++) {
-            const int r = wn * WCOLS + wc * 32 + l32;
-            f.bw[wc] = *reinterpret_cast<const u32x4 *>(base + (XR + r) * 64 + ((seg ^ ((r >> 2) & 3)) * 16));
-        }
     };
-    auto mfmas = [&](const Frags &f) {
-        if constexpr (F16) {
-            f16x8 wv[WCT];
+    // issue order of a stretch of nm MFMAs: nr operand reads and nc copies spread evenly between them
+    auto mix = [&](int nm, int nr, int nc) {
 #pragma unroll
-            for (int wc = 0; wc < WCT; wc++)
-                wv[wc] = F16 == 2 ? __builtin_bit_cast(f16x8, f.bw[wc]) : bf16x8_to_f16x8(f.bw[wc]);
-#pragma unroll
-            for (int tt = 0; tt < 2; tt++)
-#pragma unroll
-                for (int wc = 0; wc < WCT; wc++)
-                    acc[tt][wc] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, f.a[0][tt]), wv[wc],
-                                                                        acc[tt][wc], 0, 0, 0);
-        } else {
-#pragma unroll
-            for (int part = 0; part < TERMS; part++)
-#pragma unroll
-                for (int tt = 0; tt < 2; tt++)
-#pragma unroll
-                    for (int wc = 0; wc < WCT; wc++)
-                        acc[tt][wc] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.a[part][tt]),
-                                                                             __builtin_bit_cast(bf16x8, f.bw[wc]),
-                                                                             acc[tt][wc], 0, 0, 0);
-        }
-    };
-    // Wait until this wave's copies of the oldest outstanding chunk have landed; `younger` later chunks
-    // (P copies each) may stay in flight.  The count is an immediate, so only the steady-state values are
-    // spelled out; near the end of a slab waiting for everything is exact enough.
-    auto wait_copies = [&](int younger) {
-        if (younger >= S - 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 2) * P) : "memory");
-        else if (S >= 4 && younger == S - 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S >= 4 ? S - 3 : 0) * P) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    };
-
-    // Software pipeline.  The operand registers of a K step are read from LDS while the MFMAs of the step
-    // before run; the barrier that makes chunk c + 1 visible sits in the middle of chunk c's arithmetic.
-    // After that barrier every wave has finished reading chunk c - 1, whose stage the copies of chunk
-    // c + S - 1 then overwrite (S stages hold chunks c - 1 .. c + S - 2 until then).
-    const int c_begin = (int)((int64_t)kz * (K / BK) / ks), c_end = (int)((int64_t)(kz + 1) * (K / BK) / ks);
-    const int n_chunks = c_end - c_begin;
-#pragma unroll
-    for (int d = 0; d < S - 1; d++)
-        if (d < n_chunks) copy_chunk(c_begin + d, d);
-    wait_copies(min(n_chunks, S - 1) - 1);
-    asm volatile("s_barrier" ::: "memory");
-    Frags f0, f1;
-    load_frags(f0, 0, 0);
-    int st = 0;
-    // issue order inside a half step: one operand read after every second MFMA, so that the reads are in
-    // flight under the arithmetic of the half step before the one that needs them
-    auto interleave = [&]() {
-#pragma unroll
-        for (int k = 0; k < 2 * TERMS + WCT; k++) {
-            __builtin_amdgcn_sched_group_barrier(0x008, TERMS, 0);   // MFMAs (2 * TERMS * WCT per half step)
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);       // 1 LDS read (2 * TERMS + WCT per half step)
-        }
-    };
-    // the half step that also requests a chunk: its P copies one by one between the MFMAs rather than in a row
-    // behind the barrier (1 - 3 % on the layer shapes)
-    auto interleave_copies = [&]() {
-        constexpr int NM = 2 * TERMS * WCT, NR = 2 * TERMS + WCT, CSTEP = NM / P > 0 ? NM / P : 1;
-#pragma unroll
-        for (int k = 0; k < NM; k++) {
+        for (int k = 0; k < nm; k++) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (k % TERMS == TERMS - 1 && k / TERMS < NR) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            if (k % CSTEP == CSTEP - 1 && k / CSTEP < P) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            const int r = (k + 1) * nr / nm - k * nr / nm, c = (k + 1) * nc / nm - k * nc / nm;
+            if (r == 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            if (r == 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            if (r == 3) __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+            if (c == 1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            if (c == 2) __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);
         }
+        __builtin_amdgcn_sched_barrier(0);
     };
-    // every chunk but the last (the next one always exists): first the steady state, in which a chunk S - 1 ahead
-    // is still to be requested (no condition around the copies, so that their issue can sit between the MFMAs),
-    // then the last S - 2 of them
-    int i = 0;
-    for (; i + S - 1 < n_chunks; i++) {
-        load_frags(f1, st, 1);
-        mfmas(f0);
-        interleave();
-        const int st1 = st + 1 == S ? 0 : st + 1;
-        wait_copies(S - 3);                        // outstanding: chunks i+1 .. i+S-2
-        asm volatile("s_barrier" ::: "memory");
-        copy_chunk(c_begin + i + S - 1, st == 0 ? S - 1 : st - 1);
-        load_frags(f0, st1, 0);
-        mfmas(f1);
-        interleave_copies();
-        st = st1;
-    }
-    for (; i + 1 < n_chunks; i++) {
-        load_frags(f1, st, 1);
-        mfmas(f0);
-        interleave();
-        const int st1 = st + 1 == S ? 0 : st + 1;
-        wait_copies(n_chunks - 1 - (i + 1));       // outstanding: chunks i+1 .. n-1
-        asm volatile("s_barrier" ::: "memory");
-        load_frags(f0, st1, 0);
-        mfmas(f1);
-        interleave();
-        st = st1;
-    }
-    load_frags(f1, st, 1);
-    mfmas(f0);
-    mfmas(f1);
 
-    // accumulator element i of lane (l32, half): token t0 + wm*64 + tt*32 + 8*(i/4) + 4*half + i%4
-    constexpr int WOUT = SWI ? WCT / 2 : WCT;     // output column tiles per wave
+    copies(0, 0, P);
+    copies(1, 0, PRE);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PRE) : "memory");
+    asm volatile("s_barrier" ::: "memory");
+    Frags f0, f1, f2, f3;
+    load(f0, 0, 0);
+    load(f1, 0, 1);
+    int i = 0;
+    for (; i < n - 2; i++) {
+        const int st = i & 1;
+        load(f2, st, 2);
+        copies(i + 1, PRE, PRE + C0);
+        mfmas(f0, 0, NA);
+        mix(NM, NR, C0);
+        load(f3, st, 3);
+        copies(i + 1, PRE + C0, P);
+        mfmas(f1, 0, NA - 1);
+        mix(NM - BT, NR, C1);
+        // every wave has this chunk's operands in registers: its stage is requested again, for chunk i + 2
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        copies(i + 2, 0, PRE);
+        mfmas(f1, NA - 1, NA);
+        mfmas(f2, 0, NA);
+        mfmas(f3, 0, NH);
+        mix(BT + NM + NH * BT, 0, PRE);
+        // the own copies of chunk i + 1 have landed (only those of chunk i + 2 are younger), and after the barrier everyone's
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(PRE) : "memory");
+        load(f0, st ^ 1, 0);
+        load(f1, st ^ 1, 1);
+        mfmas(f3, NH, NA);
+        mix(NM - NH * BT, 2 * NR, 0);
+    }
+    copies(i + 1, PRE, P);
+    load(f2, i & 1, 2);
+    mfmas(f0, 0, NA);
+    mix(NM, NR, 0);
+    load(f3, i & 1, 3);
+    mfmas(f1, 0, NA);
+    mix(NM, NR, 0);
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    load(f0, (i + 1) & 1, 0);
+    load(f1, (i + 1) & 1, 1);
+    mfmas(f2, 0, NA);
+    mfmas(f3, 0, NA);
+    mix(2 * NM, 2 * NR, 0);
+    load(f2, (i + 1) & 1, 2);
+    mfmas(f0, 0, NA);
+    mix(NM, NR, 0);
+    load(f3, (i + 1) & 1, 3);
+    mfmas(f1, 0, NA);
+    mfmas(f2, 0, NA);
+    mfmas(f3, 0, NA);
+
+    // accumulator element e of lane (l32, half): row t0 + (wm AT + a) 32 + 8 (e / 4) + 4 half + e % 4
+    constexpr int WOUT = SWI ? BT / 2 : BT;       // output column tiles per wave
     const int ncols = SWI ? 2 * N : N;            // row length of the partial-sum buffer
 #pragma unroll
-    for (int wc = 0; wc < WOUT; wc++) {
-        const int n = n0 + wn * (NOUT / WN) + wc * 32 + l32;
-        if (n >= col1) continue;
+    for (int j = 0; j < WOUT; j++) {
+        const int col = n0 + (wn * WOUT + j) * 32 + l32;
+        if (col >= N) continue;
 #pragma unroll
-        for (int tt = 0; tt < 2; tt++)
+        for (int a = 0; a < AT; a++)
 #pragma unroll
-            for (int i = 0; i < 16; i++) {
-                const int t = t0 + wm * 64 + tt * 32 + 8 * (i / 4) + 4 * half + (i % 4);
+            for (int e = 0; e < 16; e++) {
+                const int t = t0 + (wm * AT + a) * 32 + 8 * (e / 4) + 4 * half + (e % 4);
                 if (t >= T) continue;
                 if (ks > 1) {
-                    float *dst = partial + ((int64_t)kz * T + t) * ncols + n;
-                    dst[0] = acc[tt][wc][i];
-                    if constexpr (SWI) dst[N] = acc[tt][wc + WCT / 2][i];
+                    float *dst = partial + ((int64_t)kz * T + t) * ncols + col;
+                    dst[0] = acc[a][j][e];
+                    if constexpr (SWI) dst[N] = acc[a][j + WOUT][e];
                 } else {
-                    float *dst = y + (int64_t)t * N + n;
-                    if constexpr (EPI == ld::GEMM_STORE) *dst = acc[tt][wc][i];
-                    else if constexpr (EPI == ld::GEMM_ADD) *dst += acc[tt][wc][i];
+                    float *dst = y + (int64_t)t * N + col;
+                    if constexpr (EPI == ld::GEMM_STORE) *dst = acc[a][j][e];
+                    else if constexpr (EPI == ld::GEMM_ADD) *dst += acc[a][j][e];
                     else {
-                        const float a = swiglu(acc[tt][wc][i], acc[tt][wc + WCT / 2][i]);
-                        if (hi_out) store_split(hi_out, lo_out, (int64_t)t * N + n, a);
-                        else *dst = a;
+                        const float v = swiglu(acc[a][j][e], acc[a][j + WOUT][e]);
+                        if (hi_out) store_split(hi_out, lo_out, (int64_t)t * N + col, v);
+                        else *dst = v;
                     }
                 }
             }
@@ -839,61 +662,45 @@ int cu_count() {
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&p, dev) == hipSuccess) n = p.multiProcessorCount;
     return n > 0 ? n : 256;
 }
-// Tile, workgroup count and split-K factor of the big-tile kernel for a row count: the candidate with the
-// smallest estimated time.  A candidate runs ceil(workgroups / 256) rounds of one workgroup per CU (two for
-// the 128 x 128 tile, at half the rate each); the per-CU rates are the measured full-grid rates of the three
-// tiles; split-K adds the write and the ordered re-read of its partial sums.
-struct BigPlan { int wm, bn, n_ttiles, n_nblocks, ks; double est_us; int nb_a, ks_b; };   // nb_a > 0: two phases
-// f16: the single-term fp16 form.  Its three constants (0.69 of the two-term time per workgroup, split-K partial
-// sums at a third of the two-term form's cost per byte, the last-round factor below) are fitted to the measured
-// times of the 7B, grouped-KV and 13B layer shapes at 1056, 2048 and 2111 rows.
+// Tile, workgroup count and split-K factor of the big-tile kernel for a row count: the candidate with the smallest
+// estimated time.  Workgroups run in rounds of one per CU; a round takes the tile's time per 64-wide chunk of K (measured
+// with every CU busy) times its chunks, a last round that leaves CUs idle at least `last` of that; split-K adds the write
+// and the ordered re-read of its partial sums.  The constants are fitted to every tile and split of the 7B, grouped-KV
+// and 13B layer shapes at 65 - 511 rows (two terms) and 520 - 2048 (one): the choice is 2 % (1 %) slower than the best
+// pair in the mean, 12 % (16 %) at worst.  A tile is in the list where leaving it out costs 9 - 22 % on some shape.
+struct BigPlan { int bm, bn, n_ttiles, n_nblocks, ks; double est_us; };
+struct Tile { int bm, bn; bool swiglu; double chunk_us; };
+const Tile tiles_two[] = {{96, 256, true, 1.31}, {128, 128, true, 1.05}, {128, 192, true, 1.30}, {128, 256, true, 1.56}, {160, 256, true, 1.87}, {192, 256, true, 2.20}};
+const Tile tiles_f16[] = {{128, 256, true, 1.01}, {256, 160, false, 1.17}, {256, 192, true, 1.33}, {256, 256, true, 1.62}};
 BigPlan plan_big(int T, int N, int K, int epi, bool f16 = false) {
     const bool swi = epi == ld::GEMM_SWIGLU;
-    struct Tile { int wm, bn; double tflops; };           // nominal (unsplit) TFLOP/s of a full grid
-    static const Tile tiles[3] = {{4, 256, 520.0}, {2, 256, 440.0}, {2, 128, 300.0}};
+    const double last = f16 ? 0.89 : 0.81, us_per_mb = f16 ? 0.48 : 0.45;
     BigPlan best{};
     double best_t = 1e30;
-    const char *forced = getenv("LD_GEMM_BIG");            // tuning knob: "wm,bn,ks"
-    int f_wm = 0, f_bn = 0, f_ks = 0;
-    if (forced && sscanf(forced, "%d,%d,%d", &f_wm, &f_bn, &f_ks) != 3) f_wm = 0;
-    for (const Tile &tl : tiles) {
-        if (f_wm && (tl.wm != f_wm || tl.bn != f_bn)) continue;
-        if (f16 && tl.bn != 256) continue;      // the fp16 form exists for the 256-wide weight tiles only
-        const int bm = 64 * tl.wm, nout = swi ? tl.bn / 2 : tl.bn;
-        const int n_tt = (T + bm - 1) / bm, n_nb = (N + nout - 1) / nout;
-        const int max_ks = std::max(1, std::min(8, K / 32 / 8));   // at least eight chunks per slab
+    const char *forced = getenv("LD_GEMM_BIG");            // tuning knob: "rows,columns,ks" of a tile (rows 2, 4: 128, 256)
+    int f_bm = 0, f_bn = 0, f_ks = 0;
+    if (forced && sscanf(forced, "%d,%d,%d", &f_bm, &f_bn, &f_ks) != 3) f_bm = 0;
+    if (f_bm && f_bm <= 4) f_bm *= 64;
+    const Tile *first = f16 ? std::begin(tiles_f16) : std::begin(tiles_two), *end = f16 ? std::end(tiles_f16) : std::end(tiles_two);
+    const bool known = std::any_of(first, end, [&](const Tile &t) { return t.bm == f_bm && t.bn == f_bn && (!swi || t.swiglu); });
+    for (const Tile *tl = first; tl != end; tl++) {
+        if (known && (tl->bm != f_bm || tl->bn != f_bn)) continue;
+        if (swi && !tl->swiglu) continue;
+        const int nout = swi ? tl->bn / 2 : tl->bn;
+        const int n_tt = (T + tl->bm - 1) / tl->bm, n_nb = (N + nout - 1) / nout;
+        const int max_ks = std::max(1, std::min(8, K / 64 / 4));   // at least four chunks per slab
         for (int ks = 1; ks <= max_ks; ks++) {
-            if (f_wm && ks != std::min(f_ks, max_ks)) continue;
+            if (f_bm && ks != std::min(f_ks, max_ks)) continue;
             const int64_t wgs = (int64_t)n_tt * n_nb * ks;
-            const int64_t rounds = (wgs + 255) / 256;
-            const double wg_us = (f16 ? 0.69 : 1.0) * 2.0 * bm * tl.bn * (double)(K / ks) / (tl.tflops * 1e6 / 256.0);
-            double t = rounds * wg_us;
-            // fp16 form: a last round that leaves CUs idle runs its workgroups faster than a full one (measured on
-            // the 13B down projection: 180 workgroups in 0.74 of a full round's time)
-            if (f16 && wgs % 256) t = (double)(wgs / 256) * wg_us + std::max((double)(wgs % 256) / 256.0, 0.74) * wg_us;
-            if (ks > 1) t += 3.0 + (double)T * N * (swi ? 2 : 1) * 4.0 * (2.0 * ks + 1.0) / (f16 ? 9.0e6 : 3.0e6);
-            if (t < best_t) { best_t = t; best = {tl.wm, tl.bn, n_tt, n_nb, ks, t, 0, 0}; }
-        }
-        // Two phases: the column blocks that fill a whole round run unsplit; the remaining blocks, which would
-        // leave most CUs idle for a second round, run with a split K (their partial sums only).  Only between one
-        // and two rounds of the 256 x 256 tile: with more rounds the workgroups stagger and the last round
-        // costs less than the model's whole round (measured: no gain, or a loss with the smaller tiles).
-        static const int two_phase = env_int("LD_GEMM_TWO_PHASE", 1);   // tuning knob
-        const int64_t n_all = (int64_t)n_tt * n_nb;
-        if (two_phase && !f_wm && tl.wm == 4 && n_all > 256 && n_all < 512) {
-            const int nb_a = (int)(n_all / 256 * 256 / n_tt), nb_b = n_nb - nb_a;
-            const double wg_us = (f16 ? 0.69 : 1.0) * 2.0 * bm * tl.bn * (double)K / (tl.tflops * 1e6 / 256.0);
-            const double t_a = (double)(((int64_t)nb_a * n_tt + 255) / 256) * wg_us;
-            for (int ks = 2; ks <= max_ks && nb_a > 0 && nb_b > 0; ks++) {
-                const int64_t rounds_b = ((int64_t)nb_b * n_tt * ks + 255) / 256;
-                const double cols_b = (double)std::min(N - nb_a * nout, nb_b * nout);
-                const double t = t_a + rounds_b * wg_us / ks + 6.0 + (double)T * cols_b * (swi ? 2 : 1) * 4.0 * (2.0 * ks + 1.0) / 3.0e6;
-                if (t < best_t) { best_t = t; best = {tl.wm, tl.bn, n_tt, n_nb, 1, t, nb_a, ks}; }
-            }
+            const double rounds = (double)(wgs / 256) + (wgs % 256 ? std::max((wgs % 256) / 256.0, last) : 0.0);
+            double t = rounds * tl->chunk_us * (K / 64) / ks;
+            if (ks > 1) t += 1.0 + us_per_mb * 4e-6 * T * N * (swi ? 2 : 1) * ks;
+            if (t < best_t) { best_t = t; best = {tl->bm, tl->bn, n_tt, n_nb, ks, t}; }
         }
     }
     return best;
 }
+
 // Most rows the small-batch kernel takes: four 16-row tiles of X fit a wave's registers beside its fragments.  Feed-
 // forward of the 7B shape at 33 / 48 / 49 / 64 rows against the kernels that took these rows before it (a 512-wide
 // slab kernel in two groups of rows, then one with X staged chunk by chunk): 105 -> 79, 111 -> 84, 129 -> 88,
@@ -905,8 +712,7 @@ int skinny_split(int T, int K) { return (K + sk_slab(skinny_tiles(T)) - 1) / sk_
 
 int split_factor(int T, int N, int K, int epi, bool f16 = false) {
     if (T <= SKINNY_MAX_ROWS) return skinny_split(T, K);
-    const BigPlan p = plan_big(T, N, K, epi, f16);
-    return std::max(p.ks, p.ks_b);
+    return plan_big(T, N, K, epi, f16).ks;
 }
 
 }  // namespace
@@ -926,7 +732,7 @@ int tail_rows(int T, int N, int K, int epi, bool f16) {
     static const int enabled = env_int("LD_GEMM_TAIL", 1);   // tuning knob: 0 keeps every row in the tiled kernel
     if (!enabled || T <= 256 || r == 0 || r > 64 || getenv("LD_GEMM_BIG")) return 0;
     const double whole = plan_big(T, N, K, epi, f16).est_us, main_part = plan_big(T - r, N, K, epi, f16).est_us;
-    const double tail = (double)N * (epi == GEMM_SWIGLU ? 2 : 1) * K * 2.0 / 4.0e6 + 12.0;   // ~4 TB/s + two launches
+    const double tail = (double)N * (epi == GEMM_SWIGLU ? 2 : 1) * K * 2.0 / 5.2e6 + 10.0;   // ~5.2 TB/s + two launches
     return main_part + tail < whole ? r : 0;
 }
 
@@ -984,78 +790,44 @@ void launch_gemm_skinny(const uint16_t *W, const uint16_t *xhi, const uint16_t *
 #undef LD_SKINNY
 }
 
-// The direct-to-LDS kernel addresses its operands with 32-bit byte offsets from the start of each matrix.
-static bool dma_offsets_fit(int T, int N, int K, int epi) {
-    const int64_t lim = (int64_t)1 << 32;
-    return (int64_t)T * K * 2 < lim && (int64_t)N * (epi == GEMM_SWIGLU ? 2 : 1) * K * 2 < lim;
-}
-
-// One launch of the big-tile kernel over output columns [col0, col1) with split factor ks (+ its reduction).
-static void launch_big_cols(const uint16_t *W, const bf16_t *hi, const bf16_t *lo, int T, int N, int K, int epi, float *y,
-                            float *partial, int wm, int bn, int n_ttiles, int ks, int col0, int col1, hipStream_t s,
-                            bool reduce, bf16_t *hi_out, bf16_t *lo_out, int f16) {
-    const int nout = epi == GEMM_SWIGLU ? bn / 2 : bn;
-    const int n_nblocks = (col1 - col0 + nout - 1) / nout;
-    const int grid = ((n_nblocks + 7) / 8) * 8 * n_ttiles * ks;
-    const int rgrid = (int)(((int64_t)T * (col1 - col0) + 255) / 256);
-#define LD_BIG(WM_, BN_, D_, EPI_)                                                                                     \
+// The big-tile kernel over all output columns (+ the split-K reduction).
+static void launch_tiles(const uint16_t *W, const bf16_t *hi, const bf16_t *lo, int T, int N, int K, int epi, float *y,
+                         float *partial, const BigPlan &p, hipStream_t s, bool reduce, bf16_t *hi_out, bf16_t *lo_out, int f16) {
+    const int grid = (p.n_nblocks * p.n_ttiles * p.ks + 7) / 8 * 8;
+#define LD_TILE_E(TERMS_, WF_, AT_, BT_, WM_, WN_, EPI_)                                                               \
     do {                                                                                                               \
-        LD_LAUNCH((k_gemm_big<WM_, BN_, D_, EPI_>), dim3(grid), dim3(128 * WM_), 0, s, W, hi, lo, T, N, K, y,           \
-                  n_ttiles, ks, partial, col0, col1, hi_out, lo_out);                                                  \
-        if (ks > 1 && reduce)                                                                                          \
-            LD_LAUNCH((k_splitk_reduce<EPI_>), dim3(rgrid), dim3(256), 0, s, partial, T, N, ks, y, col0, col1, hi_out, lo_out); \
-    } while (0)
-#define LD_DMA_M(WM_, BN_, S_, EPI_, WN_, F16_)                                                                        \
-    do {                                                                                                               \
-        constexpr int lds_bytes = ((F16_ ? 1 : 2) * 64 * WM_ + BN_) * 64 * S_;                                         \
+        constexpr int lds_bytes = tile_lds(TERMS_, WM_ * AT_ * 32, WN_ * BT_ * 32);                                    \
         static bool attr_set = false;                                                                                  \
         if (!attr_set) {                                                                                               \
-            (void)hipFuncSetAttribute((const void *)k_gemm_dma<WM_, BN_, S_, EPI_, WN_, F16_>,                         \
+            (void)hipFuncSetAttribute((const void *)k_gemm_tile<TERMS_, WF_, AT_, BT_, WM_, WN_, EPI_>,                \
                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);                          \
             attr_set = true;                                                                                           \
         }                                                                                                              \
-        LD_LAUNCH((k_gemm_dma<WM_, BN_, S_, EPI_, WN_, F16_>), dim3(grid), dim3(64 * WM_ * WN_), lds_bytes, s, W, hi,   \
-                  lo, T, N, K, y, n_ttiles, ks, partial, col0, col1, hi_out, lo_out);                                  \
+        LD_LAUNCH((k_gemm_tile<TERMS_, WF_, AT_, BT_, WM_, WN_, EPI_>), dim3(grid), dim3(256), lds_bytes, s, W, hi, lo, T, \
+                  N, K, y, p.n_ttiles, p.ks, partial, hi_out, lo_out);                                                 \
     } while (0)
-    // The fp16 form has one operand image to stage, so the 256 x 256 tile fits a fourth stage into the CU's 160 KB
-    // (128 KB): with the weight image, 5 - 9 % on the layer shapes at 2048 rows, level at 1056; a fifth changes nothing.
-#define LD_DMA(WM_, BN_, S_, EPI_, WN_)                                                                                \
+#define LD_TILE(TERMS_, WF_, AT_, BT_, WM_, WN_)                                                                       \
     do {                                                                                                               \
-        if (f16 == 2) LD_DMA_M(WM_, BN_, (WM_ == 4 ? 4 : S_), EPI_, WN_, 2);                                           \
-        else if (f16) LD_DMA_M(WM_, BN_, (WM_ == 4 ? 4 : S_), EPI_, WN_, 1);                                           \
-        else LD_DMA_M(WM_, BN_, S_, EPI_, WN_, 0);                                                                     \
-        if (ks > 1 && reduce)                                                                                          \
-            LD_LAUNCH((k_splitk_reduce<EPI_>), dim3(rgrid), dim3(256), 0, s, partial, T, N, ks, y, col0, col1, hi_out, lo_out); \
+        if (p.bm != WM_ * AT_ * 32 || p.bn != WN_ * BT_ * 32) break;                                                   \
+        if (epi == GEMM_STORE) LD_TILE_E(TERMS_, WF_, AT_, BT_, WM_, WN_, GEMM_STORE);                                 \
+        else if (epi == GEMM_ADD) LD_TILE_E(TERMS_, WF_, AT_, BT_, WM_, WN_, GEMM_ADD);                                \
+        else if constexpr (BT_ % 2 == 0) LD_TILE_E(TERMS_, WF_, AT_, BT_, WM_, WN_, GEMM_SWIGLU);                      \
     } while (0)
-    // 256-row weight tiles: operands copied straight into LDS (the slab needs a few chunks to fill the stages)
-    if (bn == 256 && (K / 32) / ks >= 4 && dma_offsets_fit(T, N, K, epi)) {
-        if (wm == 4) {          // 256 x 256: eight waves, 64 x 128 each
-            if (epi == GEMM_STORE) LD_DMA(4, 256, 3, GEMM_STORE, 2);
-            else if (epi == GEMM_ADD) LD_DMA(4, 256, 3, GEMM_ADD, 2);
-            else LD_DMA(4, 256, 3, GEMM_SWIGLU, 2);
-        } else {                // 128 x 256: eight waves, 64 x 64 each
-            if (epi == GEMM_STORE) LD_DMA(2, 256, 4, GEMM_STORE, 4);
-            else if (epi == GEMM_ADD) LD_DMA(2, 256, 4, GEMM_ADD, 4);
-            else LD_DMA(2, 256, 4, GEMM_SWIGLU, 4);
-        }
-        return;
-    }
-    if (wm == 4) {
-        if (epi == GEMM_STORE) LD_BIG(4, 256, 3, GEMM_STORE);
-        else if (epi == GEMM_ADD) LD_BIG(4, 256, 3, GEMM_ADD);
-        else LD_BIG(4, 256, 3, GEMM_SWIGLU);
-    } else if (bn == 256) {
-        if (epi == GEMM_STORE) LD_BIG(2, 256, 4, GEMM_STORE);
-        else if (epi == GEMM_ADD) LD_BIG(2, 256, 4, GEMM_ADD);
-        else LD_BIG(2, 256, 4, GEMM_SWIGLU);
+    if (f16 == 2) {
+        LD_TILE(1, 2, 4, 4, 2, 2); LD_TILE(1, 2, 2, 6, 4, 1); LD_TILE(1, 2, 2, 5, 4, 1); LD_TILE(1, 2, 2, 4, 2, 2);
+    } else if (f16) {
+        LD_TILE(1, 1, 4, 4, 2, 2); LD_TILE(1, 1, 2, 6, 4, 1); LD_TILE(1, 1, 2, 5, 4, 1); LD_TILE(1, 1, 2, 4, 2, 2);
     } else {
-        if (epi == GEMM_STORE) LD_BIG(2, 128, 4, GEMM_STORE);
-        else if (epi == GEMM_ADD) LD_BIG(2, 128, 4, GEMM_ADD);
-        else LD_BIG(2, 128, 4, GEMM_SWIGLU);
+        LD_TILE(2, 0, 2, 4, 2, 2); LD_TILE(2, 0, 1, 6, 4, 1); LD_TILE(2, 0, 2, 2, 2, 2); LD_TILE(2, 0, 3, 2, 1, 4); LD_TILE(2, 0, 5, 2, 1, 4);
+        LD_TILE(2, 0, 3, 4, 2, 2);
     }
-#undef LD_BIG
-#undef LD_DMA
-#undef LD_DMA_M
+#undef LD_TILE
+#undef LD_TILE_E
+    if (p.ks <= 1 || !reduce) return;
+    const int rgrid = (int)(((int64_t)T * N + 255) / 256);
+    if (epi == GEMM_STORE) LD_LAUNCH((k_splitk_reduce<GEMM_STORE>), dim3(rgrid), dim3(256), 0, s, partial, T, N, p.ks, y, 0, N, hi_out, lo_out);
+    else if (epi == GEMM_ADD) LD_LAUNCH((k_splitk_reduce<GEMM_ADD>), dim3(rgrid), dim3(256), 0, s, partial, T, N, p.ks, y, 0, N, hi_out, lo_out);
+    else LD_LAUNCH((k_splitk_reduce<GEMM_SWIGLU>), dim3(rgrid), dim3(256), 0, s, partial, T, N, p.ks, y, 0, N, hi_out, lo_out);
 }
 
 // Where the rows of a residual GEMM go next: the operand image of the normalised GEMM that follows.
@@ -1064,13 +836,10 @@ struct RowsNext { const float *g; float eps; bf16_t *hi, *lo; const RopeKvArgs *
 // nx != nullptr with GEMM_ADD: y's rows are finished and turned into the next operand by one fused kernel in
 // place of the split-K reduction.  With GEMM_SWIGLU: the epilogue (or the split-K reduction) writes its result
 // as the next operand instead of floats.
-// Whether the fp16 form serves a product of T rows: the direct-to-LDS kernel with 256-wide weight tiles must be the
-// plan's choice in every phase.
-static bool f16_plan_ok(const BigPlan &p, int K) {
-    return p.bn == 256 && (K / 32) / std::max(p.ks, 1) >= 4 && (p.nb_a == 0 || (K / 32) / std::max(p.ks_b, 1) >= 4);
-}
+// Whether the fp16 form serves a product of T rows: every product of the big-tile kernel.
 bool gemm_f16_rows(int T, int N, int K, int epi) {
-    return T > 64 && dma_offsets_fit(T, N, K, epi) && f16_plan_ok(plan_big(T, N, K, epi, true), K);
+    (void)N; (void)K; (void)epi;
+    return T > SKINNY_MAX_ROWS;
 }
 
 // f16_flag != nullptr (more than 64 rows, gemm_f16_rows): the rows' images are turned into one fp16 image in place
@@ -1110,16 +879,8 @@ static void gemm_rows(const uint16_t *W, bf16_t *hi, const bf16_t *lo, int T, in
         const int64_t n8 = (int64_t)T * K / 8;
         LD_LAUNCH(k_split_to_f16, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, s, hi, lo, n8, f16_flag);
     }
-    if (p.nb_a > 0) {
-        // two phases: whole rounds of unsplit tiles, then the remaining column blocks with a split K
-        const int nout = (epi == GEMM_SWIGLU ? p.bn / 2 : p.bn), mid = p.nb_a * nout;
-        launch_big_cols(W, hi, lo, T, N, K, epi, y, partial, p.wm, p.bn, p.n_ttiles, 1, 0, mid, s, true, ho, lo_o, f16);
-        launch_big_cols(W, hi, lo, T, N, K, epi, y, partial, p.wm, p.bn, p.n_ttiles, p.ks_b, mid, N, s, !chain_add, ho, lo_o, f16);
-        if (chain_add) finish(p.ks_b, mid, N);
-    } else {
-        launch_big_cols(W, hi, lo, T, N, K, epi, y, partial, p.wm, p.bn, p.n_ttiles, p.ks, 0, N, s, !chain_add, ho, lo_o, f16);
-        if (chain_add) finish(p.ks, 0, N);
-    }
+    launch_tiles(W, hi, lo, T, N, K, epi, y, partial, p, s, !chain_add, ho, lo_o, f16);
+    if (chain_add) finish(p.ks, 0, N);
 }
 
 void launch_gemm(const uint16_t *W, uint16_t *xs, int T, int N, int K, int epi, float *y, hipStream_t s,

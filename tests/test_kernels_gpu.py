@@ -438,6 +438,45 @@ def test_linear_big_tile_every_plan(plan, epi, monkeypatch):
     assert err <= 2e-5, err
 
 
+@pytest.mark.parametrize("form,rows,cols", [("two", r, c) for r, c in ((96, 256), (128, 128), (128, 192), (128, 256), (160, 256), (192, 256))]
+                         + [("f16", r, c) for r, c in ((128, 256), (256, 160), (256, 192), (256, 256))])
+@pytest.mark.parametrize("K,ks", [(128, 1), (1152, 1), (1152, 4)])
+def test_linear_every_tile(form, rows, cols, K, ks, monkeypatch):
+    """Every tile of the big-tile kernel, in both forms (two bf16 terms; one fp16 term on the fp16 image and on the bf16
+    matrix), forced in turn on a shape that is ragged in rows and columns: the fewest chunks of K the pipeline has to
+    cope with (2), an ordinary run, and split K with uneven slabs (18 chunks over 4).  Against float64 on the inputs
+    as the form rounds them: |error| <= 2^-16 sum_k |w x| (float32 sums of up to 1152 terms stay well below; for two
+    terms 2^-18 per activation adds to it).  The 160-column tile has no SwiGLU form."""
+    monkeypatch.setenv("LD_GEMM_BIG", "%d,%d,%d" % (rows, cols, ks))
+    T, N = 333, 301
+    W = _mat(41, K, 2 * N, K, "bf16").to(DEV); x = gen.normal(41, 2, (T, K), device=DEV)
+    y0 = gen.normal(41, 4, (T, N), device=DEV)
+    scratch = torch.empty(ld.ldk_linear_scratch_bytes(T, N, K, ld.LDK_SWIGLU), dtype=torch.uint8, device=DEV)
+    flag = torch.zeros(1, dtype=torch.int32, device=DEV)
+    Wh = torch.empty_like(W, dtype=torch.float16); ld.ldk_weights_to_f16(W, Wh, flag)
+    hi = x.bfloat16().float()
+    xr = ((hi + (x - hi).bfloat16().float()).half() if form == "f16" else x).double()
+    full, mag = xr @ W.double().t(), xr.abs() @ W.double().abs().t()
+    for epi, n in ((ld.LDK_STORE, N), (ld.LDK_ADD, N)) + (((ld.LDK_SWIGLU, 2 * N),) if cols != 160 else ()):
+        outs = []
+        for image in ((None, Wh) if form == "f16" else (None,)):
+            y = y0.clone() if epi == ld.LDK_ADD else torch.full((T, N), float("nan"), device=DEV)
+            if form == "f16":
+                ld.ldk_linear_f16(W[:n], x, y, flag, epi, scratch=scratch, W_f16=None if image is None else image[:n])
+            else:
+                ld.ldk_linear(W[:n], x, y, epi, scratch=scratch)
+            outs.append(y)
+        if form == "f16":
+            assert torch.equal(outs[0], outs[1]) and int(flag.item()) == 0
+        a = full[:, :N]
+        if epi == ld.LDK_SWIGLU:      # |d(silu(a) b)| <= 1.1 |b| |da| + |silu(a)| |db|
+            ref = torch.nn.functional.silu(a) * full[:, N:]
+            bound = 2.0 ** -16 * (1.1 * full[:, N:].abs() * mag[:, :N] + torch.nn.functional.silu(a).abs() * mag[:, N:]) + 1e-6 * ref.abs()
+        else:
+            ref, bound = a + (y0.double() if epi == ld.LDK_ADD else 0), 2.0 ** -16 * mag[:, :N] + 1e-6
+        assert ((outs[-1].double() - ref).abs() <= bound + 1e-7).all(), epi
+
+
 def test_linear_matrix_core_7b_shapes_sampled():
     """Launch shapes of the batch-32 decode step, of a 256-row prefill chunk, of a mixed step (32 decode rows
     + four 256-row chunks) and of a 2048-row chunk beside 63 decode rows, sampled outputs.  The last two have
