@@ -81,8 +81,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
                                                          const int4 *__restrict__ tiles, int H, int window,
                                                          float scale_log2e, float *__restrict__ out,
                                                          float *__restrict__ part_o, float *__restrict__ part_ml,
-                                                         bf16_t *__restrict__ xs_hi, bf16_t *__restrict__ xs_lo,
-                                                         int *__restrict__ f16_flag) {
+                                                         ld::OperandImage image, int *__restrict__ f16_flag) {
     __shared__ __attribute__((aligned(16))) bf16_t ks[2][KVB][KLD];
     __shared__ __attribute__((aligned(16))) bf16_t vt[2][HD][VLD];
     const int4 tile = tiles[blockIdx.x];      // x: first row, y: rows (<= 128), z: position of first row, w: seq slot
@@ -335,11 +334,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
                 const float4 v = make_float4(mul_rounded(o[nt][4 * a], inv), mul_rounded(o[nt][4 * a + 1], inv),
                                              mul_rounded(o[nt][4 * a + 2], inv), mul_rounded(o[nt][4 * a + 3], inv));
                 const int64_t e = at + nt * 32 + 8 * a + 4 * half;
-                if (xs_hi) {      // the output projection's (hi, lo) operand instead of floats
-                    uint32_t l0, l1;
-                    const uint32_t h0 = split2_bf16(v.x, v.y, l0), h1 = split2_bf16(v.z, v.w, l1);
-                    *reinterpret_cast<uint2 *>(xs_hi + e) = make_uint2(h0, h1);
-                    *reinterpret_cast<uint2 *>(xs_lo + e) = make_uint2(l0, l1);
+                if (image.hi) {      // the output projection's operand instead of floats
+                    store_operand4(image, tile.x + qi, e, v);
                 } else {
                     *reinterpret_cast<float4 *>(out + e) = v;
                 }
@@ -352,8 +348,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
 __global__ __launch_bounds__(128) void k_attn_prefill_merge(const int4 *__restrict__ tiles, int H, int n_splits,
                                                             const float *__restrict__ part_o,
                                                             const float *__restrict__ part_ml,
-                                                            float *__restrict__ out, bf16_t *__restrict__ xs_hi,
-                                                            bf16_t *__restrict__ xs_lo) {
+                                                            float *__restrict__ out, ld::OperandImage image) {
     const int4 tile = tiles[blockIdx.y >> 7];
     const int r = blockIdx.y & 127, h = blockIdx.x, d = threadIdx.x;
     if (r >= tile.y) return;
@@ -367,7 +362,7 @@ __global__ __launch_bounds__(128) void k_attn_prefill_merge(const int4 *__restri
         L += a * part_ml[(base + z) * 2 + 1];
     }
     const int64_t e = ((int64_t)(tile.x + r) * H + h) * HD + d;
-    if (xs_hi) store_split(xs_hi, xs_lo, e, o / L);
+    if (image.hi) store_operand(image, tile.x + r, e, o / L);
     else out[e] = o / L;
 }
 
@@ -397,21 +392,21 @@ size_t prefill_attention_scratch_bytes() {
 
 void launch_prefill_attention(const float *q, int q_stride, const uint16_t *pool, int Hkv, const int32_t *table,
                               int table_stride, const int32_t *tiles, int n_tiles, int H, int window, int max_pos,
-                              float *out, void *scratch, size_t scratch_bytes, hipStream_t s, uint16_t *xs_hi,
-                              uint16_t *xs_lo, int *f16_flag) {
+                              float *out, void *scratch, size_t scratch_bytes, hipStream_t s,
+                              const OperandImage &image, int *f16_flag) {
     const float sl2 = 1.4426950408889634f / sqrtf((float)HD);
     const int ns = scratch ? prefill_attention_splits(n_tiles, H, max_pos, window, scratch_bytes) : 1;
     float *part_o = (float *)scratch;
     float *part_ml = part_o ? part_o + (size_t)n_tiles * 128 * H * ns * HD : nullptr;
     if (f16_flag)
         LD_LAUNCH(k_attn_prefill<true>, dim3(n_tiles, H, ns), dim3(256), 0, s, q, q_stride, pool, Hkv, table, table_stride,
-                  (const int4 *)tiles, H, window, sl2, out, part_o, part_ml, xs_hi, xs_lo, f16_flag);
+                  (const int4 *)tiles, H, window, sl2, out, part_o, part_ml, image, f16_flag);
     else
         LD_LAUNCH(k_attn_prefill<false>, dim3(n_tiles, H, ns), dim3(256), 0, s, q, q_stride, pool, Hkv, table, table_stride,
-                  (const int4 *)tiles, H, window, sl2, out, part_o, part_ml, xs_hi, xs_lo, f16_flag);
+                  (const int4 *)tiles, H, window, sl2, out, part_o, part_ml, image, f16_flag);
     if (ns > 1)
         LD_LAUNCH(k_attn_prefill_merge, dim3(H, n_tiles * 128), dim3(128), 0, s, (const int4 *)tiles, H, ns, part_o,
-                  part_ml, out, xs_hi, xs_lo);
+                  part_ml, out, image);
 }
 
 }  // namespace ld

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <cstdint>
+#include "ld_internal.h"
 
 namespace ldd {
 
@@ -29,12 +30,41 @@ __device__ __forceinline__ uint32_t split2_bf16(float a, float b, uint32_t &lo) 
     return hi;
 }
 
-// Writes v as a GEMM operand: high and low bf16 parts at the same index of the two images.
-__device__ __forceinline__ void store_split(bf16_t *__restrict__ hi, bf16_t *__restrict__ lo, int64_t idx, float v) {
-    uint32_t l;
-    const uint32_t h = split2_bf16(v, 0.f, l);
-    hi[idx] = (bf16_t)h;
-    lo[idx] = (bf16_t)l;
+// fp16 of the sums of the two bf16 terms of a and b (exact in float32; one rounding), packed.  big: one does not fit.
+__device__ __forceinline__ uint32_t split2_f16(float a, float b, bool &big) {
+    uint32_t lo;
+    const uint32_t hi = split2_bf16(a, b, lo);
+    const float fa = __uint_as_float(hi << 16) + __uint_as_float(lo << 16);
+    const float fb = __uint_as_float(hi & 0xffff0000u) + __uint_as_float(lo & 0xffff0000u);
+    big = big || !(fabsf(fa) <= 65504.f) || !(fabsf(fb) <= 65504.f);
+    return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)fa) | ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)fb) << 16);
+}
+
+// Writes v as a GEMM operand entry of image row t at index idx (idx: four consecutive entries, a multiple of 4).
+__device__ __forceinline__ void store_operand(const ld::OperandImage &o, int t, int64_t idx, float v) {
+    if (t < o.f16_rows) {
+        bool big = false;
+        o.hi[idx] = (bf16_t)split2_f16(v, 0.f, big);
+        if (big) *o.f16_flag = 1;
+    } else {
+        uint32_t l;
+        const uint32_t h = split2_bf16(v, 0.f, l);
+        o.hi[idx] = (bf16_t)h;
+        o.lo[idx] = (bf16_t)l;
+    }
+}
+__device__ __forceinline__ void store_operand4(const ld::OperandImage &o, int t, int64_t idx, const float4 &v) {
+    if (t < o.f16_rows) {
+        bool big = false;
+        const uint32_t a = split2_f16(v.x, v.y, big), b = split2_f16(v.z, v.w, big);
+        *reinterpret_cast<uint2 *>(o.hi + idx) = make_uint2(a, b);
+        if (big) *o.f16_flag = 1;
+    } else {
+        uint32_t l0, l1;
+        const uint32_t h0 = split2_bf16(v.x, v.y, l0), h1 = split2_bf16(v.z, v.w, l1);
+        *reinterpret_cast<uint2 *>(o.hi + idx) = make_uint2(h0, h1);
+        *reinterpret_cast<uint2 *>(o.lo + idx) = make_uint2(l0, l1);
+    }
 }
 // Index of entry (row t, column k) of an operand image of T rows laid out [K / 8][T][8].
 __device__ __forceinline__ int64_t octet_index(int t, int k, int T) { return ((int64_t)(k >> 3) * T + t) * 8 + (k & 7); }

@@ -20,7 +20,9 @@ size_t gemm_scratch_bytes(int T, int N, int K, int epi);
 // hi = bf16(v), lo = bf16(v - hi), stored as two [T, K] bf16 matrices (hi first); octets: each as [K / 8][T][8]
 // instead, the layout the small-batch kernel reads faster (gemm_takes_octets(T); launch_gemm has to be told).
 bool gemm_takes_octets(int T);
-void launch_norm_split(const float *x, const float *g, float eps, int T, int K, uint16_t *xs, hipStream_t s, bool octets = false);
+// The first f16_rows rows are written as one fp16 image instead (see OperandImage).
+void launch_norm_split(const float *x, const float *g, float eps, int T, int K, uint16_t *xs, hipStream_t s, bool octets = false,
+                       int f16_rows = 0, int *f16_flag = nullptr);
 
 // y = epilogue(X W^T) with X given by its split image at the start of the scratch area xs
 // (gemm_scratch_bytes bytes); W bf16 [N, K] ([2N, K] for GEMM_SWIGLU).
@@ -33,17 +35,18 @@ void launch_norm_split(const float *x, const float *g, float eps, int T, int K, 
 // with the values the separate rotate-and-append pass would write (k and v are not stored to y).
 //
 // f16_flag != nullptr: the caller allows the rows of this pass to enter the product rounded to fp16 (11 significant
-// bits instead of the 16 of the two-term split) where that pays: more than 64 rows in the big-tile kernel
-// (gemm_f16_rows), i.e. the rows of prefill chunks; the rows of the split image that take this form are overwritten
-// with their fp16 values.  The caller has made sure that the matrix holds nothing beyond the fp16 range
-// (launch_weight_range_check); *f16_flag (device memory) is set to 1 when an activation does not fit, and the
-// results of the pass are then to be thrown away and the pass repeated without the flag.  W16 != nullptr: W's fp16
-// image (launch_weight_to_f16), read in W's place by the rows that take the fp16 form, which otherwise turn every
-// weight fragment into fp16 on its way to the matrix cores; same values either way, bit-equal results.
-struct GemmNext { const float *g; float eps; uint16_t *xs; const RopeKvArgs *rope = nullptr; };
+// bits instead of the 16 of the two-term split) where that pays: more than 64 rows in the big-tile kernel, i.e. the rows
+// of prefill chunks.  The first gemm_f16_rows(T, N, K, epi) rows of the image are then one fp16 image, which its producer
+// has written (OperandImage: *f16_flag, device memory, is set to 1 when an activation does not fit, and the results of the
+// pass are to be thrown away and the pass repeated without the flag); next->f16_rows is that number for the product that
+// takes the next operand.  The caller has made sure that the matrix holds nothing beyond the fp16 range
+// (launch_weight_range_check).  W16 != nullptr: W's fp16 image (launch_weight_to_f16), read in W's place by the rows that
+// take the fp16 form, which otherwise turn every weight fragment into fp16 on its way to the matrix cores; same values
+// either way, bit-equal results.
+struct GemmNext { const float *g; float eps; uint16_t *xs; const RopeKvArgs *rope = nullptr; int f16_rows = 0; };
 void launch_gemm(const uint16_t *W, uint16_t *xs, int T, int N, int K, int epi, float *y, hipStream_t s,
                  const GemmNext *next = nullptr, int *f16_flag = nullptr, const uint16_t *W16 = nullptr, bool octets = false);
-bool gemm_f16_rows(int T, int N, int K, int epi);
+int gemm_f16_rows(int T, int N, int K, int epi);
 // *flag (device memory) = 1 if the bf16 matrix W (n elements, a multiple of 8) holds a value beyond +-65504 or not a number.
 void launch_weight_range_check(const uint16_t *W, int64_t n, int *flag, hipStream_t s);
 // The same check, and out[n] = W as fp16 (exact where the flag stays clear, values below 2^-14 in magnitude aside).

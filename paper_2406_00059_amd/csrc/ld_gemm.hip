@@ -66,11 +66,11 @@ __device__ __forceinline__ float4 scale4(const float4 &v, float rstd, const floa
 }
 
 // One workgroup per row.  ROW_REGS > 0: the row (at most 1024 * ROW_REGS long) is read once and kept in registers, all
-// loads in flight together.  OCT: the images are written as [K / 8][T][8] (see k_gemm_skinny), else row-major.
+// loads in flight together.  OCT: the images are written as [K / 8][T][8] (see k_gemm_skinny), else row-major.  (The fp16
+// rows of a long pass, 2111 x 5120, were split here and rounded in a pass of their own before: 30 + 18 us.)
 template <int ROW_REGS, bool OCT>
 __global__ __launch_bounds__(256) void k_norm_split(const float *__restrict__ x, const float *__restrict__ g,
-                                                    float eps, int K, bf16_t *__restrict__ hi,
-                                                    bf16_t *__restrict__ lo) {
+                                                    float eps, int K, ld::OperandImage out) {
     __shared__ float red[4];
     const int t = blockIdx.x;
     const float *row = x + (int64_t)t * K;
@@ -99,11 +99,7 @@ __global__ __launch_bounds__(256) void k_norm_split(const float *__restrict__ x,
     }
     auto store = [&](int i, float4 v) {
         if (g) v = scale4(v, rstd, *reinterpret_cast<const float4 *>(g + i));
-        uint32_t l0, l1;
-        const uint32_t h0 = split2_bf16(v.x, v.y, l0), h1 = split2_bf16(v.z, v.w, l1);
-        const int64_t at = OCT ? octet_index(t, i, gridDim.x) : (int64_t)t * K + i;
-        *reinterpret_cast<uint2 *>(hi + at) = make_uint2(h0, h1);
-        *reinterpret_cast<uint2 *>(lo + at) = make_uint2(l0, l1);
+        store_operand4(out, t, OCT ? octet_index(t, i, gridDim.x) : (int64_t)t * K + i, v);
     };
     if constexpr (ROW_REGS > 0) {
 #pragma unroll
@@ -112,27 +108,6 @@ __global__ __launch_bounds__(256) void k_norm_split(const float *__restrict__ x,
     } else {
         for (int i = threadIdx.x * 4; i < K; i += 1024) store(i, *reinterpret_cast<const float4 *>(row + i));
     }
-}
-
-// The (hi, lo) images of n8 * 8 activations become one fp16 image in place of the high one (hi + lo is exact in
-// float32; one rounding to fp16).  *flag is set when a value does not fit into fp16.
-__global__ __launch_bounds__(256) void k_split_to_f16(bf16_t *__restrict__ hi, const bf16_t *__restrict__ lo, int64_t n8,
-                                                      int *__restrict__ flag) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n8) return;
-    const u32x4 h = *reinterpret_cast<const u32x4 *>(hi + i * 8), l = *reinterpret_cast<const u32x4 *>(lo + i * 8);
-    uint32_t o[4];
-    bool big = false;
-#pragma unroll
-    for (int e = 0; e < 4; e++) {
-        const float a = __uint_as_float(h[e] << 16) + __uint_as_float(l[e] << 16);
-        const float b = __uint_as_float(h[e] & 0xffff0000u) + __uint_as_float(l[e] & 0xffff0000u);
-        big = big || !(fabsf(a) <= F16_LIMIT) || !(fabsf(b) <= F16_LIMIT);
-        const _Float16 ha = (_Float16)a, hb = (_Float16)b;
-        o[e] = (uint32_t)__builtin_bit_cast(uint16_t, ha) | ((uint32_t)__builtin_bit_cast(uint16_t, hb) << 16);
-    }
-    *reinterpret_cast<u32x4 *>(hi + i * 8) = (u32x4){o[0], o[1], o[2], o[3]};
-    if (big) *flag = 1;
 }
 
 // *flag is set when a bf16 matrix holds a value that fp16 cannot (beyond +-65504, or not a number).
@@ -371,7 +346,7 @@ template <int TERMS, int WF, int AT, int BT, int WM, int WN, int EPI>
 __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16_t *__restrict__ W, const bf16_t *__restrict__ xhi,
                                                       const bf16_t *__restrict__ xlo, int T, int N, int K,
                                                       float *__restrict__ y, int n_ttiles, int ks,
-                                                      float *__restrict__ partial, bf16_t *__restrict__ hi_out, bf16_t *__restrict__ lo_out) {
+                                                      float *__restrict__ partial, ld::OperandImage out) {
     constexpr bool SWI = (EPI == ld::GEMM_SWIGLU);
     static_assert(WM * WN == 4 && (!SWI || BT % 2 == 0), "four waves; a wave column holds gate and up tiles");
     constexpr int BM = WM * AT * 32, BN = WN * BT * 32, NOUT = SWI ? BN / 2 : BN;
@@ -545,7 +520,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16_t *__restrict__
                     else if constexpr (EPI == ld::GEMM_ADD) *dst += acc[a][j][e];
                     else {
                         const float v = swiglu(acc[a][j][e], acc[a][j + WOUT][e]);
-                        if (hi_out) store_split(hi_out, lo_out, (int64_t)t * N + col, v);
+                        if (out.hi) store_operand(out, t, (int64_t)t * N + col, v);
                         else *dst = v;
                     }
                 }
@@ -556,13 +531,11 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16_t *__restrict__
 // Adds the ks K-slab partial sums in slab order and applies the epilogue.  One thread per output.
 template <int EPI>
 __global__ __launch_bounds__(256) void k_splitk_reduce(const float *__restrict__ partial, int T, int N, int ks,
-                                                       float *__restrict__ y, int col0, int col1,
-                                                       bf16_t *__restrict__ hi_out, bf16_t *__restrict__ lo_out) {
+                                                       float *__restrict__ y, ld::OperandImage out) {
     constexpr int WR = (EPI == ld::GEMM_SWIGLU) ? 2 : 1;
-    const int nc = col1 - col0;                    // output columns [col0, col1) of N
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)T * nc) return;
-    const int t = (int)(idx / nc), n = col0 + (int)(idx % nc);
+    if (idx >= (int64_t)T * N) return;
+    const int t = (int)(idx / N), n = (int)(idx % N);
     const float *p0 = partial + (int64_t)t * (WR * N) + n;
     const float a = slab_sum(p0, (int64_t)T * (WR * N), ks, 0.f);
     const float b = WR == 2 ? slab_sum(p0 + N, (int64_t)T * (WR * N), ks, 0.f) : 0.f;
@@ -571,67 +544,72 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float *__restrict__
     else if constexpr (EPI == ld::GEMM_ADD) *dst += a;
     else {
         const float v = swiglu(a, b);
-        if (hi_out) store_split(hi_out, lo_out, (int64_t)t * N + n, v);
+        if (out.hi) store_operand(out, t, (int64_t)t * N + n, v);
         else *dst = v;
     }
 }
 
-// Residual rows that feed the next normalised GEMM: finishes y (adds the ks K-slab partial sums of the
-// output columns [col0, col1) in slab order, as k_splitk_reduce<GEMM_ADD> does; the other columns were
-// already added by the product kernel's epilogue) and writes the next operand split(y * rsqrt(mean y^2 + eps) * g)
-// in the same pass over the row, with k_norm_split's arithmetic in k_norm_split's order: the results are those
-// of the two separate kernels, bit for bit.  One workgroup per row; N a multiple of 4.
+// Residual rows that feed the next normalised GEMM: finishes y (adds the ks K-slab partial sums in slab order, as
+// k_splitk_reduce<GEMM_ADD> does; ks 0: the product kernel's epilogue has added them) and writes the next operand
+// split(y * rsqrt(mean y^2 + eps) * g) in the same pass over the row, with k_norm_split's arithmetic in
+// k_norm_split's order: the results are those of the two separate kernels, bit for bit.  One workgroup per row; N a
+// multiple of 4.  ROW_REGS as there: the row stays in registers between the two halves.
+template <int ROW_REGS>
 __global__ __launch_bounds__(256) void k_reduce_add_norm_split(const float *__restrict__ partial, int T, int N, int ks,
-                                                               int col0, int col1, float *__restrict__ y,
-                                                               const float *__restrict__ g, float eps,
-                                                               bf16_t *__restrict__ hi, bf16_t *__restrict__ lo) {
+                                                               float *__restrict__ y, const float *__restrict__ g, float eps,
+                                                               ld::OperandImage out) {
     __shared__ float red[4];
     const int t = blockIdx.x;
     float *row = y + (int64_t)t * N;
     const float *prow = partial + (int64_t)t * N;
     const int64_t slab = (int64_t)T * N;
     float ss = 0.f;
-    for (int i = threadIdx.x * 4; i < N; i += 1024) {
+    float4 keep[ROW_REGS > 0 ? ROW_REGS : 1];
+    auto finish = [&](int i) {
         float4 v = *reinterpret_cast<const float4 *>(row + i);
-        if (i >= col0 && i + 3 < col1) {      // all four columns still miss their slab sums
+        if (ks) {
             const float4 a = slab_sum(reinterpret_cast<const float4 *>(prow + i), slab / 4, ks, make_float4(0.f, 0.f, 0.f, 0.f));
             v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
             *reinterpret_cast<float4 *>(row + i) = v;
-        } else if (i + 3 >= col0 && i < col1) {      // some of them do
-            if (i >= col0 && i < col1) v.x += slab_sum(prow + i, slab, ks, 0.f);
-            if (i + 1 >= col0 && i + 1 < col1) v.y += slab_sum(prow + i + 1, slab, ks, 0.f);
-            if (i + 2 >= col0 && i + 2 < col1) v.z += slab_sum(prow + i + 2, slab, ks, 0.f);
-            if (i + 3 >= col0 && i + 3 < col1) v.w += slab_sum(prow + i + 3, slab, ks, 0.f);
-            *reinterpret_cast<float4 *>(row + i) = v;
         }
-        ss = add_squares(ss, v);
+        return v;
+    };
+    if constexpr (ROW_REGS > 0) {
+#pragma unroll
+        for (int u = 0; u < ROW_REGS; u++)
+            if (threadIdx.x * 4 + u * 1024 < N) keep[u] = finish(threadIdx.x * 4 + u * 1024);
+#pragma unroll
+        for (int u = 0; u < ROW_REGS; u++)
+            if (threadIdx.x * 4 + u * 1024 < N) ss = add_squares(ss, keep[u]);
+    } else {
+        for (int i = threadIdx.x * 4; i < N; i += 1024) ss = add_squares(ss, finish(i));
     }
     ss = wave_sum(ss);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
     __syncthreads();
     const float rstd = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / N + eps);
-    for (int i = threadIdx.x * 4; i < N; i += 1024) {
-        float4 v = *reinterpret_cast<const float4 *>(row + i);     // this thread's own stores of the first pass
-        const float4 gv = *reinterpret_cast<const float4 *>(g + i);
-        v = scale4(v, rstd, gv);
-        uint32_t l0, l1;
-        const uint32_t h0 = split2_bf16(v.x, v.y, l0), h1 = split2_bf16(v.z, v.w, l1);
-        *reinterpret_cast<uint2 *>(hi + (int64_t)t * N + i) = make_uint2(h0, h1);
-        *reinterpret_cast<uint2 *>(lo + (int64_t)t * N + i) = make_uint2(l0, l1);
+    auto store = [&](int i, const float4 &v) {
+        store_operand4(out, t, (int64_t)t * N + i, scale4(v, rstd, *reinterpret_cast<const float4 *>(g + i)));
+    };
+    if constexpr (ROW_REGS > 0) {
+#pragma unroll
+        for (int u = 0; u < ROW_REGS; u++)
+            if (threadIdx.x * 4 + u * 1024 < N) store(threadIdx.x * 4 + u * 1024, keep[u]);
+    } else {
+        for (int i = threadIdx.x * 4; i < N; i += 1024) store(i, *reinterpret_cast<const float4 *>(row + i));   // this thread's own stores
     }
 }
 
-// Rows of the q-k-v projection: finishes them (split-K slab sums of the columns [col0, col1) in slab order; the
-// other columns are already in y) and does what the rotate-and-append pass does, one wave per (head, row): q heads
+// Rows of the q-k-v projection: finishes them (split-K slab sums in slab order; ks 0: they are already in y) and does what the rotate-and-append pass does, one wave per (head, row): q heads
 // rotated into y, rotated k heads and v heads into the paged pool.  Row t of this launch is row row0 + t of the pass.
-__global__ __launch_bounds__(64) void k_reduce_rope_kv(const float *__restrict__ partial, int T, int N, int ks, int col0,
-                                                       int col1, float *__restrict__ y, ld::RopeKvArgs rk, int row0) {
+__global__ __launch_bounds__(64) void k_reduce_rope_kv(const float *__restrict__ partial, int T, int N, int ks,
+                                                       float *__restrict__ y, ld::RopeKvArgs rk, int row0) {
     const int t = blockIdx.y, hh = blockIdx.x, i = threadIdx.x, half = rk.hd / 2, hd = rk.hd;
     if (i >= half) return;
     const float *prow = partial + (int64_t)t * N;
     float *row = y + (int64_t)t * N;
     const int64_t slab = (int64_t)T * N;
-    auto val = [&](int col) { return col >= col0 && col < col1 ? slab_sum(prow + col, slab, ks, 0.f) : row[col]; };
+    auto val = [&](int col) { return ks ? slab_sum(prow + col, slab, ks, 0.f) : row[col]; };
     const float2 c = rk.cos_sin[(int64_t)(row0 + t) * half + i];
     if (hh < rk.H) {
         const float2 r = rope_rotate(val(hh * hd + i), val(hh * hd + i + half), c);
@@ -754,12 +732,13 @@ size_t gemm_scratch_bytes(int T, int N, int K, int epi) {
 
 bool gemm_takes_octets(int T) { return T >= 2 && T <= SKINNY_MAX_ROWS; }
 
-void launch_norm_split(const float *x, const float *g, float eps, int T, int K, uint16_t *xs, hipStream_t s, bool octets) {
-    bf16_t *lo = xs + (size_t)T * K;
+void launch_norm_split(const float *x, const float *g, float eps, int T, int K, uint16_t *xs, hipStream_t s, bool octets,
+                       int f16_rows, int *f16_flag) {
+    const OperandImage out{xs, xs + (size_t)T * K, f16_rows, f16_flag};
 #define LD_NS(R_)                                                                                                      \
     do {                                                                                                               \
-        if (octets) LD_LAUNCH((k_norm_split<R_, true>), dim3(T), dim3(256), 0, s, x, g, eps, K, xs, lo);               \
-        else LD_LAUNCH((k_norm_split<R_, false>), dim3(T), dim3(256), 0, s, x, g, eps, K, xs, lo);                     \
+        if (octets) LD_LAUNCH((k_norm_split<R_, true>), dim3(T), dim3(256), 0, s, x, g, eps, K, out);                  \
+        else LD_LAUNCH((k_norm_split<R_, false>), dim3(T), dim3(256), 0, s, x, g, eps, K, out);                        \
     } while (0)
     if (K <= 5 * 1024) LD_NS(5);
     else if (K <= 14 * 1024) LD_NS(14);
@@ -792,7 +771,7 @@ void launch_gemm_skinny(const uint16_t *W, const uint16_t *xhi, const uint16_t *
 
 // The big-tile kernel over all output columns (+ the split-K reduction).
 static void launch_tiles(const uint16_t *W, const bf16_t *hi, const bf16_t *lo, int T, int N, int K, int epi, float *y,
-                         float *partial, const BigPlan &p, hipStream_t s, bool reduce, bf16_t *hi_out, bf16_t *lo_out, int f16) {
+                         float *partial, const BigPlan &p, hipStream_t s, bool reduce, const OperandImage &out, int f16) {
     const int grid = (p.n_nblocks * p.n_ttiles * p.ks + 7) / 8 * 8;
 #define LD_TILE_E(TERMS_, WF_, AT_, BT_, WM_, WN_, EPI_)                                                               \
     do {                                                                                                               \
@@ -804,7 +783,7 @@ static void launch_tiles(const uint16_t *W, const bf16_t *hi, const bf16_t *lo, 
             attr_set = true;                                                                                           \
         }                                                                                                              \
         LD_LAUNCH((k_gemm_tile<TERMS_, WF_, AT_, BT_, WM_, WN_, EPI_>), dim3(grid), dim3(256), lds_bytes, s, W, hi, lo, T, \
-                  N, K, y, p.n_ttiles, p.ks, partial, hi_out, lo_out);                                                 \
+                  N, K, y, p.n_ttiles, p.ks, partial, out);                                                            \
     } while (0)
 #define LD_TILE(TERMS_, WF_, AT_, BT_, WM_, WN_)                                                                       \
     do {                                                                                                               \
@@ -825,85 +804,67 @@ static void launch_tiles(const uint16_t *W, const bf16_t *hi, const bf16_t *lo, 
 #undef LD_TILE_E
     if (p.ks <= 1 || !reduce) return;
     const int rgrid = (int)(((int64_t)T * N + 255) / 256);
-    if (epi == GEMM_STORE) LD_LAUNCH((k_splitk_reduce<GEMM_STORE>), dim3(rgrid), dim3(256), 0, s, partial, T, N, p.ks, y, 0, N, hi_out, lo_out);
-    else if (epi == GEMM_ADD) LD_LAUNCH((k_splitk_reduce<GEMM_ADD>), dim3(rgrid), dim3(256), 0, s, partial, T, N, p.ks, y, 0, N, hi_out, lo_out);
-    else LD_LAUNCH((k_splitk_reduce<GEMM_SWIGLU>), dim3(rgrid), dim3(256), 0, s, partial, T, N, p.ks, y, 0, N, hi_out, lo_out);
+    if (epi == GEMM_STORE) LD_LAUNCH((k_splitk_reduce<GEMM_STORE>), dim3(rgrid), dim3(256), 0, s, partial, T, N, p.ks, y, out);
+    else if (epi == GEMM_ADD) LD_LAUNCH((k_splitk_reduce<GEMM_ADD>), dim3(rgrid), dim3(256), 0, s, partial, T, N, p.ks, y, out);
+    else LD_LAUNCH((k_splitk_reduce<GEMM_SWIGLU>), dim3(rgrid), dim3(256), 0, s, partial, T, N, p.ks, y, out);
 }
 
-// Where the rows of a residual GEMM go next: the operand image of the normalised GEMM that follows.
-struct RowsNext { const float *g; float eps; bf16_t *hi, *lo; const RopeKvArgs *rope; int row0; };
+// Where the rows of a product go next.
+struct RowsNext { const float *g; float eps; OperandImage out; const RopeKvArgs *rope; int row0; };
+
+int gemm_f16_rows(int T, int N, int K, int epi) { return T > SKINNY_MAX_ROWS ? T - tail_rows(T, N, K, epi, true) : 0; }
 
 // nx != nullptr with GEMM_ADD: y's rows are finished and turned into the next operand by one fused kernel in
 // place of the split-K reduction.  With GEMM_SWIGLU: the epilogue (or the split-K reduction) writes its result
 // as the next operand instead of floats.
-// Whether the fp16 form serves a product of T rows: every product of the big-tile kernel.
-bool gemm_f16_rows(int T, int N, int K, int epi) {
-    (void)N; (void)K; (void)epi;
-    return T > SKINNY_MAX_ROWS;
-}
-
-// f16_flag != nullptr (more than 64 rows, gemm_f16_rows): the rows' images are turned into one fp16 image in place
-// and multiplied in the single-term form; *f16_flag is set if an activation does not fit.  W16: the matrix's fp16
+// f16 (more than 64 rows): the rows are one fp16 image (hi), multiplied in the single-term form; W16: the matrix's fp16
 // image where the caller keeps one (the kernel then reads it in W's place and converts nothing), else nullptr.
-static void gemm_rows(const uint16_t *W, bf16_t *hi, const bf16_t *lo, int T, int N, int K, int epi, float *y,
-                      float *partial, hipStream_t s, const RowsNext *nx = nullptr, int *f16_flag = nullptr,
-                      const uint16_t *W16 = nullptr, bool octets = false) {
+static void gemm_rows(const uint16_t *W, const bf16_t *hi, const bf16_t *lo, int T, int N, int K, int epi, float *y,
+                      float *partial, hipStream_t s, const RowsNext *nx, bool f16, const uint16_t *W16, bool octets) {
     const bool chain_rope = nx && epi == GEMM_STORE && nx->rope;
     const bool chain_add = (nx && epi == GEMM_ADD) || chain_rope;      // a finishing kernel replaces the split-K reduction
-    bf16_t *ho = nx && epi == GEMM_SWIGLU ? nx->hi : nullptr, *lo_o = nx && epi == GEMM_SWIGLU ? nx->lo : nullptr;
-    // slabs and output columns whose partial sums the finishing kernel still has to add (none: ks 1)
-    auto finish = [&](int ks, int col0, int col1, bool always_partial = false) {
-        if (ks <= 1 && !always_partial) col0 = col1 = 0;
-        if (chain_rope)
-            LD_LAUNCH(k_reduce_rope_kv, dim3(nx->rope->H + nx->rope->Hkv, T), dim3(64), 0, s, partial, T, N, ks, col0, col1, y,
-                      *nx->rope, nx->row0);
-        else
-            LD_LAUNCH(k_reduce_add_norm_split, dim3(T), dim3(256), 0, s, partial, T, N, ks, col0, col1, y, nx->g, nx->eps,
-                      nx->hi, nx->lo);
+    const OperandImage out = nx && epi == GEMM_SWIGLU ? nx->out : OperandImage{};
+    auto finish = [&](int ks) {      // ks: slabs whose partial sums the finishing kernel still has to add
+        if (chain_rope) {
+            LD_LAUNCH(k_reduce_rope_kv, dim3(nx->rope->H + nx->rope->Hkv, T), dim3(64), 0, s, partial, T, N, ks, y, *nx->rope, nx->row0);
+        } else if (N <= 5 * 1024) {
+            LD_LAUNCH((k_reduce_add_norm_split<5>), dim3(T), dim3(256), 0, s, partial, T, N, ks, y, nx->g, nx->eps, nx->out);
+        } else {
+            LD_LAUNCH((k_reduce_add_norm_split<0>), dim3(T), dim3(256), 0, s, partial, T, N, ks, y, nx->g, nx->eps, nx->out);
+        }
     };
     if (T <= SKINNY_MAX_ROWS) {
         const int ks = split_factor(T, N, K, epi), n_rows = N * (epi == GEMM_SWIGLU ? 2 : 1);
         launch_gemm_skinny(W, hi, lo, T, n_rows, K, partial, s, octets);
         const int rgrid = (int)(((int64_t)T * N + 255) / 256);
-        bf16_t *none = nullptr;
-        if (chain_add) finish(ks, 0, N, true);     // the skinny kernel writes partial sums even for one slab
-        else if (epi == GEMM_STORE) LD_LAUNCH((k_splitk_reduce<GEMM_STORE>), dim3(rgrid), dim3(256), 0, s, partial, T, N, ks, y, 0, N, none, none);
-        else if (epi == GEMM_ADD) LD_LAUNCH((k_splitk_reduce<GEMM_ADD>), dim3(rgrid), dim3(256), 0, s, partial, T, N, ks, y, 0, N, none, none);
-        else LD_LAUNCH((k_splitk_reduce<GEMM_SWIGLU>), dim3(rgrid), dim3(256), 0, s, partial, T, N, ks, y, 0, N, ho, lo_o);
+        if (chain_add) finish(ks);     // the skinny kernel writes partial sums even for one slab
+        else if (epi == GEMM_STORE) LD_LAUNCH((k_splitk_reduce<GEMM_STORE>), dim3(rgrid), dim3(256), 0, s, partial, T, N, ks, y, out);
+        else if (epi == GEMM_ADD) LD_LAUNCH((k_splitk_reduce<GEMM_ADD>), dim3(rgrid), dim3(256), 0, s, partial, T, N, ks, y, out);
+        else LD_LAUNCH((k_splitk_reduce<GEMM_SWIGLU>), dim3(rgrid), dim3(256), 0, s, partial, T, N, ks, y, out);
         return;
     }
-    const int f16 = f16_flag ? (W16 ? 2 : 1) : 0;
-    const BigPlan p = plan_big(T, N, K, epi, f16 != 0);
-    if (f16 == 2) W = W16;
-    if (f16) {
-        const int64_t n8 = (int64_t)T * K / 8;
-        LD_LAUNCH(k_split_to_f16, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, s, hi, lo, n8, f16_flag);
-    }
-    launch_tiles(W, hi, lo, T, N, K, epi, y, partial, p, s, !chain_add, ho, lo_o, f16);
-    if (chain_add) finish(p.ks, 0, N);
+    const BigPlan p = plan_big(T, N, K, epi, f16);
+    launch_tiles(f16 && W16 ? W16 : W, hi, lo, T, N, K, epi, y, partial, p, s, !chain_add, out, f16 ? (W16 ? 2 : 1) : 0);
+    if (chain_add) finish(p.ks > 1 ? p.ks : 0);
 }
 
 void launch_gemm(const uint16_t *W, uint16_t *xs, int T, int N, int K, int epi, float *y, hipStream_t s,
                  const GemmNext *next, int *f16_flag, const uint16_t *W16, bool octets) {
     float *partial = (float *)((char *)xs + gemm_split_bytes(T, K));
-    bf16_t *hi = xs, *lo = xs + (size_t)T * K;
-    // the rows beyond a multiple of 256 that the cost model sends through the small-batch kernels keep both terms
-    int r = tail_rows(T, N, K, epi, f16_flag != nullptr);
-    if (f16_flag && !gemm_f16_rows(T - r, N, K, epi)) {
-        f16_flag = nullptr;
-        r = tail_rows(T, N, K, epi, false);
-    }
+    const bf16_t *hi = xs, *lo = xs + (size_t)T * K;
+    // the rows beyond a multiple of 256 that the cost model sends through the small-batch kernel keep both terms
+    const bool f16 = f16_flag && T > SKINNY_MAX_ROWS;
+    const int r = tail_rows(T, N, K, epi, f16), m = T - r;
     // the next operand is a [2][T][N] image: rows of the main part first, the tail's rows behind them
     RowsNext a{}, b{};
     if (next) {
-        a = {next->g, next->eps, next->xs, next->xs ? next->xs + (size_t)T * N : nullptr, next->rope, 0};
-        b = {next->g, next->eps, next->xs ? a.hi + (size_t)(T - r) * N : nullptr, next->xs ? a.lo + (size_t)(T - r) * N : nullptr,
-             next->rope, T - r};
+        uint16_t *nh = next->xs, *nl = nh ? nh + (size_t)T * N : nullptr;
+        a = {next->g, next->eps, {nh, nl, next->f16_rows, f16_flag}, next->rope, 0};
+        b = {next->g, next->eps, {nh ? nh + (size_t)m * N : nh, nh ? nl + (size_t)m * N : nl, next->f16_rows - m, f16_flag}, next->rope, m};
     }
-    gemm_rows(W, hi, lo, T - r, N, K, epi, y, partial, s, next ? &a : nullptr, f16_flag, W16, octets);
+    gemm_rows(W, hi, lo, m, N, K, epi, y, partial, s, next ? &a : nullptr, f16, W16, octets);
     // the tail reuses the partial-sum scratch: the stream orders it behind the main part's reduction
-    if (r) gemm_rows(W, hi + (size_t)(T - r) * K, lo + (size_t)(T - r) * K, r, N, K, epi, y + (size_t)(T - r) * N, partial, s,
-                     next ? &b : nullptr);
+    if (r) gemm_rows(W, hi + (size_t)m * K, lo + (size_t)m * K, r, N, K, epi, y + (size_t)m * N, partial, s, next ? &b : nullptr, false, nullptr, false);
 }
 
 void launch_weight_range_check(const uint16_t *W, int64_t n, int *flag, hipStream_t s) {

@@ -375,13 +375,17 @@ ld_status enqueue_pass(ld_kv *kv, const std::vector<Row> &rows, int n_single, co
         uint16_t *A = (uint16_t *)w.lin_scratch, *B = (uint16_t *)w.lin_scratch2;
         auto mat = [](const void *p) { return (const uint16_t *)p; };
         auto img = [&](const std::vector<const uint16_t *> &v, int l) { return f16_flag && !v.empty() ? v[l] : nullptr; };
+        // rows that enter each of the four products as one fp16 term: their producers write them so
+        auto f16_rows = [&](int N, int K, int epi) { return f16_flag ? ld::gemm_f16_rows(T, N, K, epi) : 0; };
+        const int f_qkv = f16_rows(nqkv, d, ld::GEMM_STORE), f_wo = f16_rows(d, nq, ld::GEMM_ADD),
+                  f_gate_up = f16_rows(c.d_ffn, d, ld::GEMM_SWIGLU), f_down = f16_rows(d, c.d_ffn, ld::GEMM_ADD);
         for (int l = 0; l < c.n_layers; l++) {
             void *pool_l = kv->pool + (size_t)l * layer_bytes;
             // the kernel that finishes the q-k-v rows also rotates them and appends k, v to the cache
             const ld::RopeKvArgs rk{(const float2 *)w.cos_sin, d_pos, d_slot, w.table, kv->max_blocks, (uint16_t *)pool_l, H, Hkv, hd};
             const ld::GemmNext to_cache{nullptr, 0.f, nullptr, &rk};
             LD_TIMED(LD_PROF_QKV, timed_void([&] {
-                if (l == 0) ld::launch_norm_split(w.x, m.attn_norm[0], c.rms_eps, T, d, B, st);
+                if (l == 0) ld::launch_norm_split(w.x, m.attn_norm[0], c.rms_eps, T, d, B, st, false, f_qkv, f16_flag);
                 ld::launch_gemm(mat(m.wqkv[l]), B, T, nqkv, d, ld::GEMM_STORE, w.qkv, st, &to_cache, f16_flag, img(m.h_qkv, l));
             }));
             // attention writes the output projection's operand (A) directly: the single-query rows, then the tiles' rows
@@ -389,17 +393,17 @@ ld_status enqueue_pass(ld_kv *kv, const std::vector<Row> &rows, int n_single, co
                 LD_TIMED(LD_PROF_ATTENTION, ld::paged_attention_split(w.qkv + (size_t)dec0 * nqkv, nqkv, pool_l, c.dtype, w.table,
                                                                       kv->max_blocks, d_slot + dec0, d_ctx + dec0, max_ctx_dec,
                                                                       n_dec_rows, H, Hkv, hd, c.window, A + (size_t)dec0 * nq,
-                                                                      w.att_scratch, w.att_scratch_bytes, st, T));
+                                                                      w.att_scratch, w.att_scratch_bytes, st, T, false, f_wo - dec0, f16_flag));
             if (n_tiles)
                 LD_TIMED(LD_PROF_ATTENTION, timed_void([&] {
                     ld::launch_prefill_attention(w.qkv, nqkv, (const uint16_t *)pool_l, Hkv, w.table, kv->max_blocks, d_tiles,
                                                  n_tiles, H, c.window, max_ctx - 1, w.attn, w.att_scratch,
-                                                 w.att_scratch_bytes, st, A, A + (size_t)T * nq, f16_flag);
+                                                 w.att_scratch_bytes, st, {A, A + (size_t)T * nq, f_wo, f16_flag}, f16_flag);
                 }));
-            const ld::GemmNext to_ffn{m.ffn_norm[l], c.rms_eps, B};
-            const ld::GemmNext to_next{l + 1 < c.n_layers ? m.attn_norm[l + 1] : nullptr, c.rms_eps, B};
+            const ld::GemmNext to_ffn{m.ffn_norm[l], c.rms_eps, B, nullptr, f_gate_up};
+            const ld::GemmNext to_next{l + 1 < c.n_layers ? m.attn_norm[l + 1] : nullptr, c.rms_eps, B, nullptr, f_qkv};
             LD_TIMED(LD_PROF_WO, timed_void([&] { ld::launch_gemm(mat(m.wo[l]), A, T, d, nq, ld::GEMM_ADD, w.x, st, &to_ffn, f16_flag, img(m.h_wo, l)); }));
-            const ld::GemmNext to_down{nullptr, 0.f, A};      // the gated activation goes straight into the down projection's operand
+            const ld::GemmNext to_down{nullptr, 0.f, A, nullptr, f_down};      // the gated activation goes straight into the down projection's operand
             LD_TIMED(LD_PROF_GATE_UP, timed_void([&] { ld::launch_gemm(mat(m.wgate_up[l]), B, T, c.d_ffn, d, ld::GEMM_SWIGLU, w.act, st, &to_down, f16_flag, img(m.h_gate_up, l)); }));
             LD_TIMED(LD_PROF_DOWN, timed_void([&] {
                 ld::launch_gemm(mat(m.wdown[l]), A, T, d, c.d_ffn, ld::GEMM_ADD, w.x, st, to_next.g ? &to_next : nullptr, f16_flag, img(m.h_down, l));

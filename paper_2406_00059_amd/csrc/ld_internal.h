@@ -35,10 +35,19 @@ struct LaunchTimer {
 };
 extern thread_local LaunchTimer *g_launch_timer;
 
+// Where a producer leaves its rows as the operand of a matrix-core product: hi and lo bf16 images; of the rows below
+// f16_rows one fp16 image in hi's place, the fp16 of the two terms' sum (*f16_flag is set when a value does not fit).
+struct OperandImage {
+    uint16_t *hi = nullptr, *lo = nullptr;
+    int f16_rows = 0;
+    int *f16_flag = nullptr;
+};
+
 ld_status paged_attention_split(const float *q, int q_stride, const void *pool_layer, int dtype, const int32_t *table,
                                 int table_stride, const int32_t *seq_slot, const int32_t *ctx_len, int max_ctx, int T,
                                 int H, int Hkv, int hd, int window, uint16_t *xs_out, void *scratch,
-                                size_t scratch_bytes, hipStream_t stream, int image_rows = 0, bool octets = false);
+                                size_t scratch_bytes, hipStream_t stream, int image_rows = 0, bool octets = false, int f16_rows = 0,
+                                int *f16_flag = nullptr);
 
 // ldk_linear for the rows of an engine pass: f16_flag and W_f16 as in launch_gemm (nullptr: ldk_linear itself).
 ld_status linear_pass(const void *W, int32_t dtype, const float *x, const float *g, float eps, int32_t T, int32_t N,

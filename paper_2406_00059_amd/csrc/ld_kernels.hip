@@ -349,7 +349,7 @@ template <int HD>
 __global__ __launch_bounds__(256) void k_attn_merge(const float *__restrict__ part_o, const float *__restrict__ part_ml,
                                                     const int32_t *__restrict__ ctx_len, int H, int window,
                                                     int max_chunks, int cb, float *__restrict__ out,
-                                                    bf16_t *__restrict__ xs_out, int T, bool octets) {
+                                                    ld::OperandImage image, int T, bool octets) {
     constexpr int NGRP = 256 / HD, MAXC = 512;   // MAXC: chunks whose statistics fit the LDS cache
     __shared__ float sm_m[MAXC], sm_l[MAXC], sm_o[NGRP][HD], sm_L[NGRP], sm_red[4];
     const int h = blockIdx.x, t = blockIdx.y, d = threadIdx.x % HD, grp = threadIdx.x / HD;
@@ -384,11 +384,8 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float *__restrict__ pa
 #pragma unroll
     for (int g = 0; g < NGRP; g++) { o += sm_o[g][d]; L += sm_L[g]; }   // fixed order
     const float r = o / L;
-    if (xs_out) {   // operand of the output projection: split (hi, lo) image [2][T][H * HD], or [2][H * HD / 8][T][8]
-        const bf16_t hi = f32_to_bf16(r);
-        const int64_t at = octets ? octet_index(t, h * HD + d, T) : ((int64_t)t * H + h) * HD + d;
-        xs_out[at] = hi;
-        xs_out[at + (int64_t)T * H * HD] = f32_to_bf16(r - bf16_to_f32(hi));
+    if (image.hi) {   // operand of the output projection: row-major images, or with octets [H * HD / 8][T][8]
+        store_operand(image, t, octets ? octet_index(t, h * HD + d, T) : ((int64_t)t * H + h) * HD + d, r);
     } else {
         out[((int64_t)t * H + h) * HD + d] = r;
     }
@@ -593,7 +590,7 @@ ld_status ld::linear_pass(const void *W, int32_t dtype, const float *x, const fl
     }
     if (dtype == LD_BF16 && scratch && ld::gemm_supported(T, N, K) && scratch_bytes >= ld::gemm_scratch_bytes(T, N, K, epilogue)) {
         const bool octets = ld::gemm_takes_octets(T);
-        ld::launch_norm_split(x, g, eps, T, K, (uint16_t *)scratch, s, octets);
+        ld::launch_norm_split(x, g, eps, T, K, (uint16_t *)scratch, s, octets, f16_flag ? ld::gemm_f16_rows(T, N, K, epilogue) : 0, f16_flag);
         ld::launch_gemm((const bf16_t *)W, (uint16_t *)scratch, T, N, K, epilogue, y, s, nullptr, f16_flag, (const uint16_t *)W_f16, octets);
         return launched("k_gemm_mfma");
     }
@@ -713,7 +710,7 @@ static ld_status paged_attention_impl(const float *q, int32_t q_stride, const vo
                                       const int32_t *table, int32_t table_stride, const int32_t *seq_slot,
                                       const int32_t *ctx_len, int32_t max_ctx, int32_t T, int32_t H, int32_t Hkv,
                                       int32_t hd, int32_t window, float *out, uint16_t *xs_out, void *scratch,
-                                      size_t scratch_bytes, void *stream, int image_rows = 0, bool octets = false) {
+                                      size_t scratch_bytes, void *stream, int image_rows = 0, bool octets = false, int f16_rows = 0, int *f16_flag = nullptr) {
     if (T == 0) return LD_OK;
     if (!q || !pool_layer || !table || !seq_slot || !ctx_len || (!out && !xs_out) || !scratch || T < 0 || H <= 0 ||
         Hkv <= 0 || H % Hkv || (hd != 64 && hd != 128) || max_ctx <= 0 || window < 0)
@@ -730,11 +727,12 @@ static ld_status paged_attention_impl(const float *q, int32_t q_stride, const vo
     dim3 grid(mc, H / G, T), block(256);
     hipStream_t s = (hipStream_t)stream;
     const int img = image_rows > 0 ? image_rows : T;     // rows of the split image the low parts sit behind
+    const ld::OperandImage image{xs_out, xs_out ? xs_out + (size_t)img * H * hd : nullptr, f16_rows, f16_flag};
     if (mfma) {
         ld::launch_grouped_decode_partial(q, q_stride, (const uint16_t *)pool_layer, Hkv, table, table_stride, seq_slot,
                                           ctx_len, T, H, window, mc, cb, part_o, part_ml, s);
         LD_LAUNCH((k_attn_merge<128>), dim3(H, T), dim3(256), 0, s, part_o, part_ml, ctx_len, H, window, mc, cb, out,
-                  xs_out, img, octets);
+                  image, img, octets);
         return launched("k_attn (grouped)");
     }
 #define LD_ATT_G(HD_, KVT_, G_)                                                                                    \
@@ -747,7 +745,7 @@ static ld_status paged_attention_impl(const float *q, int32_t q_stride, const vo
         else if (G == 2) LD_ATT_G(HD_, KVT_, 2);                                                                  \
         else LD_ATT_G(HD_, KVT_, 1);                                                                              \
         LD_LAUNCH((k_attn_merge<HD_>), dim3(H, T), dim3(256), 0, s, part_o, part_ml, ctx_len, H, window, mc, cb,  \
-                  out, xs_out, img, octets);                                                                       \
+                  out, image, img, octets);                                                                        \
     } while (0)
     if (dtype == LD_BF16 && hd == 128) LD_ATT(128, bf16_t);
     else if (dtype == LD_BF16 && hd == 64) LD_ATT(64, bf16_t);
@@ -836,7 +834,7 @@ ld_status ldk_prefill_attention_f16(const float *q, int32_t q_stride, const void
         return ld::fail(LD_E_INVAL, "ldk_prefill_attention: needs a bf16 pool and head_dim 128");
     if (n_tiles == 0) return LD_OK;
     ld::launch_prefill_attention(q, q_stride, (const uint16_t *)pool_layer, Hkv, table, table_stride, tiles, n_tiles, H,
-                                 window, max_pos, out, scratch, scratch_bytes, (hipStream_t)stream, nullptr, nullptr, overflow);
+                                 window, max_pos, out, scratch, scratch_bytes, (hipStream_t)stream, {}, overflow);
     return launched("k_attn_prefill");
 }
 
@@ -862,13 +860,14 @@ namespace ld {
 
 // Single-query paged attention whose output is written as the split (hi, lo) bf16 operand of the
 // output projection: xs_out [2][image_rows][H * hd], of which these T rows are the first (image_rows 0: T), or with
-// octets [2][H * hd / 8][T][8].
+// octets [2][H * hd / 8][T][8].  The first f16_rows of these rows as one fp16 image (OperandImage).
 ld_status paged_attention_split(const float *q, int q_stride, const void *pool_layer, int dtype, const int32_t *table,
                                 int table_stride, const int32_t *seq_slot, const int32_t *ctx_len, int max_ctx, int T,
                                 int H, int Hkv, int hd, int window, uint16_t *xs_out, void *scratch,
-                                size_t scratch_bytes, hipStream_t stream, int image_rows, bool octets) {
+                                size_t scratch_bytes, hipStream_t stream, int image_rows, bool octets, int f16_rows,
+                                int *f16_flag) {
     return paged_attention_impl(q, q_stride, pool_layer, dtype, table, table_stride, seq_slot, ctx_len, max_ctx, T, H, Hkv,
-                                hd, window, nullptr, xs_out, scratch, scratch_bytes, (void *)stream, image_rows, octets);
+                                hd, window, nullptr, xs_out, scratch, scratch_bytes, (void *)stream, image_rows, octets, f16_rows, f16_flag);
 }
 
 }  // namespace ld
