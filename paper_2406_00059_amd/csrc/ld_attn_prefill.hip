@@ -7,11 +7,17 @@
 // starts at the first position the tile's first row sees, and a wave skips the steps that lie wholly
 // before the band of its own first row.
 //
-// Work split: a workgroup (4 waves) takes 128 consecutive rows of a segment and one head; wave w
-// owns rows [32w, 32w+32).  All four waves walk the same KV positions in steps of 32 tokens; the key
-// rows and the (transposed) value tile of a step are copied into LDS once, in 16-byte pieces that were
-// loaded into registers one step earlier, and shared by the four waves.  LDS is double buffered: one
-// barrier per step.  Two workgroups fit a CU, so that one wave's softmax overlaps another's MFMAs.
+// Work split: a workgroup (4 waves) takes 128 consecutive rows of a segment and one head; wave w owns rows
+// [32w, 32w+32).  All four waves walk the same KV positions in steps of 32; the key rows and the (transposed) value
+// tile of two steps (a unit) are copied into LDS in 16-byte pieces that were loaded into registers one unit earlier,
+// behind block-table entries read another unit earlier, and shared by the four waves.  LDS is double buffered, with one
+// barrier per unit.  Two workgroups fit a CU, so that one wave's softmax overlaps another's MFMAs.
+//
+// What bounds it: a unit takes two co-resident workgroups about 3.4 us, of which the vector arithmetic of the softmax
+// and the staging fill about a half and the MFMAs a quarter (F16); the rest is operand and barrier latency at two waves
+// per SIMD.  So the work per step is what counts: two steps a barrier, in F16 one maximum, one exchange and one look at the
+// rescaling for both (scores start at -m, which saves the subtraction before the exponential).  12 tiles x 32 heads at
+// contexts 2.2k .. 6.4k: 322 -> 220 us with its merge 338 -> 235; one 256-row chunk behind 1500: 44 -> 37 us.
 //
 // Both products are computed transposed, so that the query index is the MFMA column (= lane % 32)
 // everywhere and the online-softmax statistics of a query live in the lanes that hold its scores:
@@ -28,10 +34,11 @@
 // 16-byte piece of the transposed value tile.
 // Scores are kept in the log2 domain (q is pre-multiplied by log2(e)/sqrt(hd)); m, l and O are float32.
 //
-// Few tiles with long contexts (an observation appended to one long sequence) would leave most CUs idle
-// and make every workgroup walk the whole context, so the KV range of a tile can be split over gridDim.z
-// workgroups; each then writes its unnormalised output with its maximum and sum, and a merge kernel
-// combines the splits in fixed order.
+// Few tiles with long contexts (an observation appended to one long sequence) would leave most CUs idle and make every
+// workgroup walk the whole context, and tiles of different length would leave them waiting for the longest, so the KV range
+// of a tile is dealt out in shares of `per` steps to as many workgroups as it has shares; each writes its unnormalised
+// output with its maximum and sum, and a merge kernel combines them in order.  Shares of one length, not one number of
+// shares: four segments behind 0.5k .. 2.9k positions take 98 + 16 us per layer (walk + merge) in two shares each, 86 + 9 so.
 #include "ld_attn_prefill.h"
 #include "ld_device.h"
 #include "ld_internal.h"
@@ -50,6 +57,7 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 constexpr int HD = 128;
 constexpr int KVB = 32;          // kv positions per step
 constexpr int KLD = HD + 8;      // LDS row stride of the key tile (elements): 272 bytes, conflict-free 16-byte reads
+constexpr int MAX_SPLITS = 16;   // shares of a tile's KV steps, at most
 constexpr int VLD = KVB + 8;     // LDS row stride of the transposed value tile (elements): 80 bytes
 
 __device__ __forceinline__ int tau(int r) { return (r & 19) | ((r & 4) << 1) | ((r & 8) >> 1); }
@@ -70,6 +78,24 @@ __device__ __forceinline__ u32x4 bf16x8_to_f16x8(const u32x4 &w, u16x2 &mag) {
     return h;
 }
 
+// Steps of KVB positions that a tile walks: from the first position its first row sees (rounded down) to its last row's.
+__device__ __forceinline__ int tile_start(const int4 &tile, int window) { return window > 0 ? (max(tile.z - window + 1, 0) & ~(KVB - 1)) : 0; }
+__device__ __forceinline__ int tile_steps(const int4 &tile, int window) { return (tile.z + tile.y - 1 - tile_start(tile, window)) / KVB + 1; }
+
+// The tile that comes rank-th when they are sorted by their steps (longest first, ties by index); more than a wave's
+// lanes of them stay in their own order.
+__device__ __forceinline__ int nth_longest(const int4 *__restrict__ tiles, int n_tiles, int window, int rank) {
+    if (n_tiles > WAVE) return rank;
+    const int lane = threadIdx.x & 63;
+    const int own = lane < n_tiles ? tile_steps(tiles[lane], window) : 0;
+    int before = 0;
+    for (int i = 0; i < n_tiles; i++) {
+        const int other = __builtin_amdgcn_readlane(own, i);
+        before += other > own || (other == own && i < lane);
+    }
+    return __ffsll(__ballot(lane < n_tiles && before == rank)) - 1;
+}
+
 // F16 (the long passes whose rows the engine lets enter the products rounded to fp16): queries and probabilities as
 // one fp16 term instead of two bf16 terms, keys and values widened from bf16 to fp16 when they are staged in LDS
 // (once per workgroup, exact within the fp16 range): half the matrix-core work.  *f16_flag is set when a query, a
@@ -80,12 +106,21 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
                                                          const int32_t *__restrict__ table, int table_stride,
                                                          const int4 *__restrict__ tiles, int H, int window,
                                                          float scale_log2e, float *__restrict__ out,
-                                                         float *__restrict__ part_o, float *__restrict__ part_ml,
+                                                         int per, float *__restrict__ part_o, float *__restrict__ part_ml,
                                                          ld::OperandImage image, int *__restrict__ f16_flag) {
-    __shared__ __attribute__((aligned(16))) bf16_t ks[2][KVB][KLD];
-    __shared__ __attribute__((aligned(16))) bf16_t vt[2][HD][VLD];
-    const int4 tile = tiles[blockIdx.x];      // x: first row, y: rows (<= 128), z: position of first row, w: seq slot
-    const int h = blockIdx.y;
+    __shared__ __attribute__((aligned(16))) bf16_t ks[2][2][KVB][KLD];      // [buffer][step of the unit]
+    __shared__ __attribute__((aligned(16))) bf16_t vt[2][2][HD][VLD];
+    // Work items longest first: shares in order, in each the tiles by their length, heads fastest.  Two workgroups share a
+    // CU and run at each other's expense: in the tiles' own order long ones meet long ones.  Blocks b, b + 8, ... run on
+    // one XCD: with the heads dealt out in eighths, the heads that read the same keys and values go through one L2.
+    const int tile_idx = nth_longest(tiles, gridDim.y, window, blockIdx.y);
+    const int h = H % 8 == 0 ? (blockIdx.x & 7) * (H / 8) + (blockIdx.x >> 3) : blockIdx.x;
+    const int4 tile = tiles[tile_idx];      // x: first row, y: rows (<= 128), z: position of first row, w: seq slot
+    // this workgroup's share of the tile's KV steps: `per` of them, as many shares as the tile has (a short tile of an uneven
+    // batch has fewer than the grid)
+    const int n_steps = tile_steps(tile, window), split = blockIdx.z;
+    if (split * per >= n_steps) return;
+    const bool whole = n_steps <= per || gridDim.z == 1;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l32 = lane & 31, half = lane >> 5;
     const int kvh = h / (H / Hkv);
@@ -104,7 +139,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
     const int wave_low = window > 0 ? max(tile.z + wave * 32 - window + 1, 0) : 0;
     const int wave_first_pos = tile.z + wave * 32;                      // position of the wave's first query
     const int wave_low_hi = window > 0 ? max(wave_last_pos - window + 1, 0) : 0;   // lowest position its last query sees
-    const int kv_start = window > 0 ? (max(tile.z - window + 1, 0) & ~(KVB - 1)) : 0;
+    const int kv_start = tile_start(tile, window);
     // first position of the lowest block any row of the tile sees: block-table entries below it may belong
     // to blocks the sequence has given up (ld_kv_trim) and are never dereferenced
     const int first_held_pos = window > 0 ? (max(tile.z - window + 1, 0) & ~15) : 0;
@@ -147,171 +182,200 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
     // value pieces (dimension vd, positions 8*vh .. +8 of block v of the step).
     const int kr = threadIdx.x >> 4, kc = (threadIdx.x & 15) * 8;       // + 16 rows for the second piece
     const int vd = threadIdx.x >> 1, vh = (threadIdx.x & 1) * 8;
-    // Global loads run PF steps ahead of the arithmetic, in PF register sets: with one or two workgroups on
-    // a CU the arithmetic of a single step is much shorter than the memory latency it would have to cover.
-    constexpr int PF = 3;
-    u32x4 kreg[PF][2], vreg[PF][2];
-    auto load_step = [&](int set, int kv0) {
+    // Two steps of 32 positions make a unit, with one barrier each; the global loads run one unit ahead.
+    u32x4 kreg[2][2], vreg[2][2];
+    int entry[2][2];      // the table's entries of the unit to be loaded next, read one unit before
+    auto look_up = [&](int kv0) {
 #pragma unroll
-        for (int v = 0; v < 2; v++) {
-            // a block past the last needed position is read again from the last needed block, one below
-            // the first visible block from that block; never used
-            const int pos = max(min(kv0 + 16 * v, wg_last_pos), first_held_pos);
-            const bf16_t *blk = pool + (int64_t)trow[pos >> 4] * block_stride;
-            kreg[set][v] = *reinterpret_cast<const u32x4 *>(blk + kv_k_offset(HD, kvh, kr, kc));
-            vreg[set][v] = *reinterpret_cast<const u32x4 *>(blk + kv_v_offset(Hkv, HD, kvh, vh, vd));
-        }
+        for (int u = 0; u < 2; u++)
+#pragma unroll
+            for (int v = 0; v < 2; v++)
+                // a block past the last needed position is read again from the last needed block, one below
+                // the first visible block from that block; never used
+                entry[u][v] = trow[max(min(kv0 + KVB * u + 16 * v, wg_last_pos), first_held_pos) >> 4];
+    };
+    auto load_unit = [&] {
+#pragma unroll
+        for (int u = 0; u < 2; u++)
+#pragma unroll
+            for (int v = 0; v < 2; v++) {
+                const bf16_t *blk = pool + (int64_t)entry[u][v] * block_stride;
+                kreg[u][v] = *reinterpret_cast<const u32x4 *>(blk + kv_k_offset(HD, kvh, kr, kc));
+                vreg[u][v] = *reinterpret_cast<const u32x4 *>(blk + kv_v_offset(Hkv, HD, kvh, vh, vd));
+            }
     };
     // Values of positions past the tile's last row were never written (the rest of the last block, or the
     // second block of a step that ends the walk): they may hold anything, also NaN, and a probability of zero
     // does not neutralise a NaN, so they are staged as zeros.  (Keys need nothing: their scores are replaced,
     // not multiplied.)
-    auto stage = [&](int st, int set, int kv0) {
+    auto stage = [&](int st, int kv_unit) {
 #pragma unroll
-        for (int v = 0; v < 2; v++) {
-            if constexpr (F16) {
-                // a key row past the tile's last position was never written (its scores are masked): whatever it
-                // holds does not count as out of range
-                u16x2 seen = mag;
-                *reinterpret_cast<u32x4 *>(&ks[st][16 * v + kr][kc]) = bf16x8_to_f16x8(kreg[set][v], seen);
-                if (kv0 + 16 * v + kr <= wg_last_pos) mag = seen;
-            } else {
-                *reinterpret_cast<u32x4 *>(&ks[st][16 * v + kr][kc]) = kreg[set][v];
-            }
-            u32x4 vv = vreg[set][v];
-            const int p0 = kv0 + 16 * v + vh;      // position of this piece's first element
-            if (p0 + 7 > wg_last_pos) {
+        for (int u = 0; u < 2; u++)
 #pragma unroll
-                for (int e = 0; e < 4; e++)
-                    vv[e] = (p0 + 2 * e <= wg_last_pos ? vv[e] & 0x0000ffffu : 0u) |
-                            (p0 + 2 * e + 1 <= wg_last_pos ? vv[e] & 0xffff0000u : 0u);
+            for (int v = 0; v < 2; v++) {
+                const int kv0 = kv_unit + KVB * u;
+                if constexpr (F16) {
+                    // a key row past the tile's last position was never written (its scores are masked): whatever it
+                    // holds does not count as out of range
+                    u16x2 seen = mag;
+                    *reinterpret_cast<u32x4 *>(&ks[st][u][16 * v + kr][kc]) = bf16x8_to_f16x8(kreg[u][v], seen);
+                    if (kv0 + 16 * v + kr <= wg_last_pos) mag = seen;
+                } else {
+                    *reinterpret_cast<u32x4 *>(&ks[st][u][16 * v + kr][kc]) = kreg[u][v];
+                }
+                u32x4 vv = vreg[u][v];
+                const int p0 = kv0 + 16 * v + vh;      // position of this piece's first element
+                if (p0 + 7 > wg_last_pos) {
+#pragma unroll
+                    for (int e = 0; e < 4; e++)
+                        vv[e] = (p0 + 2 * e <= wg_last_pos ? vv[e] & 0x0000ffffu : 0u) |
+                                (p0 + 2 * e + 1 <= wg_last_pos ? vv[e] & 0xffff0000u : 0u);
+                }
+                if constexpr (F16) vv = bf16x8_to_f16x8(vv, mag);
+                *reinterpret_cast<u32x4 *>(&vt[st][u][vd][16 * v + vh]) = vv;
             }
-            if constexpr (F16) vv = bf16x8_to_f16x8(vv, mag);
-            *reinterpret_cast<u32x4 *>(&vt[st][vd][16 * v + vh]) = vv;
-        }
     };
-    // this workgroup's share of the tile's steps (all of them when the grid has one split)
-    const int n_splits = gridDim.z, split = blockIdx.z;
-    const int n_steps = (wg_last_pos - kv_start) / KVB + 1, per = (n_steps + n_splits - 1) / n_splits;
     const int kv_begin = kv_start + split * per * KVB;
-    const int kv_end = min(kv_begin + per * KVB, wg_last_pos + 1);      // exclusive; may be <= kv_begin (empty share)
+    const int kv_end = split + 1 == gridDim.z ? wg_last_pos + 1 : min(kv_begin + per * KVB, wg_last_pos + 1);      // exclusive; the last share takes what is left
+    // NT consecutive steps [u0, u0 + NT) of the unit at kv_unit: scores, softmax, output.  Two steps at a time (F16; the
+    // two-term form has no registers left for that) give the matrix cores two independent chains of scores and the
+    // softmax one maximum, one exchange and one look at the rescaling for 64 positions.
+    constexpr int NT = F16 ? 2 : 1;
+    auto compute = [&](int kv_unit, int st, int u0) {
+        const int kv0 = kv_unit + KVB * u0;
+        // ---- S^T = K Q^T for 32 kv positions x 32 queries a step; tile row l32 is position kv0 + tau(l32).  The sums start
+        // at -m, so that the scores come out relative to the exponents' reference
+        const float m_in = m > -INFINITY ? m : 0.f;
+        f32x16 sc_t[NT];
 #pragma unroll
-    for (int pf = 0; pf < PF; pf++)
-        if (kv_begin + pf * KVB < kv_end) load_step(pf, kv_begin + pf * KVB);
-
-    auto compute = [&](int kv0, int st) {
-
-        // ---- S^T = K Q^T for 32 kv positions x 32 queries; tile row l32 is position kv0 + tau(l32)
-        f32x16 sc_t;
+        for (int n = 0; n < NT; n++)
 #pragma unroll
-        for (int i = 0; i < 16; i++) sc_t[i] = 0.f;
-        const bf16_t *krow = &ks[st][tau(l32)][half * 64];
+            for (int i = 0; i < 16; i++) sc_t[n][i] = -m_in;
         // The matrix-core phases run at a raised wave priority: the other workgroup's wave on this SIMD then
         // fills the issue slots between the MFMAs with its softmax arithmetic instead of competing for them.
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-        for (int j = 0; j < 8; j++) {
-            const u32x4 ka = *reinterpret_cast<const u32x4 *>(krow + j * 8);
-            if constexpr (F16) {
-                sc_t = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, ka), __builtin_bit_cast(f16x8, qh[j]), sc_t, 0, 0, 0);
-            } else {
-                sc_t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka), __builtin_bit_cast(bf16x8, qh[j]), sc_t, 0, 0, 0);
-                sc_t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka), __builtin_bit_cast(bf16x8, ql[j]), sc_t, 0, 0, 0);
+        for (int j = 0; j < 8; j++)
+#pragma unroll
+            for (int n = 0; n < NT; n++) {
+                const u32x4 ka = *reinterpret_cast<const u32x4 *>(&ks[st][u0 + n][tau(l32)][half * 64 + j * 8]);
+                if constexpr (F16) {
+                    sc_t[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, ka), __builtin_bit_cast(f16x8, qh[j]), sc_t[n], 0, 0, 0);
+                } else {
+                    sc_t[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka), __builtin_bit_cast(bf16x8, qh[j]), sc_t[n], 0, 0, 0);
+                    sc_t[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka), __builtin_bit_cast(bf16x8, ql[j]), sc_t[n], 0, 0, 0);
+                }
             }
-        }
         __builtin_amdgcn_s_setprio(0);
         // ---- online softmax; accumulator element i is row 8*(i/4) + 4*half + i%4 of the tile, which holds
         // position kv0 + 16*(i/8) + 8*half + i%8
         float mb = -INFINITY;
-        if (kv0 + KVB - 1 <= wave_first_pos && kv0 >= wave_low_hi) {
-            // every position of the step is visible to every query of the wave (the common case away from
+        if (kv0 + NT * KVB - 1 <= wave_first_pos && kv0 >= wave_low_hi) {
+            // every position of the steps is visible to every query of the wave (the common case away from
             // the diagonal and the band edge): no masks; rows past the tile compute on a copy of the last row
 #pragma unroll
-            for (int i = 0; i < 16; i++) mb = fmaxf(mb, sc_t[i]);
+            for (int n = 0; n < NT; n++)
+#pragma unroll
+                for (int i = 0; i < 16; i++) mb = fmaxf(mb, sc_t[n][i]);
         } else {
 #pragma unroll
-            for (int i = 0; i < 16; i++) {
-                const int kv_pos = kv0 + 16 * (i / 8) + 8 * half + (i % 8);
-                const bool ok = q_valid && kv_pos <= q_pos && kv_pos >= q_low;
-                sc_t[i] = ok ? sc_t[i] : -INFINITY;
-                mb = fmaxf(mb, sc_t[i]);
-            }
+            for (int n = 0; n < NT; n++)
+#pragma unroll
+                for (int i = 0; i < 16; i++) {
+                    const int kv_pos = kv0 + KVB * n + 16 * (i / 8) + 8 * half + (i % 8);
+                    const bool ok = q_valid && kv_pos <= q_pos && kv_pos >= q_low;
+                    sc_t[n][i] = ok ? sc_t[n][i] : -INFINITY;
+                    mb = fmaxf(mb, sc_t[n][i]);
+                }
         }
         mb = fmaxf(mb, __shfl_xor(mb, 32, WAVE));
         // m is the reference the exponents are taken against, not necessarily the running maximum: it moves up
         // only when the maximum has outgrown it by more than 2^8, so p stays below 256 and the accumulators
         // are rescaled on few steps instead of most.  o, l and m stay consistent, which is all the final
-        // division and the split merge need.
-        const float m_new = mb > m + 8.f ? mb : m;
+        // division and the split merge need.  (mb is relative to m_in.)
+        const bool first = !(m > -INFINITY), move = first ? mb > -INFINITY : mb > 8.f;
         float sc = 1.f;
-        uint32_t ph[8], pl[8];
-        if (m_new > -INFINITY) {
-            sc = fast_exp2(m - m_new);
-            float psum = 0.f;
+        const bool any_move = __any(move);
+        if (any_move) {
+            const float up = move ? mb : 0.f;
+            sc = first ? (move ? 0.f : 1.f) : fast_exp2(-up);
+            if (move) m = m_in + up;
+#pragma unroll
+            for (int n = 0; n < NT; n++)
+#pragma unroll
+                for (int i = 0; i < 16; i++) sc_t[n][i] -= up;
+            l *= sc;
+        }
+        uint32_t ph[NT][8], pl[NT][F16 ? 1 : 8];
+        float psum = 0.f;
+#pragma unroll
+        for (int n = 0; n < NT; n++)
 #pragma unroll
             for (int i = 0; i < 16; i += 2) {
-                const float p0 = fast_exp2(sc_t[i] - m_new), p1 = fast_exp2(sc_t[i + 1] - m_new);
+                const float p0 = fast_exp2(sc_t[n][i]), p1 = fast_exp2(sc_t[n][i + 1]);      // masked: exp2(-inf) = 0
                 psum += p0 + p1;
-                if constexpr (F16) ph[i / 2] = pack2_f16(p0, p1);      // p < 2^8: well inside fp16
-                else ph[i / 2] = split2_bf16(p0, p1, pl[i / 2]);
+                if constexpr (F16) ph[n][i / 2] = pack2_f16(p0, p1);      // p <= 2^8: well inside fp16
+                else ph[n][i / 2] = split2_bf16(p0, p1, pl[n][i / 2]);
             }
-            l = l * sc + psum;
-            m = m_new;
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; e++) ph[e] = pl[e] = 0u;
-        }
-        // ---- O^T = O^T * sc + V^T P^T; the rescale is skipped when no query of the wave raised its maximum
-        const bool rescale = __any(sc != 1.f);
+        l += psum;
+        // ---- O^T = O^T * sc + V^T P^T; the rescale is skipped when no query of the wave moved its reference
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int nt = 0; nt < 4; nt++) {
-            if (rescale) {
+            if (any_move) {
 #pragma unroll
                 for (int i = 0; i < 16; i++) o[nt][i] *= sc;
             }
 #pragma unroll
-            for (int mm = 0; mm < 2; mm++) {
-                // slot e of this lane <-> position kv0 + 16*mm + 8*half + e
-                const u32x4 va = *reinterpret_cast<const u32x4 *>(&vt[st][nt * 32 + l32][16 * mm + 8 * half]);
-                const u32x4 pbh = (u32x4){ph[4 * mm], ph[4 * mm + 1], ph[4 * mm + 2], ph[4 * mm + 3]};
-                if constexpr (F16) {
-                    o[nt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, va), __builtin_bit_cast(f16x8, pbh), o[nt], 0, 0, 0);
-                } else {
-                    const u32x4 pbl = (u32x4){pl[4 * mm], pl[4 * mm + 1], pl[4 * mm + 2], pl[4 * mm + 3]};
-                    o[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, va), __builtin_bit_cast(bf16x8, pbh), o[nt], 0, 0, 0);
-                    o[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, va), __builtin_bit_cast(bf16x8, pbl), o[nt], 0, 0, 0);
+            for (int n = 0; n < NT; n++)
+#pragma unroll
+                for (int mm = 0; mm < 2; mm++) {
+                    // slot e of this lane <-> position kv0 + 32*n + 16*mm + 8*half + e
+                    const u32x4 va = *reinterpret_cast<const u32x4 *>(&vt[st][u0 + n][nt * 32 + l32][16 * mm + 8 * half]);
+                    const u32x4 pbh = (u32x4){ph[n][4 * mm], ph[n][4 * mm + 1], ph[n][4 * mm + 2], ph[n][4 * mm + 3]};
+                    if constexpr (F16) {
+                        o[nt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, va), __builtin_bit_cast(f16x8, pbh), o[nt], 0, 0, 0);
+                    } else {
+                        const u32x4 pbl = (u32x4){pl[n][4 * mm], pl[n][4 * mm + 1], pl[n][4 * mm + 2], pl[n][4 * mm + 3]};
+                        o[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, va), __builtin_bit_cast(bf16x8, pbh), o[nt], 0, 0, 0);
+                        o[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, va), __builtin_bit_cast(bf16x8, pbl), o[nt], 0, 0, 0);
+                    }
                 }
-            }
         }
         __builtin_amdgcn_s_setprio(0);
     };
 
+    look_up(kv_begin);
+    load_unit();
+    look_up(kv_begin + 2 * KVB);
     int st = 0;
-    for (int base = kv_begin; base < kv_end; base += PF * KVB) {
+    for (int kv0 = kv_begin; kv0 < kv_end; kv0 += 2 * KVB) {
+        // Stage this unit, then fetch the next.  One barrier per unit: a wave that writes buffer st for unit n has passed
+        // the barrier of unit n-1, which every wave reaches only after it has finished reading buffer st for unit n-2.
+        // (A unit that reaches past kv_end reads positions of the next share, which are skipped, or masked ones.)
+        stage(st, kv0);
+        lds_barrier();
+        if (kv0 + 2 * KVB < kv_end) {
+            load_unit();
+            look_up(kv0 + 4 * KVB);
+        }
+        if (wave_active) {
 #pragma unroll
-        for (int u = 0; u < PF; u++) {
-            const int kv0 = base + u * KVB;
-            if (kv0 < kv_end) {      // uniform over the workgroup
-                // Stage this step, then fetch the step PF ahead into the set just emptied.  One barrier per
-                // step: a wave that writes buffer st for step n has passed the barrier of step n-1, which
-                // every wave reaches only after it has finished reading buffer st for step n-2.
-                stage(st, u, kv0);
-                lds_barrier();
-                if (kv0 + PF * KVB < kv_end) load_step(u, kv0 + PF * KVB);
-                if (wave_active && kv0 <= wave_last_pos && kv0 + KVB > wave_low) compute(kv0, st);   // else nothing visible to this wave
-                st ^= 1;
+            for (int u = 0; u < 2; u += NT) {
+                const int at = kv0 + KVB * u;
+                if (at < kv_end && at <= wave_last_pos && at + NT * KVB > wave_low) compute(kv0, st, u);   // else nothing visible to this wave
             }
         }
+        st ^= 1;
     }
     if constexpr (F16) {      // 0x4780 is 65536 as bf16: the first magnitude that fp16 cannot hold (also infinities and NaNs)
         if (out_of_range || mag[0] >= 0x4780 || mag[1] >= 0x4780) *f16_flag = 1;
     }
     // the two halves of a query's scores were summed separately
     l += __shfl_xor(l, 32, WAVE);
-    if (n_splits > 1) {      // unnormalised share: [tile][row in tile][head][split][HD] and (m, l)
+    if (!whole) {      // unnormalised share: [tile][row in tile][head][split][HD] and (m, l)
         if (q_valid) {
-            const int64_t item = (((int64_t)blockIdx.x * 128 + qi) * H + h) * n_splits + split;
+            const int64_t item = (((int64_t)tile_idx * 128 + qi) * H + h) * gridDim.z + split;
             float *op = part_o + item * HD;
 #pragma unroll
             for (int nt = 0; nt < 4; nt++)
@@ -343,27 +407,35 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
     }
 }
 
-// One workgroup per (tile row slot, head): adds the splits of a row in split order.  A split that saw no
-// visible position of the row has m = -inf and weight 0; split 0 or a later one always saw one.
-__global__ __launch_bounds__(128) void k_attn_prefill_merge(const int4 *__restrict__ tiles, int H, int n_splits,
+// Adds the shares of a tile's rows in order: half a wave per row (four dimensions a lane), eight rows of one head at a
+// time.  A share that saw no visible position of the row has m = -inf and weight 0; some share always saw one.  Tiles
+// that one workgroup walked whole are finished already.
+__global__ __launch_bounds__(256) void k_attn_prefill_merge(const int4 *__restrict__ tiles, int H, int window, int per, int ns,
                                                             const float *__restrict__ part_o,
                                                             const float *__restrict__ part_ml,
                                                             float *__restrict__ out, ld::OperandImage image) {
-    const int4 tile = tiles[blockIdx.y >> 7];
-    const int r = blockIdx.y & 127, h = blockIdx.x, d = threadIdx.x;
-    if (r >= tile.y) return;
-    const int64_t base = ((int64_t)blockIdx.y * H + h) * n_splits;
-    float M = -INFINITY;
-    for (int z = 0; z < n_splits; z++) M = fmaxf(M, part_ml[(base + z) * 2]);
-    float o = 0.f, L = 0.f;
-    for (int z = 0; z < n_splits; z++) {
-        const float a = fast_exp2(part_ml[(base + z) * 2] - M);
-        o += a * part_o[(base + z) * HD + d];
-        L += a * part_ml[(base + z) * 2 + 1];
+    const int4 tile = tiles[blockIdx.y];
+    const int n = min((tile_steps(tile, window) + per - 1) / per, ns);
+    const int r = blockIdx.z * 8 + (threadIdx.x >> 5), h = blockIdx.x, sub = threadIdx.x & 31;
+    if (n <= 1 || r >= tile.y) return;
+    const int64_t base = (((int64_t)blockIdx.y * 128 + r) * H + h) * ns;
+    const float2 ml = sub < n ? *reinterpret_cast<const float2 *>(part_ml + (base + sub) * 2) : make_float2(-INFINITY, 0.f);
+    float M = ml.x;
+#pragma unroll
+    for (int off = 1; off < MAX_SPLITS; off <<= 1) M = fmaxf(M, __shfl_xor(M, off, WAVE));
+    const float weight = fast_exp2(ml.x - M);
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+    float L = 0.f;
+    for (int z = 0; z < n; z++) {
+        const float a = __shfl(weight, z, 32);
+        const float4 v = *reinterpret_cast<const float4 *>(part_o + (base + z) * HD + sub * 4);
+        o.x += a * v.x; o.y += a * v.y; o.z += a * v.z; o.w += a * v.w;
+        L += a * __shfl(ml.y, z, 32);
     }
-    const int64_t e = ((int64_t)(tile.x + r) * H + h) * HD + d;
-    if (image.hi) store_operand(image, tile.x + r, e, o / L);
-    else out[e] = o / L;
+    const float4 v = make_float4(o.x / L, o.y / L, o.z / L, o.w / L);
+    const int64_t e = ((int64_t)(tile.x + r) * H + h) * HD + sub * 4;
+    if (image.hi) store_operand4(image, tile.x + r, e, v);
+    else *reinterpret_cast<float4 *>(out + e) = v;
 }
 
 }  // namespace
@@ -372,41 +444,47 @@ namespace ld {
 
 bool prefill_attention_supported(int dtype_is_bf16, int hd) { return dtype_is_bf16 && hd == HD; }
 
-// Splits of the KV range per tile: enough to give the launch about two workgroups per CU, at least 8 steps
-// (256 positions) each, at most 8, and only as many as the scratch holds.
-int prefill_attention_splits(int n_tiles, int H, int max_pos, int window, size_t scratch_bytes) {
-    const int span = window > 0 ? std::min(max_pos + 1, window + 128) : max_pos + 1;   // positions a tile walks
-    int s = 512 / std::max(1, n_tiles * H);
-    s = std::min(s, (span / KVB) / 8);
-    s = std::min(s, 8);
-    const size_t per_split = (size_t)n_tiles * 128 * H * (HD + 2) * sizeof(float);
-    if (per_split) s = (int)std::min<size_t>(s, scratch_bytes / per_split);
-    if (n_tiles * 128 > 65535) s = 1;       // the merge launch has one grid row per tile row slot
-    return std::max(s, 1);
+// Shares of the KV walk for the longest tile, and the steps of a share (shorter tiles have fewer shares).  Modelled in
+// steps of a workgroup: rounds of two workgroups per CU, a share costs its steps and about three more (queries, first
+// loads, partial result), and the merge a step and a half and 1 / 200 for each partial result of 64 KB (5 us at 400 of them,
+// 15 at 1500).  At least 8 steps a share, and only as many shares as the scratch holds.
+static int prefill_shares(int n_tiles, int H, int max_pos, int window, size_t scratch_bytes, int *per) {
+    const int span = window > 0 ? std::min(max_pos + 1, window + 128 + KVB) : max_pos + 1;   // positions a tile walks
+    const int steps = (span + KVB - 1) / KVB;
+    const int64_t items = (int64_t)n_tiles * H;
+    const size_t per_share = (size_t)items * 128 * (HD + 2) * sizeof(float);
+    int best = 1;
+    double best_t = 1e30;
+    for (int n = 1; n <= MAX_SPLITS; n++) {
+        const int p = ((steps + n - 1) / n + 1) & ~1;      // whole units of two steps
+        if (n > 1 && (p < 8 || per_share * n > scratch_bytes)) break;
+        const double t = (double)((items * n + 511) / 512) * (p + 3) + (n > 1 ? 1.5 + items * n / 200.0 : 0.0);
+        if (t < best_t) { best_t = t; best = n; }
+    }
+    *per = ((steps + best - 1) / best + 1) & ~1;
+    return best;
 }
 
-size_t prefill_attention_scratch_bytes() {
-    // splits > 1 only while n_tiles * H * splits <= 512; 128 rows per tile
-    return (size_t)512 * 128 * (HD + 2) * sizeof(float);
-}
+size_t prefill_attention_scratch_bytes() { return (size_t)1536 * 128 * (HD + 2) * sizeof(float); }      // shares of 128 rows
 
 void launch_prefill_attention(const float *q, int q_stride, const uint16_t *pool, int Hkv, const int32_t *table,
                               int table_stride, const int32_t *tiles, int n_tiles, int H, int window, int max_pos,
                               float *out, void *scratch, size_t scratch_bytes, hipStream_t s,
                               const OperandImage &image, int *f16_flag) {
     const float sl2 = 1.4426950408889634f / sqrtf((float)HD);
-    const int ns = scratch ? prefill_attention_splits(n_tiles, H, max_pos, window, scratch_bytes) : 1;
+    int per = 0;
+    const int ns = prefill_shares(n_tiles, H, max_pos, window, scratch ? scratch_bytes : 0, &per);
     float *part_o = (float *)scratch;
     float *part_ml = part_o ? part_o + (size_t)n_tiles * 128 * H * ns * HD : nullptr;
     if (f16_flag)
-        LD_LAUNCH(k_attn_prefill<true>, dim3(n_tiles, H, ns), dim3(256), 0, s, q, q_stride, pool, Hkv, table, table_stride,
-                  (const int4 *)tiles, H, window, sl2, out, part_o, part_ml, image, f16_flag);
+        LD_LAUNCH(k_attn_prefill<true>, dim3(H, n_tiles, ns), dim3(256), 0, s, q, q_stride, pool, Hkv, table, table_stride,
+                  (const int4 *)tiles, H, window, sl2, out, per, part_o, part_ml, image, f16_flag);
     else
-        LD_LAUNCH(k_attn_prefill<false>, dim3(n_tiles, H, ns), dim3(256), 0, s, q, q_stride, pool, Hkv, table, table_stride,
-                  (const int4 *)tiles, H, window, sl2, out, part_o, part_ml, image, f16_flag);
+        LD_LAUNCH(k_attn_prefill<false>, dim3(H, n_tiles, ns), dim3(256), 0, s, q, q_stride, pool, Hkv, table, table_stride,
+                  (const int4 *)tiles, H, window, sl2, out, per, part_o, part_ml, image, f16_flag);
     if (ns > 1)
-        LD_LAUNCH(k_attn_prefill_merge, dim3(H, n_tiles * 128), dim3(128), 0, s, (const int4 *)tiles, H, ns, part_o,
-                  part_ml, out, image);
+        LD_LAUNCH(k_attn_prefill_merge, dim3(H, n_tiles, 16), dim3(256), 0, s, (const int4 *)tiles, H, window, per, ns, part_o, part_ml,
+                  out, image);
 }
 
 }  // namespace ld

@@ -257,13 +257,11 @@ ld_status enqueue_pass(ld_kv *kv, const std::vector<Row> &rows, int n_single, co
 
     // metadata: tok | pos | seq_slot | ctx_len | emit_row, each T (emit: R) entries at stride T
     int32_t *pm = kv->pin_meta + (size_t)slot * kv->meta_ints();
-    int max_ctx = 1;
     for (int t = 0; t < T; t++) {
         pm[t] = rows[t].tok;
         pm[T + t] = rows[t].pos;
         pm[2 * T + t] = rows[t].seq;
         pm[3 * T + t] = rows[t].pos + 1;
-        max_ctx = std::max(max_ctx, rows[t].pos + 1);
     }
     for (int r = 0; r < R; r++) pm[4 * T + r] = emit[r];
     // prefill tiles: (first row, rows <= 128, first position, sequence) for the rows after the decode rows
@@ -281,7 +279,8 @@ ld_status enqueue_pass(ld_kv *kv, const std::vector<Row> &rows, int n_single, co
     }
     const int n_dec_rows = mfma_attn ? n_single : T;   // rows that go through the single-query kernel: [dec0, T)
     const int dec0 = T - n_dec_rows;
-    int max_ctx_dec = 1;
+    int max_ctx_dec = 1, max_ctx_pre = 1;
+    for (int t = 0; t < dec0; t++) max_ctx_pre = std::max(max_ctx_pre, rows[t].pos + 1);
     for (int t = dec0; t < T; t++) max_ctx_dec = std::max(max_ctx_dec, rows[t].pos + 1);
     // sampling parameters of the emitting rows, only when some sequence samples: seeds (8-byte aligned),
     // temperatures, position the emitted token will take
@@ -397,7 +396,7 @@ ld_status enqueue_pass(ld_kv *kv, const std::vector<Row> &rows, int n_single, co
             if (n_tiles)
                 LD_TIMED(LD_PROF_ATTENTION, timed_void([&] {
                     ld::launch_prefill_attention(w.qkv, nqkv, (const uint16_t *)pool_l, Hkv, w.table, kv->max_blocks, d_tiles,
-                                                 n_tiles, H, c.window, max_ctx - 1, w.attn, w.att_scratch,
+                                                 n_tiles, H, c.window, max_ctx_pre - 1, w.attn, w.att_scratch,
                                                  w.att_scratch_bytes, st, {A, A + (size_t)T * nq, f_wo, f16_flag}, f16_flag);
                 }));
             const ld::GemmNext to_ffn{m.ffn_norm[l], c.rms_eps, B, nullptr, f_gate_up};
@@ -428,7 +427,7 @@ ld_status enqueue_pass(ld_kv *kv, const std::vector<Row> &rows, int n_single, co
                                                             w.attn + (size_t)dec0 * nq, w.att_scratch, w.att_scratch_bytes, st));
         if (n_tiles)
             LD_TIMED(LD_PROF_ATTENTION, ldk_prefill_attention_f16(w.qkv, nqkv, pool_l, c.dtype, w.table, kv->max_blocks, d_tiles,
-                                                                  n_tiles, H, Hkv, hd, c.window, max_ctx - 1, w.attn,
+                                                                  n_tiles, H, Hkv, hd, c.window, max_ctx_pre - 1, w.attn,
                                                                   w.att_scratch, w.att_scratch_bytes, f16_flag, st));
         LD_TIMED(LD_PROF_WO, ld::linear_pass(m.wo[l], c.dtype, w.attn, nullptr, 0.f, T, d, nq, LDK_ADD, w.x, w.lin_scratch, w.lin_scratch_bytes, st, f16_flag, img(m.h_wo)));
         LD_TIMED(LD_PROF_GATE_UP, ld::linear_pass(m.wgate_up[l], c.dtype, w.x, m.ffn_norm[l], c.rms_eps, T, c.d_ffn, d, LDK_SWIGLU, w.act, w.lin_scratch,

@@ -677,6 +677,41 @@ def test_prefill_attention_fp16_form(H, Hkv, window, split):
     assert run(qb, pool)[1] == 1
 
 
+@pytest.mark.parametrize("shares", [1, 2, 16])
+@pytest.mark.parametrize("window", [0, 333])
+@pytest.mark.parametrize("H,Hkv,many", [(3, 3, False), (16, 4, False), (2, 1, True)])
+def test_prefill_attention_uneven_tiles(H, Hkv, many, window, shares):
+    """Tiles of 1, 32, 33, 64, 65 and 128 rows behind contexts of very different length (walks of 1 to 99 steps, even and odd), so that a
+    short tile has fewer shares than a long one and the last share of each is cut; head counts that do and don't divide into
+    the eight chip dies; more tiles than a wave has lanes (which then keep their own order); scratch for one, two and all shares,
+    and a max_pos beyond every row.  Both forms against the oracle, with the bounds of the two tests around this one."""
+    hd = 128
+    segs = [(31 * i % 97, 1 + 5 * i % 40) for i in range(70)] if many else [(3000, 129), (17, 64), (700, 33), (0, 1), (1503, 32), (1000, 65)]
+    table, pool, _ = _attention_case(35, [p + n for p, n in segs], H, Hkv, hd, "bf16")
+    T = sum(n for _, n in segs)
+    q = gen.normal(35, 9, (T, H, hd), device=DEV)
+    tiles, row_seq, row_pos, r = [], [], [], 0
+    for s, (p0, n) in enumerate(segs):
+        for off in range(0, n, 128):
+            tiles.append([r + off, min(128, n - off), p0 + off, s])
+        row_seq += [s] * n; row_pos += list(range(p0, p0 + n)); r += n
+    tiles_d, flag = torch.tensor(tiles, dtype=torch.int32, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
+    size = min(shares * len(tiles) * H * 128 * (hd + 2) * 4, ld.ldk_prefill_attention_scratch_bytes())
+    scratch = torch.empty(size, dtype=torch.uint8, device=DEV) if shares > 1 else None
+    out, out16 = torch.zeros(T, H, hd, device=DEV), torch.zeros(T, H, hd, device=DEV)
+    args = (H * hd, device_pool(pool), table.to(DEV), tiles_d, H, Hkv, hd)
+    ld.ldk_prefill_attention(q, *args, out, max(row_pos) + 500 * (shares - 1), window=window, scratch=scratch)
+    ld.ldk_prefill_attention_f16(q, *args, out16, max(row_pos), flag, window=window, scratch=scratch)
+    torch.cuda.synchronize()
+    assert int(flag.item()) == 0
+    ph = oracle.to_host_matrix(pool.reshape(pool.shape[0], -1)).reshape(-1)
+    ref = oracle.paged_attention(q.cpu().numpy(), ph, ph[Hkv * 16 * hd:], (2 * Hkv * 16 * hd, 16 * hd, hd),
+                                 table.numpy()[row_seq], [p + 1 for p in row_pos], Hkv, window=window)
+    for got, bound in ((out, 3e-5), (out16, 1e-3)):
+        err = np.max(np.abs(got.cpu().numpy() - ref), axis=(1, 2)) / np.abs(ref).max()
+        assert err.max() <= bound, (err.max(), int(err.argmax()), row_pos[int(err.argmax())])
+
+
 @pytest.mark.parametrize("split", [False, True], ids=["whole", "kv-split"])
 @pytest.mark.parametrize("window", [0, 1, 40, 128, 200, 5000])
 @pytest.mark.parametrize("H,Hkv", [(4, 4), (8, 2)])
