@@ -4,20 +4,24 @@
 // 16-byte loads in flight per CU as possible, with as few vector-ALU instructions per loaded byte
 // as possible, and with the same amount of work on every CU.
 //
-//  - The grid is a small multiple of the CU count; workgroup i owns the contiguous output range
+//  - Two workgroups of eight waves per CU; workgroup i owns the contiguous output range
 //    [i N / G, (i+1) N / G), so all workgroups stream the same number of bytes (+-1 row).
-//  - Inside a workgroup the K dimension is split over the waves: wave w owns the column slab
-//    [w * 512 * CPW, (w+1) * 512 * CPW).  Its slice of the input vector (already multiplied by the
-//    RMSNorm gain) lives in 8*CPW registers per lane for the whole kernel; the input is read once
-//    per wave instead of once per output row.
-//  - Matrix rows are processed in groups of GL loads per lane.  All loads of a group are issued
-//    back to back (they are independent), and the next group's loads are issued before the
-//    current group is reduced (double buffering in registers).
-//  - A group's per-lane partial sums are reduced across the 64 lanes with a transposing butterfly
-//    (GL - 1 + log2(64 / GL) shuffles for GL rows instead of 6 per row), then across the waves
-//    through LDS, one barrier per group.
+//  - A workgroup's work is cut into items of two rows (the two of a pair, or neighbours) and one slab of 2048 columns:
+//    eight 16-byte loads per lane, 4 KB of a row in one run by one wave.  Its items, slab by slab, are dealt to the waves in
+//    equal runs, and a wave keeps two items in flight (16 KB; 256 KB a CU).
+//  - The input, multiplied by the RMSNorm gain, sits in LDS: it is requested before the first rows, and an item reads
+//    its slab once for two rows, as many bytes as the rows have.
+//  - An item ends in two sums across a wave (six shuffles), which wait in LDS: the only barriers are the one after
+//    the input has arrived and the one before the epilogue.
+//  What bounds it: HBM, and at both ends of the launch the latency of the input and of the last rows.  Requests of
+//  a wave that lie together stream faster (gate/up of the 7B shape, loads alone: 32.7 us with 128-byte runs, 28.7 with
+//  4 KB), and waves that need not meet at a barrier for every eight rows keep their loads going.  7B shape, us, a form with
+//  512-column slabs per wave and a barrier per group before -> this one: q/k/v 21.4 -> 19.3, gate/up 31.8 -> 31.3, down
+//  18.3 -> 17.8, output projection 8.0 -> 8.4; 13B shape (calls alone): 43.7 -> 26.8, 66.8 -> 45.1, 24.9 -> 24.6, 17.1 -> 12.0.  Sixteen waves in one workgroup per CU: 19.3, 33.5, 17.9, 8.6 (one
+//  prologue and one end for a whole CU); four waves in four: 20.8, 33.9, 21.7, 9.5; items row by row instead of slab
+//  by slab: 19.8, 33.0, 19.0, 8.3.
 //  - The RMSNorm scale 1 / rms(x) is a scalar, so it is applied to the finished dot products; its
-//    sum of squares is accumulated from the same input slice and shares the first barrier.
+//    sum of squares is accumulated when the input goes to LDS.
 //  - Epilogues: store, residual add, SwiGLU (gate row r with up row N + r), and "RoPE + cache
 //    append" for the fused q/k/v projection (row i of a head with row i + hd/2, then rotate by
 //    the position's angle and write k, v straight into the paged pool).
@@ -30,46 +34,11 @@ using namespace ldd;
 
 namespace {
 
-constexpr int MAX_WAVES = 16;
-constexpr int MAX_GL = 16;
-
-// Transposing butterfly: on entry every lane holds G partial sums a[0..G); on exit lane L holds in
-// a[0] the sum over all 64 lanes of row row_of_lane<G>(L).
-template <int G>
-__device__ __forceinline__ float transpose_reduce(float (&a)[G], int lane) {
-    int off = 32;
-#pragma unroll
-    for (int n = G; n > 1; n >>= 1) {
-        const int half = n >> 1;
-        const bool upper = (lane & off) != 0;
-#pragma unroll
-        for (int j = 0; j < half; j++) {
-            const float send = upper ? a[j] : a[j + half];
-            const float keep = upper ? a[j + half] : a[j];
-            a[j] = keep + __shfl_xor(send, off, WAVE);
-        }
-        off >>= 1;
-    }
-    for (; off > 0; off >>= 1) a[0] += __shfl_xor(a[0], off, WAVE);
-    return a[0];
-}
-template <int G>
-__device__ __forceinline__ int row_of_lane(int lane) {
-    int row = 0, bit = 5;
-#pragma unroll
-    for (int n = G; n > 1; n >>= 1) {
-        row = (row << 1) | ((lane >> bit) & 1);
-        bit--;
-    }
-    return row;
-}
-template <int G>
-__device__ __forceinline__ bool lane_writes(int lane) {
-    // one lane per row: the lanes whose bits below the row bits are zero
-    int used = 0;
-    for (int n = G; n > 1; n >>= 1) used++;
-    return (lane & ((1 << (6 - used)) - 1)) == 0;
-}
+constexpr int WAVES = 8;             // per workgroup, two workgroups per CU
+constexpr int CPS = 4;               // 512-column pieces of a slab: one 16-byte load per lane and row each
+constexpr int SLAB = CPS * WAVE * 8; // columns of a slab
+constexpr int MAX_K = 16384;
+constexpr int MAX_PARTS = 2048;      // partial sums of a workgroup: with the largest input 72 KB of LDS, two fit a CU
 
 __device__ __forceinline__ float dot8(const u32x4_t &w, const float (&x)[8]) {
     float s = 0.f;
@@ -92,56 +61,66 @@ __device__ __forceinline__ int unit_row(int u, int m, int N, int half_hd) {
     else return u;
 }
 
-// GL = 16-byte loads issued per lane per group: 8 keeps the kernel under 128 VGPRs (up to 16 waves
-// per workgroup, 4 waves per SIMD) with two groups in flight.
-template <int CPW, int GL, int EPI, bool NORM>
-__global__ __launch_bounds__(1024) void k_gemv1(const bf16_t *__restrict__ W, const float *__restrict__ x,
-                                                const float *__restrict__ g, float eps, int N, int K,
-                                                float *__restrict__ y, ld::RopeKvArgs rk) {
+// KMAX: columns the input's place in LDS is for.
+template <int KMAX, int EPI, bool NORM>
+__global__ __launch_bounds__(WAVES * WAVE, 4) void k_gemv1(const bf16_t *__restrict__ W, const float *__restrict__ x,
+                                                        const float *__restrict__ g, float eps, int N, int K,
+                                                        float *__restrict__ y, ld::RopeKvArgs rk) {
     constexpr bool PAIRED = (EPI == ld::GEMV_SWIGLU || EPI == ld::GEMV_ROPE_KV);
-    constexpr int G = GL / CPW;                // matrix rows per group
-    constexpr int UG = PAIRED ? G / 2 : G;     // output units per group
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
+    constexpr int UPI = PAIRED ? 1 : 2;        // output units of an item: it has two rows either way
+    __shared__ __attribute__((aligned(16))) float xs[KMAX / 8][2][4];      // [512-column piece][half][lane] as float4: see xpos
+    __shared__ float part[MAX_PARTS];
+    __shared__ float part_ss[WAVES];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half_hd = (EPI == ld::GEMV_ROPE_KV) ? rk.hd / 2 : 1;
     const int n_units = (EPI == ld::GEMV_ROPE_KV) ? N / 2 : N;
     const int u_begin = (int)((int64_t)blockIdx.x * n_units / gridDim.x);
-    const int u_end = (int)((int64_t)(blockIdx.x + 1) * n_units / gridDim.x);
-    const int n_groups = (u_end - u_begin + UG - 1) / UG;
-    __shared__ float part[2][MAX_WAVES][MAX_GL];
-    __shared__ float part_ss[MAX_WAVES];
+    const int units = (int)((int64_t)(blockIdx.x + 1) * n_units / gridDim.x) - u_begin;
+    const int n_slabs = (K + SLAB - 1) / SLAB, per_slab = (units + UPI - 1) / UPI, n_items = per_slab * n_slabs;
+    const int it_end = (wave + 1) * n_items / WAVES;
 
-    // column offsets of this lane inside a row; a lane past the end of the row contributes zeros
-    int kofs[CPW];
-    bool kval[CPW];
+    // the input is requested before the first rows, so that waiting for it does not wait for them
+    constexpr int XT = KMAX / 8 / (WAVES * WAVE);      // groups of eight columns a thread brings in
+    float xv[XT][8], gv[NORM ? XT : 1][8];
 #pragma unroll
-    for (int c = 0; c < CPW; c++) {
-        kofs[c] = (wave * CPW + c) * (WAVE * 8) + lane * 8;
-        kval[c] = kofs[c] < K;
-        if (!kval[c]) kofs[c] = 0;
+    for (int i = 0; i < XT; i++) {
+        const int col = (i * WAVES * WAVE + tid) * 8;
+        if (col < K) {
+            load8(x + col, xv[i]);
+            if (NORM) load8(g + col, gv[i]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; e++) xv[i][e] = 0.f;
+            if (NORM) {
+#pragma unroll
+                for (int e = 0; e < 8; e++) gv[i][e] = 0.f;
+            }
+        }
     }
 
-    u32x4_t bufA[G][CPW], bufB[G][CPW];
-    auto issue = [&](u32x4_t (&buf)[G][CPW], int gi) {
-        const int u0 = u_begin + gi * UG;
+    float before = 0.f;      // the old value for the residual add
+    if (EPI == ld::GEMV_ADD && tid < units) before = y[u_begin + tid];
+
+    u32x4_t bufA[2][CPS], bufB[2][CPS];
+    auto issue = [&](u32x4_t (&buf)[2][CPS], int it) {
+        const int slab = it / per_slab, u0 = u_begin + (it - slab * per_slab) * UPI;
 #pragma unroll
-        for (int r = 0; r < G; r++) {
-            const int u = u0 + (PAIRED ? r % UG : r);
-            if (u < u_end) {   // uniform over the workgroup: units past the range are not fetched
-                const int row = unit_row<EPI>(u, PAIRED ? r / UG : 0, N, half_hd);
-                const bf16_t *p = W + (int64_t)row * K;
+        for (int r = 0; r < 2; r++) {
+            // an odd last row reads the one before it again; its sum is not used
+            const int u = PAIRED ? u0 : min(u0 + r, u_begin + units - 1);
+            const bf16_t *p = W + (int64_t)unit_row<EPI>(u, PAIRED ? r : 0, N, half_hd) * K;
 #pragma unroll
-                for (int c = 0; c < CPW; c++) buf[r][c] = load_stream16(p + kofs[c]);
-            } else {
-#pragma unroll
-                for (int c = 0; c < CPW; c++) buf[r][c] = (u32x4_t){0u, 0u, 0u, 0u};
+            for (int c = 0; c < CPS; c++) {
+                const int col = slab * SLAB + c * (WAVE * 8) + lane * 8;
+                buf[r][c] = col < K ? load_stream16(p + col) : (u32x4_t){0u, 0u, 0u, 0u};
             }
         }
     };
-    if (n_groups > 0) issue(bufA, 0);
+    int it = wave * n_items / WAVES;
+    if (it < it_end) issue(bufA, it);
+    if (it + 1 < it_end) issue(bufB, it + 1);
 
-    // cache append: position and physical block are looked up once, right after the first weight loads are
-    // on their way, so that the chain of dependent loads (position -> block table) overlaps the weight
-    // stream instead of ending every output group
+    // cache append: position and physical block, looked up while the weights are on their way
     int kv_pos = 0;
     int64_t kv_phys = 0;
     if constexpr (EPI == ld::GEMV_ROPE_KV) {
@@ -149,112 +128,111 @@ __global__ __launch_bounds__(1024) void k_gemv1(const bf16_t *__restrict__ W, co
         kv_phys = rk.table[(int64_t)rk.seq_slot[0] * rk.table_stride + (kv_pos >> 4)];
     }
 
-    // this wave's slice of the input (gain applied), and its share of the sum of squares
-    float xs[CPW][8];
+    // the input (gain applied) goes to LDS, piece by piece in two planes, so that 64 lanes read 1 KB without conflicts
     float ss = 0.f;
 #pragma unroll
-    for (int c = 0; c < CPW; c++) {
-        if (kval[c]) {
-            load8(x + kofs[c], xs[c]);
-            if (NORM) {
-                float gv[8];
-                load8(g + kofs[c], gv);
+    for (int i = 0; i < XT; i++) {
+        const int o = i * WAVES * WAVE + tid;      // group of eight columns; piece o / 64, lane o % 64
+        if (NORM) {
 #pragma unroll
-                for (int e = 0; e < 8; e++) {
-                    ss = fmaf(xs[c][e], xs[c][e], ss);
-                    xs[c][e] *= gv[e];
-                }
+            for (int e = 0; e < 8; e++) {
+                ss = fmaf(xv[i][e], xv[i][e], ss);
+                xv[i][e] *= gv[i][e];
             }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; e++) xs[c][e] = 0.f;
         }
+        float4 *at = reinterpret_cast<float4 *>(xs) + (o >> 6) * 128 + (o & 63);
+        at[0] = make_float4(xv[i][0], xv[i][1], xv[i][2], xv[i][3]);
+        at[64] = make_float4(xv[i][4], xv[i][5], xv[i][6], xv[i][7]);
     }
     if (NORM) {
         ss = wave_sum(ss);
         if (lane == 0) part_ss[wave] = ss;
     }
-    float rstd = 1.f;
+    lds_barrier();
 
-    auto consume = [&](u32x4_t (&buf)[G][CPW], int gi) {
-        // the old value for the residual add is requested before the arithmetic, not after the barrier
-        const int u = u_begin + gi * UG + (int)threadIdx.x;
-        const bool mine = threadIdx.x < UG && u < u_end;
-        float pre0 = 0.f;
-        if constexpr (EPI == ld::GEMV_ADD) {
-            if (mine) pre0 = y[u];
-        }
-        float acc[G];
+    auto consume = [&](u32x4_t (&buf)[2][CPS], int item) {
+        const int slab = item / per_slab;
+        float a0 = 0.f, a1 = 0.f;
 #pragma unroll
-        for (int r = 0; r < G; r++) {
-            acc[r] = 0.f;
+        for (int c = 0; c < CPS; c++) {
+            const float4 *at = reinterpret_cast<const float4 *>(xs) + (slab * CPS + c) * 128 + lane;
+            const float4 lo = at[0], hi = at[64];
+            const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+            a0 += dot8(buf[0][c], v);
+            a1 += dot8(buf[1][c], v);
+        }
+        // lanes below 32 end up with the first row's sum, the others with the second's
+        const bool upper = lane >= 32;
+        float s = (upper ? a1 : a0) + __shfl_xor(upper ? a0 : a1, 32, WAVE);
 #pragma unroll
-            for (int c = 0; c < CPW; c++) acc[r] += dot8(buf[r][c], xs[c]);
-        }
-        const float tot = transpose_reduce<G>(acc, lane);
-        if (lane_writes<G>(lane)) part[gi & 1][wave][row_of_lane<G>(lane)] = tot;
-        lds_barrier();
-        if (NORM && gi == 0) {
-            float s2 = 0.f;
-            for (int w = 0; w < nwaves; w++) s2 += part_ss[w];
-            rstd = 1.0f / sqrtf(s2 / K + eps);
-        }
-        if (mine) {
-            float a = 0.f, b = 0.f;
-            for (int w = 0; w < nwaves; w++) {
-                a += part[gi & 1][w][threadIdx.x];
-                if (PAIRED) b += part[gi & 1][w][threadIdx.x + UG];
-            }
-            a *= rstd;
-            b *= rstd;
-            if constexpr (EPI == ld::GEMV_STORE) {
-                y[u] = a;
-            } else if constexpr (EPI == ld::GEMV_ADD) {
-                y[u] = pre0 + a;
-            } else if constexpr (EPI == ld::GEMV_SWIGLU) {
-                y[u] = a / (1.0f + __expf(-a)) * b;
-            } else {
-                const int hh = u / half_hd, i = u % half_hd, hd = 2 * half_hd;
-                if (hh < rk.H + rk.Hkv) {   // q or k head: rotate the pair
-                    const float2 cs = rk.cos_sin[i];
-                    const float ra = a * cs.x - b * cs.y, rb = a * cs.y + b * cs.x;
-                    a = ra;
-                    b = rb;
-                }
-                if (hh < rk.H) {
-                    y[hh * hd + i] = a;
-                    y[hh * hd + i + half_hd] = b;
-                } else {
-                    const int which = hh < rk.H + rk.Hkv ? 0 : 1;
-                    const int j = hh - rk.H - which * rk.Hkv;
-                    bf16_t *blk = rk.pool + kv_phys * kv_block_elems(rk.Hkv, hd);
-                    const int slot = kv_pos & 15;
-                    if (which == 0) {
-                        blk[kv_k_offset(hd, j, slot, i)] = f32_to_bf16(a);
-                        blk[kv_k_offset(hd, j, slot, i + half_hd)] = f32_to_bf16(b);
-                    } else {
-                        blk[kv_v_offset(rk.Hkv, hd, j, slot, i)] = f32_to_bf16(a);
-                        blk[kv_v_offset(rk.Hkv, hd, j, slot, i + half_hd)] = f32_to_bf16(b);
-                    }
-                }
-            }
-        }
+        for (int off = 16; off > 0; off >>= 1) s += __shfl_xor(s, off, WAVE);
+        if ((lane & 31) == 0) part[item * 2 + (lane >> 5)] = s;
     };
+    for (; it < it_end; it += 2) {
+        consume(bufA, it);
+        if (it + 2 < it_end) issue(bufA, it + 2);
+        if (it + 1 < it_end) {
+            consume(bufB, it + 1);
+            if (it + 3 < it_end) issue(bufB, it + 3);
+        }
+    }
+    lds_barrier();
 
-    for (int gi = 0; gi < n_groups; gi += 2) {
-        if (gi + 1 < n_groups) issue(bufB, gi + 1);
-        consume(bufA, gi);
-        if (gi + 1 < n_groups) {
-            if (gi + 2 < n_groups) issue(bufA, gi + 2);
-            consume(bufB, gi + 1);
+    float rstd = 1.f;
+    if (NORM) {
+        float s2 = 0.f;
+#pragma unroll
+        for (int w = 0; w < WAVES; w++) s2 += part_ss[w];
+        rstd = 1.0f / sqrtf(s2 / K + eps);
+    }
+    for (int i = tid; i < units; i += WAVES * WAVE) {
+        const int u = u_begin + i;
+        float a = 0.f, b = 0.f;
+        for (int sl = 0; sl < n_slabs; sl++) {
+            const float *p = part + sl * per_slab * 2 + (PAIRED ? 2 * i : i);
+            a += p[0];
+            if (PAIRED) b += p[1];
+        }
+        a *= rstd;
+        b *= rstd;
+        if constexpr (EPI == ld::GEMV_STORE) {
+            y[u] = a;
+        } else if constexpr (EPI == ld::GEMV_ADD) {
+            y[u] = (i == tid ? before : y[u]) + a;
+        } else if constexpr (EPI == ld::GEMV_SWIGLU) {
+            y[u] = a / (1.0f + __expf(-a)) * b;
+        } else {
+            const int hh = u / half_hd, i = u % half_hd, hd = 2 * half_hd;
+            if (hh < rk.H + rk.Hkv) {   // q or k head: rotate the pair
+                const float2 cs = rk.cos_sin[i];
+                const float ra = a * cs.x - b * cs.y, rb = a * cs.y + b * cs.x;
+                a = ra;
+                b = rb;
+            }
+            if (hh < rk.H) {
+                y[hh * hd + i] = a;
+                y[hh * hd + i + half_hd] = b;
+            } else {
+                const int which = hh < rk.H + rk.Hkv ? 0 : 1;
+                const int j = hh - rk.H - which * rk.Hkv;
+                bf16_t *blk = rk.pool + kv_phys * kv_block_elems(rk.Hkv, hd);
+                const int slot = kv_pos & 15;
+                if (which == 0) {
+                    blk[kv_k_offset(hd, j, slot, i)] = f32_to_bf16(a);
+                    blk[kv_k_offset(hd, j, slot, i + half_hd)] = f32_to_bf16(b);
+                } else {
+                    blk[kv_v_offset(rk.Hkv, hd, j, slot, i)] = f32_to_bf16(a);
+                    blk[kv_v_offset(rk.Hkv, hd, j, slot, i + half_hd)] = f32_to_bf16(b);
+                }
+            }
         }
     }
 }
 
-template <int CPW, int GL, bool NORM>
-void launch_cpw(const bf16_t *W, const float *x, const float *g, float eps, int N, int K, int epi, float *y,
-                const ld::RopeKvArgs &rk, int grid, int threads, hipStream_t s) {
-#define LD_GEMV1(EPI_) LD_LAUNCH((k_gemv1<CPW, GL, EPI_, NORM>), dim3(grid), dim3(threads), 0, s, W, x, g, eps, N, K, y, rk)
+template <int KMAX, bool NORM>
+void launch_kmax(const bf16_t *W, const float *x, const float *g, float eps, int N, int K, int epi, float *y,
+                 const ld::RopeKvArgs &rk, int grid, hipStream_t s) {
+#define LD_GEMV1(EPI_) LD_LAUNCH((k_gemv1<KMAX, EPI_, NORM>), dim3(grid), dim3(WAVES * WAVE), 0, s, W, x, g, eps, N, K, y, rk)
     switch (epi) {
         case ld::GEMV_STORE: LD_GEMV1(ld::GEMV_STORE); break;
         case ld::GEMV_ADD: LD_GEMV1(ld::GEMV_ADD); break;
@@ -275,8 +253,7 @@ namespace ld {
 
 bool gemv1_supported(int N, int K, int epi) {
     if (K % 8 || K <= 0 || N <= 0) return false;
-    const int chunks = (K + 511) / 512;
-    if (chunks > 2 * MAX_WAVES) return false;
+    if (K > MAX_K) return false;
     if (epi == GEMV_ROPE_KV && N % 2) return false;
     return true;
 }
@@ -290,24 +267,24 @@ void launch_gemv1(const uint16_t *W, const float *x, const float *g, float eps, 
         if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&p, dev) == hipSuccess) n_cu = p.multiProcessorCount;
         if (n_cu <= 0) n_cu = 256;
     }
-    const int chunks = (K + 511) / 512;
-    const int cpw = chunks <= MAX_WAVES ? 1 : 2;
-    const int waves = (chunks + cpw - 1) / cpw;
     const int n_units = epi == GEMV_ROPE_KV ? N / 2 : N;
-    // Workgroups per CU (measured on the 7B shapes): long rows (two slabs per wave) like one resident
-    // workgroup, matrices with many outputs like six, the rest two.
+    // Two workgroups per CU; more (which then follow one another) where a workgroup's partial sums would not fit.
+    const int n_slabs = (K + SLAB - 1) / SLAB;
+    const bool paired = epi == GEMV_SWIGLU || epi == GEMV_ROPE_KV;
+    const int max_units = MAX_PARTS / n_slabs / (paired ? 2 : 1) - 2;
     static const int forced = env_int("LD_GEMV_WGS_PER_CU", 0);   // tuning knob
-    const int grid_per_cu = forced > 0 ? forced : (cpw == 2 ? 1 : (n_units >= 10000 ? 6 : 2));
-    int grid = n_cu * grid_per_cu;
+    const int least = (n_units + max_units - 1) / max_units;
+    int grid = n_cu * (forced > 0 ? forced : 2);
+    while (grid < least) grid += n_cu;
     if (grid > n_units) grid = n_units;
     RopeKvArgs none{};
     const RopeKvArgs &r = rk ? *rk : none;
-    if (cpw == 1) {
-        if (g) launch_cpw<1, 8, true>(W, x, g, eps, N, K, epi, y, r, grid, waves * 64, s);
-        else launch_cpw<1, 8, false>(W, x, g, eps, N, K, epi, y, r, grid, waves * 64, s);
+    if (K <= 8192) {
+        if (g) launch_kmax<8192, true>(W, x, g, eps, N, K, epi, y, r, grid, s);
+        else launch_kmax<8192, false>(W, x, g, eps, N, K, epi, y, r, grid, s);
     } else {
-        if (g) launch_cpw<2, 8, true>(W, x, g, eps, N, K, epi, y, r, grid, waves * 64, s);
-        else launch_cpw<2, 8, false>(W, x, g, eps, N, K, epi, y, r, grid, waves * 64, s);
+        if (g) launch_kmax<MAX_K, true>(W, x, g, eps, N, K, epi, y, r, grid, s);
+        else launch_kmax<MAX_K, false>(W, x, g, eps, N, K, epi, y, r, grid, s);
     }
 }
 

@@ -677,6 +677,41 @@ def test_prefill_attention_fp16_form(H, Hkv, window, split):
     assert run(qb, pool)[1] == 1
 
 
+@pytest.mark.parametrize("N,K,epi,norm", [(N, K, epi, norm) for epi in ("store", "add", "swiglu") for norm in (False, True) for N, K in [
+    (1, 8), (2, 2040), (3, 2048), (513, 2056), (1025, 6152), (1537, 8192), (770, 8200), (1026, 16384)]] + [(140000, 16384, "store", False)])
+def test_gemv_slab_edges(N, K, epi, norm):
+    """The one-row product at the edges of its slabs of 2048 columns, of the two sizes its input has in LDS (8192 columns and
+    16384), of the two-row items (odd and single rows, fewer outputs than workgroups, one more than two each) and beyond the
+    partial sums that one workgroup per slot can hold, against float64.  Bound: a sum passes through at most 4 x 8 additions in a lane,
+    6 across the wave and 8 over the slabs, so 64 roundings of 2^-24 of the sum of magnitudes cover it with the norm's."""
+    e = {"store": ld.LDK_STORE, "add": ld.LDK_ADD, "swiglu": ld.LDK_SWIGLU}[epi]
+    rows = N * (2 if epi == "swiglu" else 1)
+    torch.manual_seed(N * 31 + K)
+    W = torch.empty(rows, K, dtype=torch.bfloat16, device=DEV).normal_(0, 0.05)
+    x, g = torch.randn(1, K, device=DEV), 1 + 0.1 * torch.randn(K, device=DEV)
+    y0 = torch.randn(1, N, device=DEV)
+    y = y0.clone()
+    scratch = torch.empty(max(1, ld.ldk_linear_scratch_bytes(1, N, K, e)), dtype=torch.uint8, device=DEV)
+    ld.ldk_linear(W, x, y, e, g if norm else None, 1e-5, scratch)
+    xd = x[0].double()
+    if norm:
+        xd = xd * g.double() / torch.sqrt((xd * xd).mean() + 1e-5)
+    s, mag = torch.empty(rows, dtype=torch.float64, device=DEV), torch.empty(rows, dtype=torch.float64, device=DEV)
+    for r in range(0, rows, 20000):
+        w = W[r:r + 20000].double()
+        s[r:r + 20000], mag[r:r + 20000] = (w * xd).sum(1), (w * xd).abs().sum(1)
+    tol = 64 * 2.0 ** -24 * mag
+    if epi == "store":
+        ref = s
+    elif epi == "add":
+        ref, tol = y0[0].double() + s, tol + 2.0 ** -23 * (y0[0].double().abs() + s.abs())
+    else:      # |silu'| <= 1.1, |silu(a)| <= |a|; the exponential is good to some 2^-20 of the result
+        a, b = s[:N], s[N:]
+        ref = a * torch.sigmoid(a) * b
+        tol = 1.1 * tol[:N] * (b.abs() + tol[N:]) + a.abs() * tol[N:] + 2.0 ** -20 * (a * b).abs()
+    assert bool(((y[0].double() - ref).abs() <= tol).all()), float(((y[0].double() - ref).abs() / tol).max())
+
+
 @pytest.mark.parametrize("shares", [1, 2, 16])
 @pytest.mark.parametrize("window", [0, 333])
 @pytest.mark.parametrize("H,Hkv,many", [(3, 3, False), (16, 4, False), (2, 1, True)])
