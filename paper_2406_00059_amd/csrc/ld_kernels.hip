@@ -343,21 +343,33 @@ __global__ __launch_bounds__(256) void k_attn_partial(const float *__restrict__ 
 }
 
 // Merges the chunk partials of one (row, head): 256 threads = 256/HD thread groups, group g takes the
-// chunks g, g + 256/HD, ...; the chunk maxima and sums go through LDS first so that the loop over the
-// partial outputs has no dependent loads.
+// chunks g, g + 256/HD, ...; the chunk maxima and sums go through LDS.  Bound by its chain of memory round trips (a few
+// hundred KB in all), so the first AHEAD partial outputs of a group and the statistics are requested at once with the context
+// length that says how many of them count: what lies beyond it was never written and is not used.
+// 32 heads x 16 chunks at batch 1: 3.9 -> 3.0 us at best, 4.7 on average either way under the profiler; the 7B step 2972 -> 2954,
+// attention of sixteen rows with its merge 97.4 -> 96.6, of 32 grouped rows 76.2 -> 75.4.
 template <int HD>
 __global__ __launch_bounds__(256) void k_attn_merge(const float *__restrict__ part_o, const float *__restrict__ part_ml,
                                                     const int32_t *__restrict__ ctx_len, int H, int window,
                                                     int max_chunks, int cb, float *__restrict__ out,
                                                     ld::OperandImage image, int T, bool octets) {
     constexpr int NGRP = 256 / HD, MAXC = 512;   // MAXC: chunks whose statistics fit the LDS cache
+    constexpr int AHEAD = 12;
     __shared__ float sm_m[MAXC], sm_l[MAXC], sm_o[NGRP][HD], sm_L[NGRP], sm_red[4];
     const int h = blockIdx.x, t = blockIdx.y, d = threadIdx.x % HD, grp = threadIdx.x / HD;
+    const int64_t base = ((int64_t)t * H + h) * max_chunks;
+    const float2 ml0 = (int)threadIdx.x < max_chunks ? *reinterpret_cast<const float2 *>(part_ml + (base + threadIdx.x) * 2) : make_float2(0.f, 0.f);
+    float ahead[AHEAD];
+#pragma unroll
+    for (int u = 0; u < AHEAD; u++) ahead[u] = grp + u * NGRP < max_chunks ? part_o[(base + grp + u * NGRP) * HD + d] : 0.f;
     const int ctx = ctx_len[t];
     const int nch = ((ctx + 15) / 16 - (band_first(ctx, window) >> 4) + cb - 1) / cb;
-    const int64_t base = ((int64_t)t * H + h) * max_chunks;
     float mx = -INFINITY;
-    for (int c = threadIdx.x; c < nch; c += 256) {
+    if ((int)threadIdx.x < nch) {
+        sm_m[threadIdx.x] = mx = ml0.x;
+        sm_l[threadIdx.x] = ml0.y;
+    }
+    for (int c = threadIdx.x + 256; c < nch; c += 256) {
         const float2 ml = *reinterpret_cast<const float2 *>(part_ml + (base + c) * 2);
         if (c < MAXC) { sm_m[c] = ml.x; sm_l[c] = ml.y; }
         mx = fmaxf(mx, ml.x);
@@ -368,8 +380,16 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float *__restrict__ pa
     __syncthreads();
     const float M = fmaxf(fmaxf(sm_red[0], sm_red[1]), fmaxf(sm_red[2], sm_red[3]));
     float o = 0.f, L = 0.f;
+#pragma unroll
+    for (int u = 0; u < AHEAD; u++) {
+        const int c = grp + u * NGRP;
+        if (c >= nch) break;
+        const float a = fast_exp2(sm_m[c] - M);
+        o += a * ahead[u];
+        L += a * sm_l[c];
+    }
 #pragma unroll 4
-    for (int c = grp; c < nch; c += NGRP) {
+    for (int c = grp + AHEAD * NGRP; c < nch; c += NGRP) {
         const float mc = c < MAXC ? sm_m[c] : part_ml[(base + c) * 2];
         const float lc = c < MAXC ? sm_l[c] : part_ml[(base + c) * 2 + 1];
         const float a = fast_exp2(mc - M);

@@ -198,6 +198,22 @@ def test_paged_attention_edge_lengths(dtype, hd, H, Hkv):
         np.testing.assert_allclose(got[0, h], v0[h // (H // Hkv)], rtol=1e-5, atol=1e-7)
 
 
+@pytest.mark.parametrize("dtype,hd", [("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("chunks", [1, 2, 23, 24, 25, 47, 48, 49, 200, 257])
+def test_paged_attention_chunk_counts(dtype, hd, chunks):
+    """Decode attention merged from as many chunks of 64 positions, around the number the merge requests before it knows how
+    many there are (12 per thread group: 24 and 48) and the 256 statistics its threads take at once; beside it, where the grid
+    allows, a row of one position, whose other chunks are never written: the scratch is NaN before the call."""
+    lens = [64 * chunks - 7] + [1] * (chunks < 250)
+    table, pool, q = _attention_case(24, lens, 1, 1, hd, dtype)
+    out = torch.empty(len(lens), 1, hd, device=DEV)
+    scratch = torch.full((ld.ldk_attention_scratch_bytes(len(lens), 1, 1, hd, max(lens), 0) // 4,), float("nan"), device=DEV)
+    ld.ldk_paged_attention(q, hd, device_pool(pool), table.to(DEV), torch.arange(len(lens), dtype=torch.int32, device=DEV),
+                           torch.tensor(lens, dtype=torch.int32, device=DEV), max(lens), 1, 1, hd, out, scratch)
+    ref = _oracle_attention(table, pool, q, lens, 1, hd)
+    assert np.max(np.abs(out.cpu().numpy() - ref)) <= _attn_tol(dtype, hd, 1, 1) * np.abs(ref).max() + 1e-6
+
+
 @pytest.mark.parametrize("window", [1, 5, 16, 17, 100, 256, 4096])
 @pytest.mark.parametrize("dtype,hd,H,Hkv", [("bf16", 128, 8, 2), ("f32", 64, 4, 4)])
 def test_paged_attention_band(dtype, hd, H, Hkv, window):
