@@ -27,10 +27,10 @@ sys.path.insert(0, ROOT)
 HBM_PEAK = 8.0e12          # bytes/s, MI355X HBM3E
 # HBM bytes per launch of the dominant kernel from rocprofv3 FETCH_SIZE + WRITE_SIZE counters, scaled by a
 # 256 MiB copy (profiles/gate_up_gemv_hbm_traffic.md); valid only for the kernel source it was taken on.
-TRAFFIC_BYTES = 180_870_000
-TRAFFIC_KERNEL_MD5 = "0468ef4efdc5"
-ATTN_TRAFFIC_RATIO = 1.007
-ATTN_TRAFFIC_MD5 = "ef39af836308"
+TRAFFIC_BYTES = 180_820_000
+TRAFFIC_KERNEL_MD5 = "7db47ba421d7"
+ATTN_TRAFFIC_RATIO = 1.008
+ATTN_TRAFFIC_MD5 = "5fddc9eaeb42"
 ROUND_TOKENS = 256         # tokens emitted per round (1 by the preceding prefill + 255 decode steps)
 CHUNK = 256
 
@@ -244,7 +244,7 @@ def run_batch1(args, ld, torch, shape, weights, model):
     ev1.record(stream)
     torch.cuda.synchronize()
     b2b_s = ev0.elapsed_time(ev1) * 1e-3 / (reps * L)
-    roofline = {"bound": "hbm", "kernel": "k_gemv1<1, 8, 2, true> (gate/up projection, fused RMSNorm + SwiGLU)",
+    roofline = {"bound": "hbm", "kernel": "k_gemv1<8192, 2, true> (gate/up projection, fused RMSNorm + SwiGLU)",
                 "achieved": round(alg_bytes[dominant] / avg_s / 1e9, 1),
                 "peak": HBM_PEAK / 1e9, "unit": "GB/s", "frac": round(alg_bytes[dominant] / avg_s / HBM_PEAK, 4),
                 "traffic": kernel_traffic(), "avg_launch_us": round(avg_s * 1e6, 2),
