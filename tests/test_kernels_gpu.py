@@ -795,3 +795,33 @@ def test_prefill_attention_segments(H, Hkv, window, split):
                                  table.numpy()[row_seq], [p + 1 for p in row_pos], Hkv, window=window)
     err = np.max(np.abs(got - ref), axis=(1, 2)) / np.abs(ref).max()
     assert err.max() <= 3e-5, (err.max(), int(err.argmax()), row_pos[int(err.argmax())])
+
+
+@pytest.mark.parametrize("f16", [False, True], ids=["two-term", "fp16"])
+@pytest.mark.parametrize("window", [1, 5, 13])
+def test_prefill_attention_band_inside_the_last_block(window, f16):
+    """Bands of fewer than 16 positions over tiles whose first visible block is also the last, partly written one and lies in the
+    upper half of a 32-position step: the lower half of the step then has no block of its own and reads that one, whose
+    unwritten slots hold NaN.  They neither reach an output nor count as beyond the fp16 range.  Bounds as in the tests above
+    (two terms 3e-5, one fp16 term 1e-3 of the largest output)."""
+    hd, H, Hkv = 128, 4, 2
+    segs = [(1300, 1), (1300, 3), (16, 1), (20, 2), (1317, 1), (1310, 2), (55, 9)]
+    table, pool, _ = _attention_case(37, [p + n for p, n in segs], H, Hkv, hd, "bf16")
+    tiles, row_seq, row_pos = [], [], []
+    for s, (p0, n) in enumerate(segs):
+        tiles.append([len(row_pos), n, p0, s])
+        row_seq += [s] * n; row_pos += list(range(p0, p0 + n))
+    q = gen.normal(37, 9, (len(row_pos), H, hd), device=DEV)
+    out, flag = torch.zeros_like(q), torch.zeros(1, dtype=torch.int32, device=DEV)
+    args = (q, H * hd, device_pool(pool), table.to(DEV), torch.tensor(tiles, dtype=torch.int32, device=DEV), H, Hkv, hd, out, max(row_pos))
+    if f16:
+        ld.ldk_prefill_attention_f16(*args, flag, window=window)
+    else:
+        ld.ldk_prefill_attention(*args, window=window)
+    got = out.cpu().numpy()
+    ph = oracle.to_host_matrix(pool.reshape(pool.shape[0], -1)).reshape(-1)
+    ref = oracle.paged_attention(q.cpu().numpy(), ph, ph[Hkv * 16 * hd:], (2 * Hkv * 16 * hd, 16 * hd, hd),
+                                 table.numpy()[row_seq], [p + 1 for p in row_pos], Hkv, window=window)
+    assert int(flag.item()) == 0
+    err = np.max(np.abs(got - ref), axis=(1, 2)) / np.abs(ref).max()
+    assert err.max() <= (1e-3 if f16 else 3e-5), (err.max(), row_pos[int(err.argmax())])
