@@ -47,6 +47,8 @@ struct GemmNext { const float *g; float eps; uint16_t *xs; const RopeKvArgs *rop
 void launch_gemm(const uint16_t *W, uint16_t *xs, int T, int N, int K, int epi, float *y, hipStream_t s,
                  const GemmNext *next = nullptr, int *f16_flag = nullptr, const uint16_t *W16 = nullptr, bool octets = false);
 int gemm_f16_rows(int T, int N, int K, int epi);
+// Rows past the last whole 256-row tile that go through the small-batch kernel instead (0: none); f16: in the one-term form.
+int tail_rows(int T, int N, int K, int epi, bool f16);
 // *flag (device memory) = 1 if the bf16 matrix W (n elements, a multiple of 8) holds a value beyond +-65504 or not a number.
 void launch_weight_range_check(const uint16_t *W, int64_t n, int *flag, hipStream_t s);
 // The same check, and out[n] = W as fp16 (exact where the flag stays clear, values below 2^-14 in magnitude aside).

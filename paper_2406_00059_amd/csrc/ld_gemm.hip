@@ -701,14 +701,47 @@ bool gemm_supported(int T, int N, int K) { return T >= 2 && N > 0 && K > 0 && K 
 
 size_t gemm_split_bytes(int T, int K) { return (((size_t)2 * T * K * sizeof(bf16_t)) + 255) / 256 * 256; }
 
+// Which rows past the last whole 256-row tile keep both bf16 terms in the one-term form.  The number of terms is part of a
+// product's results, so it has a rule of its own that does not move when tiles or their measured times change: the rows
+// keep both wherever a second stream of W (4 TB/s and 12 us) costs less than what they add to the time of 256 x 256 and
+// 128 x 256 tiles at nominal rates (754 and 638 TFLOP/s; a last round that leaves CUs idle at least 0.74 of a whole one; K
+// split in up to eight slabs at 9 TB/s for the partial sums, for the last column blocks alone at 3).
+static double nominal_us(int T, int N, int K, int wr) {
+    const int nout = 256 / wr, n_nb = (N + nout - 1) / nout, max_ks = std::max(1, std::min(8, K / 256));
+    double best = 1e30;
+    for (const int bm : {256, 128}) {
+        const int64_t n_tt = (T + bm - 1) / bm, n_all = n_tt * n_nb;
+        auto tile_us = [&](int k) { return 0.69 * 2.0 * bm * 256 * (double)k / ((bm == 256 ? 520.0 : 440.0) * 1e6 / 256.0); };
+        for (int ks = 1; ks <= max_ks; ks++) {
+            const int64_t wgs = n_all * ks;
+            double t = ((double)(wgs / 256) + (wgs % 256 ? std::max((wgs % 256) / 256.0, 0.74) : 0.0)) * tile_us(K / ks);
+            if (ks > 1) t += 3.0 + (double)T * N * wr * 4.0 * (2.0 * ks + 1.0) / 9.0e6;
+            best = std::min(best, t);
+        }
+        const int64_t nb_a = n_all / 256 * 256 / n_tt, nb_b = n_nb - nb_a;
+        if (bm != 256 || n_all <= 256 || n_all >= 512 || nb_a <= 0 || nb_b <= 0) continue;
+        for (int ks = 2; ks <= max_ks; ks++) {
+            const double cols_b = (double)std::min<int64_t>(N - nb_a * nout, nb_b * nout);
+            best = std::min(best, (double)((nb_a * n_tt + 255) / 256) * tile_us(K) + (double)((nb_b * n_tt * ks + 255) / 256) * tile_us(K) / ks +
+                                      6.0 + (double)T * cols_b * wr * 4.0 * (2.0 * ks + 1.0) / 3.0e6);
+        }
+    }
+    return best;
+}
+static bool tail_keeps_both_terms(int T, int r, int N, int K, int epi) {
+    const int wr = epi == GEMM_SWIGLU ? 2 : 1;
+    return nominal_us(T - r, N, K, wr) + (double)N * wr * K * 2.0 / 4.0e6 + 12.0 < nominal_us(T, N, K, wr);
+}
+
 // Rows that would only start one more, nearly empty 256-row tile (a mixed step's 4 x 257 + 28 rows, a 2048-row
-// chunk beside 63 decode rows) are cut off and go through the small-batch kernels: the weights are streamed
-// once more, which costs less than a tile of padding.  Returns the number of such tail rows (0: no cut),
-// decided by the same cost model that picks the tile.
+// chunk beside 63 decode rows) are cut off and go through the small-batch kernels where that costs less by the cost model
+// that picks the tile (the weights are streamed once more), and in the one-term form also where the rule above wants them
+// there.  Returns the number of such tail rows (0: no cut).
 int tail_rows(int T, int N, int K, int epi, bool f16) {
     const int r = T % 256;
     static const int enabled = env_int("LD_GEMM_TAIL", 1);   // tuning knob: 0 keeps every row in the tiled kernel
     if (!enabled || T <= 256 || r == 0 || r > 64 || getenv("LD_GEMM_BIG")) return 0;
+    if (f16 && tail_keeps_both_terms(T, r, N, K, epi)) return r;
     const double whole = plan_big(T, N, K, epi, f16).est_us, main_part = plan_big(T - r, N, K, epi, f16).est_us;
     const double tail = (double)N * (epi == GEMM_SWIGLU ? 2 : 1) * K * 2.0 / 5.2e6 + 10.0;   // ~5.2 TB/s + two launches
     return main_part + tail < whole ? r : 0;

@@ -242,9 +242,10 @@ ld_status ensure_pinned(ld_kv *kv) {
 // the row whose logits / greedy token are wanted, in callback order; once step_ev[slot] has passed,
 // pin_out[slot * max_seqs + i] holds the tokens.  The last n_single rows are one-row segments (decode rows);
 // the rows before them form multi-row prefill segments, each a run of consecutive rows of one sequence at
-// consecutive positions.  (The one-row segments come last because the rows past the last full 256-row tile of a
-// pass are the ones that the small-batch kernels take with both bf16 terms also when the rest of a long pass
-// goes with one fp16 term: with whole chunks in front these are the decode rows, which emit.)  tok_from_prev: row t's input token is the token that the previous pass on this stream
+// consecutive positions.  (The one-row segments come last because rows are cut off a long pass at its end: where the
+// rows past the last whole 256-row tile of a product are cut off (tail_rows), they keep both bf16 terms when the others go
+// with one fp16 term, and with whole chunks in front they are decode rows, which emit.  Where they are not cut off, which
+// depends on the product's shape, they go with one term as well.)  tok_from_prev: row t's input token is the token that the previous pass on this stream
 // emitted for its row t (read on the device), not rows[t].tok.
 ld_status enqueue_pass(ld_kv *kv, const std::vector<Row> &rows, int n_single, const std::vector<int32_t> &emit,
                        hipStream_t st, float *logits_out, int slot, bool tok_from_prev, int *ops, bool allow_f16 = false) {

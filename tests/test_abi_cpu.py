@@ -318,3 +318,31 @@ def test_bench_refuses_more_than_one_gpu():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert r.returncode != 0 and "ONE GPU" in r.stderr and not r.stdout.strip().startswith("{")
+
+
+# (N, K, epilogue) of layer products, and the multiples of 256 rows after which up to 64 rows more keep both bf16 terms
+_TWO_TERM_TAILS = [
+    (12288, 4096, ld.LDK_STORE, (1280, 2560, 4096)), (4096, 4096, ld.LDK_ADD, (2048, 4096)), (4096, 11008, ld.LDK_ADD, (2048, 4096)),
+    (11008, 4096, ld.LDK_SWIGLU, (768, 1280, 2048, 2816, 3584)), (6144, 4096, ld.LDK_STORE, (1280, 2560, 2816, 3072)),
+    (14336, 4096, ld.LDK_SWIGLU, (512, 1024, 1536, 2304, 2816, 3328, 4096)), (4096, 14336, ld.LDK_ADD, (2048, 4096)),
+    (15360, 5120, ld.LDK_STORE, (1024, 2048, 3072, 4096)), (5120, 5120, ld.LDK_ADD, (1536, 3072)),
+    (13824, 5120, ld.LDK_SWIGLU, (512, 1024, 1792, 2304, 2816, 3584, 4096)), (5120, 13824, ld.LDK_ADD, (1280, 1536, 2560, 2816, 3072, 4096)),
+    (9001, 3072, ld.LDK_STORE, (1792, 2048, 3584)), (5000, 6016, ld.LDK_SWIGLU, (768, 1536, 3072))]
+
+
+def _f16_rows(*shape):
+    return C.CFUNCTYPE(C.c_int, C.c_int, C.c_int, C.c_int, C.c_int)(("_ZN2ld13gemm_f16_rowsEiiii", ld.lib()))(*shape)
+
+
+@pytest.mark.parametrize("N,K,epi,after", _TWO_TERM_TAILS)
+def test_rows_that_keep_both_terms_in_the_one_term_form(N, K, epi, after):
+    """How many terms a row's activations have is part of a product's results: the rows named here keep both whatever tiles the
+    product is cut into (the planner may send others of the last 64 the same way); whole tiles and longer remainders go with one."""
+    for base in after:
+        for r in (1, 2, 28, 31, 32, 33, 63, 64):
+            assert _f16_rows(base + r, N, K, epi) == base, (base, r)
+    for T in (65, 256, 512, 1024, 1024 + 65, 2048, 2048 + 200, 4096 + 255):
+        assert _f16_rows(T, N, K, epi) == T
+    for T in range(257, 4200, 13):
+        assert _f16_rows(T, N, K, epi) in ((T, T - T % 256) if 0 < T % 256 <= 64 else (T,))
+    assert _f16_rows(64, N, K, epi) == 0

@@ -825,3 +825,32 @@ def test_prefill_attention_band_inside_the_last_block(window, f16):
     assert int(flag.item()) == 0
     err = np.max(np.abs(got - ref), axis=(1, 2)) / np.abs(ref).max()
     assert err.max() <= (1e-3 if f16 else 3e-5), (err.max(), row_pos[int(err.argmax())])
+
+
+@pytest.mark.parametrize("T,N,K,epi", [(1056, 14336, 4096, "swiglu"), (2111, 4096, 4096, "add"), (1537, 5120, 5120, "store")])
+def test_linear_f16_tail_keeps_both_terms(T, N, K, epi):
+    """Decode rows behind whole 256-row tiles in the one-term form, at shapes where they keep both terms: every output of theirs
+    within 2^-16 sum_k |w x| of float64 (two terms leave 2^-18 of an activation, the rest is float32 sums), which one fp16
+    term (2^-12 of an activation) does not meet; the rows in front do show that term."""
+    e = {"store": ld.LDK_STORE, "add": ld.LDK_ADD, "swiglu": ld.LDK_SWIGLU}[epi]
+    rows = N * (2 if epi == "swiglu" else 1)
+    W = gen.normal(43, 1, (rows, K), std=0.02, device=DEV).bfloat16()
+    x, y0 = gen.normal(43, 2, (T, K), device=DEV), gen.normal(43, 3, (T, N), device=DEV)
+    y, flag = y0.clone(), torch.zeros(1, dtype=torch.int32, device=DEV)
+    scratch = torch.empty(ld.ldk_linear_scratch_bytes(T, N, K, e), dtype=torch.uint8, device=DEV)
+    ld.ldk_linear_f16(W, x, y, flag, e, scratch=scratch)
+    assert int(flag.item()) == 0
+
+    def worst(sel):
+        xs, w = x[sel].double(), W.double()
+        s, mag = xs @ w.t(), xs.abs() @ w.abs().t()
+        if epi == "swiglu":      # |d(silu(a) b)| <= 1.1 |b| |da| + |silu(a)| |db|
+            a, b = s[:, :N], s[:, N:]
+            ref, mag = torch.nn.functional.silu(a) * b, 1.1 * b.abs() * mag[:, :N] + torch.nn.functional.silu(a).abs() * mag[:, N:]
+        else:
+            ref = s + (y0[sel].double() if epi == "add" else 0)
+        return float((((y[sel].double() - ref).abs() - 1e-6 * ref.abs()).clamp_min(0) / mag).max())
+
+    last = T // 256 * 256
+    assert worst(slice(last, T)) <= 2.0 ** -16
+    assert worst(slice(last - 64, last)) > 2.0 ** -16
