@@ -52,8 +52,8 @@ ld_status ldk_linear(const void *W, int32_t dtype, const float *x, const float *
  * later tokens only through cached keys and values; the paper's section 4.1 fixes no precision): where more than 64
  * rows run on the big-tile matrix-core kernel, the activations enter the product rounded to fp16 (11 significant
  * bits) in one term instead of the two bf16 terms (16 bits), and the bf16 matrix entries are widened to fp16 on the
- * way to the matrix cores, which is exact for 2^-14 <= |w| <= 65504.  Other row counts and shapes: exactly
- * ldk_linear.  overflow (device memory, 4 bytes, the caller clears it) is set to 1 when the matrix or an
+ * way to the matrix cores, which is exact for 2^-14 <= |w| <= 65504.  Other row counts and shapes, and products with
+ * an operand of 4 GiB or more: exactly ldk_linear.  overflow (device memory, 4 bytes, the caller clears it) is set to 1 when the matrix or an
  * activation holds a value beyond +-65504 or not a number; y is then not to be used (the engine repeats such a
  * pass with ldk_linear's arithmetic).  scratch: ldk_linear_scratch_bytes(...) bytes.
  * W_f16 (device memory, may be NULL): the matrix as fp16, same layout as W, written by ldk_weights_to_f16 with its

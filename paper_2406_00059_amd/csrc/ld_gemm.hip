@@ -845,7 +845,13 @@ static void launch_tiles(const uint16_t *W, const bf16_t *hi, const bf16_t *lo, 
 // Where the rows of a product go next.
 struct RowsNext { const float *g; float eps; OperandImage out; const RopeKvArgs *rope; int row0; };
 
-int gemm_f16_rows(int T, int N, int K, int epi) { return T > SKINNY_MAX_ROWS ? T - tail_rows(T, N, K, epi, true) : 0; }
+// Products with an operand of 4 GiB or more keep both terms in every row.
+int gemm_f16_rows(int T, int N, int K, int epi) {
+    if (T <= SKINNY_MAX_ROWS) return 0;
+    const int m = T - tail_rows(T, N, K, epi, true);
+    const int64_t limit = (int64_t)1 << 31;      // elements
+    return (int64_t)m * K < limit && (int64_t)N * (epi == GEMM_SWIGLU ? 2 : 1) * K < limit ? m : 0;
+}
 
 // nx != nullptr with GEMM_ADD: y's rows are finished and turned into the next operand by one fused kernel in
 // place of the split-K reduction.  With GEMM_SWIGLU: the epilogue (or the split-K reduction) writes its result
@@ -886,7 +892,7 @@ void launch_gemm(const uint16_t *W, uint16_t *xs, int T, int N, int K, int epi, 
     float *partial = (float *)((char *)xs + gemm_split_bytes(T, K));
     const bf16_t *hi = xs, *lo = xs + (size_t)T * K;
     // the rows beyond a multiple of 256 that the cost model sends through the small-batch kernel keep both terms
-    const bool f16 = f16_flag && T > SKINNY_MAX_ROWS;
+    const bool f16 = f16_flag && gemm_f16_rows(T, N, K, epi) > 0;
     const int r = tail_rows(T, N, K, epi, f16), m = T - r;
     // the next operand is a [2][T][N] image: rows of the main part first, the tail's rows behind them
     RowsNext a{}, b{};

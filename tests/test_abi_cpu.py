@@ -346,3 +346,12 @@ def test_rows_that_keep_both_terms_in_the_one_term_form(N, K, epi, after):
     for T in range(257, 4200, 13):
         assert _f16_rows(T, N, K, epi) in ((T, T - T % 256) if 0 < T % 256 <= 64 else (T,))
     assert _f16_rows(64, N, K, epi) == 0
+
+
+def test_operands_of_4_gib_keep_both_terms():
+    """Rows enter as one fp16 term only while the matrix (gate and up rows together) and the rows' image stay below 4 GiB."""
+    for N, K, epi in ((1 << 19, 4096, ld.LDK_STORE), (1 << 18, 4096, ld.LDK_SWIGLU), (1 << 17, 16384, ld.LDK_ADD)):
+        assert _f16_rows(600, N, K, epi) == 0
+        assert _f16_rows(600, N - 8192, K, epi) == 600
+    assert _f16_rows(1 << 19, 1024, 4096, ld.LDK_STORE) == 0
+    assert _f16_rows((1 << 19) - 256, 1024, 4096, ld.LDK_STORE) == (1 << 19) - 256
