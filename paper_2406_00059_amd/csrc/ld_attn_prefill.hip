@@ -475,19 +475,24 @@ void launch_prefill_attention(const float *q, int q_stride, const uint16_t *pool
                               float *out, void *scratch, size_t scratch_bytes, hipStream_t s,
                               const OperandImage &image, int *f16_flag) {
     const float sl2 = 1.4426950408889634f / sqrtf((float)HD);
-    int per = 0;
-    const int ns = prefill_shares(n_tiles, H, max_pos, window, scratch ? scratch_bytes : 0, &per);
-    float *part_o = (float *)scratch;
-    float *part_ml = part_o ? part_o + (size_t)n_tiles * 128 * H * ns * HD : nullptr;
-    if (f16_flag)
-        LD_LAUNCH(k_attn_prefill<true>, dim3(H, n_tiles, ns), dim3(256), 0, s, q, q_stride, pool, Hkv, table, table_stride,
-                  (const int4 *)tiles, H, window, sl2, out, per, part_o, part_ml, image, f16_flag);
-    else
-        LD_LAUNCH(k_attn_prefill<false>, dim3(H, n_tiles, ns), dim3(256), 0, s, q, q_stride, pool, Hkv, table, table_stride,
-                  (const int4 *)tiles, H, window, sl2, out, per, part_o, part_ml, image, f16_flag);
-    if (ns > 1)
-        LD_LAUNCH(k_attn_prefill_merge, dim3(H, n_tiles, 16), dim3(256), 0, s, (const int4 *)tiles, H, window, per, ns, part_o, part_ml,
-                  out, image);
+    // tiles are the second dimension of the grid, which ends at 65535: more of them go in several launches, one after the
+    // other through the same scratch
+    constexpr int MAX_TILES = 65535;
+    for (int first = 0; first < n_tiles; first += MAX_TILES) {
+        const int n = std::min(n_tiles - first, MAX_TILES);
+        const int4 *t = (const int4 *)tiles + first;
+        int per = 0;
+        const int ns = prefill_shares(n, H, max_pos, window, scratch ? scratch_bytes : 0, &per);
+        float *part_o = (float *)scratch;
+        float *part_ml = part_o ? part_o + (size_t)n * 128 * H * ns * HD : nullptr;
+        if (f16_flag)
+            LD_LAUNCH(k_attn_prefill<true>, dim3(H, n, ns), dim3(256), 0, s, q, q_stride, pool, Hkv, table, table_stride, t, H, window,
+                      sl2, out, per, part_o, part_ml, image, f16_flag);
+        else
+            LD_LAUNCH(k_attn_prefill<false>, dim3(H, n, ns), dim3(256), 0, s, q, q_stride, pool, Hkv, table, table_stride, t, H, window,
+                      sl2, out, per, part_o, part_ml, image, f16_flag);
+        if (ns > 1) LD_LAUNCH(k_attn_prefill_merge, dim3(H, n, 16), dim3(256), 0, s, t, H, window, per, ns, part_o, part_ml, out, image);
+    }
 }
 
 }  // namespace ld

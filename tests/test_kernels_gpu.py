@@ -854,3 +854,25 @@ def test_linear_f16_tail_keeps_both_terms(T, N, K, epi):
     last = T // 256 * 256
     assert worst(slice(last, T)) <= 2.0 ** -16
     assert worst(slice(last - 64, last)) > 2.0 ** -16
+
+
+@pytest.mark.parametrize("n_tiles", [65535, 65536, 65600])
+def test_prefill_attention_more_tiles_than_a_grid_dimension(n_tiles):
+    """As many one-row tiles as a grid's second dimension holds, and more (they go in two launches), over three cached
+    sequences: every tile's row equals the row that one tile of the same position and sequence gives alone, bit for bit."""
+    hd, lens = 128, [40, 7, 300]
+    table, pool, _ = _attention_case(41, lens, 1, 1, hd, "bf16")
+    i = torch.arange(n_tiles)
+    seq = i % 3
+    pos = (i * 7) % torch.tensor(lens)[seq]
+    tiles = torch.stack([i, torch.ones_like(i), pos, seq], 1).int().to(DEV)
+    q = gen.normal(41, 9, (1, 1, hd), device=DEV).expand(n_tiles, 1, hd).contiguous()
+    out = torch.full((n_tiles, 1, hd), float("nan"), device=DEV)
+    args = (device_pool(pool), table.to(DEV))
+    ld.ldk_prefill_attention(q, hd, *args, tiles, 1, 1, hd, out, max(lens) - 1)
+    kinds, back = torch.unique(torch.stack([pos, seq], 1), dim=0, return_inverse=True)
+    few = torch.stack([torch.arange(len(kinds)), torch.ones(len(kinds)), kinds[:, 0], kinds[:, 1]], 1).int().to(DEV)
+    ref = torch.full((len(kinds), 1, hd), float("nan"), device=DEV)
+    for k in range(0, len(kinds), 50):
+        ld.ldk_prefill_attention(q, hd, *args, few[k:k + 50].contiguous(), 1, 1, hd, ref, max(lens) - 1)
+    assert torch.isfinite(out).all() and torch.equal(out, ref[back.to(DEV)])
