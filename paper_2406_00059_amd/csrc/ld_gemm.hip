@@ -340,6 +340,8 @@ struct BufferCopy {
 };
 #endif
 
+constexpr int TILE_MAX_K = 1 << 23;      // the lane offsets of the copies reach over 256 rows in 32 bits
+
 constexpr int tile_lds(int terms, int bm, int bn) { return 2 * (terms * bm + bn) * 128; }
 
 template <int TERMS, int WF, int AT, int BT, int WM, int WN, int EPI>
@@ -753,6 +755,7 @@ static size_t partial_bytes(int T, int N, int K, int epi, bool f16 = false) {
 }
 
 size_t gemm_scratch_bytes(int T, int N, int K, int epi) {
+    if (T > SKINNY_MAX_ROWS && K > TILE_MAX_K) return gemm_split_bytes(T, K) + partial_bytes(SKINNY_MAX_ROWS, N, K, epi);
     const int r = tail_rows(T, N, K, epi, false);
     size_t part = r ? std::max(partial_bytes(T - r, N, K, epi), partial_bytes(r, N, K, epi)) : partial_bytes(T, N, K, epi);
     if (T > 64) {      // the same pass in the fp16 form may split K differently
@@ -847,7 +850,7 @@ struct RowsNext { const float *g; float eps; OperandImage out; const RopeKvArgs 
 
 // Products with an operand of 4 GiB or more keep both terms in every row.
 int gemm_f16_rows(int T, int N, int K, int epi) {
-    if (T <= SKINNY_MAX_ROWS) return 0;
+    if (T <= SKINNY_MAX_ROWS || K > TILE_MAX_K) return 0;
     const int m = T - tail_rows(T, N, K, epi, true);
     const int64_t limit = (int64_t)1 << 31;      // elements
     return (int64_t)m * K < limit && (int64_t)N * (epi == GEMM_SWIGLU ? 2 : 1) * K < limit ? m : 0;
@@ -891,19 +894,26 @@ void launch_gemm(const uint16_t *W, uint16_t *xs, int T, int N, int K, int epi, 
                  const GemmNext *next, int *f16_flag, const uint16_t *W16, bool octets) {
     float *partial = (float *)((char *)xs + gemm_split_bytes(T, K));
     const bf16_t *hi = xs, *lo = xs + (size_t)T * K;
-    // the rows beyond a multiple of 256 that the cost model sends through the small-batch kernel keep both terms
     const bool f16 = f16_flag && gemm_f16_rows(T, N, K, epi) > 0;
-    const int r = tail_rows(T, N, K, epi, f16), m = T - r;
-    // the next operand is a [2][T][N] image: rows of the main part first, the tail's rows behind them
-    RowsNext a{}, b{};
-    if (next) {
-        uint16_t *nh = next->xs, *nl = nh ? nh + (size_t)T * N : nullptr;
-        a = {next->g, next->eps, {nh, nl, next->f16_rows, f16_flag}, next->rope, 0};
-        b = {next->g, next->eps, {nh ? nh + (size_t)m * N : nh, nh ? nl + (size_t)m * N : nl, next->f16_rows - m, f16_flag}, next->rope, m};
+    // n rows from row0 on.  The next operand is a [2][T][N] image
+    auto rows = [&](int row0, int n, bool one_term, const uint16_t *w16, bool oct) {
+        RowsNext nx{};
+        if (next) {
+            uint16_t *nh = next->xs ? next->xs + (size_t)row0 * N : nullptr, *nl = nh ? nh + (size_t)T * N : nullptr;
+            nx = {next->g, next->eps, {nh, nl, next->f16_rows - row0, f16_flag}, next->rope, row0};
+        }
+        gemm_rows(W, hi + (size_t)row0 * K, lo + (size_t)row0 * K, n, N, K, epi, y + (size_t)row0 * N, partial, s, next ? &nx : nullptr,
+                  one_term, w16, oct);
+    };
+    // groups of rows share the partial-sum scratch: the stream orders each behind the reduction of the one before
+    if (T > SKINNY_MAX_ROWS && K > TILE_MAX_K) {
+        for (int row0 = 0; row0 < T; row0 += SKINNY_MAX_ROWS) rows(row0, std::min(SKINNY_MAX_ROWS, T - row0), false, nullptr, false);
+        return;
     }
-    gemm_rows(W, hi, lo, m, N, K, epi, y, partial, s, next ? &a : nullptr, f16, W16, octets);
-    // the tail reuses the partial-sum scratch: the stream orders it behind the main part's reduction
-    if (r) gemm_rows(W, hi + (size_t)m * K, lo + (size_t)m * K, r, N, K, epi, y + (size_t)m * N, partial, s, next ? &b : nullptr, false, nullptr, false);
+    // the rows beyond a multiple of 256 that go through the small-batch kernel keep both terms
+    const int r = tail_rows(T, N, K, epi, f16);
+    rows(0, T - r, f16, W16, octets);
+    if (r) rows(T - r, r, false, nullptr, false);
 }
 
 void launch_weight_range_check(const uint16_t *W, int64_t n, int *flag, hipStream_t s) {

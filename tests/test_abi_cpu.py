@@ -355,3 +355,12 @@ def test_operands_of_4_gib_keep_both_terms():
         assert _f16_rows(600, N - 8192, K, epi) == 600
     assert _f16_rows(1 << 19, 1024, 4096, ld.LDK_STORE) == 0
     assert _f16_rows((1 << 19) - 256, 1024, 4096, ld.LDK_STORE) == (1 << 19) - 256
+
+
+def test_rows_too_long_for_32_bit_offsets_take_no_tile():
+    """A tile's copies reach over up to 256 rows by 32-bit offsets: beyond 2^23 columns a product asks for the scratch of the small-batch
+    kernel (one partial sum per 1024 columns of 64 rows, behind the two images) and never takes the one-term form."""
+    K = (1 << 23) + 128
+    assert _f16_rows(65, 100, K, ld.LDK_STORE) == 0
+    for T in (65, 300):
+        assert ld.ldk_linear_scratch_bytes(T, 8, K, ld.LDK_STORE) == 4 * T * K + -(-K // 1024) * 64 * 8 * 4

@@ -876,3 +876,18 @@ def test_prefill_attention_more_tiles_than_a_grid_dimension(n_tiles):
     for k in range(0, len(kinds), 50):
         ld.ldk_prefill_attention(q, hd, *args, few[k:k + 50].contiguous(), 1, 1, hd, ref, max(lens) - 1)
     assert torch.isfinite(out).all() and torch.equal(out, ref[back.to(DEV)])
+
+
+def test_linear_rows_too_long_for_32_bit_offsets():
+    """Matrix rows so long that 255 of them lie more than 4 GiB apart, at a row count that would take the big-tile kernel: first and
+    last outputs against float64 (bound as in test_linear_small_batch_edges; a lane adds some 2^14 terms, the slabs' sums 2^13)."""
+    T, N, K = 65, 256, (1 << 32) // 510 // 128 * 128 + 128
+    torch.manual_seed(5)
+    W = torch.empty(N, K, dtype=torch.bfloat16, device=DEV).normal_(0, 0.02)
+    x, y = torch.randn(T, K, device=DEV), torch.full((T, N), float("nan"), device=DEV)
+    ld.ldk_linear(W, x, y, ld.LDK_STORE, scratch=torch.empty(ld.ldk_linear_scratch_bytes(T, N, K, ld.LDK_STORE), dtype=torch.uint8, device=DEV))
+    for n in (0, 1, 128, 254, 255):
+        w = W[n].double()
+        for t in (0, 31, 63, 64):
+            p = x[t].double() * w
+            assert abs(float(y[t, n].double() - p.sum())) <= 2.0 ** -16 * float(p.abs().sum()), (t, n)
