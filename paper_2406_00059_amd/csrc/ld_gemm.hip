@@ -16,6 +16,7 @@
 #include "ld_device.h"
 #include "ld_internal.h"
 #include <algorithm>
+#include <cstdio>
 #include <cstdlib>
 
 using namespace ldd;
@@ -653,17 +654,19 @@ struct BigPlan { int bm, bn, n_ttiles, n_nblocks, ks; double est_us; };
 struct Tile { int bm, bn; bool swiglu; double chunk_us; };
 const Tile tiles_two[] = {{96, 256, true, 1.31}, {128, 128, true, 1.05}, {128, 192, true, 1.30}, {128, 256, true, 1.56}, {160, 256, true, 1.87}, {192, 256, true, 2.20}};
 const Tile tiles_f16[] = {{128, 256, true, 1.01}, {256, 160, false, 1.17}, {256, 192, true, 1.33}, {256, 256, true, 1.62}};
-BigPlan plan_big(int T, int N, int K, int epi, bool f16 = false) {
+BigPlan plan_big(int T, int N, int K, int epi, bool f16 = false, bool *ignored = nullptr) {
     const bool swi = epi == ld::GEMM_SWIGLU;
     const double last = f16 ? 0.89 : 0.81, us_per_mb = f16 ? 0.48 : 0.45;
     BigPlan best{};
     double best_t = 1e30;
-    const char *forced = getenv("LD_GEMM_BIG");            // tuning knob: "rows,columns,ks" of a tile (rows 2, 4: 128, 256)
-    int f_bm = 0, f_bn = 0, f_ks = 0;
-    if (forced && sscanf(forced, "%d,%d,%d", &f_bm, &f_bn, &f_ks) != 3) f_bm = 0;
-    if (f_bm && f_bm <= 4) f_bm *= 64;
     const Tile *first = f16 ? std::begin(tiles_f16) : std::begin(tiles_two), *end = f16 ? std::end(tiles_f16) : std::end(tiles_two);
-    const bool known = std::any_of(first, end, [&](const Tile &t) { return t.bm == f_bm && t.bn == f_bn && (!swi || t.swiglu); });
+    // tuning knob: "rows,columns,ks" of a tile (rows 2, 4: 128, 256); what is no plan of this form is ignored (see gemm_rows)
+    const char *forced = getenv("LD_GEMM_BIG");
+    int f_bm = 0, f_bn = 0, f_ks = 0;
+    const bool parsed = forced && sscanf(forced, "%d,%d,%d", &f_bm, &f_bn, &f_ks) == 3 && f_ks >= 1;
+    if (f_bm <= 4) f_bm *= 64;
+    const bool known = parsed && std::any_of(first, end, [&](const Tile &t) { return t.bm == f_bm && t.bn == f_bn && (!swi || t.swiglu); });
+    if (ignored) *ignored = forced && !known;
     for (const Tile *tl = first; tl != end; tl++) {
         if (known && (tl->bm != f_bm || tl->bn != f_bn)) continue;
         if (swi && !tl->swiglu) continue;
@@ -671,7 +674,7 @@ BigPlan plan_big(int T, int N, int K, int epi, bool f16 = false) {
         const int n_tt = (T + tl->bm - 1) / tl->bm, n_nb = (N + nout - 1) / nout;
         const int max_ks = std::max(1, std::min(8, K / 64 / 4));   // at least four chunks per slab
         for (int ks = 1; ks <= max_ks; ks++) {
-            if (f_bm && ks != std::min(f_ks, max_ks)) continue;
+            if (known && ks != std::min(f_ks, max_ks)) continue;
             const int64_t wgs = (int64_t)n_tt * n_nb * ks;
             const double rounds = (double)(wgs / 256) + (wgs % 256 ? std::max((wgs % 256) / 256.0, last) : 0.0);
             double t = rounds * tl->chunk_us * (K / 64) / ks;
@@ -886,7 +889,9 @@ static void gemm_rows(const uint16_t *W, const bf16_t *hi, const bf16_t *lo, int
         else LD_LAUNCH((k_splitk_reduce<GEMM_SWIGLU>), dim3(rgrid), dim3(256), 0, s, partial, T, N, ks, y, out);
         return;
     }
-    const BigPlan p = plan_big(T, N, K, epi, f16);
+    bool ignored = false;
+    const BigPlan p = plan_big(T, N, K, epi, f16, &ignored);
+    if (ignored) fprintf(stderr, "libld: LD_GEMM_BIG names no plan of the %s form: ignored\n", f16 ? "one-term" : "two-term");
     launch_tiles(f16 && W16 ? W16 : W, hi, lo, T, N, K, epi, y, partial, p, s, !chain_add, out, f16 ? (W16 ? 2 : 1) : 0);
     if (chain_add) finish(p.ks > 1 ? p.ks : 0);
 }

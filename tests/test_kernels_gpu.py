@@ -430,12 +430,12 @@ def test_linear_small_batch_edges(T, N, K):
     assert ((y.double() - ref).abs() <= 2.0 ** -16 * mag).all()
 
 
-@pytest.mark.parametrize("plan", ["2,128,1", "2,128,3", "2,256,1", "2,256,2", "4,256,1", "4,256,4"])
+@pytest.mark.parametrize("plan", ["2,128,1", "2,128,3", "2,256,1", "2,256,2", "192,256,1", "192,256,4"])
 @pytest.mark.parametrize("epi", ["store", "add", "swiglu"])
-def test_linear_big_tile_every_plan(plan, epi, monkeypatch):
-    """The big-tile kernel picks its tile and split-K factor from a cost estimate; here every tile
-    (128 x 128, 128 x 256, 256 x 256) is forced in turn, with and without split-K, on a shape that is ragged
-    in tokens and in output columns, against the oracle on every output."""
+def test_linear_big_tile_every_plan(plan, epi, monkeypatch, capfd):
+    """The big-tile kernel picks its tile and split-K factor from a cost estimate; here three of its tiles
+    (128 x 128, 128 x 256, 192 x 256) are forced in turn, with and without split-K, on a shape that is ragged
+    in tokens and in output columns, against the oracle on every output.  (A plan that was not taken is reported.)"""
     monkeypatch.setenv("LD_GEMM_BIG", plan)
     T, N, K = 333, 301, 1152
     rows = 2 * N if epi == "swiglu" else N
@@ -452,12 +452,29 @@ def test_linear_big_tile_every_plan(plan, epi, monkeypatch):
         ref = _silu(ref[:, :N]) * ref[:, N:]
     err = np.max(np.abs(y.cpu().numpy() - ref)) / np.abs(ref).max()
     assert err <= 2e-5, err
+    assert "LD_GEMM_BIG" not in capfd.readouterr().err
+
+
+@pytest.mark.parametrize("plan", ["256,256,1", "100,100,1", "128,256,0", "nonsense"])
+def test_linear_unknown_forced_plan_is_reported(plan, monkeypatch, capfd):
+    """A forced plan that the form does not have (256 x 256 exists for one term only) leaves the planner's choice and says so."""
+    T, N, K = 333, 301, 1152
+    W = _mat(11, 1, N, K, "bf16").to(DEV); x = gen.normal(11, 2, (T, K), device=DEV)
+    scratch = torch.empty(ld.ldk_linear_scratch_bytes(T, N, K, ld.LDK_STORE), dtype=torch.uint8, device=DEV)
+    ys = []
+    for env in (None, plan):
+        if env:
+            monkeypatch.setenv("LD_GEMM_BIG", env)
+        ys.append(torch.full((T, N), float("nan"), device=DEV))
+        ld.ldk_linear(W, x, ys[-1], ld.LDK_STORE, scratch=scratch)
+        assert ("LD_GEMM_BIG" in capfd.readouterr().err) == bool(env)
+    assert torch.isfinite(ys[0]).all() and torch.equal(*ys)
 
 
 @pytest.mark.parametrize("form,rows,cols", [("two", r, c) for r, c in ((96, 256), (128, 128), (128, 192), (128, 256), (160, 256), (192, 256))]
                          + [("f16", r, c) for r, c in ((128, 256), (256, 160), (256, 192), (256, 256))])
 @pytest.mark.parametrize("K,ks", [(128, 1), (1152, 1), (1152, 4)])
-def test_linear_every_tile(form, rows, cols, K, ks, monkeypatch):
+def test_linear_every_tile(form, rows, cols, K, ks, monkeypatch, capfd):
     """Every tile of the big-tile kernel, in both forms (two bf16 terms; one fp16 term on the fp16 image and on the bf16
     matrix), forced in turn on a shape that is ragged in rows and columns: the fewest chunks of K the pipeline has to
     cope with (2), an ordinary run, and split K with uneven slabs (18 chunks over 4).  Against float64 on the inputs
@@ -491,6 +508,7 @@ def test_linear_every_tile(form, rows, cols, K, ks, monkeypatch):
         else:
             ref, bound = a + (y0.double() if epi == ld.LDK_ADD else 0), 2.0 ** -16 * mag[:, :N] + 1e-6
         assert ((outs[-1].double() - ref).abs() <= bound + 1e-7).all(), epi
+    assert "LD_GEMM_BIG" not in capfd.readouterr().err
 
 
 def test_linear_matrix_core_7b_shapes_sampled():
