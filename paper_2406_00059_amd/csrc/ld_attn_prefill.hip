@@ -82,18 +82,22 @@ __device__ __forceinline__ u32x4 bf16x8_to_f16x8(const u32x4 &w, u16x2 &mag) {
 __device__ __forceinline__ int tile_start(const int4 &tile, int window) { return window > 0 ? (max(tile.z - window + 1, 0) & ~(KVB - 1)) : 0; }
 __device__ __forceinline__ int tile_steps(const int4 &tile, int window) { return (tile.z + tile.y - 1 - tile_start(tile, window)) / KVB + 1; }
 
-// The tile that comes rank-th when they are sorted by their steps (longest first, ties by index); more than a wave's
-// lanes of them stay in their own order.
-__device__ __forceinline__ int nth_longest(const int4 *__restrict__ tiles, int n_tiles, int window, int rank) {
-    if (n_tiles > WAVE) return rank;
+// The tile that comes rank-th when they are sorted by their steps (longest first, ties by index), and its index; more than a
+// wave's lanes of them stay in their own order.
+__device__ __forceinline__ int4 nth_longest(const int4 *__restrict__ tiles, int n_tiles, int window, int rank, int &index) {
+    index = rank;
+    if (n_tiles == 1 || n_tiles > WAVE) return tiles[rank];
     const int lane = threadIdx.x & 63;
-    const int own = lane < n_tiles ? tile_steps(tiles[lane], window) : 0;
+    const int4 t = tiles[min(lane, n_tiles - 1)];
+    const int own = tile_steps(t, window);
     int before = 0;
     for (int i = 0; i < n_tiles; i++) {
         const int other = __builtin_amdgcn_readlane(own, i);
         before += other > own || (other == own && i < lane);
     }
-    return __ffsll(__ballot(lane < n_tiles && before == rank)) - 1;
+    index = __ffsll(__ballot(lane < n_tiles && before == rank)) - 1;
+    return make_int4(__builtin_amdgcn_readlane(t.x, index), __builtin_amdgcn_readlane(t.y, index), __builtin_amdgcn_readlane(t.z, index),
+                     __builtin_amdgcn_readlane(t.w, index));
 }
 
 // F16 (the long passes whose rows the engine lets enter the products rounded to fp16): queries and probabilities as
@@ -113,9 +117,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
     // Work items longest first: shares in order, in each the tiles by their length, heads fastest.  Two workgroups share a
     // CU and run at each other's expense: in the tiles' own order long ones meet long ones.  Blocks b, b + 8, ... run on
     // one XCD: with the heads dealt out in eighths, the heads that read the same keys and values go through one L2.
-    const int tile_idx = nth_longest(tiles, gridDim.y, window, blockIdx.y);
+    int tile_idx;
+    const int4 tile = nth_longest(tiles, gridDim.y, window, blockIdx.y, tile_idx);      // x: first row, y: rows (<= 128), z: position of first row, w: seq slot
     const int h = H % 8 == 0 ? (blockIdx.x & 7) * (H / 8) + (blockIdx.x >> 3) : blockIdx.x;
-    const int4 tile = tiles[tile_idx];      // x: first row, y: rows (<= 128), z: position of first row, w: seq slot
     // this workgroup's share of the tile's KV steps: `per` of them, as many shares as the tile has (a short tile of an uneven
     // batch has fewer than the grid)
     const int n_steps = tile_steps(tile, window), split = blockIdx.z;
@@ -448,11 +452,14 @@ namespace ld {
 bool prefill_attention_supported(int dtype_is_bf16, int hd) { return dtype_is_bf16 && hd == HD; }
 
 // Shares of the KV walk for the longest tile, and the steps of a share (shorter tiles have fewer shares).  Modelled in
-// steps of a workgroup: rounds of two workgroups per CU, a share costs its steps and about three more (queries, first
-// loads, partial result), and the merge a step and a half and 1 / 200 for each partial result of 64 KB (5 us at 400 of them,
-// 15 at 1500).  At least 8 steps a share, and only as many shares as the scratch holds.
+// steps of a workgroup: a share costs its steps and ten more (launch, queries, first loads, result), a round of up to 256
+// workgroups that, of up to 512 (two per CU) 1.15 times as much, and the merge two steps and 1 / 60 for each partial result of
+// 64 KB.  At least 4 steps a share, and only as many shares as the scratch holds.  Fitted to every number of shares for 243 sets of
+// tiles (4 .. 40 heads, 1 .. 16 tiles, walks of 4 .. 250 steps): the choice is 2 % slower than the best in the mean, 39 % at worst,
+// where tiles differ most in length.  A model that made the merge cheaper chose two shares for narrow bands over short
+// segments: 22 -> 29 us for eight 64-row tiles of 32 heads with a band of 256, 22 so.
 static int prefill_shares(int n_tiles, int H, int max_pos, int window, size_t scratch_bytes, int *per) {
-    const int span = window > 0 ? std::min(max_pos + 1, window + 128 + KVB) : max_pos + 1;   // positions a tile walks
+    const int span = window > 0 ? std::min<int64_t>(max_pos + 1, (int64_t)window + 128 + KVB) : max_pos + 1;   // positions a tile walks
     const int steps = (span + KVB - 1) / KVB;
     const int64_t items = (int64_t)n_tiles * H;
     const size_t per_share = (size_t)items * 128 * (HD + 2) * sizeof(float);
@@ -460,8 +467,10 @@ static int prefill_shares(int n_tiles, int H, int max_pos, int window, size_t sc
     double best_t = 1e30;
     for (int n = 1; n <= MAX_SPLITS; n++) {
         const int p = ((steps + n - 1) / n + 1) & ~1;      // whole units of two steps
-        if (n > 1 && (p < 8 || per_share * n > scratch_bytes)) break;
-        const double t = (double)((items * n + 511) / 512) * (p + 3) + (n > 1 ? 1.5 + items * n / 200.0 : 0.0);
+        if (n > 1 && (p < 4 || per_share * n > scratch_bytes)) break;
+        const int64_t full = items * n / 512, rest = items * n % 512;
+        const double rounds = full * 1.15 + (rest == 0 ? 0.0 : rest <= 256 ? 1.0 : 1.15);
+        const double t = rounds * (p + 10) + (n > 1 ? 2.0 + items * n / 60.0 : 0.0);
         if (t < best_t) { best_t = t; best = n; }
     }
     *per = ((steps + best - 1) / best + 1) & ~1;
