@@ -6,20 +6,17 @@
 //
 //  - Two workgroups of eight waves per CU; workgroup i owns the contiguous output range
 //    [i N / G, (i+1) N / G), so all workgroups stream the same number of bytes (+-1 row).
-//  - A workgroup's work is cut into items of two rows (the two of a pair, or neighbours) and one slab of 2048 columns:
-//    eight 16-byte loads per lane, 4 KB of a row in one run by one wave.  Its items, slab by slab, are dealt to the waves in
-//    equal runs, and a wave keeps two items in flight (16 KB; 256 KB a CU).
+//  - A workgroup's work is cut into items of two rows (the two of a pair, or neighbours) and one slab of columns, 2048 or 512
+//    (CPS 4 or 1): a run of 4 KB or 1 KB of each row by one wave, 16 bytes a lane and load.  Its items, slab by slab, are
+//    dealt to the waves in equal runs, and a wave keeps two items in flight.
 //  - The input, multiplied by the RMSNorm gain, sits in LDS: it is requested before the first rows, and an item reads
 //    its slab once for two rows, as many bytes as the rows have.
 //  - An item ends in two sums across a wave (six shuffles), which wait in LDS: the only barriers are the one after
 //    the input has arrived and the one before the epilogue.
-//  What bounds it: HBM, and at both ends of the launch the latency of the input and of the last rows.  Requests of
-//  a wave that lie together stream faster (gate/up of the 7B shape, loads alone: 32.7 us with 128-byte runs, 28.7 with
-//  4 KB), and waves that need not meet at a barrier for every eight rows keep their loads going.  7B shape, us, a form with
-//  512-column slabs per wave and a barrier per group before -> this one: q/k/v 21.4 -> 19.3, gate/up 31.8 -> 31.3, down
-//  18.3 -> 17.8, output projection 8.0 -> 8.4; 13B shape (calls alone): 43.7 -> 26.8, 66.8 -> 45.1, 24.9 -> 24.6, 17.1 -> 12.0.  Sixteen waves in one workgroup per CU: 19.3, 33.5, 17.9, 8.6 (one
-//  prologue and one end for a whole CU); four waves in four: 20.8, 33.9, 21.7, 9.5; items row by row instead of slab
-//  by slab: 19.8, 33.0, 19.0, 8.3.
+//  What bounds it: HBM, and at both ends of the launch the latency of the input and of the last rows.  Long runs stream
+//  faster (gate/up of the 7B shape, loads alone: 32.7 us in 128-byte runs, 28.7 in 4 KB), but where a wave would get two items
+//  or fewer of 2048 columns it has nothing to overlap its sums with, and short slabs win (us, 2048 / 512 columns: 4096x4096
+//  8.8 / 8.2, 2048x8192 8.9 / 8.1, 6144x4096 11.5 / 10.8; the other way about 4096x11008 17.4 / 18.5, 14336x4096 36.0 / 37.7).
 //  - The RMSNorm scale 1 / rms(x) is a scalar, so it is applied to the finished dot products; its
 //    sum of squares is accumulated when the input goes to LDS.
 //  - Epilogues: store, residual add, SwiGLU (gate row r with up row N + r), and "RoPE + cache
@@ -35,8 +32,8 @@ using namespace ldd;
 namespace {
 
 constexpr int WAVES = 8;             // per workgroup, two workgroups per CU
-constexpr int CPS = 4;               // 512-column pieces of a slab: one 16-byte load per lane and row each
-constexpr int SLAB = CPS * WAVE * 8; // columns of a slab
+constexpr int PIECE = WAVE * 8;      // columns that one load instruction of a wave covers
+constexpr int LONG_SLAB = 4;         // pieces of a slab
 constexpr int MAX_K = 16384;
 constexpr int MAX_PARTS = 2048;      // partial sums of a workgroup: with the largest input 72 KB of LDS, two fit a CU
 
@@ -61,14 +58,15 @@ __device__ __forceinline__ int unit_row(int u, int m, int N, int half_hd) {
     else return u;
 }
 
-// KMAX: columns the input's place in LDS is for.
-template <int KMAX, int EPI, bool NORM>
+// KMAX: columns the input's place in LDS is for.  CPS: pieces of a slab.
+template <int KMAX, int CPS, int EPI, bool NORM>
 __global__ __launch_bounds__(WAVES * WAVE, 4) void k_gemv1(const bf16_t *__restrict__ W, const float *__restrict__ x,
                                                         const float *__restrict__ g, float eps, int N, int K,
                                                         float *__restrict__ y, ld::RopeKvArgs rk) {
+    constexpr int SLAB = CPS * PIECE;
     constexpr bool PAIRED = (EPI == ld::GEMV_SWIGLU || EPI == ld::GEMV_ROPE_KV);
     constexpr int UPI = PAIRED ? 1 : 2;        // output units of an item: it has two rows either way
-    __shared__ __attribute__((aligned(16))) float xs[KMAX / 8][2][4];      // [512-column piece][half][lane] as float4: see xpos
+    __shared__ __attribute__((aligned(16))) float xs[KMAX / 8][2][4];      // group g of eight columns: float4s (g / 64) 128 + g % 64 and 64 further
     __shared__ float part[MAX_PARTS];
     __shared__ float part_ss[WAVES];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -106,12 +104,16 @@ __global__ __launch_bounds__(WAVES * WAVE, 4) void k_gemv1(const bf16_t *__restr
         const int slab = it / per_slab, u0 = u_begin + (it - slab * per_slab) * UPI;
 #pragma unroll
         for (int r = 0; r < 2; r++) {
-            // an odd last row reads the one before it again; its sum is not used
-            const int u = PAIRED ? u0 : min(u0 + r, u_begin + units - 1);
+            if (!PAIRED && u0 + r >= u_begin + units) {      // an odd last row has no neighbour; the sum is not used
+#pragma unroll
+                for (int c = 0; c < CPS; c++) buf[r][c] = (u32x4_t){0u, 0u, 0u, 0u};
+                continue;
+            }
+            const int u = PAIRED ? u0 : u0 + r;
             const bf16_t *p = W + (int64_t)unit_row<EPI>(u, PAIRED ? r : 0, N, half_hd) * K;
 #pragma unroll
             for (int c = 0; c < CPS; c++) {
-                const int col = slab * SLAB + c * (WAVE * 8) + lane * 8;
+                const int col = slab * SLAB + c * PIECE + lane * 8;
                 buf[r][c] = col < K ? load_stream16(p + col) : (u32x4_t){0u, 0u, 0u, 0u};
             }
         }
@@ -229,10 +231,10 @@ __global__ __launch_bounds__(WAVES * WAVE, 4) void k_gemv1(const bf16_t *__restr
     }
 }
 
-template <int KMAX, bool NORM>
+template <int KMAX, int CPS, bool NORM>
 void launch_kmax(const bf16_t *W, const float *x, const float *g, float eps, int N, int K, int epi, float *y,
                  const ld::RopeKvArgs &rk, int grid, hipStream_t s) {
-#define LD_GEMV1(EPI_) LD_LAUNCH((k_gemv1<KMAX, EPI_, NORM>), dim3(grid), dim3(WAVES * WAVE), 0, s, W, x, g, eps, N, K, y, rk)
+#define LD_GEMV1(EPI_) LD_LAUNCH((k_gemv1<KMAX, CPS, EPI_, NORM>), dim3(grid), dim3(WAVES * WAVE), 0, s, W, x, g, eps, N, K, y, rk)
     switch (epi) {
         case ld::GEMV_STORE: LD_GEMV1(ld::GEMV_STORE); break;
         case ld::GEMV_ADD: LD_GEMV1(ld::GEMV_ADD); break;
@@ -269,7 +271,7 @@ void launch_gemv1(const uint16_t *W, const float *x, const float *g, float eps, 
     }
     const int n_units = epi == GEMV_ROPE_KV ? N / 2 : N;
     // Two workgroups per CU; more (which then follow one another) where a workgroup's partial sums would not fit.
-    const int n_slabs = (K + SLAB - 1) / SLAB;
+    const int n_slabs = (K + LONG_SLAB * PIECE - 1) / (LONG_SLAB * PIECE);
     const bool paired = epi == GEMV_SWIGLU || epi == GEMV_ROPE_KV;
     const int max_units = MAX_PARTS / n_slabs / (paired ? 2 : 1) - 2;
     static const int forced = env_int("LD_GEMV_WGS_PER_CU", 0);   // tuning knob
@@ -279,13 +281,20 @@ void launch_gemv1(const uint16_t *W, const float *x, const float *g, float eps, 
     if (grid > n_units) grid = n_units;
     RopeKvArgs none{};
     const RopeKvArgs &r = rk ? *rk : none;
-    if (K <= 8192) {
-        if (g) launch_kmax<8192, true>(W, x, g, eps, N, K, epi, y, r, grid, s);
-        else launch_kmax<8192, false>(W, x, g, eps, N, K, epi, y, r, grid, s);
-    } else {
-        if (g) launch_kmax<MAX_K, true>(W, x, g, eps, N, K, epi, y, r, grid, s);
-        else launch_kmax<MAX_K, false>(W, x, g, eps, N, K, epi, y, r, grid, s);
-    }
+    // Slabs of one piece where a wave would get two items of long slabs or fewer (see the top of the file); a workgroup with
+    // a single row has half-empty items and stays with few of them (640x16384: 7.8 us, 8.5 in short slabs).  At most
+    // 2 WAVES LONG_SLAB items of two sums: well below MAX_PARTS.
+    const int units = (n_units + grid - 1) / grid, items = (paired ? units : (units + 1) / 2) * n_slabs;
+    const bool short_slabs = items <= 2 * WAVES && n_units >= 2 * grid && K <= 8192;
+#define LD_KMAX(KMAX_, CPS_)                                                                 \
+    do {                                                                                     \
+        if (g) launch_kmax<KMAX_, CPS_, true>(W, x, g, eps, N, K, epi, y, r, grid, s);       \
+        else launch_kmax<KMAX_, CPS_, false>(W, x, g, eps, N, K, epi, y, r, grid, s);        \
+    } while (0)
+    if (short_slabs) LD_KMAX(8192, 1);
+    else if (K <= 8192) LD_KMAX(8192, LONG_SLAB);
+    else LD_KMAX(MAX_K, LONG_SLAB);
+#undef LD_KMAX
 }
 
 }  // namespace ld

@@ -712,9 +712,9 @@ def test_prefill_attention_fp16_form(H, Hkv, window, split):
 
 
 @pytest.mark.parametrize("N,K,epi,norm", [(N, K, epi, norm) for epi in ("store", "add", "swiglu") for norm in (False, True) for N, K in [
-    (1, 8), (2, 2040), (3, 2048), (513, 2056), (1025, 6152), (1537, 8192), (770, 8200), (1026, 16384)]] + [(140000, 16384, "store", False)])
+    (1, 8), (2, 2040), (3, 2048), (513, 2056), (1025, 6152), (1537, 8192), (770, 8200), (1026, 16384), (4099, 2056), (4099, 8200), (2050, 16384), (16391, 1032)]] + [(140000, 16384, "store", False)])
 def test_gemv_slab_edges(N, K, epi, norm):
-    """The one-row product at the edges of its slabs of 2048 columns, of the two sizes its input has in LDS (8192 columns and
+    """The one-row product at the edges of its slabs of 2048 and 512 columns (the latter where a wave gets few items), of the two sizes its input has in LDS (8192 columns and
     16384), of the two-row items (odd and single rows, fewer outputs than workgroups, one more than two each) and beyond the
     partial sums that one workgroup per slot can hold, against float64.  Bound: a sum passes through at most 4 x 8 additions in a lane,
     6 across the wave and 8 over the slabs, so 64 roundings of 2^-24 of the sum of magnitudes cover it with the norm's."""
