@@ -415,13 +415,14 @@ def test_linear_matrix_core_path(T, epi):
 
 
 @pytest.mark.parametrize("T", [2, 15, 16, 17, 32, 33, 48, 49, 63, 64])
-@pytest.mark.parametrize("N,K", [(5, 128), (301, 2048), (4099, 2176), (66, 11008)])
+@pytest.mark.parametrize("N,K", [(5, 128), (301, 2048), (4099, 2176), (66, 11008), (7, 8192), (4105, 8192), (1023, 16384)])
 def test_linear_small_batch_edges(T, N, K):
     """The small-batch kernel at the edges of its tiles: one row below, at and above each count of 16-row tiles of X; fewer
     output rows than a tile, odd and ragged counts; K slabs where most waves have no share (128), of exactly the width a
-    workgroup holds (2048), just beyond it (2176: two uneven slabs) and a ragged FFN width.  Against float64 on every
+    workgroup holds (2048), just beyond it (2176: two uneven slabs), a ragged FFN width, and rows a multiple of
+    16 KB apart, whose tiles are dealt out in turn.  Against float64 on every
     output: the two bf16 terms leave 2^-18 of an activation, float32 sums about as much (2^-24 per addition, a random walk
-    over K <= 11008 terms), so |error| <= 2^-16 sum_k |w x| holds with room, and a lost low term (2^-9) does not pass."""
+    over K <= 16384 terms), so |error| <= 2^-16 sum_k |w x| holds with room, and a lost low term (2^-9) does not pass."""
     W = _mat(31, 1, N, K, "bf16").to(DEV); x = gen.normal(31, 2, (T, K), device=DEV)
     scratch = torch.empty(ld.ldk_linear_scratch_bytes(T, N, K, ld.LDK_STORE), dtype=torch.uint8, device=DEV)
     y = torch.full((T, N), float("nan"), device=DEV)
