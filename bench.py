@@ -80,8 +80,8 @@ MFMA_PEAK = 2.5e15         # flop/s, bf16 dense
 
 def ld_gemm_terms(rows):
     """Matrix-core terms per float32 activation in a pass of `rows` rows: two bf16 terms (high + low part); one
-    fp16 term in passes of at least LD_GEMM_F16_MIN_ROWS (512) rows unless LD_GEMM_F16=0 (the few rows past the
-    last full 256-row tile, which keep both terms, are not counted apart)."""
+    fp16 term in passes of at least LD_GEMM_F16_MIN_ROWS (512) rows unless LD_GEMM_F16=0 (the up to 64 rows past
+    the last full 256-row tile, which keep both terms in some products, are not counted apart)."""
     on = os.environ.get("LD_GEMM_F16", "1") != "0"
     return 1 if on and rows >= int(os.environ.get("LD_GEMM_F16_MIN_ROWS", "512")) else 2
 
@@ -244,7 +244,7 @@ def run_batch1(args, ld, torch, shape, weights, model):
     ev1.record(stream)
     torch.cuda.synchronize()
     b2b_s = ev0.elapsed_time(ev1) * 1e-3 / (reps * L)
-    roofline = {"bound": "hbm", "kernel": "k_gemv1<8192, 2, true> (gate/up projection, fused RMSNorm + SwiGLU)",
+    roofline = {"bound": "hbm", "kernel": "k_gemv1<8192, 4, 2, true> (gate/up projection, fused RMSNorm + SwiGLU)",
                 "achieved": round(alg_bytes[dominant] / avg_s / 1e9, 1),
                 "peak": HBM_PEAK / 1e9, "unit": "GB/s", "frac": round(alg_bytes[dominant] / avg_s / HBM_PEAK, 4),
                 "traffic": kernel_traffic(), "avg_launch_us": round(avg_s * 1e6, 2),

@@ -67,8 +67,8 @@ ld_status ldk_linear_f16(const void *W, const void *W_f16, const float *x, const
 /* out[i] = W[i] as fp16 for the n entries of a bf16 matrix (n a multiple of 8; both device memory, out n * 2
  * bytes, not overlapping W): exact for 2^-14 <= |w| <= 65504, smaller magnitudes lose their low bits (truncated
  * toward zero).  overflow (device memory, 4 bytes, the caller clears it) is set to 1 when an entry lies beyond
- * +-65504 or is not a number; the image is then not to be used.  The engine keeps such an image of every layer
- * matrix from its first pass of 512 rows or more on (see ld.h, Arithmetic). */
+ * +-65504 or is not a number; the image is then not to be used.  The engine keeps such
+ * images where its caller attaches a buffer for them (ld_model_attach_f16_image). */
 ld_status ldk_weights_to_f16(const void *W, int64_t n, void *out, int32_t *overflow, void *stream);
 
 /* cos_sin[t, i] = (cos, sin)(pos[t] * rope_base^(-2i/hd)) for i < hd/2, as float32 pairs; the

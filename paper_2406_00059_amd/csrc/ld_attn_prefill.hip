@@ -211,8 +211,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
     // Values of positions past the tile's last row were never written (the rest of the last block, or the
     // second block of a step that ends the walk): they may hold anything, also NaN, and a probability of zero
     // does not neutralise a NaN, so they are staged as zeros.  (Keys need nothing: their scores are replaced,
-    // not multiplied.)  So are those of positions before the first held block: there a step that starts below the band
-    // holds another position's values, which may be unwritten slots of the first held block where that is also the last.
+    // not multiplied.)
     auto stage = [&](int st, int kv_unit) {
 #pragma unroll
         for (int u = 0; u < 2; u++)
@@ -220,19 +219,17 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
             for (int v = 0; v < 2; v++) {
                 const int kv0 = kv_unit + KVB * u;
                 if constexpr (F16) {
-                    // a key row past the tile's last position was never written (its scores are masked), nor perhaps the
-                    // slot read for a position before the first held block: what they hold does not count as out of range
+                    // a key row past the tile's last position was never written (its scores are masked): whatever it
+                    // holds does not count as out of range
                     u16x2 seen = mag;
                     *reinterpret_cast<u32x4 *>(&ks[st][u][16 * v + kr][kc]) = bf16x8_to_f16x8(kreg[u][v], seen);
-                    if (kv0 + 16 * v + kr <= wg_last_pos && kv0 + 16 * v >= first_held_pos) mag = seen;
+                    if (kv0 + 16 * v + kr <= wg_last_pos) mag = seen;
                 } else {
                     *reinterpret_cast<u32x4 *>(&ks[st][u][16 * v + kr][kc]) = kreg[u][v];
                 }
                 u32x4 vv = vreg[u][v];
                 const int p0 = kv0 + 16 * v + vh;      // position of this piece's first element
-                if (kv0 + 16 * v < first_held_pos) {
-                    vv = (u32x4){0u, 0u, 0u, 0u};
-                } else if (p0 + 7 > wg_last_pos) {
+                if (p0 + 7 > wg_last_pos) {
 #pragma unroll
                     for (int e = 0; e < 4; e++)
                         vv[e] = (p0 + 2 * e <= wg_last_pos ? vv[e] & 0x0000ffffu : 0u) |
@@ -354,6 +351,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
 
     look_up(kv_begin);
     load_unit();
+    // A walk that starts 16 positions before the first held block has read that block in their place.  Where it is also the
+    // last, its unwritten slots pass for visible positions: neither as values nor for the range check.
+    if (kv_begin < first_held_pos) kreg[0][0] = vreg[0][0] = (u32x4){0u, 0u, 0u, 0u};
     look_up(kv_begin + 2 * KVB);
     int st = 0;
     for (int kv0 = kv_begin; kv0 < kv_end; kv0 += 2 * KVB) {

@@ -40,7 +40,8 @@ __device__ __forceinline__ uint32_t split2_f16(float a, float b, bool &big) {
     return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)fa) | ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)fb) << 16);
 }
 
-// Writes v as a GEMM operand entry of image row t at index idx (idx: four consecutive entries, a multiple of 4).
+// Writes v as the GEMM operand entry idx, which belongs to image row t; store_operand4: four consecutive entries from idx on, a
+// multiple of 4.
 __device__ __forceinline__ void store_operand(const ld::OperandImage &o, int t, int64_t idx, float v) {
     if (t < o.f16_rows) {
         bool big = false;

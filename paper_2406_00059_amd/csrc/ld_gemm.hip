@@ -25,7 +25,6 @@ namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
-typedef __attribute__((ext_vector_type(2))) __fp16 fp16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;   // native 16-byte vector (keeps arrays of it in registers)
@@ -140,15 +139,18 @@ __global__ __launch_bounds__(256) void k_weight_to_f16(const bf16_t *__restrict_
 
 // Up to 64 rows (decode batches, short chunks): the weight stream is everything, so the kernel is built around never
 // interrupting it and around asking for it in long runs.  One workgroup of eight waves per CU stays for the whole
-// launch and owns a range of W rows and a slab of K (2048 wide, 1024 for more than 32 rows); its waves split the slab
+// launch and owns a set of W rows and a slab of K (2048 wide, 1024 for more than 32 rows); its waves split the slab
 // and keep the (hi, lo) X fragments of their share in registers for good.  W arrives 16 rows at a time, each row's
-// whole slab (4 KB in a row) by one wave, copied straight into LDS (global_load_lds, non-temporal): 128 KB per CU are
-// in flight and no register waits for them.  The access shape is what the rate depends on: streaming the 7B gate/up
-// (down) matrix alone takes 28.7 (17.4) us in runs of 4 KB per wave, 31.6 (20.7) us with 512 bytes of two rows per
-// instruction and 32.7 (21.8) us with 128 bytes of eight.
+// whole slab (4 KB in a row, 2 KB for more than 32 rows) by one wave, copied straight into LDS (global_load_lds,
+// non-temporal): 128 KB (96 KB) per CU are in flight and no register waits for them.  The access shape is what the rate
+// depends on: streaming the 7B gate/up (down) matrix alone takes 28.7 (17.4) us in runs of 4 KB per wave, 31.6 (20.7) us
+// with 512 bytes of two rows per instruction and 32.7 (21.8) us with 128 bytes of eight.
 // Per 16-row tile: wait for the own copies, barrier, read fragments (lane = row), barrier, request the tile that takes
-// this one's place, add up the tile before, multiply.  The sum over the eight waves goes through LDS in wave order; one partial sum per K slab goes to scratch and a reduction kernel adds the slabs in order (for
-// SwiGLU the gate and up rows are plain rows here and are paired by the reduce kernel).
+// this one's place, add up the tile before, multiply.  The sum over the eight waves goes through LDS in wave order; one
+// partial sum per K slab goes to scratch and a reduction kernel adds the slabs in order (for SwiGLU the gate and up rows
+// are plain rows here and are paired by the reduce kernel).  What bounds small matrices instead is the X fragments, which
+// come before the first tile (256 KB a workgroup at 32 rows): 4096x4096 at 17 - 32 rows is 1.5 us slower than a form that
+// held 512 columns of X a workgroup.
 // LDS: piece p (16 bytes) of a row's slab sits in slot p ^ row: the 16 rows that a fragment read touches at one p then
 // lie in 16 different bank groups, and a lane of a copy may fetch any piece into its fixed slot.
 constexpr int SK_WAVES = 8;
@@ -609,8 +611,9 @@ __global__ __launch_bounds__(256) void k_reduce_add_norm_split(const float *__re
     }
 }
 
-// Rows of the q-k-v projection: finishes them (split-K slab sums in slab order; ks 0: they are already in y) and does what the rotate-and-append pass does, one wave per (head, row): q heads
-// rotated into y, rotated k heads and v heads into the paged pool.  Row t of this launch is row row0 + t of the pass.
+// Rows of the q-k-v projection: finishes them (split-K slab sums in slab order; ks 0: they are already in y) and does what
+// the rotate-and-append pass does, one wave per (head, row): q heads rotated into y, rotated k heads and v heads into the
+// paged pool.  Row t of this launch is row row0 + t of the pass.
 __global__ __launch_bounds__(64) void k_reduce_rope_kv(const float *__restrict__ partial, int T, int N, int ks,
                                                        float *__restrict__ y, ld::RopeKvArgs rk, int row0) {
     const int t = blockIdx.y, hh = blockIdx.x, i = threadIdx.x, half = rk.hd / 2, hd = rk.hd;
@@ -650,7 +653,7 @@ int cu_count() {
     return n > 0 ? n : 256;
 }
 // Tile, workgroup count and split-K factor of the big-tile kernel for a row count: the candidate with the smallest
-// estimated time.  Workgroups run in rounds of one per CU; a round takes the tile's time per 64-wide chunk of K (measured
+// estimated time.  Workgroups run in rounds of one per CU (256 of them); a round takes the tile's time per 64-wide chunk of K (measured
 // with every CU busy) times its chunks, a last round that leaves CUs idle at least `last` of that; split-K adds the write
 // and the ordered re-read of its partial sums.  The constants are fitted to every tile and split of the 7B, grouped-KV
 // and 13B layer shapes at 65 - 511 rows (two terms) and 520 - 2048 (one): the choice is 2 % (1 %) slower than the best

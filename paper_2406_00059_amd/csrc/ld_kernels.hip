@@ -346,8 +346,10 @@ __global__ __launch_bounds__(256) void k_attn_partial(const float *__restrict__ 
 // chunks g, g + 256/HD, ...; the chunk maxima and sums go through LDS.  Bound by its chain of memory round trips (a few
 // hundred KB in all), so the first AHEAD partial outputs of a group and the statistics are requested at once with the context
 // length that says how many of them count: what lies beyond it was never written and is not used.
-// 32 heads x 16 chunks at batch 1: 3.9 -> 3.0 us at best, 4.7 on average either way under the profiler; the 7B step 2972 -> 2954,
-// attention of sixteen rows with its merge 97.4 -> 96.6, of 32 grouped rows 76.2 -> 75.4.
+// (Only short contexts beside long ones pay for it: 8.4 instead of 5.5 MB fetched for 32 rows of 512 .. 8192 positions, of
+// 2.6 GB in all.)  With their merge, against a merge that waits for the length first, each measured three times within 0.1: sixteen
+// rows 93.0 -> 92.3 us, 32 grouped rows 74.0 -> 73.3, one row of 8000 positions 23.8 -> 23.4; the 7B step 2952 -> 2925.
+// AHEAD of 8, 12 and 20 are level, 4 loses half of it at one row of 8000.
 template <int HD>
 __global__ __launch_bounds__(256) void k_attn_merge(const float *__restrict__ part_o, const float *__restrict__ part_ml,
                                                     const int32_t *__restrict__ ctx_len, int H, int window,
@@ -612,7 +614,7 @@ ld_status ld::linear_pass(const void *W, int32_t dtype, const float *x, const fl
         const bool octets = ld::gemm_takes_octets(T);
         ld::launch_norm_split(x, g, eps, T, K, (uint16_t *)scratch, s, octets, f16_flag ? ld::gemm_f16_rows(T, N, K, epilogue) : 0, f16_flag);
         ld::launch_gemm((const bf16_t *)W, (uint16_t *)scratch, T, N, K, epilogue, y, s, nullptr, f16_flag, (const uint16_t *)W_f16, octets);
-        return launched("k_gemm_mfma");
+        return launched("the matrix-core product");
     }
     if (dtype == LD_BF16) {
         if (g) launch_linear<bf16_t, true>((const bf16_t *)W, x, g, eps, T, N, K, epilogue, y, s);

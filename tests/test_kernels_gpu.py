@@ -558,7 +558,8 @@ def test_linear_fp16_rows_sampled():
     dot product on the inputs rounded as the kernel rounds them (the 16-bit sum of the split image, then fp16; what
     remains is float32 accumulation: the two-term test's bound) and
     against the oracle on the exact inputs (the rounding itself: 2^-12 per term, random walk over K terms).  Row
-    counts with a tail that keeps both terms (1056, 2111), with three and one row tiles, and one that stays on the
+    counts with a remainder of up to 64 rows (1056, 2111), which keeps both terms in some products and is not compared with the
+    one-term result, with three and one row tiles, and one that stays on the
     small-batch kernel (32: bit-equal to ldk_linear).  With the matrix's fp16 image (ldk_weights_to_f16: equal to the
     bf16 values entry by entry, truncated toward zero below 2^-17 where fp16 has no bits left) the same call gives
     bit-equal results.  A value beyond the fp16 range in the input or in the matrix raises the flag."""
@@ -574,7 +575,7 @@ def test_linear_fp16_rows_sampled():
             ld.ldk_linear_f16(W, x, y, flag, epi, scratch=scratch)
             assert int(flag.item()) == 0
             ld.ldk_linear(W, x, y2, epi, scratch=scratch)
-            r = T % 256 if T > 256 and T % 256 <= 64 else 0       # tail rows: both terms in either form
+            r = T % 256 if T > 256 and T % 256 <= 64 else 0       # rows that may keep both terms
             if T <= 64:
                 assert torch.equal(y, y2)
             else:
