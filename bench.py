@@ -28,9 +28,9 @@ HBM_PEAK = 8.0e12          # bytes/s, MI355X HBM3E
 # HBM bytes per launch of the dominant kernel from rocprofv3 FETCH_SIZE + WRITE_SIZE counters, scaled by a
 # 256 MiB copy (profiles/gate_up_gemv_hbm_traffic.md); valid only for the kernel source it was taken on.
 TRAFFIC_BYTES = 180_820_000
-TRAFFIC_KERNEL_MD5 = "7db47ba421d7"
+TRAFFIC_KERNEL_MD5 = "f8ec7a0a7d93"
 ATTN_TRAFFIC_RATIO = 1.008
-ATTN_TRAFFIC_MD5 = "5fddc9eaeb42"
+ATTN_TRAFFIC_MD5 = "a9c5b81ccd35"
 ROUND_TOKENS = 256         # tokens emitted per round (1 by the preceding prefill + 255 decode steps)
 CHUNK = 256
 
@@ -560,7 +560,7 @@ def main():
         print(json.dumps({"probe": "gate/up projection, 7B shape, 32 rows (k_norm_split + k_gemm_skinny + k_splitk_reduce)",
                           "launches": 16, "weight_bytes_per_launch": 2 * f * d * 2,
                           "algorithmic_bytes_per_launch": 2 * f * d * 2 + 32 * d * 4 + 32 * f * 4,
-                          "partial_sum_bytes_written_per_launch": (d // 512) * 32 * 2 * f * 4,
+                          "partial_sum_bytes_written_per_launch": -(-d // 2048) * 32 * 2 * f * 4,
                           "copy_bytes_each_way": 256 << 20, "copies": 4}))
         return
     if args.mfma_probe:

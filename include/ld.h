@@ -32,7 +32,8 @@
  *    activations as two bf16 terms (16 significant bits), except in passes of 512 rows or more (long prefill
  *    chunks, steps that mix decode rows with chunks), whose big-tile products take them rounded to fp16 (11
  *    bits) as long as every value of the pass and of the layer matrices lies within the fp16 range (+-65504);
- *    a pass that meets a larger value is repeated with two terms.  LD_GEMM_F16=0 in the environment keeps two
+ *    a pass that meets a larger value is repeated with two terms.  Up to 64 rows past a multiple of 256 (decode rows)
+ *    keep both terms in some of these products, by their shape.  LD_GEMM_F16=0 in the environment keeps two
  *    terms everywhere.  ld_model_attach_f16_image trades memory for time in those passes, with equal results.
  *  - Sequence state: n_cached tokens have keys/values in the pool; `pending` is a token
  *    that was emitted but not fed yet (none right after ld_kv_alloc).
