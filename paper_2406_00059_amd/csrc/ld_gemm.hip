@@ -454,7 +454,8 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16_t *__restrict__
     };
 
     copies(0, 0, P);
-    __builtin_amdgcn_sched_barrier(0);      // the count below lets the last PRE copies be outstanding: they have to be chunk 1's
+    // the count below lets the last PRE copies be outstanding: they have to be chunk 1's (arithmetic may cross)
+    __builtin_amdgcn_sched_barrier(7);
     copies(1, 0, PRE);
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PRE) : "memory");
     asm volatile("s_barrier" ::: "memory");
