@@ -28,7 +28,7 @@ HBM_PEAK = 8.0e12          # bytes/s, MI355X HBM3E
 # HBM bytes per launch of the dominant kernel from rocprofv3 FETCH_SIZE + WRITE_SIZE counters, scaled by a
 # 256 MiB copy (profiles/gate_up_gemv_hbm_traffic.md); valid only for the kernel source it was taken on.
 TRAFFIC_BYTES = 180_820_000
-TRAFFIC_KERNEL_MD5 = "f8ec7a0a7d93"
+TRAFFIC_KERNEL_MD5 = "3cc22b0a375e"
 ATTN_TRAFFIC_RATIO = 1.008
 ATTN_TRAFFIC_MD5 = "a9c5b81ccd35"
 ROUND_TOKENS = 256         # tokens emitted per round (1 by the preceding prefill + 255 decode steps)

@@ -281,9 +281,10 @@ void launch_gemv1(const uint16_t *W, const float *x, const float *g, float eps, 
     if (grid > n_units) grid = n_units;
     RopeKvArgs none{};
     const RopeKvArgs &r = rk ? *rk : none;
-    // Slabs of one piece where a wave would get two items of long slabs or fewer (see the top of the file); a workgroup with
-    // a single row has half-empty items and stays with few of them (640x16384: 7.8 us, 8.5 in short slabs).  At most
-    // 2 WAVES LONG_SLAB items of two sums: well below MAX_PARTS.
+    // Slabs of one piece where a wave would get two items of long slabs or fewer (see the top of the file).  A workgroup with a
+    // single row has half-empty items and stays with few of them (640x16384: 7.8 us, 8.5 in short slabs), and so do long
+    // inputs, which every workgroup brings in for few rows (1024x16384: 8.9, 11.6).  At most 2 WAVES LONG_SLAB items of two
+    // sums: well below MAX_PARTS.
     const int units = (n_units + grid - 1) / grid, items = (paired ? units : (units + 1) / 2) * n_slabs;
     const bool short_slabs = items <= 2 * WAVES && n_units >= 2 * grid && K <= 8192;
 #define LD_KMAX(KMAX_, CPS_)                                                                 \
