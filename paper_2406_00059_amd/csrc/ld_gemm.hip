@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
+#include <utility>
 
 using namespace ldd;
 
@@ -314,16 +315,22 @@ __global__ __launch_bounds__(64 * SK_WAVES, 2) void k_gemm_skinny(const bf16_t *
 }
 
 // The big-tile kernel.  Four waves, one per SIMD (512 registers each), WM x WN of them, a wave owning AT x BT accumulator
-// tiles of 32 x 32: the fewest operand bytes out of LDS per MFMA that the registers allow.  K advances in chunks of 64
+// tiles of 16 x 16: the fewest operand bytes out of LDS per MFMA that the registers allow.  K advances in chunks of 64
 // (rows of 128 bytes: whole cache lines), two stages, copied straight into LDS (buffer loads with the lds bit: a
 // scalar base, a lane offset that never changes and a scalar step along K, so that a copy costs no vector
-// arithmetic).  What decides the rate is how the copies are issued.  A copy whose turn comes while the CU's address
+// arithmetic).
+// What bounds it with real numbers in the operands is the power the matrix cores draw: on zeros 2048 x 8192 x 13824 takes
+// 293 us, on normal ones 386 (32 x 32 x 16 MFMAs).  A loop of MFMAs alone reaches, on normal operands, 1688 TFLOP/s in fp16 and 1842
+// in bf16 with 32 x 32 x 16, 1968 and 2105 with 16 x 16 x 32 (2440 - 2470 both on zeros): half as many accumulator bytes go in
+// and out per product.  Hence the small MFMA: products with their operand passes 2048 x 8192 x 13824 430 -> 401 us,
+// 2048 x 5120 x 13824 339 -> 281, 2111 x 27648 x 5120 568 -> 527, in two terms 152 x 4096 x 11008 54 -> 50.
+// Beside that it is how the copies are issued.  A copy whose turn comes while the CU's address
 // unit is busy holds up the MFMAs behind it, and two stages leave a copy less than a chunk's time to arrive; so
-//  - the operands of a chunk are all in registers before its last two k-steps (112 - 128 registers), its stage is free
+//  - the operands of a chunk are all in registers before its second half (112 - 128 registers), its stage is free
 //    from then on, and
-//  - the copies of the chunk after next are spread over a whole chunk's MFMAs, a few per k-step, none in a row.
-// A product of 2048 x 8192 x 13824 in fp16 runs at 1245 TFLOP/s so, 1118 with the copies in two k-steps, 1454 without
-// any copies; the eight-wave kernel with 32-wide chunks before this one at 1178.
+//  - the copies of the chunk after next are spread over a whole chunk's MFMAs, a few per k-step, none in a row
+//    (1118 -> 1245 TFLOP/s with the larger MFMA; 1454 without any copies).
+// The matrix instructions are assembly, issued exactly in the order written here (see tile_mfma_bf16).
 // One copy instruction covers 8 rows x 128 bytes; piece p (16 bytes) of row r sits in slot p ^ ((r >> 1) & 7) of its row:
 // 16 consecutive rows at one p lie in 16 bank groups.
 //
@@ -348,24 +355,56 @@ struct BufferCopy {
 };
 #endif
 
+// c += w x on the matrix cores, c in accumulation registers.  In assembly because the result has to land in the registers it
+// came from: left to the compiler, which sees no need for that with MFMAs this short, a chunk carries some 400 copies.  The operands come from LDS reads
+// (the compiler waits for those); an operand that vector arithmetic has just written needs two wait states.
+__device__ __forceinline__ void tile_mfma_bf16(f32x4 &c, const u32x4 &w, const u32x4 &x) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(w), "v"(x));
+}
+__device__ __forceinline__ void tile_mfma_f16(f32x4 &c, const u32x4 &w, const u32x4 &x) {
+    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(w), "v"(x));
+}
+// Moved out of the accumulation registers here and not earlier: all at once they do not fit beside the rest.
+__device__ __forceinline__ f32x4 tile_result(const f32x4 &c) {
+    f32x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; e++) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v[e]) : "a"(c[e]));
+    return v;
+}
+__device__ __forceinline__ void tile_mfma_f16_after_valu(f32x4 &c, const u32x4 &w, const u32x4 &x) {
+    asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(w), "v"(x));
+}
+
+// f(0), f(1), .. f(N - 1) with the number as a constant.
+template <int... I, typename F>
+__device__ __forceinline__ void each_of(std::integer_sequence<int, I...>, F &&f) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, typename F>
+__device__ __forceinline__ void each(F &&f) { each_of(std::make_integer_sequence<int, N>{}, f); }
+
 constexpr int TILE_MAX_K = 1 << 23;      // the lane offsets of the copies reach over 256 rows in 32 bits
 
 constexpr int tile_lds(int terms, int bm, int bn) { return 2 * (terms * bm + bn) * 128; }
+
+template <int N>
+using count = std::integral_constant<int, N>;
 
 template <int TERMS, int WF, int AT, int BT, int WM, int WN, int EPI>
 __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16_t *__restrict__ W, const bf16_t *__restrict__ xhi,
                                                       const bf16_t *__restrict__ xlo, int T, int N, int K,
                                                       float *__restrict__ y, int n_ttiles, int ks,
-                                                      float *__restrict__ partial, ld::OperandImage out) {
+                                                      float *__restrict__ partial, ld::OperandImage out, bool quads) {
     constexpr bool SWI = (EPI == ld::GEMM_SWIGLU);
     static_assert(WM * WN == 4 && (!SWI || BT % 2 == 0), "four waves; a wave column holds gate and up tiles");
-    constexpr int BM = WM * AT * 32, BN = WN * BT * 32, NOUT = SWI ? BN / 2 : BN;
-    constexpr int ROWS = TERMS * BM + BN, STAGE = ROWS * 128, WC = BT * 32;
+    constexpr int BM = WM * AT * 16, BN = WN * BT * 16, NOUT = SWI ? BN / 2 : BN;
+    constexpr int ROWS = TERMS * BM + BN, STAGE = ROWS * 128, WC = BT * 16;
+    static_assert(BM % 32 == 0 && BN % 32 == 0 && (!SWI || WC % 64 == 0), "the four waves' copies j cover 32 rows of one matrix");
     constexpr int P = ROWS / 32;                      // copies per wave and chunk: copy j of wave w covers rows (4 j + w) 8 .. + 8
     constexpr int NA = TERMS * AT, NM = NA * BT, NR = NA + BT;      // A tiles, MFMAs and operand reads of a k-step
-    // copies (for the chunk after next) issued in k-steps 2 and 3 of a chunk, then in 0 and in 1 of the chunk that follows
-    constexpr int PRE = (P * 10 + 15) / 16, C0 = (P * 14 + 15) / 16 - PRE, C1 = P - PRE - C0;
-    constexpr int NH = NA / 2;                        // A tiles of the last k-step that are multiplied before the next chunk is looked at
+    // copies (for the chunk after next) issued in the second half of a chunk; the rest in the first half of the chunk that follows
+    constexpr int PRE = (P * 10 + 15) / 16;
+    // A tiles of the first k-step that are multiplied after its stage is given up, and of the last one that are multiplied
+    // while the next chunk's operands are read
+    constexpr int NL = NA >= 8 ? NA / 8 : 1, NF = NA >= 4 ? NA / 4 : 1;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
 
     // Blocks b, b + 8, ... run on one XCD.  Each XCD takes an equal run of the work items (K slab fastest, then row tile,
@@ -376,7 +415,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16_t *__restrict__
     const int kz = item % ks, tt_idx = item / ks % n_ttiles, nb = item / (ks * n_ttiles);
     const int t0 = tt_idx * BM, n0 = nb * NOUT;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int l32 = lane & 31, half = lane >> 5;
+    const int l16 = lane & 15, kg = lane >> 4;
     const int wm = wave / WN, wn = wave % WN;
 
     // lane offsets of the copies from the tile's first row of each matrix (rows clamped: clamped rows are never stored)
@@ -396,148 +435,135 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16_t *__restrict__
     const BufferCopy from_hi(xhi + (int64_t)t0 * K), from_lo((TERMS == 2 ? xlo : xhi) + (int64_t)t0 * K), from_w(W + (int64_t)n0 * K),
         from_up(W + (int64_t)(SWI ? N + n0 : n0) * K);
     const int c_begin = (int)((int64_t)kz * (K / 64) / ks), n = (int)((int64_t)(kz + 1) * (K / 64) / ks) - c_begin;      // >= 2 chunks
-    auto copies = [&](int c, int lo, int hi) {      // copies [lo, hi) of chunk c into its stage
-#pragma unroll
-        for (int j = lo; j < hi; j++) {
-            char *dst = lds + (c & 1) * STAGE + (4 * j + wave) * 1024;
-            const uint32_t off = (uint32_t)(c_begin + c) * 128u;
-            if (32 * j < BM) from_hi(dst, coff[j], off);
-            else if (32 * j < TERMS * BM) from_lo(dst, coff[j], off);
-            else if (SWI && (32 * j - TERMS * BM) % WC >= WC / 2) from_up(dst, coff[j], off);
-            else from_w(dst, coff[j], off);
-        }
+    auto copy = [&](int c, int j) {      // copy j of chunk c into its stage
+        char *dst = lds + (c & 1) * STAGE + (4 * j + wave) * 1024;
+        const uint32_t off = (uint32_t)(c_begin + min(c, n - 1)) * 128u;
+        if (32 * j < BM) from_hi(dst, coff[j], off);
+        else if (32 * j < TERMS * BM) from_lo(dst, coff[j], off);
+        else if (SWI && (32 * j - TERMS * BM) % WC >= WC / 2) from_up(dst, coff[j], off);
+        else from_w(dst, coff[j], off);
     };
 
-    f32x16 acc[AT][BT];
+    f32x4 acc[AT][BT];
 #pragma unroll
     for (int i = 0; i < AT; i++)
 #pragma unroll
-        for (int j = 0; j < BT; j++)
-#pragma unroll
-            for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
+        for (int j = 0; j < BT; j++) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
     struct Frags { u32x4 a[NA], w[BT]; };
-    const int sw = (l32 >> 1) & 7;
-    auto load = [&](Frags &f, int st, int kstep) {
-        const char *base = lds + st * STAGE + l32 * 128 + (((kstep * 2 + half) ^ sw) * 16);
-#pragma unroll
-        for (int i = 0; i < NA; i++) f.a[i] = *reinterpret_cast<const u32x4 *>(base + ((i / AT) * BM + (wm * AT + i % AT) * 32) * 128);
-#pragma unroll
-        for (int j = 0; j < BT; j++) f.w[j] = *reinterpret_cast<const u32x4 *>(base + (TERMS * BM + (wn * BT + j) * 32) * 128);
+    const int sw = (l16 >> 1) & 7;
+    auto read = [&](Frags &f, int st, int kstep, int r) {      // operand read r of a k-step, in the order of use
+        const char *base = lds + st * STAGE + l16 * 128 + (((kstep * 4 + kg) ^ sw) * 16);
+        const int i = r == 0 ? 0 : r - BT, j = r - 1;
+        if (r == 0 || r > BT) f.a[i] = *reinterpret_cast<const u32x4 *>(base + ((i / AT) * BM + (wm * AT + i % AT) * 16) * 128);
+        else f.w[j] = *reinterpret_cast<const u32x4 *>(base + (TERMS * BM + (wn * BT + j) * 16) * 128);
     };
-    auto mfmas = [&](const Frags &f, int lo, int hi) {      // A tiles [lo, hi)
-#pragma unroll
-        for (int i = lo; i < hi; i++)
-#pragma unroll
-            for (int j = 0; j < BT; j++) {
-                f32x16 &c = acc[i % AT][j];
-                if constexpr (WF == 0) {
-                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.a[i]), __builtin_bit_cast(bf16x8, f.w[j]), c, 0, 0, 0);
-                } else {
-                    const f16x8 wv = WF == 2 ? __builtin_bit_cast(f16x8, f.w[j]) : bf16x8_to_f16x8(f.w[j]);
-                    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, f.a[i]), wv, c, 0, 0, 0);
-                }
-            }
+    // MFMA m of a k-step: A tile m / BT, W tile m % BT
+    auto mfma = [&](Frags &f, int m) {
+        const int i = m / BT, j = m % BT;
+        if (WF == 1 && i == 0) f.w[j] = __builtin_bit_cast(u32x4, bf16x8_to_f16x8(f.w[j]));
+        if constexpr (WF == 0) tile_mfma_bf16(acc[i % AT][j], f.w[j], f.a[i]);
+        else if (WF == 1 && i == 0) tile_mfma_f16_after_valu(acc[i % AT][j], f.w[j], f.a[i]);
+        else tile_mfma_f16(acc[i % AT][j], f.w[j], f.a[i]);
     };
-    // issue order of a stretch of nm MFMAs: nr operand reads and nc copies spread evenly between them
-    auto mix = [&](int nm, int nr, int nc) {
+    // nm MFMAs (from number m0 of f on, then from the first of g on) in this order, nr operand reads and nc copies spread
+    // evenly between them
+    auto mix = [&](Frags &f, Frags &g, int m0, auto count, int nr, auto &&rd, int nc, auto &&cp) {
+        constexpr int nm = decltype(count)::value;
+        each<nm>([&](auto k) __attribute__((always_inline)) {
+            if (m0 + k < NM) mfma(f, m0 + k);
+            else mfma(g, m0 + k - NM);
 #pragma unroll
-        for (int k = 0; k < nm; k++) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            const int r = (k + 1) * nr / nm - k * nr / nm, c = (k + 1) * nc / nm - k * nc / nm;
-            if (r == 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            if (r == 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            if (r == 3) __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
-            if (c == 1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-            if (c == 2) __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+            for (int r = k * nr / nm; r < (k + 1) * nr / nm; r++) rd(r);
+#pragma unroll
+            for (int c = k * nc / nm; c < (k + 1) * nc / nm; c++) cp(c);
+            __builtin_amdgcn_sched_barrier(0);
+        });
     };
 
-    copies(0, 0, P);
+#pragma unroll
+    for (int j = 0; j < P; j++) copy(0, j);
     // the count below lets the last PRE copies be outstanding: they have to be chunk 1's (arithmetic may cross)
     __builtin_amdgcn_sched_barrier(7);
-    copies(1, 0, PRE);
+#pragma unroll
+    for (int j = 0; j < PRE; j++) copy(1, j);
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PRE) : "memory");
     asm volatile("s_barrier" ::: "memory");
-    Frags f0, f1, f2, f3;
-    load(f0, 0, 0);
-    load(f1, 0, 1);
+    Frags f0, f1;
+#pragma unroll
+    for (int r = 0; r < NR; r++) read(f0, 0, 0, r);
+    auto none = [](int) {};
+    // One loop for all chunks.  Past the last one the copies fetch it again, into the stage that nobody reads any more
     int i = 0;
-    for (; i < n - 2; i++) {
+    do {
         const int st = i & 1;
-        load(f2, st, 2);
-        copies(i + 1, PRE, PRE + C0);
-        mfmas(f0, 0, NA);
-        mix(NM, NR, C0);
-        load(f3, st, 3);
-        copies(i + 1, PRE + C0, P);
-        mfmas(f1, 0, NA - 1);
-        mix(NM - BT, NR, C1);
+        asm volatile("s_nop 1" ::: "memory");      // before the first pass: the cleared accumulators
+        mix(f0, f0, 0, count<NM - NL * BT>{}, NR, [&](int r) { read(f1, st, 1, r); }, P - PRE, [&](int c) { copy(i + 1, PRE + c); });
         // every wave has this chunk's operands in registers: its stage is requested again, for chunk i + 2
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
-        copies(i + 2, 0, PRE);
-        mfmas(f1, NA - 1, NA);
-        mfmas(f2, 0, NA);
-        mfmas(f3, 0, NH);
-        mix(BT + NM + NH * BT, 0, PRE);
+        mix(f0, f1, NM - NL * BT, count<(NL + NA - NF) * BT>{}, 0, none, PRE, [&](int c) { copy(i + 2, c); });
         // the own copies of chunk i + 1 have landed (only those of chunk i + 2 are younger), and after the barrier everyone's
         asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(PRE) : "memory");
-        load(f0, st ^ 1, 0);
-        load(f1, st ^ 1, 1);
-        mfmas(f3, NH, NA);
-        mix(NM - NH * BT, 2 * NR, 0);
-    }
-    copies(i + 1, PRE, P);
-    load(f2, i & 1, 2);
-    mfmas(f0, 0, NA);
-    mix(NM, NR, 0);
-    load(f3, i & 1, 3);
-    mfmas(f1, 0, NA);
-    mix(NM, NR, 0);
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-    load(f0, (i + 1) & 1, 0);
-    load(f1, (i + 1) & 1, 1);
-    mfmas(f2, 0, NA);
-    mfmas(f3, 0, NA);
-    mix(2 * NM, 2 * NR, 0);
-    load(f2, (i + 1) & 1, 2);
-    mfmas(f0, 0, NA);
-    mix(NM, NR, 0);
-    load(f3, (i + 1) & 1, 3);
-    mfmas(f1, 0, NA);
-    mfmas(f2, 0, NA);
-    mfmas(f3, 0, NA);
+        mix(f1, f1, NM - NF * BT, count<NF * BT>{}, NR, [&](int r) { read(f0, st ^ 1, 0, r); }, 0, none);
+    } while (++i < n);
+    // the copies have left, and the last results are in their registers before anything reads them (the compiler does not
+    // see into the assembly)
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 
-    // accumulator element e of lane (l32, half): row t0 + (wm AT + a) 32 + 8 (e / 4) + 4 half + e % 4
+    // accumulator (a, j) of lane (l16, kg): row t0 + (wm AT + a) 16 + l16, four columns from n0 + (wn WOUT + j) 16 + 4 kg on
     constexpr int WOUT = SWI ? BT / 2 : BT;       // output column tiles per wave
     const int ncols = SWI ? 2 * N : N;            // row length of the partial-sum buffer
+    auto put = [&](float *dst, const f32x4 &v, int left) {      // quads: rows are multiples of four floats, 16-byte aligned
+        if (quads) {
+            *reinterpret_cast<f32x4 *>(dst) = v;
+        } else {
 #pragma unroll
-    for (int j = 0; j < WOUT; j++) {
-        const int col = n0 + (wn * WOUT + j) * 32 + l32;
-        if (col >= N) continue;
-#pragma unroll
-        for (int a = 0; a < AT; a++)
-#pragma unroll
-            for (int e = 0; e < 16; e++) {
-                const int t = t0 + (wm * AT + a) * 32 + 8 * (e / 4) + 4 * half + (e % 4);
-                if (t >= T) continue;
-                if (ks > 1) {
-                    float *dst = partial + ((int64_t)kz * T + t) * ncols + col;
-                    dst[0] = acc[a][j][e];
-                    if constexpr (SWI) dst[N] = acc[a][j + WOUT][e];
+            for (int e = 0; e < 4; e++)
+                if (e < left) dst[e] = v[e];
+        }
+    };
+    each<WOUT>([&](auto j) __attribute__((always_inline)) {
+        const int col = n0 + (wn * WOUT + j) * 16 + 4 * kg, left = N - col;
+        if (left <= 0) return;
+        each<AT>([&](auto a) __attribute__((always_inline)) {
+            const int t = t0 + (wm * AT + a) * 16 + l16;
+            if (t >= T) return;
+            if (ks > 1) {
+                float *dst = partial + ((int64_t)kz * T + t) * ncols + col;
+                put(dst, tile_result(acc[a][j]), left);
+                if constexpr (SWI) put(dst + N, tile_result(acc[a][j + WOUT]), left);
+                return;
+            }
+            float *dst = y + (int64_t)t * N + col;
+            f32x4 v = tile_result(acc[a][j]);
+            if constexpr (EPI == ld::GEMM_ADD) {
+                if (quads) {
+                    v += *reinterpret_cast<const f32x4 *>(dst);
                 } else {
-                    float *dst = y + (int64_t)t * N + col;
-                    if constexpr (EPI == ld::GEMM_STORE) *dst = acc[a][j][e];
-                    else if constexpr (EPI == ld::GEMM_ADD) *dst += acc[a][j][e];
-                    else {
-                        const float v = swiglu(acc[a][j][e], acc[a][j + WOUT][e]);
-                        if (out.hi) store_operand(out, t, (int64_t)t * N + col, v);
-                        else *dst = v;
-                    }
+#pragma unroll
+                    for (int e = 0; e < 4; e++)
+                        if (e < left) v[e] += dst[e];
                 }
             }
-    }
+            if constexpr (SWI) {
+                const f32x4 up = tile_result(acc[a][j + WOUT]);
+#pragma unroll
+                for (int e = 0; e < 4; e++) v[e] = swiglu(v[e], up[e]);
+                if (out.hi) {
+                    if (quads) {
+                        store_operand4(out, t, (int64_t)t * N + col, make_float4(v[0], v[1], v[2], v[3]));
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; e++)
+                            if (e < left) store_operand(out, t, (int64_t)t * N + col + e, v[e]);
+                    }
+                    return;
+                }
+            }
+            put(dst, v, left);
+        });
+    });
 }
 
 // Adds the ks K-slab partial sums in slab order and applies the epilogue.  One thread per output.
@@ -822,9 +848,10 @@ void launch_gemm_skinny(const uint16_t *W, const uint16_t *xhi, const uint16_t *
 static void launch_tiles(const uint16_t *W, const bf16_t *hi, const bf16_t *lo, int T, int N, int K, int epi, float *y,
                          float *partial, const BigPlan &p, hipStream_t s, bool reduce, const OperandImage &out, int f16) {
     const int grid = (p.n_nblocks * p.n_ttiles * p.ks + 7) / 8 * 8;
+    const bool quads = N % 4 == 0 && (((uintptr_t)y | (uintptr_t)partial | (uintptr_t)out.hi | (uintptr_t)out.lo) & 15) == 0;
 #define LD_TILE_E(TERMS_, WF_, AT_, BT_, WM_, WN_, EPI_)                                                               \
     do {                                                                                                               \
-        constexpr int lds_bytes = tile_lds(TERMS_, WM_ * AT_ * 32, WN_ * BT_ * 32);                                    \
+        constexpr int lds_bytes = tile_lds(TERMS_, WM_ * AT_ * 16, WN_ * BT_ * 16);                                    \
         static bool attr_set = false;                                                                                  \
         if (!attr_set) {                                                                                               \
             (void)hipFuncSetAttribute((const void *)k_gemm_tile<TERMS_, WF_, AT_, BT_, WM_, WN_, EPI_>,                \
@@ -832,22 +859,22 @@ static void launch_tiles(const uint16_t *W, const bf16_t *hi, const bf16_t *lo, 
             attr_set = true;                                                                                           \
         }                                                                                                              \
         LD_LAUNCH((k_gemm_tile<TERMS_, WF_, AT_, BT_, WM_, WN_, EPI_>), dim3(grid), dim3(256), lds_bytes, s, W, hi, lo, T, \
-                  N, K, y, p.n_ttiles, p.ks, partial, out);                                                            \
+                  N, K, y, p.n_ttiles, p.ks, partial, out, quads);                                                     \
     } while (0)
 #define LD_TILE(TERMS_, WF_, AT_, BT_, WM_, WN_)                                                                       \
     do {                                                                                                               \
-        if (p.bm != WM_ * AT_ * 32 || p.bn != WN_ * BT_ * 32) break;                                                   \
+        if (p.bm != WM_ * AT_ * 16 || p.bn != WN_ * BT_ * 16) break;                                                   \
         if (epi == GEMM_STORE) LD_TILE_E(TERMS_, WF_, AT_, BT_, WM_, WN_, GEMM_STORE);                                 \
         else if (epi == GEMM_ADD) LD_TILE_E(TERMS_, WF_, AT_, BT_, WM_, WN_, GEMM_ADD);                                \
-        else if constexpr (BT_ % 2 == 0) LD_TILE_E(TERMS_, WF_, AT_, BT_, WM_, WN_, GEMM_SWIGLU);                      \
+        else if constexpr (BT_ % 4 == 0) LD_TILE_E(TERMS_, WF_, AT_, BT_, WM_, WN_, GEMM_SWIGLU);                      \
     } while (0)
     if (f16 == 2) {
-        LD_TILE(1, 2, 4, 4, 2, 2); LD_TILE(1, 2, 2, 6, 4, 1); LD_TILE(1, 2, 2, 5, 4, 1); LD_TILE(1, 2, 2, 4, 2, 2);
+        LD_TILE(1, 2, 8, 8, 2, 2); LD_TILE(1, 2, 4, 12, 4, 1); LD_TILE(1, 2, 4, 10, 4, 1); LD_TILE(1, 2, 4, 8, 2, 2);
     } else if (f16) {
-        LD_TILE(1, 1, 4, 4, 2, 2); LD_TILE(1, 1, 2, 6, 4, 1); LD_TILE(1, 1, 2, 5, 4, 1); LD_TILE(1, 1, 2, 4, 2, 2);
+        LD_TILE(1, 1, 8, 8, 2, 2); LD_TILE(1, 1, 4, 12, 4, 1); LD_TILE(1, 1, 4, 10, 4, 1); LD_TILE(1, 1, 4, 8, 2, 2);
     } else {
-        LD_TILE(2, 0, 2, 4, 2, 2); LD_TILE(2, 0, 1, 6, 4, 1); LD_TILE(2, 0, 2, 2, 2, 2); LD_TILE(2, 0, 3, 2, 1, 4); LD_TILE(2, 0, 5, 2, 1, 4);
-        LD_TILE(2, 0, 3, 4, 2, 2);
+        LD_TILE(2, 0, 4, 8, 2, 2); LD_TILE(2, 0, 2, 12, 4, 1); LD_TILE(2, 0, 4, 4, 2, 2); LD_TILE(2, 0, 6, 4, 1, 4); LD_TILE(2, 0, 10, 4, 1, 4);
+        LD_TILE(2, 0, 6, 8, 2, 2);
     }
 #undef LD_TILE
 #undef LD_TILE_E

@@ -512,6 +512,42 @@ def test_linear_every_tile(form, rows, cols, K, ks, monkeypatch, capfd):
     assert "LD_GEMM_BIG" not in capfd.readouterr().err
 
 
+@pytest.mark.parametrize("form", ["two", "f16"])
+@pytest.mark.parametrize("T,N,ks", [(65, 4, 1), (333, 300, 1), (333, 300, 3), (257, 1028, 2), (300, 302, 1)])
+def test_linear_tile_stores_of_four_columns(form, T, N, ks, monkeypatch):
+    """The big-tile kernel stores four columns at a time where rows are a multiple of four floats and 16-byte aligned, one at a
+    time elsewhere (302 columns; an output that starts 4 bytes past an aligned address): the same bits, nothing written beside
+    the output, and within 2^-16 sum_k |w x| of float64 on the inputs as the form rounds them (see test_linear_every_tile)."""
+    monkeypatch.setenv("LD_GEMM_BIG", "128,256,%d" % ks)
+    K = 1152
+    W = _mat(43, N, 2 * N, K, "bf16").to(DEV); x = gen.normal(43, 2, (T, K), device=DEV); y0 = gen.normal(43, 4, (T, N), device=DEV)
+    scratch = torch.empty(2 * T * K * 2 + 256 + ks * T * 2 * N * 4, dtype=torch.uint8, device=DEV)
+    flag = torch.zeros(1, dtype=torch.int32, device=DEV)
+    hi = x.bfloat16().float()
+    xr = ((hi + (x - hi).bfloat16().float()).half() if form == "f16" else x).double()
+    full, mag = xr @ W.double().t(), xr.abs() @ W.double().abs().t()
+    for epi, n in ((ld.LDK_STORE, N), (ld.LDK_ADD, N), (ld.LDK_SWIGLU, 2 * N)):
+        outs = []
+        for shift in (0, 1):
+            buf = torch.full((T * N + 8,), 7.0, device=DEV)
+            y = buf[4 + shift:4 + shift + T * N].view(T, N)
+            y.copy_(y0)
+            if form == "f16":
+                ld.ldk_linear_f16(W[:n], x, y, flag, epi, scratch=scratch)
+            else:
+                ld.ldk_linear(W[:n], x, y, epi, scratch=scratch)
+            assert (buf[:4 + shift] == 7.0).all() and (buf[4 + shift + T * N:] == 7.0).all()
+            outs.append(y)
+        assert torch.equal(*outs)
+        a = full[:, :N]
+        if epi == ld.LDK_SWIGLU:
+            ref = torch.nn.functional.silu(a) * full[:, N:]
+            bound = 2.0 ** -16 * (1.1 * full[:, N:].abs() * mag[:, :N] + torch.nn.functional.silu(a).abs() * mag[:, N:]) + 1e-6 * ref.abs()
+        else:
+            ref, bound = a + (y0.double() if epi == ld.LDK_ADD else 0), 2.0 ** -16 * mag[:, :N] + 1e-6
+        assert ((outs[0].double() - ref).abs() <= bound + 1e-7).all(), epi
+
+
 def test_linear_matrix_core_7b_shapes_sampled():
     """Launch shapes of the batch-32 decode step, of a 256-row prefill chunk, of a mixed step (32 decode rows
     + four 256-row chunks) and of a 2048-row chunk beside 63 decode rows, sampled outputs.  The last two have
