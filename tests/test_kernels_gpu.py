@@ -472,8 +472,8 @@ def test_linear_unknown_forced_plan_is_reported(plan, monkeypatch, capfd):
     assert torch.isfinite(ys[0]).all() and torch.equal(*ys)
 
 
-@pytest.mark.parametrize("form,rows,cols", [("two", r, c) for r, c in ((96, 256), (128, 128), (128, 192), (128, 256), (160, 256), (192, 256))]
-                         + [("f16", r, c) for r, c in ((128, 256), (256, 160), (256, 192), (256, 256))])
+@pytest.mark.parametrize("form,rows,cols", [("two", r, c) for r, c in ((96, 128), (96, 192), (96, 256), (128, 128), (128, 192), (128, 256), (160, 192), (160, 256), (192, 192), (192, 256))]
+                         + [("f16", r, c) for r, c in ((128, 192), (128, 256), (192, 192), (192, 256), (224, 256), (256, 160), (256, 192), (256, 256))])
 @pytest.mark.parametrize("K,ks", [(128, 1), (1152, 1), (1152, 4)])
 def test_linear_every_tile(form, rows, cols, K, ks, monkeypatch, capfd):
     """Every tile of the big-tile kernel, in both forms (two bf16 terms; one fp16 term on the fp16 image and on the bf16
