@@ -13,11 +13,15 @@
 // behind block-table entries read another unit earlier, and shared by the four waves.  LDS is double buffered, with one
 // barrier per unit.  Two workgroups fit a CU, so that one wave's softmax overlaps another's MFMAs.
 //
-// What bounds it: a unit takes two co-resident workgroups about 3.4 us, of which the vector arithmetic of the softmax
-// and the staging fill about a half and the MFMAs a quarter (F16); the rest is operand and barrier latency at two waves
-// per SIMD.  So the work per step is what counts: two steps a barrier, in F16 one maximum, one exchange and one look at the
-// rescaling for both (scores start at -m, which saves the subtraction before the exponential).  12 tiles x 32 heads at
-// contexts 2.2k .. 6.4k: 322 -> 220 us with its merge 338 -> 235; one 256-row chunk behind 1500: 44 -> 37 us.
+// What bounds it: the work per step at two waves per SIMD (a third of the cycles issue vector arithmetic, a fifth run MFMAs, the
+// rest waits for operands and barriers).  Hence two steps a barrier; in F16 one maximum, one exchange and one look at the
+// rescaling for both (scores start at -m, which saves the subtraction before the exponential); and as little as possible
+// around them: blocks are addressed in scalar registers, the range check of a widened pair is one instruction, a unit that
+// lies below the last position is staged without a look at each piece, the two halves of a query exchange maxima without LDS.
+// 12 tiles x 32 heads at contexts 2.2k .. 6.4k: 322 -> 214 -> 181 us with these (one step at a time, two, now); four segments
+// of 256 rows behind 0.5k .. 2.9k 98 -> 85 -> 76; one 256-row chunk behind 1500, in two terms, 33 -> 30 -> 30.
+// Forming the next unit's scores between this one's exponentials, and staging between its value products, was level
+// (209 and 79 us: its second set of scores fills the registers).
 //
 // Both products are computed transposed, so that the query index is the MFMA column (= lane % 32)
 // everywhere and the online-softmax statistics of a query live in the lanes that hold its scores:
@@ -42,6 +46,7 @@
 #include "ld_attn_prefill.h"
 #include "ld_device.h"
 #include "ld_internal.h"
+#include <type_traits>
 
 using namespace ldd;
 
@@ -50,7 +55,6 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
-typedef __attribute__((ext_vector_type(2))) uint16_t u16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
@@ -67,16 +71,28 @@ __device__ __forceinline__ uint32_t pack2_f16(float a, float b) {
     return __builtin_bit_cast(uint32_t, (f16x2){(_Float16)a, (_Float16)b});
 }
 // Eight bf16 numbers as fp16: exact where fp16 can hold the value (truncation below 2^-14, the largest finite
-// fp16 beyond +-65504: the caller looks for such values with `mag`, the running maximum of the magnitudes).
-__device__ __forceinline__ u32x4 bf16x8_to_f16x8(const u32x4 &w, u16x2 &mag) {
+// fp16 beyond +-65504: the caller looks for such values with `mag`, the running maximum of the magnitudes, which passes
+// over NaNs: those reach the result).
+__device__ __forceinline__ u32x4 bf16x8_to_f16x8(const u32x4 &w, float &mag) {
     u32x4 h;
 #pragma unroll
     for (int i = 0; i < 4; i++) {
-        h[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(w[i] << 16), __uint_as_float(w[i] & 0xffff0000u)));
-        mag = __builtin_elementwise_max(mag, __builtin_bit_cast(u16x2, w[i] & 0x7fff7fffu));
+        const float a = __uint_as_float(w[i] << 16), b = __uint_as_float(w[i] & 0xffff0000u);
+        h[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(a, b));
+        asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(mag) : "v"(a), "v"(b));
     }
     return h;
 }
+
+// 16 bytes from a lane's offset in a block that is the same for the whole wave: no address arithmetic in vector registers.
+#if defined(__HIP_DEVICE_COMPILE__)
+__device__ __forceinline__ u32x4 load_in_block(const bf16_t *block, uint32_t off) {
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(block), 0, -1, 0x00020000), off, 0, 0));
+}
+#else
+__device__ u32x4 load_in_block(const bf16_t *, uint32_t) { return u32x4{}; }
+#endif
 
 // Steps of KVB positions that a tile walks: from the first position its first row sees (rounded down) to its last row's.
 __device__ __forceinline__ int tile_start(const int4 &tile, int window) { return window > 0 ? (max(tile.z - window + 1, 0) & ~(KVB - 1)) : 0; }
@@ -125,7 +141,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
     const int n_steps = tile_steps(tile, window), split = blockIdx.z;
     if (split * per >= n_steps) return;
     const bool whole = n_steps <= per || gridDim.z == 1;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l32 = lane & 31, half = lane >> 5;
     const int kvh = h / (H / Hkv);
     const int64_t block_stride = kv_block_elems(Hkv, HD);
@@ -152,7 +168,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
     // fp16 term in qh)
     u32x4 qh[8], ql[F16 ? 1 : 8];
     bool out_of_range = false;      // F16: a value beyond the fp16 range was seen by this lane
-    u16x2 mag = {0, 0};             // F16: largest bf16 magnitude (bit pattern) among the keys and values this lane staged
+    float mag = 0.f;                // F16: largest magnitude among the keys and values this lane staged
     {
         const float *qp = q + (int64_t)(tile.x + min(qi, tile.y - 1)) * q_stride + h * HD + half * 64;
 #pragma unroll
@@ -186,6 +202,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
     // value pieces (dimension vd, positions 8*vh .. +8 of block v of the step).
     const int kr = threadIdx.x >> 4, kc = (threadIdx.x & 15) * 8;       // + 16 rows for the second piece
     const int vd = threadIdx.x >> 1, vh = (threadIdx.x & 1) * 8;
+    // lane offsets in bytes from a block's first element (a block has at most a few MB)
+    const uint32_t k_off = (uint32_t)kv_k_offset(HD, kvh, kr, kc) * 2u, v_off = (uint32_t)kv_v_offset(Hkv, HD, kvh, vh, vd) * 2u;
     // Two steps of 32 positions make a unit, with one barrier each; the global loads run one unit ahead.
     u32x4 kreg[2][2], vreg[2][2];
     int entry[2][2];      // the table's entries of the unit to be loaded next, read one unit before
@@ -204,32 +222,31 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
 #pragma unroll
             for (int v = 0; v < 2; v++) {
                 const bf16_t *blk = pool + (int64_t)entry[u][v] * block_stride;
-                kreg[u][v] = *reinterpret_cast<const u32x4 *>(blk + kv_k_offset(HD, kvh, kr, kc));
-                vreg[u][v] = *reinterpret_cast<const u32x4 *>(blk + kv_v_offset(Hkv, HD, kvh, vh, vd));
+                kreg[u][v] = load_in_block(blk, k_off);
+                vreg[u][v] = load_in_block(blk, v_off);
             }
     };
     // Values of positions past the tile's last row were never written (the rest of the last block, or the
     // second block of a step that ends the walk): they may hold anything, also NaN, and a probability of zero
     // does not neutralise a NaN, so they are staged as zeros.  (Keys need nothing: their scores are replaced,
     // not multiplied.)
-    auto stage = [&](int st, int kv_unit) {
+    auto stage_pieces = [&](int st, int kv_unit, auto whole_unit) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < 2; u++)
 #pragma unroll
             for (int v = 0; v < 2; v++) {
                 const int kv0 = kv_unit + KVB * u;
+                u32x4 kk = kreg[u][v], vv = vreg[u][v];
                 if constexpr (F16) {
                     // a key row past the tile's last position was never written (its scores are masked): whatever it
                     // holds does not count as out of range
-                    u16x2 seen = mag;
-                    *reinterpret_cast<u32x4 *>(&ks[st][u][16 * v + kr][kc]) = bf16x8_to_f16x8(kreg[u][v], seen);
-                    if (kv0 + 16 * v + kr <= wg_last_pos) mag = seen;
-                } else {
-                    *reinterpret_cast<u32x4 *>(&ks[st][u][16 * v + kr][kc]) = kreg[u][v];
+                    float seen = mag;
+                    kk = bf16x8_to_f16x8(kk, seen);
+                    if (whole_unit || kv0 + 16 * v + kr <= wg_last_pos) mag = seen;
                 }
-                u32x4 vv = vreg[u][v];
+                *reinterpret_cast<u32x4 *>(&ks[st][u][16 * v + kr][kc]) = kk;
                 const int p0 = kv0 + 16 * v + vh;      // position of this piece's first element
-                if (p0 + 7 > wg_last_pos) {
+                if (!whole_unit && p0 + 7 > wg_last_pos) {
 #pragma unroll
                     for (int e = 0; e < 4; e++)
                         vv[e] = (p0 + 2 * e <= wg_last_pos ? vv[e] & 0x0000ffffu : 0u) |
@@ -238,6 +255,10 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
                 if constexpr (F16) vv = bf16x8_to_f16x8(vv, mag);
                 *reinterpret_cast<u32x4 *>(&vt[st][u][vd][16 * v + vh]) = vv;
             }
+    };
+    auto stage = [&](int st, int kv_unit) {      // most units lie wholly below the last position: no look at each piece
+        if (kv_unit + 2 * KVB - 1 <= wg_last_pos) stage_pieces(st, kv_unit, std::true_type{});
+        else stage_pieces(st, kv_unit, std::false_type{});
     };
     const int kv_begin = kv_start + split * per * KVB;
     const int kv_end = split + 1 == gridDim.z ? wg_last_pos + 1 : min(kv_begin + per * KVB, wg_last_pos + 1);      // exclusive; the last share takes what is left
@@ -292,7 +313,10 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
                     mb = fmaxf(mb, sc_t[n][i]);
                 }
         }
-        mb = fmaxf(mb, __shfl_xor(mb, 32, WAVE));
+        {      // the other half of the wave holds the query's other scores
+            const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(mb), __float_as_uint(mb), false, false);
+            mb = fmaxf(__uint_as_float(both[0]), __uint_as_float(both[1]));
+        }
         // m is the reference the exponents are taken against, not necessarily the running maximum: it moves up
         // only when the maximum has outgrown it by more than 2^8, so p stays below 256 and the accumulators
         // are rescaled on few steps instead of most.  o, l and m stay consistent, which is all the final
@@ -375,11 +399,16 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
         }
         st ^= 1;
     }
-    if constexpr (F16) {      // 0x4780 is 65536 as bf16: the first magnitude that fp16 cannot hold (also infinities and NaNs)
-        if (out_of_range || mag[0] >= 0x4780 || mag[1] >= 0x4780) *f16_flag = 1;
-    }
     // the two halves of a query's scores were summed separately
     l += __shfl_xor(l, 32, WAVE);
+    if constexpr (F16) {      // a magnitude that fp16 cannot hold, or a NaN (they all reach l or o of the queries that see them)
+        float sum = l;
+#pragma unroll
+        for (int nt = 0; nt < 4; nt++)
+#pragma unroll
+            for (int i = 0; i < 16; i++) sum += o[nt][i];
+        if (out_of_range || mag > 65504.f || sum != sum) *f16_flag = 1;
+    }
     if (!whole) {      // unnormalised share: [tile][row in tile][head][split][HD] and (m, l)
         if (q_valid) {
             const int64_t item = (((int64_t)tile_idx * 128 + qi) * H + h) * gridDim.z + split;

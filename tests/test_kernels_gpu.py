@@ -749,6 +749,24 @@ def test_prefill_attention_fp16_form(H, Hkv, window, split):
     assert run(qb, pool)[1] == 1
 
 
+@pytest.mark.parametrize("what", [float("nan"), float("inf"), -float("inf"), 65536.0, 65280.0])
+@pytest.mark.parametrize("part", [0, 1], ids=["key", "value"])
+@pytest.mark.parametrize("pos", [0, 63, 64, 127, 190])
+def test_prefill_attention_fp16_range_check(what, part, pos):
+    """What raises the flag of the fp16 form: a NaN, an infinity or 65536 (the first magnitude fp16 cannot hold) in a key or a value
+    that a row sees, in units that lie below the last position and in the last one, also beside the first and last position of a
+    unit of 64; 65280, the largest bf16 number that fp16 holds, does not."""
+    H, hd, lens = 2, 128, [191]
+    table, pool, _ = _attention_case(53, lens, H, H, hd, "bf16")
+    q = gen.normal(53, 9, (40, H, hd), device=DEV)
+    tiles = torch.tensor([[0, 40, 151, 0]], dtype=torch.int32, device=DEV)
+    pool = pool.clone()
+    pool[int(table[0, pos // 16]), part, 1, pos % 16, 17] = what
+    flag, out = torch.zeros(1, dtype=torch.int32, device=DEV), torch.zeros(40, H, hd, device=DEV)
+    ld.ldk_prefill_attention_f16(q, H * hd, device_pool(pool), table.to(DEV), tiles, H, H, hd, out, 190, flag)
+    assert int(flag.item()) == (what != 65280.0)
+
+
 @pytest.mark.parametrize("N,K,epi,norm", [(N, K, epi, norm) for epi in ("store", "add", "swiglu") for norm in (False, True) for N, K in [
     (1, 8), (2, 2040), (3, 2048), (513, 2056), (1025, 6152), (1537, 8192), (770, 8200), (1026, 16384), (4099, 2056), (4099, 8200), (2050, 16384), (16391, 1032)]] + [(140000, 16384, "store", False)])
 def test_gemv_slab_edges(N, K, epi, norm):
