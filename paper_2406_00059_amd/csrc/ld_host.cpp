@@ -143,8 +143,10 @@ struct ld_kv {
     // slots) so that a step can be prepared while the previous one is still in flight; step_ev[slot] marks
     // the end of the pass that used the slot.
     int32_t *pin_meta = nullptr, *pin_out = nullptr, *pin_table = nullptr;
+    int32_t *dev_meta = nullptr, *dev_out = nullptr, *dev_table = nullptr;      // the same as the GPU sees them
     hipEvent_t step_ev[2] = {nullptr, nullptr};
-    size_t meta_ints() const { return (size_t)max_tokens * 9 + 2 + (size_t)max_seqs * 4; }
+    size_t range_off() const { return (size_t)max_tokens * 9 + 2 + (size_t)max_seqs * 4; }      // changed runs of the block table, behind the metadata
+    size_t meta_ints() const { return range_off() + (size_t)max_seqs * 3; }
     // optional per-kernel timing
     bool prof_on = false;
     ld_profile prof{};
@@ -234,7 +236,12 @@ ld_status ensure_pinned(ld_kv *kv) {
     LD_HIP_TRY(hipHostMalloc((void **)&kv->pin_out, ((size_t)2 * kv->max_seqs + 2) * 4, hipHostMallocDefault));   // + one flag per slot
     LD_HIP_TRY(hipHostMalloc((void **)&kv->pin_table, (size_t)kv->max_seqs * kv->max_blocks * 4, hipHostMallocDefault));
     for (hipEvent_t &e : kv->step_ev) LD_HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    LD_HIP_TRY(hipHostMalloc((void **)&kv->pin_meta, 2 * kv->meta_ints() * 4, hipHostMallocDefault));
+    LD_HIP_TRY(hipHostGetDevicePointer((void **)&kv->dev_out, kv->pin_out, 0));
+    LD_HIP_TRY(hipHostGetDevicePointer((void **)&kv->dev_table, kv->pin_table, 0));
+    int32_t *meta = nullptr;
+    LD_HIP_TRY(hipHostMalloc((void **)&meta, 2 * kv->meta_ints() * 4, hipHostMallocDefault));
+    kv->pin_meta = meta;
+    LD_HIP_TRY(hipHostGetDevicePointer((void **)&kv->dev_meta, meta, 0));
     return LD_OK;
 }
 
@@ -299,22 +306,23 @@ ld_status enqueue_pass(ld_kv *kv, const std::vector<Row> &rows, int n_single, co
         }
         meta_ints = samp_off + 4 * R;
     }
-    LD_HIP_TRY(hipMemcpyAsync(w.meta, pm, (size_t)meta_ints * 4, hipMemcpyHostToDevice, st));
     // allow_f16: the multi-row products may take their rows rounded to fp16 (launch_gemm); flags[0] tells afterwards
     // whether a value did not fit, pin_out[2 * max_seqs + slot] carries it to the host
     int *f16_flag = allow_f16 ? w.flags : nullptr;
-    if (f16_flag) LD_HIP_TRY(hipMemsetAsync(w.flags, 0, 4, st));
-    const int32_t *d_tok = tok_from_prev ? w.out_tok : w.meta, *d_pos = w.meta + T, *d_slot = w.meta + 2 * T, *d_ctx = w.meta + 3 * T,
-                  *d_emit = w.meta + 4 * T, *d_tiles = w.meta + 5 * T;
+    const int32_t *d_pos = w.meta + T, *d_slot = w.meta + 2 * T, *d_ctx = w.meta + 3 * T, *d_emit = w.meta + 4 * T, *d_tiles = w.meta + 5 * T;
 
     // block-table rows that changed since the last pass
+    ld::PassStart begin{T, meta_ints, 0, kv->dev_meta + (pm - kv->pin_meta), nullptr, kv->dev_table, w.meta, w.table, kv->max_blocks, f16_flag};
+    begin.ranges_host = begin.meta_host + kv->range_off();
+    int32_t *pr = pm + kv->range_off();
     for (int t = 0; t < T; t++) {
         Seq &q = kv->seqs[rows[t].seq];
         if (q.dirty_lo == q.dirty_hi) continue;
         const size_t o = (size_t)rows[t].seq * kv->max_blocks + q.dirty_lo;
-        const size_t n = q.dirty_hi - q.dirty_lo;
-        memcpy(kv->pin_table + o, kv->table.data() + o, n * 4);
-        LD_HIP_TRY(hipMemcpyAsync(w.table + o, kv->pin_table + o, n * 4, hipMemcpyHostToDevice, st));
+        const int32_t n = q.dirty_hi - q.dirty_lo;
+        memcpy(kv->pin_table + o, kv->table.data() + o, (size_t)n * 4);
+        pr[3 * begin.n_ranges] = rows[t].seq; pr[3 * begin.n_ranges + 1] = q.dirty_lo; pr[3 * begin.n_ranges + 2] = n;
+        begin.n_ranges++;
         q.dirty_lo = q.dirty_hi = 0;
     }
 
@@ -333,8 +341,7 @@ ld_status enqueue_pass(ld_kv *kv, const std::vector<Row> &rows, int n_single, co
     } while (0)
     const int d = c.d_model, nq = m.nq(), nqkv = m.nqkv(), H = c.n_heads, Hkv = c.n_kv_heads, hd = c.head_dim;
     const size_t layer_bytes = (size_t)kv->n_blocks * m.block_elems() * m.elem();
-    LD_TIMED(LD_PROF_OTHER, ldk_embed(m.embed, c.dtype, d_tok, T, d, w.x, st));
-    LD_TIMED(LD_PROF_OTHER, ldk_rope_table(d_pos, T, hd, c.rope_base, w.cos_sin, st));
+    LD_TIMED(LD_PROF_OTHER, ld::pass_begin(m.embed, c.dtype, tok_from_prev ? w.out_tok : nullptr, d, w.x, hd, c.rope_base, w.cos_sin, begin, st));
     // Decode batches of 2..32 rows on bf16 weights take the fused batch layer; everything else the
     // general per-step composition below.
     const bool batch_path = c.dtype == LD_BF16 && n_tiles == 0 && c.n_layers > 0 &&
@@ -444,19 +451,19 @@ ld_status enqueue_pass(ld_kv *kv, const std::vector<Row> &rows, int n_single, co
         LD_TIMED(LD_PROF_LM_HEAD, ldk_linear(m.lm_head, c.dtype, w.hn, nullptr, 0.f, R, c.vocab, d, LDK_STORE, w.logits,
                                              w.lin_scratch, w.lin_scratch_bytes, st));
     }
+    // the last kernel of a pass that emits hands tokens and flag to the host itself
+    const ld::PassEnd end{kv->dev_out + (size_t)slot * kv->max_seqs, f16_flag, f16_flag ? kv->dev_out + (size_t)2 * kv->max_seqs + slot : nullptr};
     if (sampling)
-        LD_TIMED(LD_PROF_OTHER, ldk_sample(w.logits, R, c.vocab, reinterpret_cast<const float *>(w.meta + samp_off + 2 * R),
+        LD_TIMED(LD_PROF_OTHER, ld::sample(w.logits, R, c.vocab, reinterpret_cast<const float *>(w.meta + samp_off + 2 * R),
                                            reinterpret_cast<const uint64_t *>(w.meta + samp_off), w.meta + samp_off + 3 * R,
-                                           w.out_tok, st));
+                                           w.out_tok, st, end));
     else
-        LD_TIMED(LD_PROF_OTHER, ldk_argmax(w.logits, R, c.vocab, w.out_tok, st));
+        LD_TIMED(LD_PROF_OTHER, ld::argmax(w.logits, R, c.vocab, w.out_tok, st, end));
 #undef LD_TIMED
 #undef LD_TRY
-    if (R)
-        LD_HIP_TRY(hipMemcpyAsync(kv->pin_out + (size_t)slot * kv->max_seqs, w.out_tok, (size_t)R * 4, hipMemcpyDeviceToHost, st));
     if (logits_out && R)
         LD_HIP_TRY(hipMemcpyAsync(logits_out, w.logits, (size_t)R * c.vocab * 4, hipMemcpyDeviceToHost, st));
-    if (f16_flag)
+    if (f16_flag && !R)
         LD_HIP_TRY(hipMemcpyAsync(kv->pin_out + (size_t)2 * kv->max_seqs + slot, w.flags, 4, hipMemcpyDeviceToHost, st));
     LD_HIP_TRY(hipEventRecord(kv->step_ev[slot], st));
     return LD_OK;

@@ -43,6 +43,29 @@ struct OperandImage {
     int *f16_flag = nullptr;
 };
 
+// What the kernels at the two ends of a pass exchange with page-locked host memory (device addresses of it: *_host), in place
+// of copies around them.  Metadata: tokens, positions, .. (meta_ints of them); ranges: (table row, first entry, number) of each run of
+// block-table entries that changed, which lie in the host's copy of the table at the same place.
+struct PassStart {
+    int T, meta_ints, n_ranges;
+    const int32_t *meta_host, *ranges_host, *table_host;
+    int32_t *meta, *table;
+    int table_stride;
+    int *clear_flag;      // set to 0 where not null
+};
+struct PassEnd {
+    int32_t *tok = nullptr;          // emitted tokens
+    const int *flag = nullptr;       // copied to *flag_host
+    int *flag_host = nullptr;
+};
+// Embeddings and rotary table of the pass's rows, and what PassStart names.  prev_tok: the input tokens, where not the metadata's.
+ld_status pass_begin(const void *embed, int dtype, const int32_t *prev_tok, int d, float *x, int hd, float rope_base, float *cos_sin,
+                     const PassStart &p, hipStream_t s);
+// ldk_argmax, ldk_sample; what PassEnd names beside it.
+ld_status argmax(const float *logits, int R, int V, int32_t *out, hipStream_t s, const PassEnd &host);
+ld_status sample(const float *logits, int R, int V, const float *temperature, const uint64_t *seed, const int32_t *pos, int32_t *out,
+                 hipStream_t s, const PassEnd &host);
+
 ld_status paged_attention_split(const float *q, int q_stride, const void *pool_layer, int dtype, const int32_t *table,
                                 int table_stride, const int32_t *seq_slot, const int32_t *ctx_len, int max_ctx, int T,
                                 int H, int Hkv, int hd, int window, uint16_t *xs_out, void *scratch,

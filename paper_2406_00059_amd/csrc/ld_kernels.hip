@@ -135,14 +135,50 @@ __global__ __launch_bounds__(256) void k_linear_valu(const WT *__restrict__ W, c
 
 // ---------------------------------------------------------------- rotary tables, RoPE + cache append
 
-// cs[t][i] = (cos, sin)(pos[t] * base^(-2i/hd)), angle formed in float64.
+// (cos, sin)(pos * base^(-2i/hd)), angle formed in float64.
+__device__ __forceinline__ float2 rope_entry(int pos, int i, int hd, double base) {
+    const double theta = pow(base, -2.0 * (double)i / (double)hd);
+    double s, c;
+    sincos((double)pos * theta, &s, &c);
+    return make_float2((float)c, (float)s);
+}
+
 __global__ void k_rope_table(const int32_t *__restrict__ pos, int hd, double base, float2 *__restrict__ cs) {
     const int t = blockIdx.x, i = threadIdx.x, half = hd / 2;
     if (i >= half) return;
-    const double theta = pow(base, -2.0 * (double)i / (double)hd);
-    double s, c;
-    sincos((double)pos[t] * theta, &s, &c);
-    cs[(int64_t)t * half + i] = make_float2((float)c, (float)s);
+    cs[(int64_t)t * half + i] = rope_entry(pos[t], i, hd, base);
+}
+
+// Start of a pass, in one launch: block t < T gathers row t's embedding and forms its rotary table; the blocks after them
+// copy the pass's metadata and the block-table entries that changed, which they read from page-locked host memory.  A pass is
+// a chain of short kernels, and a copy in front of it costs as much as one of them: with a copy for the metadata and one for
+// each changed sequence, a decode step of 32 sequences that were just forked waited some 200 us for its first kernel.
+template <typename WT>
+__global__ __launch_bounds__(256) void k_begin(const WT *__restrict__ E, const int32_t *__restrict__ prev_tok, int d, float *__restrict__ x, int hd,
+                                               double base, float2 *__restrict__ cs, ld::PassStart p) {
+    const int t = blockIdx.x;
+    if (t < p.T) {
+        const int tok = prev_tok ? prev_tok[t] : p.meta_host[t];
+        const WT *row = E + (int64_t)tok * d;
+        for (int i = threadIdx.x * 8; i < d; i += 256 * 8) {
+            float v[8];
+            load8(row + i, v);
+#pragma unroll
+            for (int e = 0; e < 8; e++) x[(int64_t)t * d + i + e] = v[e];
+        }
+        if (threadIdx.x < hd / 2) cs[(int64_t)t * (hd / 2) + threadIdx.x] = rope_entry(p.meta_host[p.T + t], threadIdx.x, hd, base);
+        return;
+    }
+    if (t < p.T + p.n_ranges) {
+        const int32_t *r = p.ranges_host + 3 * (t - p.T);
+        const int64_t first = (int64_t)r[0] * p.table_stride + r[1];
+        const int n = r[2];
+        for (int i = threadIdx.x; i < n; i += 256) p.table[first + i] = p.table_host[first + i];
+        return;
+    }
+    const int i = (t - p.T - p.n_ranges) * 256 + threadIdx.x;
+    if (i < p.meta_ints) p.meta[i] = p.meta_host[i];
+    if (i == 0 && p.clear_flag) *p.clear_flag = 0;
 }
 
 template <typename KVT>
@@ -415,7 +451,7 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float *__restrict__ pa
 
 // ---------------------------------------------------------------- greedy argmax (lowest index on ties)
 
-__global__ __launch_bounds__(1024) void k_argmax(const float *__restrict__ logits, int V, int32_t *__restrict__ out) {
+__global__ __launch_bounds__(1024) void k_argmax(const float *__restrict__ logits, int V, int32_t *__restrict__ out, ld::PassEnd host) {
     __shared__ float sv[16];
     __shared__ int si[16];
     const int r = blockIdx.x;
@@ -449,6 +485,8 @@ __global__ __launch_bounds__(1024) void k_argmax(const float *__restrict__ logit
         for (int w = 1; w < 16; w++)
             if (sv[w] > bv || (sv[w] == bv && si[w] < bi)) { bv = sv[w]; bi = si[w]; }
         out[r] = bi;
+        if (host.tok) host.tok[r] = bi;
+        if (r == 0 && host.flag) *host.flag_host = *host.flag;
     }
 }
 
@@ -471,7 +509,7 @@ __device__ __forceinline__ float gumbel_noise(uint64_t seed, uint64_t counter) {
 __global__ __launch_bounds__(1024) void k_sample(const float *__restrict__ logits, int V,
                                                  const float *__restrict__ temperature,
                                                  const uint64_t *__restrict__ seed, const int32_t *__restrict__ pos,
-                                                 int32_t *__restrict__ out) {
+                                                 int32_t *__restrict__ out, ld::PassEnd host) {
     __shared__ float sv[16];
     __shared__ int si[16];
     const int r = blockIdx.x;
@@ -498,6 +536,8 @@ __global__ __launch_bounds__(1024) void k_sample(const float *__restrict__ logit
         for (int w = 1; w < 16; w++)
             if (sv[w] > bv || (sv[w] == bv && si[w] < bi)) { bv = sv[w]; bi = si[w]; }
         out[r] = bi;
+        if (host.tok) host.tok[r] = bi;
+        if (r == 0 && host.flag) *host.flag_host = *host.flag;
     }
 }
 
@@ -861,24 +901,41 @@ ld_status ldk_prefill_attention_f16(const float *q, int32_t q_stride, const void
 }
 
 ld_status ldk_argmax(const float *logits, int32_t R, int32_t V, int32_t *out, void *stream) {
-    if (R == 0) return LD_OK;
-    if (!logits || !out || R < 0 || V <= 0) return ld::fail(LD_E_INVAL, "ldk_argmax: bad argument");
-    LD_LAUNCH(k_argmax, dim3(R), dim3(1024), 0, (hipStream_t)stream, logits, V, out);
-    return launched("k_argmax");
+    return ld::argmax(logits, R, V, out, (hipStream_t)stream, ld::PassEnd{});
 }
 
 ld_status ldk_sample(const float *logits, int32_t R, int32_t V, const float *temperature, const uint64_t *seed,
                      const int32_t *pos, int32_t *out, void *stream) {
-    if (R == 0) return LD_OK;
-    if (!logits || !temperature || !seed || !pos || !out || R < 0 || V <= 0)
-        return ld::fail(LD_E_INVAL, "ldk_sample: bad argument");
-    LD_LAUNCH(k_sample, dim3(R), dim3(1024), 0, (hipStream_t)stream, logits, V, temperature, seed, pos, out);
-    return launched("k_sample");
+    return ld::sample(logits, R, V, temperature, seed, pos, out, (hipStream_t)stream, ld::PassEnd{});
 }
 
 }  // extern "C"
 
 namespace ld {
+
+ld_status argmax(const float *logits, int R, int V, int32_t *out, hipStream_t s, const PassEnd &host) {
+    if (R == 0) return LD_OK;
+    if (!logits || !out || R < 0 || V <= 0) return fail(LD_E_INVAL, "ldk_argmax: bad argument");
+    LD_LAUNCH(k_argmax, dim3(R), dim3(1024), 0, s, logits, V, out, host);
+    return launched("k_argmax");
+}
+
+ld_status sample(const float *logits, int R, int V, const float *temperature, const uint64_t *seed, const int32_t *pos, int32_t *out,
+                 hipStream_t s, const PassEnd &host) {
+    if (R == 0) return LD_OK;
+    if (!logits || !temperature || !seed || !pos || !out || R < 0 || V <= 0) return fail(LD_E_INVAL, "ldk_sample: bad argument");
+    LD_LAUNCH(k_sample, dim3(R), dim3(1024), 0, s, logits, V, temperature, seed, pos, out, host);
+    return launched("k_sample");
+}
+
+ld_status pass_begin(const void *embed, int dtype, const int32_t *prev_tok, int d, float *x, int hd, float rope_base, float *cos_sin,
+                     const PassStart &p, hipStream_t s) {
+    const dim3 grid(p.T + p.n_ranges + (p.meta_ints + 255) / 256), block(256);
+    float2 *cs = (float2 *)cos_sin;
+    if (dtype == LD_BF16) LD_LAUNCH(k_begin<bf16_t>, grid, block, 0, s, (const bf16_t *)embed, prev_tok, d, x, hd, (double)rope_base, cs, p);
+    else LD_LAUNCH(k_begin<float>, grid, block, 0, s, (const float *)embed, prev_tok, d, x, hd, (double)rope_base, cs, p);
+    return launched("k_begin");
+}
 
 // Single-query paged attention whose output is written as the split (hi, lo) bf16 operand of the
 // output projection: xs_out [2][image_rows][H * hd], of which these T rows are the first (image_rows 0: T), or with
