@@ -54,6 +54,12 @@ void launch_weight_range_check(const uint16_t *W, int64_t n, int *flag, hipStrea
 // The same check, and out[n] = W as fp16 (exact where the flag stays clear, values below 2^-14 in magnitude aside).
 void launch_weight_to_f16(const uint16_t *W, int64_t n, uint16_t *out, int *flag, hipStream_t s);
 
+// y = epilogue(x W^T) for up to 64 rows straight from the float rows, normalised where g is not null;
+// scratch as for the image form.  gemm_takes_floats: where that is the faster form.
+bool gemm_takes_floats(int T, int K);
+void launch_gemm_floats(const uint16_t *W, const float *x, const float *g, float eps, int T, int N, int K, int epi, float *y, void *scratch,
+                        hipStream_t s);
+
 // Skinny product alone (T <= 64 rows, K a multiple of 128): partial[z][t][row] for the skinny_slabs(T, K) K slabs z;
 // the caller adds the slabs in order.  octets: the layout of the images, see launch_norm_split.
 int skinny_slabs(int T, int K);

@@ -155,13 +155,17 @@ __device__ __forceinline__ void ds_read_b128xn(u32x4 (&w)[4], const uint32_t (&a
                  : "memory");
 }
 
-// TT: 16-row tiles of X.  OCT: X comes as [part][K / 8][T][8] (the layout the producers of a decode batch write: a
+// TT: 16-row tiles of X.  SRC: X comes as [part][K / 8][T][8] (OCTETS, the layout the producers of a decode batch write: a
 // fragment load is then four runs of 256 bytes instead of sixteen of 64, 2 us less per launch at 32 rows and 4 us at
-// 64), else row-major.  grid: ks * row groups, block b takes K slab b % ks of row group b / ks.
-template <int TT, bool OCT>
+// 64), as row-major images (ROWS), or as the float rows themselves (FLOATS), multiplied by the gain g and split here, with the
+// sums of squares of each wave's share in ss_part[row][slab][wave] for the kernel that adds the slabs: as many bytes as two
+// images, and no pass in front that writes them.  grid: ks * row groups, block b takes K slab b % ks of row group b / ks.
+enum SkinnySource { SK_ROWS, SK_OCTETS, SK_FLOATS };
+struct FloatRows { const float *x, *g; float *ss_part; };
+template <int TT, SkinnySource SRC>
 __global__ __launch_bounds__(64 * SK_WAVES, 2) void k_gemm_skinny(const bf16_t *__restrict__ W, const bf16_t *__restrict__ xhi,
                                                                   const bf16_t *__restrict__ xlo, int T, int n_rows, int K,
-                                                                  int ks, float *__restrict__ partial) {
+                                                                  int ks, float *__restrict__ partial, FloatRows fr) {
     constexpr int STEPS = sk_steps(TT), ROWB = sk_slab(TT) * 2;      // ROWB: bytes of LDS per row of a stage
     constexpr int STAGE = 16 * ROWB, S = TT > 2 ? 3 : 2;             // 2 stages of 64 KB, or 3 of 32 KB
     constexpr int IPR = ROWB / 1024, P = 2 * IPR;                    // copy instructions per row; per wave and stage
@@ -201,7 +205,8 @@ __global__ __launch_bounds__(64 * SK_WAVES, 2) void k_gemm_skinny(const bf16_t *
     };
     // X fragments: lane (row l16, k group kg) holds 8 consecutive k of each 32-wide step; rows past T are never stored.
     // Requested ahead of W (loads return in order: behind it they cost 5 us more)
-    bf16x8 xf[TT][2][STEPS];
+    u32x4 xf[TT][2][STEPS];      // FLOATS: the eight floats of a fragment until they are split
+    float4 gain[SRC == SK_FLOATS ? STEPS : 1][2];
 #pragma unroll
     for (int tt = 0; tt < TT; tt++)
 #pragma unroll
@@ -209,8 +214,13 @@ __global__ __launch_bounds__(64 * SK_WAVES, 2) void k_gemm_skinny(const bf16_t *
 #pragma unroll
             for (int s = 0; s < STEPS; s++) {
                 const int t = min(tt * 16 + l16, T - 1), k = k0 + (s0 + min(s, max(ns - 1, 0))) * 32 + kg * 8;
-                const bf16_t *src = (part ? xlo : xhi) + (OCT ? ((int64_t)(k >> 3) * T + t) * 8 : (int64_t)t * K + k);
-                xf[tt][part][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(src));
+                if constexpr (SRC == SK_FLOATS) {
+                    xf[tt][part][s] = *reinterpret_cast<const u32x4 *>(fr.x + (int64_t)t * K + k + 4 * part);
+                    if (tt == 0 && fr.g) gain[s][part] = *reinterpret_cast<const float4 *>(fr.g + k + 4 * part);
+                } else {
+                    const bf16_t *src = (part ? xlo : xhi) + (SRC == SK_OCTETS ? ((int64_t)(k >> 3) * T + t) * 8 : (int64_t)t * K + k);
+                    xf[tt][part][s] = *reinterpret_cast<const u32x4 *>(src);
+                }
             }
 
     __builtin_amdgcn_sched_barrier(0);
@@ -225,6 +235,31 @@ __global__ __launch_bounds__(64 * SK_WAVES, 2) void k_gemm_skinny(const bf16_t *
         for (int part = 0; part < 2; part++)
 #pragma unroll
             for (int s = 0; s < STEPS; s++) asm volatile("" : "+v"(xf[tt][part][s]));
+    if constexpr (SRC == SK_FLOATS) {
+#pragma unroll
+        for (int tt = 0; tt < TT; tt++) {
+            float ss = 0.f;
+#pragma unroll
+            for (int s = 0; s < STEPS; s++) {
+                float4 a = __builtin_bit_cast(float4, xf[tt][0][s]), b = __builtin_bit_cast(float4, xf[tt][1][s]);
+                if (fr.g) {
+                    if (s < ns) ss = add_squares(add_squares(ss, a), b);
+                    a = scale4(a, 1.f, gain[s][0]);
+                    b = scale4(b, 1.f, gain[s][1]);
+                }
+                uint32_t l0, l1, l2, l3;
+                const uint32_t h0 = split2_bf16(a.x, a.y, l0), h1 = split2_bf16(a.z, a.w, l1), h2 = split2_bf16(b.x, b.y, l2), h3 = split2_bf16(b.z, b.w, l3);
+                xf[tt][0][s] = (u32x4){h0, h1, h2, h3};
+                xf[tt][1][s] = (u32x4){l0, l1, l2, l3};
+            }
+            if (fr.g && grp == 0) {      // one group of each slab: the sums of squares of this wave's share
+                ss += __shfl_xor(ss, 16, WAVE);
+                ss += __shfl_xor(ss, 32, WAVE);
+                const int t = tt * 16 + l16;
+                if (kg == 0 && t < T) fr.ss_part[((int64_t)t * ks + kz) * SK_WAVES + wave] = ss;
+            }
+        }
+    }
 
     // adds the eight waves' sums of a tile (in LDS since the barrier before) and stores them
     auto finish = [&](int tile) {
@@ -280,7 +315,7 @@ __global__ __launch_bounds__(64 * SK_WAVES, 2) void k_gemm_skinny(const bf16_t *
                 for (int tt = 0; tt < TT; tt++)
 #pragma unroll
                     for (int part = 0; part < 2; part++)
-                        acc[tt][part] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[s]), xf[tt][part][s], acc[tt][part], 0, 0, 0);
+                        acc[tt][part] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[s]), __builtin_bit_cast(bf16x8, xf[tt][part][s]), acc[tt][part], 0, 0, 0);
         // lane (l16, kg) holds W rows 4 kg .. + 4 of the tile for X row l16
 #pragma unroll
         for (int tt = 0; tt < TT; tt++) {
@@ -292,17 +327,27 @@ __global__ __launch_bounds__(64 * SK_WAVES, 2) void k_gemm_skinny(const bf16_t *
     finish(n_tiles - 1);
 }
 
-// Adds the ks K-slab partial sums in slab order and applies the epilogue.  One thread per output.
+// Adds the ks K-slab partial sums in slab order and applies the epilogue.  One thread per output.  norm.ss_part: the sums are
+// scaled by the row's 1 / rms first, whose square sum comes in n parts.
+struct RowNorm { const float *ss_part; int n, K; float eps; };
 template <int EPI>
 __global__ __launch_bounds__(256) void k_splitk_reduce(const float *__restrict__ partial, int T, int N, int ks,
-                                                       float *__restrict__ y, ld::OperandImage out) {
+                                                       float *__restrict__ y, ld::OperandImage out, RowNorm norm) {
     constexpr int WR = (EPI == ld::GEMM_SWIGLU) ? 2 : 1;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= (int64_t)T * N) return;
     const int t = (int)(idx / N), n = (int)(idx % N);
     const float *p0 = partial + (int64_t)t * (WR * N) + n;
-    const float a = slab_sum(p0, (int64_t)T * (WR * N), ks, 0.f);
-    const float b = WR == 2 ? slab_sum(p0 + N, (int64_t)T * (WR * N), ks, 0.f) : 0.f;
+    float a = slab_sum(p0, (int64_t)T * (WR * N), ks, 0.f);
+    float b = WR == 2 ? slab_sum(p0 + N, (int64_t)T * (WR * N), ks, 0.f) : 0.f;
+    if (norm.ss_part) {
+        const float4 *ss = reinterpret_cast<const float4 *>(norm.ss_part + (int64_t)t * norm.n);      // n is a multiple of 8
+        float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int i = 0; i < norm.n / 4; i++) { const float4 v = ss[i]; sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w; }
+        const float rstd = 1.0f / sqrtf((sum.x + sum.y + sum.z + sum.w) / norm.K + norm.eps);
+        a = mul_rounded(a, rstd);
+        b = mul_rounded(b, rstd);
+    }
     float *dst = y + (int64_t)t * N + n;
     if constexpr (EPI == ld::GEMM_STORE) *dst = a;
     else if constexpr (EPI == ld::GEMM_ADD) *dst += a;
@@ -574,17 +619,18 @@ void launch_norm_split(const float *x, const float *g, float eps, int T, int K, 
 
 int skinny_slabs(int T, int K) { return skinny_split(T, K); }
 
-void launch_gemm_skinny(const uint16_t *W, const uint16_t *xhi, const uint16_t *xlo, int T, int n_rows, int K,
-                        float *partial, hipStream_t s, bool octets) {
+static void launch_skinny(const uint16_t *W, const uint16_t *xhi, const uint16_t *xlo, int T, int n_rows, int K, float *partial, hipStream_t s,
+                          SkinnySource src, const FloatRows &fr) {
     const int ks = skinny_split(T, K);
     static const int n_cu = cu_count();
     // one workgroup per CU; fewer where a row group would get less than a tile
     const int n_grp = std::max(1, std::min(n_cu / ks, (n_rows + 15) / 16));
     const dim3 grid(n_grp * ks), block(64 * SK_WAVES);
-#define LD_SKINNY(TT_)                                                                                                 \
-    do {                                                                                                               \
-        if (octets) LD_LAUNCH((k_gemm_skinny<TT_, true>), grid, block, 0, s, W, xhi, xlo, T, n_rows, K, ks, partial);  \
-        else LD_LAUNCH((k_gemm_skinny<TT_, false>), grid, block, 0, s, W, xhi, xlo, T, n_rows, K, ks, partial);        \
+#define LD_SKINNY(TT_)                                                                                                              \
+    do {                                                                                                                            \
+        if (src == SK_FLOATS) LD_LAUNCH((k_gemm_skinny<TT_, SK_FLOATS>), grid, block, 0, s, W, xhi, xlo, T, n_rows, K, ks, partial, fr);       \
+        else if (src == SK_OCTETS) LD_LAUNCH((k_gemm_skinny<TT_, SK_OCTETS>), grid, block, 0, s, W, xhi, xlo, T, n_rows, K, ks, partial, fr);  \
+        else LD_LAUNCH((k_gemm_skinny<TT_, SK_ROWS>), grid, block, 0, s, W, xhi, xlo, T, n_rows, K, ks, partial, fr);                \
     } while (0)
     switch (skinny_tiles(T)) {
         case 1: LD_SKINNY(1); break;
@@ -593,6 +639,32 @@ void launch_gemm_skinny(const uint16_t *W, const uint16_t *xhi, const uint16_t *
         default: LD_SKINNY(4);
     }
 #undef LD_SKINNY
+}
+void launch_gemm_skinny(const uint16_t *W, const uint16_t *xhi, const uint16_t *xlo, int T, int n_rows, int K,
+                        float *partial, hipStream_t s, bool octets) {
+    launch_skinny(W, xhi, xlo, T, n_rows, K, partial, s, octets ? SK_OCTETS : SK_ROWS, FloatRows{});
+}
+
+static void launch_reduce(const float *partial, int T, int N, int ks, int epi, float *y, const OperandImage &out, const RowNorm &norm, hipStream_t s) {
+    const dim3 grid((unsigned)(((int64_t)T * N + 255) / 256)), block(256);
+    if (epi == GEMM_STORE) LD_LAUNCH((k_splitk_reduce<GEMM_STORE>), grid, block, 0, s, partial, T, N, ks, y, out, norm);
+    else if (epi == GEMM_ADD) LD_LAUNCH((k_splitk_reduce<GEMM_ADD>), grid, block, 0, s, partial, T, N, ks, y, out, norm);
+    else LD_LAUNCH((k_splitk_reduce<GEMM_SWIGLU>), grid, block, 0, s, partial, T, N, ks, y, out, norm);
+}
+
+// The float rows are read in pieces of 32 bytes, twice the requests of octets: ahead of the pass they replace (4.8 us) while
+// that pass is long or the rows are few.  Calls through images -> from floats: 2 rows 4096 x 4096 16.2 -> 13.3 us, 4096 x 11008
+// 26.0 -> 21.8; 16 rows 16.4 -> 15.6, 27.7 -> 24.9; 20: 22016 x 4096 41.0 -> 40.2, 5120 x 13824 38.5 -> 34.4; 33: 4096 x 4096 19.4 -> 17.7;
+// 64: 5120 x 13824 49.1 -> 47.1; but 32: 4096 x 4096 18.2 -> 20.1, 22016 x 4096 42.4 -> 43.8, 48: 20.1 -> 20.5, 64: 22.2 -> 23.3.
+bool gemm_takes_floats(int T, int K) { return gemm_takes_octets(T) && (K > 8192 || T <= 20 || (T > 32 && T <= 40)); }
+
+void launch_gemm_floats(const uint16_t *W, const float *x, const float *g, float eps, int T, int N, int K, int epi, float *y, void *scratch,
+                        hipStream_t s) {
+    // the scratch of the image form: its images' place holds the sums of squares (at most K / 128 a row)
+    float *ss = (float *)scratch, *partial = (float *)((char *)scratch + gemm_split_bytes(T, K));
+    const int ks = skinny_split(T, K);
+    launch_skinny(W, nullptr, nullptr, T, N * (epi == GEMM_SWIGLU ? 2 : 1), K, partial, s, SK_FLOATS, {x, g, ss});
+    launch_reduce(partial, T, N, ks, epi, y, {}, {g ? ss : nullptr, ks * SK_WAVES, K, eps}, s);
 }
 
 // The big-tile kernel over all output columns (+ the split-K reduction).
@@ -605,10 +677,7 @@ static void launch_tiles(const uint16_t *W, const bf16_t *hi, const bf16_t *lo, 
     else if (f16) launch_tile_widen(p.bm, p.bn, l);
     else launch_tile_two(p.bm, p.bn, l);
     if (p.ks <= 1 || !reduce) return;
-    const int rgrid = (int)(((int64_t)T * N + 255) / 256);
-    if (epi == GEMM_STORE) LD_LAUNCH((k_splitk_reduce<GEMM_STORE>), dim3(rgrid), dim3(256), 0, s, partial, T, N, p.ks, y, out);
-    else if (epi == GEMM_ADD) LD_LAUNCH((k_splitk_reduce<GEMM_ADD>), dim3(rgrid), dim3(256), 0, s, partial, T, N, p.ks, y, out);
-    else LD_LAUNCH((k_splitk_reduce<GEMM_SWIGLU>), dim3(rgrid), dim3(256), 0, s, partial, T, N, p.ks, y, out);
+    launch_reduce(partial, T, N, p.ks, epi, y, out, {}, s);
 }
 
 // Where the rows of a product go next.
@@ -644,11 +713,8 @@ static void gemm_rows(const uint16_t *W, const bf16_t *hi, const bf16_t *lo, int
     if (T <= SKINNY_MAX_ROWS) {
         const int ks = split_factor(T, N, K, epi), n_rows = N * (epi == GEMM_SWIGLU ? 2 : 1);
         launch_gemm_skinny(W, hi, lo, T, n_rows, K, partial, s, octets);
-        const int rgrid = (int)(((int64_t)T * N + 255) / 256);
         if (chain_add) finish(ks);     // the skinny kernel writes partial sums even for one slab
-        else if (epi == GEMM_STORE) LD_LAUNCH((k_splitk_reduce<GEMM_STORE>), dim3(rgrid), dim3(256), 0, s, partial, T, N, ks, y, out);
-        else if (epi == GEMM_ADD) LD_LAUNCH((k_splitk_reduce<GEMM_ADD>), dim3(rgrid), dim3(256), 0, s, partial, T, N, ks, y, out);
-        else LD_LAUNCH((k_splitk_reduce<GEMM_SWIGLU>), dim3(rgrid), dim3(256), 0, s, partial, T, N, ks, y, out);
+        else launch_reduce(partial, T, N, ks, epi, y, out, {}, s);
         return;
     }
     bool ignored = false;

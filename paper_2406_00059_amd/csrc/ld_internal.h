@@ -72,10 +72,12 @@ ld_status paged_attention_split(const float *q, int q_stride, const void *pool_l
                                 size_t scratch_bytes, hipStream_t stream, int image_rows = 0, bool octets = false, int f16_rows = 0,
                                 int *f16_flag = nullptr);
 
-// ldk_linear for the rows of an engine pass: f16_flag and W_f16 as in launch_gemm (nullptr: ldk_linear itself).
+// ldk_linear for the rows of an engine pass: f16_flag and W_f16 as in launch_gemm (nullptr: none).  own_norm: a small batch may be
+// normalised inside the product (ldk_linear itself); the rows of a pass are normalised ahead of it, with the bits of the kernels
+// that finish a residual product.
 ld_status linear_pass(const void *W, int32_t dtype, const float *x, const float *g, float eps, int32_t T, int32_t N,
                       int32_t K, int32_t epilogue, float *y, void *scratch, size_t scratch_bytes, void *stream,
-                      int *f16_flag, const void *W_f16 = nullptr);
+                      int *f16_flag, const void *W_f16 = nullptr, bool own_norm = false);
 // Integer value of an environment variable (a tuning knob), dflt when unset.
 int env_flag(const char *name, int dflt);
 

@@ -612,7 +612,7 @@ size_t ldk_linear_scratch_bytes(int32_t T, int32_t N, int32_t K, int32_t epilogu
 
 ld_status ldk_linear(const void *W, int32_t dtype, const float *x, const float *g, float eps, int32_t T, int32_t N,
                      int32_t K, int32_t epilogue, float *y, void *scratch, size_t scratch_bytes, void *stream) {
-    return ld::linear_pass(W, dtype, x, g, eps, T, N, K, epilogue, y, scratch, scratch_bytes, stream, nullptr);
+    return ld::linear_pass(W, dtype, x, g, eps, T, N, K, epilogue, y, scratch, scratch_bytes, stream, nullptr, nullptr, true);
 }
 
 ld_status ldk_linear_f16(const void *W, const void *W_f16, const float *x, const float *g, float eps, int32_t T,
@@ -622,7 +622,7 @@ ld_status ldk_linear_f16(const void *W, const void *W_f16, const float *x, const
     if (!W_f16 && T > 0 && W && N > 0 && K > 0 && K % 8 == 0)   // an image was checked when it was made
         ld::launch_weight_range_check((const uint16_t *)W, (int64_t)N * (epilogue == LDK_SWIGLU ? 2 : 1) * K, overflow,
                                       (hipStream_t)stream);
-    return ld::linear_pass(W, LD_BF16, x, g, eps, T, N, K, epilogue, y, scratch, scratch_bytes, stream, overflow, W_f16);
+    return ld::linear_pass(W, LD_BF16, x, g, eps, T, N, K, epilogue, y, scratch, scratch_bytes, stream, overflow, W_f16, true);
 }
 
 ld_status ldk_weights_to_f16(const void *W, int64_t n, void *out, int32_t *overflow, void *stream) {
@@ -641,7 +641,7 @@ int ld::env_flag(const char *name, int dflt) {
 
 ld_status ld::linear_pass(const void *W, int32_t dtype, const float *x, const float *g, float eps, int32_t T, int32_t N,
                           int32_t K, int32_t epilogue, float *y, void *scratch, size_t scratch_bytes, void *stream,
-                          int *f16_flag, const void *W_f16) {
+                          int *f16_flag, const void *W_f16, bool own_norm) {
     if (T == 0) return LD_OK;   // nothing to do: pointers of empty buffers may be null
     if (!W || !x || !y || T < 0 || N <= 0 || K <= 0 || K % 8 || epilogue < 0 || epilogue > 2)
         return ld::fail(LD_E_INVAL, "ldk_linear: bad argument (K must be a multiple of 8)");
@@ -651,6 +651,10 @@ ld_status ld::linear_pass(const void *W, int32_t dtype, const float *x, const fl
         return launched("k_gemv1");
     }
     if (dtype == LD_BF16 && scratch && ld::gemm_supported(T, N, K) && scratch_bytes >= ld::gemm_scratch_bytes(T, N, K, epilogue)) {
+        if ((!g || own_norm) && ld::gemm_takes_floats(T, K)) {
+            ld::launch_gemm_floats((const bf16_t *)W, x, g, eps, T, N, K, epilogue, y, scratch, s);
+            return launched("the small-batch product");
+        }
         const bool octets = ld::gemm_takes_octets(T);
         ld::launch_norm_split(x, g, eps, T, K, (uint16_t *)scratch, s, octets, f16_flag ? ld::gemm_f16_rows(T, N, K, epilogue) : 0, f16_flag);
         ld::launch_gemm((const bf16_t *)W, (uint16_t *)scratch, T, N, K, epilogue, y, s, nullptr, f16_flag, (const uint16_t *)W_f16, octets);

@@ -431,6 +431,32 @@ def test_linear_small_batch_edges(T, N, K):
     assert ((y.double() - ref).abs() <= 2.0 ** -16 * mag).all()
 
 
+@pytest.mark.parametrize("T", [2, 16, 17, 20, 21, 32, 33, 40, 41, 64])
+@pytest.mark.parametrize("N,K,epi", [(5, 128, "store"), (301, 4096, "swiglu"), (66, 5120, "add"), (302, 11008, "add"), (7, 8320, "swiglu")])
+def test_linear_small_batch_normalises_float_rows(T, N, K, epi):
+    """The small-batch product with a norm, on both sides of every line between float rows (split and squared in the product, the
+    scale applied to the finished sums) and images (a pass in front): rows of very different size, so that a scale or a sum of
+    squares of another row shows.  Against float64: the bound of test_linear_small_batch_edges on the normalised row, and
+    2^-20 for the sum of squares and its root."""
+    code = {"store": ld.LDK_STORE, "add": ld.LDK_ADD, "swiglu": ld.LDK_SWIGLU}[epi]
+    rows = 2 * N if epi == "swiglu" else N
+    W = _mat(37, K, rows, K, "bf16").to(DEV); g = gen.normal(37, 3, (K,), std=0.1, mean=1.0).to(DEV)
+    x = gen.normal(37, 2, (T, K), device=DEV) * (10.0 ** (torch.arange(T, device=DEV) % 5 - 2))[:, None]
+    y0 = gen.normal(37, 4, (T, N), device=DEV)
+    scratch = torch.empty(ld.ldk_linear_scratch_bytes(T, N, K, code), dtype=torch.uint8, device=DEV)
+    y = y0.clone()
+    ld.ldk_linear(W, x, y, code, g=g, eps=1e-5, scratch=scratch)
+    xn = x.double() / torch.sqrt((x.double() ** 2).mean(1, keepdim=True) + 1e-5) * g.double()
+    full, mag = xn @ W.double().t(), xn.abs() @ W.double().abs().t()
+    a, tol = full[:, :N], 2.0 ** -16 + 2.0 ** -20
+    if epi == "swiglu":      # |d(silu(a) b)| <= 1.1 |b| |da| + |silu(a)| |db|
+        ref = torch.nn.functional.silu(a) * full[:, N:]
+        bound = tol * (1.1 * full[:, N:].abs() * mag[:, :N] + torch.nn.functional.silu(a).abs() * mag[:, N:]) + 1e-6 * ref.abs() + 1e-7
+    else:
+        ref, bound = a + (y0.double() if epi == "add" else 0), tol * mag[:, :N] + 1e-6
+    assert ((y.double() - ref).abs() <= bound).all()
+
+
 @pytest.mark.parametrize("plan", ["2,128,1", "2,128,3", "2,256,1", "2,256,2", "192,256,1", "192,256,4"])
 @pytest.mark.parametrize("epi", ["store", "add", "swiglu"])
 def test_linear_big_tile_every_plan(plan, epi, monkeypatch, capfd):
