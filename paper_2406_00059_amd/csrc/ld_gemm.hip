@@ -15,6 +15,7 @@
 #include "ld_gemm.h"
 #include "ld_gemm_tile.h"
 #include "ld_device.h"
+#include "ld_rope.h"
 #include "ld_internal.h"
 #include <algorithm>
 #include <cstdio>
@@ -409,37 +410,6 @@ __global__ __launch_bounds__(256) void k_reduce_add_norm_split(const float *__re
     }
 }
 
-// Rows of the q-k-v projection: finishes them (split-K slab sums in slab order; ks 0: they are already in y) and does what
-// the rotate-and-append pass does, one wave per (head, row): q heads rotated into y, rotated k heads and v heads into the
-// paged pool.  Row t of this launch is row row0 + t of the pass.
-__global__ __launch_bounds__(64) void k_reduce_rope_kv(const float *__restrict__ partial, int T, int N, int ks,
-                                                       float *__restrict__ y, ld::RopeKvArgs rk, int row0) {
-    const int t = blockIdx.y, hh = blockIdx.x, i = threadIdx.x, half = rk.hd / 2, hd = rk.hd;
-    if (i >= half) return;
-    const float *prow = partial + (int64_t)t * N;
-    float *row = y + (int64_t)t * N;
-    const int64_t slab = (int64_t)T * N;
-    auto val = [&](int col) { return ks ? slab_sum(prow + col, slab, ks, 0.f) : row[col]; };
-    const float2 c = rk.cos_sin[(int64_t)(row0 + t) * half + i];
-    if (hh < rk.H) {
-        const float2 r = rope_rotate(val(hh * hd + i), val(hh * hd + i + half), c);
-        row[hh * hd + i] = r.x;
-        row[hh * hd + i + half] = r.y;
-        return;
-    }
-    const int j = hh - rk.H, kc = (rk.H + j) * hd, vc = (rk.H + rk.Hkv + j) * hd;
-    const float2 r = rope_rotate(val(kc + i), val(kc + i + half), c);
-    const float va = val(vc + i), vb = val(vc + i + half);
-    const int p = rk.pos[row0 + t];
-    const int64_t phys = rk.table[(int64_t)rk.seq_slot[row0 + t] * rk.table_stride + (p >> 4)];
-    bf16_t *blk = rk.pool + phys * kv_block_elems(rk.Hkv, hd);
-    const int slot = p & 15;
-    blk[kv_k_offset(hd, j, slot, i)] = f32_to_bf16(r.x);
-    blk[kv_k_offset(hd, j, slot, i + half)] = f32_to_bf16(r.y);
-    blk[kv_v_offset(rk.Hkv, hd, j, slot, i)] = f32_to_bf16(va);
-    blk[kv_v_offset(rk.Hkv, hd, j, slot, i + half)] = f32_to_bf16(vb);
-}
-
 int env_int(const char *name, int dflt) {
     const char *v = getenv(name);
     return v ? atoi(v) : dflt;
@@ -680,6 +650,12 @@ static void launch_tiles(const uint16_t *W, const bf16_t *hi, const bf16_t *lo, 
     launch_reduce(partial, T, N, p.ks, epi, y, out, {}, s);
 }
 
+static void launch_rope_rows(const float *partial, int T, int ks, float *y, const RopeKvArgs &rk, int row0, hipStream_t s) {
+    const dim3 grid(rk.H + rk.Hkv, (T + 15) / 16);
+    if (rk.hd == 128) LD_LAUNCH((k_rope_rows<128, bf16_t>), grid, dim3(256), 0, s, partial, T, ks, y, rk, rk.pool, row0, rk.store_kv && ks > 0);
+    else LD_LAUNCH((k_rope_rows<64, bf16_t>), grid, dim3(128), 0, s, partial, T, ks, y, rk, rk.pool, row0, rk.store_kv && ks > 0);
+}
+
 // Where the rows of a product go next.
 struct RowsNext { const float *g; float eps; OperandImage out; const RopeKvArgs *rope; int row0; };
 
@@ -703,7 +679,7 @@ static void gemm_rows(const uint16_t *W, const bf16_t *hi, const bf16_t *lo, int
     const OperandImage out = nx && epi == GEMM_SWIGLU ? nx->out : OperandImage{};
     auto finish = [&](int ks) {      // ks: slabs whose partial sums the finishing kernel still has to add
         if (chain_rope) {
-            LD_LAUNCH(k_reduce_rope_kv, dim3(nx->rope->H + nx->rope->Hkv, T), dim3(64), 0, s, partial, T, N, ks, y, *nx->rope, nx->row0);
+            launch_rope_rows(partial, T, ks, y, *nx->rope, nx->row0, s);
         } else if (N <= 5 * 1024) {
             LD_LAUNCH((k_reduce_add_norm_split<5>), dim3(T), dim3(256), 0, s, partial, T, N, ks, y, nx->g, nx->eps, nx->out);
         } else {

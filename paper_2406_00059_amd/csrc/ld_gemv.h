@@ -16,6 +16,7 @@ struct RopeKvArgs {
     int32_t table_stride;
     uint16_t *pool;             // one layer's slice [block][2][Hkv][16][hd], bf16
     int32_t H, Hkv, hd;
+    bool store_kv = false;      // rows of a product: the k and v columns are stored as they are, too
 };
 
 // True if the slab kernel handles this shape (bf16, one input row).

@@ -4,6 +4,7 @@
 // matrices and the KV pool are float32 or bf16.  bf16 -> float32 widening is exact.
 #include "ld_internal.h"
 #include "ld_device.h"
+#include "ld_rope.h"
 #include "ld_gemv.h"
 #include "ld_gemm.h"
 #include "ld_attn_prefill.h"
@@ -179,38 +180,6 @@ __global__ __launch_bounds__(256) void k_begin(const WT *__restrict__ E, const i
     const int i = (t - p.T - p.n_ranges) * 256 + threadIdx.x;
     if (i < p.meta_ints) p.meta[i] = p.meta_host[i];
     if (i == 0 && p.clear_flag) *p.clear_flag = 0;
-}
-
-template <typename KVT>
-__global__ void k_rope_kv_write(float *__restrict__ qkv, const float2 *__restrict__ cs,
-                                const int32_t *__restrict__ pos, const int32_t *__restrict__ seq_slot,
-                                const int32_t *__restrict__ table, int table_stride, KVT *__restrict__ pool,
-                                int H, int Hkv, int hd) {
-    const int t = blockIdx.y, hh = blockIdx.x, i = threadIdx.x, half = hd / 2;
-    if (i >= half) return;
-    const int nqkv = (H + 2 * Hkv) * hd;
-    const float2 c = cs[(int64_t)t * half + i];
-    float *row = qkv + (int64_t)t * nqkv;
-    if (hh < H) {
-        float *u = row + hh * hd;
-        const float2 r = rope_rotate(u[i], u[i + half], c);
-        u[i] = r.x;
-        u[i + half] = r.y;
-        return;
-    }
-    const int j = hh - H;
-    const float *ku = row + (H + j) * hd;
-    const float *vu = row + (H + Hkv + j) * hd;
-    const float a = ku[i], b = ku[i + half];
-    const int p = pos[t];
-    const int64_t phys = table[(int64_t)seq_slot[t] * table_stride + (p >> 4)];
-    KVT *blk = pool + phys * kv_block_elems(Hkv, hd);
-    const int slot = p & 15;
-    const float2 r = rope_rotate(a, b, c);
-    store_elem(blk + kv_k_offset(hd, j, slot, i), r.x);
-    store_elem(blk + kv_k_offset(hd, j, slot, i + half), r.y);
-    store_elem(blk + kv_v_offset(Hkv, hd, j, slot, i), vu[i]);
-    store_elem(blk + kv_v_offset(Hkv, hd, j, slot, i + half), vu[i + half]);
 }
 
 // ---------------------------------------------------------------- paged decode attention
@@ -689,16 +658,16 @@ ld_status ldk_rope_kv_write(float *qkv, const float *cos_sin, const int32_t *pos
         (hd != 64 && hd != 128))
         return ld::fail(LD_E_INVAL, "ldk_rope_kv_write: bad argument");
     if (T == 0) return LD_OK;
-    dim3 grid(H + Hkv, T), block(64);
+    if (dtype != LD_BF16 && dtype != LD_F32) return ld::fail(LD_E_INVAL, "ldk_rope_kv_write: bad dtype");
+    const dim3 grid(H + Hkv, (T + 15) / 16), block(2 * hd);
     hipStream_t s = (hipStream_t)stream;
-    if (dtype == LD_BF16)
-        LD_LAUNCH(k_rope_kv_write<bf16_t>, grid, block, 0, s, qkv, (const float2 *)cos_sin, pos, seq_slot,
-                           table, table_stride, (bf16_t *)pool_layer, H, Hkv, hd);
-    else if (dtype == LD_F32)
-        LD_LAUNCH(k_rope_kv_write<float>, grid, block, 0, s, qkv, (const float2 *)cos_sin, pos, seq_slot,
-                           table, table_stride, (float *)pool_layer, H, Hkv, hd);
-    else return ld::fail(LD_E_INVAL, "ldk_rope_kv_write: bad dtype");
-    return launched("k_rope_kv_write");
+    const ld::RopeKvArgs rk{(const float2 *)cos_sin, pos, seq_slot, table, table_stride, nullptr, H, Hkv, hd};
+#define LD_ROPE(HD_, KVT_) LD_LAUNCH((k_rope_rows<HD_, KVT_>), grid, block, 0, s, nullptr, T, 0, qkv, rk, (KVT_ *)pool_layer, 0, false)
+    if (dtype == LD_BF16) { if (hd == 128) LD_ROPE(128, bf16_t); else LD_ROPE(64, bf16_t); }
+    else if (hd == 128) LD_ROPE(128, float);
+    else LD_ROPE(64, float);
+#undef LD_ROPE
+    return launched("k_rope_rows");
 }
 
 ld_status ldk_qkv_rope(const void *W, int32_t dtype, const float *x, const float *g, float eps, float *qkv,
@@ -714,6 +683,14 @@ ld_status ldk_qkv_rope(const void *W, int32_t dtype, const float *x, const float
         ld::RopeKvArgs rk{(const float2 *)cos_sin, pos, seq_slot, table, table_stride, (bf16_t *)pool_layer, H, Hkv, hd};
         ld::launch_gemv1((const bf16_t *)W, x, g, eps, N, K, ld::GEMV_ROPE_KV, qkv, &rk, (hipStream_t)stream);
         return launched("k_gemv1 (rope + cache append)");
+    }
+    // more than 64 rows on the matrix cores: the kernel that rotates and appends also adds the product's slabs
+    if (dtype == LD_BF16 && !ld::gemm_takes_octets(T) && scratch && ld::gemm_supported(T, N, K) && scratch_bytes >= ld::gemm_scratch_bytes(T, N, K, LDK_STORE)) {
+        const ld::RopeKvArgs rk{(const float2 *)cos_sin, pos, seq_slot, table, table_stride, (bf16_t *)pool_layer, H, Hkv, hd, true};
+        const ld::GemmNext next{nullptr, 0.f, nullptr, &rk};
+        ld::launch_norm_split(x, g, eps, T, K, (uint16_t *)scratch, (hipStream_t)stream);
+        ld::launch_gemm((const bf16_t *)W, (uint16_t *)scratch, T, N, K, LDK_STORE, qkv, (hipStream_t)stream, &next);
+        return launched("the matrix-core product (rope + cache append)");
     }
     ld_status rc = ldk_linear(W, dtype, x, g, eps, T, N, K, LDK_STORE, qkv, scratch, scratch_bytes, stream);
     if (rc != LD_OK) return rc;

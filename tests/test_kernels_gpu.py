@@ -431,6 +431,45 @@ def test_linear_small_batch_edges(T, N, K):
     assert ((y.double() - ref).abs() <= 2.0 ** -16 * mag).all()
 
 
+@pytest.mark.parametrize("H,Hkv,hd", [(2, 1, 128), (3, 3, 64)])
+@pytest.mark.parametrize("T", [64, 65, 79, 257, 300])
+def test_qkv_rope_equals_product_then_rotation(T, H, Hkv, hd):
+    """ldk_qkv_rope on many rows (rotation, cache append and the sum of the product's slabs in one kernel, 16 rows a workgroup, from 65
+    rows on) against ldk_linear followed by ldk_rope_kv_write: the same bits in the whole q-k-v buffer and in the whole pool.  Rows of
+    two sequences at consecutive positions that start inside a block, single rows of a third, and a ragged last group of rows.
+    The rows of the pool also against float64: one rounding to bf16 of a sum within 2^-16 of its terms."""
+    K, N = 1152, (H + 2 * Hkv) * hd
+    W = _mat(47, hd, N, K, "bf16").to(DEV); x = gen.normal(47, 2, (T, K), device=DEV)
+    n0 = T // 2
+    pos = torch.tensor([5 + i for i in range(n0)] + [16 + i for i in range(T - n0 - 1)] + [333], dtype=torch.int32, device=DEV)
+    slot = torch.tensor([0] * n0 + [1] * (T - n0 - 1) + [2], dtype=torch.int32, device=DEV)
+    table = torch.randperm(3 * 24, generator=torch.Generator().manual_seed(T)).to(torch.int32).view(3, 24).to(DEV)
+    cs = torch.empty(T, hd, device=DEV)
+    ld.ldk_rope_table(pos, hd, 10000.0, cs)
+    scratch = torch.empty(ld.ldk_linear_scratch_bytes(T, N, K, ld.LDK_STORE), dtype=torch.uint8, device=DEV)
+    pools = [torch.full((72, 2, Hkv, 16, hd), 3.0, dtype=torch.bfloat16, device=DEV) for _ in range(2)]
+    a, b = torch.full((T, N), float("nan"), device=DEV), torch.full((T, N), float("nan"), device=DEV)
+    ld.ldk_qkv_rope(W, x, a, cs, pos, slot, table, pools[0], H, Hkv, hd, None, 1e-5, scratch)
+    ld.ldk_linear(W, x, b, ld.LDK_STORE, scratch=scratch)
+    ld.ldk_rope_kv_write(b, cs, pos, slot, table, pools[1], H, Hkv, hd)
+    assert torch.equal(a, b) and torch.equal(pools[0], pools[1])
+    ref, mag = x.double() @ W.double().t(), x.double().abs() @ W.double().abs().t()
+    c = cs.view(T, hd // 2, 2).double()
+    phys = table[slot.long(), pos.long() // 16].long()
+    for j in range(Hkv):
+        k0, v0 = (H + j) * hd, (H + Hkv + j) * hd
+        u, v = ref[:, k0:k0 + hd // 2], ref[:, k0 + hd // 2:k0 + hd]
+        rot = torch.cat([u * c[..., 0] - v * c[..., 1], u * c[..., 1] + v * c[..., 0]], 1)
+        tol = 2.0 ** -16 * (mag[:, k0:k0 + hd // 2] + mag[:, k0 + hd // 2:k0 + hd]).repeat(1, 2)
+        got = pools[0][phys, 0, j, pos.long() % 16].double()
+        assert ((got - rot).abs() <= 2.0 ** -8 * rot.abs() + 2 * tol).all()
+        got = pools[0].view(72, 2, Hkv, hd, 16)[phys, 1, j, :, pos.long() % 16].double()
+        assert ((got - ref[:, v0:v0 + hd]).abs() <= 2.0 ** -8 * ref[:, v0:v0 + hd].abs() + 2 * 2.0 ** -16 * mag[:, v0:v0 + hd]).all()
+    written = torch.zeros(72, 16, dtype=torch.bool, device=DEV); written[phys, pos.long() % 16] = True
+    assert (pools[0].permute(0, 3, 1, 2, 4)[..., 0, :, :][~written] == 3.0).all()
+    assert (pools[0].view(72, 2, Hkv, hd, 16)[:, 1].permute(0, 3, 1, 2)[~written] == 3.0).all()
+
+
 @pytest.mark.parametrize("T", [2, 16, 17, 20, 21, 32, 33, 40, 41, 64])
 @pytest.mark.parametrize("N,K,epi", [(5, 128, "store"), (301, 4096, "swiglu"), (66, 5120, "add"), (302, 11008, "add"), (7, 8320, "swiglu")])
 def test_linear_small_batch_normalises_float_rows(T, N, K, epi):
