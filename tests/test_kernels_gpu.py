@@ -198,6 +198,21 @@ def test_paged_attention_edge_lengths(dtype, hd, H, Hkv):
         np.testing.assert_allclose(got[0, h], v0[h // (H // Hkv)], rtol=1e-5, atol=1e-7)
 
 
+@pytest.mark.parametrize("window", [0, 20])
+@pytest.mark.parametrize("dtype,hd,H,Hkv", [("bf16", 128, 2, 2), ("f32", 64, 4, 4), ("f32", 128, 2, 1), ("bf16", 64, 8, 2), ("f32", 64, 8, 1)])
+def test_paged_attention_of_one_chunk(dtype, hd, H, Hkv, window):
+    """Launches in which no row has more than one chunk (up to 64 positions; with many rows longer ones) finish their results
+    without a merge: every group size of the scalar kernel, and a scratch of NaN that such a launch does not look at."""
+    for lens in ([1, 2, 16, 17, 63, 64], [5] * 40 + [190, 191]):
+        table, pool, q = _attention_case(27, lens, H, Hkv, hd, dtype)
+        out = torch.full((len(lens), H, hd), float("nan"), device=DEV)
+        scratch = torch.full((ld.ldk_attention_scratch_bytes(len(lens), H, Hkv, hd, max(lens), window) // 4,), float("nan"), device=DEV)
+        ld.ldk_paged_attention(q, H * hd, device_pool(pool), table.to(DEV), torch.arange(len(lens), dtype=torch.int32, device=DEV),
+                               torch.tensor(lens, dtype=torch.int32, device=DEV), max(lens), H, Hkv, hd, out, scratch, window=window)
+        ref = _oracle_attention(table, pool, q, lens, Hkv, hd, window=window)
+        assert np.max(np.abs(out.cpu().numpy() - ref)) <= _attn_tol(dtype, hd, H, Hkv) * np.abs(ref).max() + 1e-6
+
+
 @pytest.mark.parametrize("dtype,hd", [("bf16", 128), ("f32", 64)])
 @pytest.mark.parametrize("chunks", [1, 2, 23, 24, 25, 47, 48, 49, 200, 257])
 def test_paged_attention_chunk_counts(dtype, hd, chunks):
