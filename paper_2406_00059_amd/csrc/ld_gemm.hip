@@ -524,7 +524,7 @@ static double nominal_us(int T, int N, int K, int wr) {
 }
 // And by a second set of nominal rates, those of four tiles in rounds of 256 workgroups (0.89 of a round at least for the last
 // one; K split in up to eight slabs at 0.48 us per MB of partial sums) against a stream at 5.2 TB/s and 10 us: between the two
-// sets lie 17 - 128 row counts below 2200 per shape.
+// sets lie up to 128 row counts below 2200 per shape.
 static double nominal_tiles_us(int T, int N, int K, int epi) {
     const struct { int bm, bn; bool swiglu; double us; } tiles[] = {{128, 256, true, 1.01}, {256, 160, false, 1.17}, {256, 192, true, 1.33}, {256, 256, true, 1.62}};
     const bool swi = epi == GEMM_SWIGLU;
