@@ -642,8 +642,9 @@ static void launch_reduce(const float *partial, int T, int N, int ks, int epi, f
 #undef LD_REDUCE
 }
 
-// The float rows are read in pieces of 32 bytes, twice the requests of octets: ahead of the pass they replace (4.8 us) while
-// that pass is long or the rows are few.  Calls through images -> from floats: 2 rows 4096 x 4096 16.2 -> 13.3 us, 4096 x 11008
+// The float rows take longer to arrive than octets do (rows a multiple of 4 KB apart come out of a few channels of the cache; with
+// 64 bytes of a row in a run and an exchange between lanes they take as long): ahead of the pass they replace (4.8 us) while that
+// pass is long or the rows are few.  Calls through images -> from floats: 2 rows 4096 x 4096 16.2 -> 13.3 us, 4096 x 11008
 // 26.0 -> 21.8; 16 rows 16.4 -> 15.6, 27.7 -> 24.9; 20: 22016 x 4096 41.0 -> 40.2, 5120 x 13824 38.5 -> 34.4; 33: 4096 x 4096 19.4 -> 17.7;
 // 64: 5120 x 13824 49.1 -> 47.1; but 32: 4096 x 4096 18.2 -> 20.1, 22016 x 4096 42.4 -> 43.8, 48: 20.1 -> 20.5, 64: 22.2 -> 23.3.
 bool gemm_takes_floats(int T, int K) { return gemm_takes_octets(T) && (K > 8192 || T <= 20 || (T > 32 && T <= 40)); }
