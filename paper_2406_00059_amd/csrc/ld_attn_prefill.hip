@@ -71,15 +71,15 @@ __device__ __forceinline__ uint32_t pack2_f16(float a, float b) {
     return __builtin_bit_cast(uint32_t, (f16x2){(_Float16)a, (_Float16)b});
 }
 // Eight bf16 numbers as fp16: exact where fp16 can hold the value (truncation below 2^-14, the largest finite
-// fp16 beyond +-65504: the caller looks for such values with `mag`, the running maximum of the magnitudes, which passes
-// over NaNs: those reach the result).
+// fp16 beyond +-65504: the caller looks for such values with `mag`, the running maximum of the magnitudes, one instruction a
+// pair.  It is NaN from the first NaN on).
 __device__ __forceinline__ u32x4 bf16x8_to_f16x8(const u32x4 &w, float &mag) {
     u32x4 h;
 #pragma unroll
     for (int i = 0; i < 4; i++) {
         const float a = __uint_as_float(w[i] << 16), b = __uint_as_float(w[i] & 0xffff0000u);
         h[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(a, b));
-        asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(mag) : "v"(a), "v"(b));
+        mag = __builtin_elementwise_maximum(__builtin_elementwise_maximum(mag, fabsf(a)), fabsf(b));
     }
     return h;
 }
@@ -401,13 +401,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
     }
     // the two halves of a query's scores were summed separately
     l += __shfl_xor(l, 32, WAVE);
-    if constexpr (F16) {      // a magnitude that fp16 cannot hold, or a NaN (they all reach l or o of the queries that see them)
-        float sum = l;
-#pragma unroll
-        for (int nt = 0; nt < 4; nt++)
-#pragma unroll
-            for (int i = 0; i < 16; i++) sum += o[nt][i];
-        if (out_of_range || mag > 65504.f || sum != sum) *f16_flag = 1;
+    if constexpr (F16) {
+        if (out_of_range || !(mag <= 65504.f)) *f16_flag = 1;      // a magnitude that fp16 cannot hold, or a NaN
     }
     if (!whole) {      // unnormalised share: [tile][row in tile][head][split][HD] and (m, l)
         if (q_valid) {

@@ -847,6 +847,26 @@ def test_prefill_attention_fp16_range_check(what, part, pos):
     assert int(flag.item()) == (what != 65280.0)
 
 
+@pytest.mark.parametrize("what", [float("nan"), float("inf"), -65536.0])
+@pytest.mark.parametrize("part", [0, 1], ids=["key", "value"])
+@pytest.mark.parametrize("window,touched", [(61, range(96, 111)), (55, range(112, 117)), (33, range(128, 139))])
+def test_prefill_attention_fp16_range_check_below_the_band(what, part, window, touched):
+    """The flag of the fp16 form counts every position that the walk touches, also those below the band of every row: the walk
+    starts at a multiple of 32, or at the first block the band still holds.  A value that the flag names raises it at each
+    of them, one in the position before them does not."""
+    H, hd, lens = 2, 128, [191]
+    table, clean, _ = _attention_case(53, lens, H, H, hd, "bf16")
+    q = gen.normal(53, 9, (20, H, hd), device=DEV)
+    tiles = torch.tensor([[0, 20, 171, 0]], dtype=torch.int32, device=DEV)
+    assert 171 - window + 1 == touched.stop
+    for pos in (touched.start - 1, *touched):
+        pool = clean.clone()
+        pool[int(table[0, pos // 16]), part, 1, pos % 16, 17] = what
+        flag, out = torch.zeros(1, dtype=torch.int32, device=DEV), torch.zeros(20, H, hd, device=DEV)
+        ld.ldk_prefill_attention_f16(q, H * hd, device_pool(pool), table.to(DEV), tiles, H, H, hd, out, 190, flag, window=window)
+        assert int(flag.item()) == (pos in touched), pos
+
+
 @pytest.mark.parametrize("N,K,epi,norm", [(N, K, epi, norm) for epi in ("store", "add", "swiglu") for norm in (False, True) for N, K in [
     (1, 8), (2, 2040), (3, 2048), (513, 2056), (1025, 6152), (1537, 8192), (770, 8200), (1026, 16384), (4099, 2056), (4099, 8200), (2050, 16384), (16391, 1032)]] + [(140000, 16384, "store", False)])
 def test_gemv_slab_edges(N, K, epi, norm):
