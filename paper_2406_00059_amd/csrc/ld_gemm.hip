@@ -680,12 +680,12 @@ static void launch_rope_rows(const float *partial, int T, int ks, float *y, cons
 // Where the rows of a product go next.
 struct RowsNext { const float *g; float eps; OperandImage out; const RopeKvArgs *rope; int row0; };
 
-// Products with an operand of 4 GiB or more keep both terms in every row.
+// Products with an operand of 4 GiB or more keep both terms in every row, wherever their tails are cut.
 int gemm_f16_rows(int T, int N, int K, int epi) {
     if (T <= SKINNY_MAX_ROWS || K > TILE_MAX_K) return 0;
-    const int m = T - tail_rows(T, N, K, epi, true);
     const int64_t limit = (int64_t)1 << 31;      // elements
-    return (int64_t)m * K < limit && (int64_t)N * (epi == GEMM_SWIGLU ? 2 : 1) * K < limit ? m : 0;
+    if ((int64_t)T * K >= limit || (int64_t)N * (epi == GEMM_SWIGLU ? 2 : 1) * K >= limit) return 0;
+    return T - tail_rows(T, N, K, epi, true);
 }
 
 // nx != nullptr with GEMM_ADD: y's rows are finished and turned into the next operand by one fused kernel in

@@ -355,6 +355,10 @@ def test_operands_of_4_gib_keep_both_terms():
         assert _f16_rows(600, N - 8192, K, epi) == 600
     assert _f16_rows(1 << 19, 1024, 4096, ld.LDK_STORE) == 0
     assert _f16_rows((1 << 19) - 256, 1024, 4096, ld.LDK_STORE) == (1 << 19) - 256
+    # an image that reaches 4 GiB by its last rows only, where the planner cuts those off
+    for T, N, K, epi in ((31278, 4736, 68736, ld.LDK_ADD), (110389, 3643, 19456, ld.LDK_STORE)):
+        assert 0 < T % 256 <= 64 and T * K >= 1 << 31 > (T - T % 256) * K
+        assert _f16_rows(T, N, K, epi) == 0
 
 
 def test_rows_too_long_for_32_bit_offsets_take_no_tile():
