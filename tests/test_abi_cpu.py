@@ -312,6 +312,36 @@ def test_trim_follows_the_oracle_allocator_bit_exact():
     assert ld.ld_kv_trim(kv, e, check=False) == ld.LD_E_STATE
 
 
+def test_page_locked_logits_are_bounded(monkeypatch):
+    """Logits arrays are page-locked only while those that callers still hold, or views of them, stay within a fixed size; beyond it, and
+    where no such memory is to be had, they are ordinary ones.  (The allocation is ordinary here, and told apart by its owner.)"""
+    import torch
+    b, refused = ld.binding, []
+
+    def empty(shape, dtype, pin_memory, alloc=torch.empty):
+        if refused:
+            raise RuntimeError("no page-locked memory")
+        return alloc(shape, dtype=dtype)
+
+    monkeypatch.setattr(torch.cuda, "is_available", lambda: True)
+    monkeypatch.setattr(torch, "empty", empty)
+    monkeypatch.setattr(b, "_PINNED_LOGITS_BYTES", 5 * 4 << 18, raising=False)
+    monkeypatch.setattr(b, "_pinned_logits", [], raising=False)
+    get = lambda rows=1: b._logits_buf(True, rows, 1 << 18)[0]
+    locked = lambda a: a.base is not None
+    held = [get()[0] for _ in range(5)]                 # five rows, held through views
+    assert all(map(locked, held)) and not locked(get()) and not locked(get(6))
+    del held[1:3]
+    assert not locked(get(3))
+    two = get(2)
+    assert locked(two) and two.shape == (2, 1 << 18) and not locked(get())
+    del held, two
+    assert locked(get(5)) and not locked(get(6)) and not locked(b._logits_buf(True, 1, 1000)[0])
+    refused.append(True)
+    a = get()
+    assert not locked(a) and a.shape == (1, 1 << 18) and a.dtype == np.float32
+
+
 def test_bench_refuses_more_than_one_gpu():
     """The benchmark measures one GPU; asking for more exits with a message instead of a number."""
     import subprocess, sys
