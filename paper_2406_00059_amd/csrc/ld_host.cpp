@@ -15,6 +15,8 @@ namespace ld {
 
 static thread_local std::string g_err;
 
+size_t pass_slot_ints(int max_tokens, int max_seqs) { return align_up((size_t)max_tokens * 9 + 2 + (size_t)max_seqs * 7, 64); }
+
 void set_error(const char *fmt, ...) {
     char buf[512];
     va_list ap;
@@ -146,7 +148,7 @@ struct ld_kv {
     int32_t *dev_meta = nullptr, *dev_out = nullptr, *dev_table = nullptr;      // the same as the GPU sees them
     hipEvent_t step_ev[2] = {nullptr, nullptr};
     size_t range_off() const { return (size_t)max_tokens * 9 + 2 + (size_t)max_seqs * 4; }      // changed runs of the block table, behind the metadata
-    size_t meta_ints() const { return range_off() + (size_t)max_seqs * 3; }
+    size_t meta_ints() const { return ld::pass_slot_ints(max_tokens, max_seqs); }
     // optional per-kernel timing
     bool prof_on = false;
     ld_profile prof{};

@@ -58,6 +58,9 @@ struct PassEnd {
     const int *flag = nullptr;       // copied to *flag_host
     int *flag_host = nullptr;
 };
+// Ints of one slot of that memory: metadata (seeds, of 8 bytes, among them), then the ranges.  A multiple of 64, so that the
+// second slot is aligned as the first.
+size_t pass_slot_ints(int max_tokens, int max_seqs);
 // Embeddings and rotary table of the pass's rows, and what PassStart names.  prev_tok: the input tokens, where not the metadata's.
 ld_status pass_begin(const void *embed, int dtype, const int32_t *prev_tok, int d, float *x, int hd, float rope_base, float *cos_sin,
                      const PassStart &p, hipStream_t s);

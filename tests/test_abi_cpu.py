@@ -312,6 +312,16 @@ def test_trim_follows_the_oracle_allocator_bit_exact():
     assert ld.ld_kv_trim(kv, e, check=False) == ld.LD_E_STATE
 
 
+@pytest.mark.parametrize("max_tokens", [1, 2, 7, 64, 1057])
+@pytest.mark.parametrize("max_seqs", [1, 2, 3, 32])
+def test_pass_metadata_slots_are_aligned(max_tokens, max_seqs):
+    """The two slots of a pass's metadata lie behind each other and hold 8-byte seeds at even offsets: their size is a multiple of 256
+    bytes, and holds nine ints a row, four a sampled sequence, two of padding and three a changed run of the block table."""
+    ints = C.CFUNCTYPE(C.c_size_t, C.c_int, C.c_int)(("_ZN2ld14pass_slot_intsEii", ld.lib()))(max_tokens, max_seqs)
+    need = 9 * max_tokens + 2 + 4 * max_seqs + 3 * max_seqs
+    assert ints % 64 == 0 and need <= ints < need + 64
+
+
 def test_page_locked_logits_are_bounded(monkeypatch):
     """Logits arrays are page-locked only while those that callers still hold, or views of them, stay within a fixed size; beyond it, and
     where no such memory is to be had, they are ordinary ones.  (The allocation is ordinary here, and told apart by its owner.)"""
