@@ -643,11 +643,24 @@ static void launch_reduce(const float *partial, int T, int N, int ks, int epi, f
 }
 
 // The float rows take longer to arrive than octets do (rows a multiple of 4 KB apart come out of a few channels of the cache; with
-// 64 bytes of a row in a run and an exchange between lanes they take as long): ahead of the pass they replace (4.8 us) while that
-// pass is long or the rows are few.  Calls through images -> from floats: 2 rows 4096 x 4096 16.2 -> 13.3 us, 4096 x 11008
-// 26.0 -> 21.8; 16 rows 16.4 -> 15.6, 27.7 -> 24.9; 20: 22016 x 4096 41.0 -> 40.2, 5120 x 13824 38.5 -> 34.4; 33: 4096 x 4096 19.4 -> 17.7;
-// 64: 5120 x 13824 49.1 -> 47.1; but 32: 4096 x 4096 18.2 -> 20.1, 22016 x 4096 42.4 -> 43.8, 48: 20.1 -> 20.5, 64: 22.2 -> 23.3.
-bool gemm_takes_floats(int T, int K) { return gemm_takes_octets(T) && (K > 8192 || T <= 20 || (T > 32 && T <= 40)); }
+// 64 bytes of a row in a run and an exchange between lanes they take as long), the more the more 16-row tiles of them a workgroup
+// holds, and with a norm the kernel that adds the slabs has their squares to add.  Ahead of the pass they replace, therefore, where
+// that pass is long or the rows are few.  Every row count from 2 to 64 on 19 shapes, matrices out of HBM, images -> floats, us:
+//  one tile: 4096 x 4096 at 2 rows 14.4 -> 12.8, at 16 15.3 -> 15.0; with a norm 22016 x 4096 36.9 -> 35.5, 39.1 -> 38.9 (slower only
+//   where a short row meets many outputs: 8192 x 2048 from 10 rows on, at 16 15.3 -> 16.1);
+//  two tiles: with a norm behind everywhere up to 8192 columns (12288 x 4096 at 17 rows 27.2 -> 27.9, at 20 27.4 -> 28.3; 22016 x 4096
+//   at 20 41.1 -> 41.9); without one 4096 x 4096 at 17 16.7 -> 17.4, 5120 x 5120 at 17 20.3 -> 19.9, at 20 20.6 -> 20.5, at 24
+//   20.9 -> 21.3;
+//  three: without a norm 4096 x 4096 at 33 18.6 -> 17.6, at 40 18.6 -> 18.3, level at 48; with one 12288 x 4096 at 33 30.6 -> 31.3,
+//   at 40 31.6 -> 33.2, 27648 x 5120 level;
+//  rows of more than 8192 columns everywhere: 4096 x 11008 at 2 25.4 -> 21.4, at 20 28.8 -> 26.6, at 32 30.3 -> 29.0, at 33
+//   33.6 -> 29.1, at 64 38.9 -> 36.2; 5120 x 13824 at 20 37.7 -> 33.5, at 64 48.6 -> 46.3.
+bool gemm_takes_floats(int T, int K, bool norm) {
+    if (!gemm_takes_octets(T)) return false;
+    const int forced = env_flag("LD_GEMM_FLOATS", -1);      // tuning knob: 1 float rows, 0 images
+    if (forced >= 0) return forced != 0;
+    return K > 8192 || T <= 16 || (!norm && (T <= 32 ? K >= 5120 && T <= 20 : T <= 40));
+}
 
 void launch_gemm_floats(const uint16_t *W, const float *x, const float *g, float eps, int T, int N, int K, int epi, float *y, void *scratch,
                         hipStream_t s) {

@@ -388,6 +388,22 @@ def test_rows_that_keep_both_terms_in_the_one_term_form(N, K, epi, after):
     assert _f16_rows(64, N, K, epi) == 0
 
 
+def test_small_batch_form(monkeypatch):
+    """Where a product of up to 64 rows takes float rows instead of images: one 16-row tile, long rows, and without a norm a little further.
+    LD_GEMM_FLOATS forces either form, for these row counts only."""
+    takes = C.CFUNCTYPE(C.c_bool, C.c_int, C.c_int, C.c_bool)(("_ZN2ld17gemm_takes_floatsEiib", ld.lib()))
+    monkeypatch.delenv("LD_GEMM_FLOATS", raising=False)
+    rows = lambda K, norm: [T for T in range(0, 70) if takes(T, K, norm)]
+    for K in (128, 4096, 5120, 8192):
+        assert rows(K, True) == list(range(2, 17))
+        assert rows(K, False) == list(range(2, 21 if K >= 5120 else 17)) + list(range(33, 41))
+    for K in (8320, 13824):
+        assert rows(K, True) == rows(K, False) == list(range(2, 65))
+    for form in ("0", "1"):
+        monkeypatch.setenv("LD_GEMM_FLOATS", form)
+        assert rows(4096, True) == rows(13824, False) == (list(range(2, 65)) if form == "1" else [])
+
+
 def test_operands_of_4_gib_keep_both_terms():
     """Rows enter as one fp16 term only while the matrix (gate and up rows together) and the rows' image stay below 4 GiB."""
     for N, K, epi in ((1 << 19, 4096, ld.LDK_STORE), (1 << 18, 4096, ld.LDK_SWIGLU), (1 << 17, 16384, ld.LDK_ADD)):
