@@ -429,15 +429,17 @@ def test_linear_matrix_core_path(T, epi):
     assert err <= 2e-5, err
 
 
+@pytest.mark.parametrize("floats", ["1", "0"], ids=["floats", "images"])
 @pytest.mark.parametrize("T", [2, 15, 16, 17, 32, 33, 48, 49, 63, 64])
 @pytest.mark.parametrize("N,K", [(5, 128), (301, 2048), (4099, 2176), (66, 11008), (7, 8192), (4105, 8192), (1023, 16384)])
-def test_linear_small_batch_edges(T, N, K):
-    """The small-batch kernel at the edges of its tiles: one row below, at and above each count of 16-row tiles of X; fewer
+def test_linear_small_batch_edges(T, N, K, floats, monkeypatch):
+    """The small-batch kernel, fed by float rows and by bf16 images (the form of a decode batch's layers), at the edges of its tiles: one row below, at and above each count of 16-row tiles of X; fewer
     output rows than a tile, odd and ragged counts; K slabs where most waves have no share (128), of exactly the width a
     workgroup holds (2048), just beyond it (2176: two uneven slabs), a ragged FFN width, and rows a multiple of
     16 KB apart, whose tiles are dealt out in turn.  Against float64 on every
     output: the two bf16 terms leave 2^-18 of an activation, float32 sums about as much (2^-24 per addition, a random walk
     over K <= 16384 terms), so |error| <= 2^-16 sum_k |w x| holds with room, and a lost low term (2^-9) does not pass."""
+    monkeypatch.setenv("LD_GEMM_FLOATS", floats)
     W = _mat(31, 1, N, K, "bf16").to(DEV); x = gen.normal(31, 2, (T, K), device=DEV)
     scratch = torch.empty(ld.ldk_linear_scratch_bytes(T, N, K, ld.LDK_STORE), dtype=torch.uint8, device=DEV)
     y = torch.full((T, N), float("nan"), device=DEV)
@@ -485,13 +487,15 @@ def test_qkv_rope_equals_product_then_rotation(T, H, Hkv, hd):
     assert (pools[0].view(72, 2, Hkv, hd, 16)[:, 1].permute(0, 3, 1, 2)[~written] == 3.0).all()
 
 
+@pytest.mark.parametrize("floats", ["1", "0"], ids=["floats", "images"])
 @pytest.mark.parametrize("T", [2, 16, 17, 20, 21, 32, 33, 40, 41, 64])
 @pytest.mark.parametrize("N,K,epi", [(5, 128, "store"), (301, 4096, "swiglu"), (66, 5120, "add"), (302, 11008, "add"), (7, 8320, "swiglu")])
-def test_linear_small_batch_normalises_float_rows(T, N, K, epi):
-    """The small-batch product with a norm, on both sides of every line between float rows (split and squared in the product, the
-    scale applied to the finished sums) and images (a pass in front): rows of very different size, so that a scale or a sum of
+def test_linear_small_batch_normalises_float_rows(T, N, K, epi, floats, monkeypatch):
+    """The small-batch product with a norm, from float rows (split and squared in the product, the
+    scale applied to the finished sums) and from images (a pass in front): rows of very different size, so that a scale or a sum of
     squares of another row shows.  Against float64: the bound of test_linear_small_batch_edges on the normalised row, and
     2^-20 for the sum of squares and its root."""
+    monkeypatch.setenv("LD_GEMM_FLOATS", floats)
     code = {"store": ld.LDK_STORE, "add": ld.LDK_ADD, "swiglu": ld.LDK_SWIGLU}[epi]
     rows = 2 * N if epi == "swiglu" else N
     W = _mat(37, K, rows, K, "bf16").to(DEV); g = gen.normal(37, 3, (K,), std=0.1, mean=1.0).to(DEV)
