@@ -1,5 +1,6 @@
 """Per-kernel parity on the GPU: every kernel-level entry point against the oracle's step functions
 on the same seeded inputs, element by element, at sizes spanning several tiles and ragged tails."""
+import ctypes as C
 import math
 
 import numpy as np
@@ -201,16 +202,42 @@ def test_paged_attention_edge_lengths(dtype, hd, H, Hkv):
 @pytest.mark.parametrize("window", [0, 20])
 @pytest.mark.parametrize("dtype,hd,H,Hkv", [("bf16", 128, 2, 2), ("f32", 64, 4, 4), ("f32", 128, 2, 1), ("bf16", 64, 8, 2), ("f32", 64, 8, 1)])
 def test_paged_attention_of_one_chunk(dtype, hd, H, Hkv, window):
-    """Launches in which no row has more than one chunk (up to 64 positions; with many rows longer ones) finish their results
-    without a merge: every group size of the scalar kernel, and a scratch of NaN that such a launch does not look at."""
-    for lens in ([1, 2, 16, 17, 63, 64], [5] * 40 + [190, 191]):
+    """Launches in which no row has more than one chunk (up to 64 positions; with many rows up to 512, several blocks a wave) finish
+    their results without a merge: every group size of the scalar kernel, and a scratch of NaN that such a launch leaves as it is.  The
+    same results as the operand of the output projection, in octets and in rows of a larger image: bit for bit their split."""
+    groups = H // (H // Hkv if H // Hkv in (2, 4, 8) else 1)
+    for lens in ([1, 2, 16, 17, 63, 64], [190, 449, 512, 500, 257] + [5] * (464 // groups)):
+        T = len(lens)
         table, pool, q = _attention_case(27, lens, H, Hkv, hd, dtype)
-        out = torch.full((len(lens), H, hd), float("nan"), device=DEV)
-        scratch = torch.full((ld.ldk_attention_scratch_bytes(len(lens), H, Hkv, hd, max(lens), window) // 4,), float("nan"), device=DEV)
-        ld.ldk_paged_attention(q, H * hd, device_pool(pool), table.to(DEV), torch.arange(len(lens), dtype=torch.int32, device=DEV),
-                               torch.tensor(lens, dtype=torch.int32, device=DEV), max(lens), H, Hkv, hd, out, scratch, window=window)
+        out = torch.full((T, H, hd), float("nan"), device=DEV)
+        scratch = torch.full((ld.ldk_attention_scratch_bytes(T, H, Hkv, hd, max(lens), window) // 4,), float("nan"), device=DEV)
+        args = (q, H * hd, device_pool(pool), table.to(DEV), torch.arange(T, dtype=torch.int32, device=DEV),
+                torch.tensor(lens, dtype=torch.int32, device=DEV), max(lens), H, Hkv, hd)
+        ld.ldk_paged_attention(*args, out, scratch, window=window)
         ref = _oracle_attention(table, pool, q, lens, Hkv, hd, window=window)
         assert np.max(np.abs(out.cpu().numpy() - ref)) <= _attn_tol(dtype, hd, H, Hkv) * np.abs(ref).max() + 1e-6
+        assert torch.isnan(scratch).all()
+        rows = out.view(T, H * hd)
+        hi = rows.bfloat16(); lo = (rows - hi.float()).bfloat16()
+        images = _attention_images(args, scratch, window, T, octets=True).view(2, H * hd // 8, T, 8).transpose(1, 2).reshape(2, T, H * hd)
+        assert torch.equal(images[0], hi) and torch.equal(images[1], lo)
+        images = _attention_images(args, scratch, window, T + 3, octets=False).view(2, T + 3, H * hd)
+        assert torch.equal(images[0, :T], hi) and torch.equal(images[1, :T], lo) and (images[:, T:] == 7.0).all()
+        assert torch.isnan(scratch).all()
+
+
+def _attention_images(args, scratch, window, image_rows, octets):
+    """Decode attention that leaves (hi, lo) bf16 images, as the layers of the engine call it: args of ldk_paged_attention up to hd."""
+    q, q_stride, pool, table, slot, ctx, max_ctx, H, Hkv, hd = args
+    xs = torch.full((2 * image_rows * H * hd,), 7.0, dtype=torch.bfloat16, device=DEV)
+    P, I = C.c_void_p, C.c_int
+    f = C.CFUNCTYPE(I, P, I, P, I, P, I, P, P, I, I, I, I, I, I, P, P, C.c_size_t, P, I, C.c_bool, I, P)(
+        ("_ZN2ld21paged_attention_splitEPKfiPKviPKiiS5_S5_iiiiiiPtPvmP12ihipStream_tibiPi", ld.lib()))
+    rc = f(q.data_ptr(), q_stride, pool.data_ptr(), ld.LD_BF16 if pool.dtype == torch.bfloat16 else ld.LD_F32, table.data_ptr(), table.shape[1],
+           slot.data_ptr(), ctx.data_ptr(), max_ctx, ctx.numel(), H, Hkv, hd, window, xs.data_ptr(), scratch.data_ptr(), scratch.numel() * 4,
+           torch.cuda.current_stream().cuda_stream, image_rows, octets, 0, None)
+    assert rc == ld.LD_OK
+    return xs
 
 
 @pytest.mark.parametrize("dtype,hd", [("bf16", 128), ("f32", 64)])
