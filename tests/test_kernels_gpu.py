@@ -659,6 +659,42 @@ def test_linear_tile_stores_of_four_columns(form, T, N, ks, monkeypatch):
         assert ((outs[0].double() - ref).abs() <= bound + 1e-7).all(), epi
 
 
+@pytest.mark.parametrize("form,T,N,K", [("tiles", 257, 2044, 1152), ("tiles", 300, 1752, 1152)]
+                         + [(form, T, N, K) for form in ("floats", "images") for T, N, K in ((40, 13824, 1152), (64, 8196, 2176))])
+@pytest.mark.parametrize("epi", ["store", "add", "swiglu"])
+def test_linear_reduction_of_four_outputs(form, T, N, K, epi, monkeypatch):
+    """Slab sums of 524288 outputs and more are added four outputs a thread where the output is 16-byte aligned, one at a time where
+    it starts 4 bytes past that: the same bits, behind the big tiles (two slabs) and behind the small-batch product with a norm, from
+    float rows (whose scale the reduction applies) and from images.  Against float64 on every output: the bound of
+    test_linear_small_batch_normalises_float_rows."""
+    assert T * N >= 1 << 19 and N % 4 == 0
+    monkeypatch.setenv("LD_GEMM_BIG", "128,256,2")
+    monkeypatch.setenv("LD_GEMM_FLOATS", "1" if form == "floats" else "0")
+    code = {"store": ld.LDK_STORE, "add": ld.LDK_ADD, "swiglu": ld.LDK_SWIGLU}[epi]
+    W = _mat(59, N, N * (2 if epi == "swiglu" else 1), K, "bf16").to(DEV); g = gen.normal(59, 3, (K,), std=0.1, mean=1.0).to(DEV)
+    x = gen.normal(59, 2, (T, K), device=DEV) * (10.0 ** (torch.arange(T, device=DEV) % 5 - 2))[:, None]
+    y0 = gen.normal(59, 4, (T, N), device=DEV)
+    scratch = torch.empty(ld.ldk_linear_scratch_bytes(T, N, K, code), dtype=torch.uint8, device=DEV)
+    outs = []
+    for shift in (0, 1):
+        buf = torch.full((T * N + 8,), 7.0, device=DEV)
+        y = buf[4 + shift:4 + shift + T * N].view(T, N)
+        y.copy_(y0)
+        ld.ldk_linear(W, x, y, code, g=g, eps=1e-5, scratch=scratch)
+        assert (buf[:4 + shift] == 7.0).all() and (buf[4 + shift + T * N:] == 7.0).all()
+        outs.append(y)
+    assert torch.equal(*outs)
+    xn = x.double() / torch.sqrt((x.double() ** 2).mean(1, keepdim=True) + 1e-5) * g.double()
+    full, mag = xn @ W.double().t(), xn.abs() @ W.double().abs().t()
+    a, tol = full[:, :N], 2.0 ** -16 + 2.0 ** -20
+    if epi == "swiglu":
+        ref = torch.nn.functional.silu(a) * full[:, N:]
+        bound = tol * (1.1 * full[:, N:].abs() * mag[:, :N] + torch.nn.functional.silu(a).abs() * mag[:, N:]) + 1e-6 * ref.abs() + 1e-7
+    else:
+        ref, bound = a + (y0.double() if epi == "add" else 0), tol * mag[:, :N] + 1e-6
+    assert ((outs[0].double() - ref).abs() <= bound).all()
+
+
 def test_linear_matrix_core_7b_shapes_sampled():
     """Launch shapes of the batch-32 decode step, of a 256-row prefill chunk, of a mixed step (32 decode rows
     + four 256-row chunks) and of a 2048-row chunk beside 63 decode rows, sampled outputs.  The last two have
