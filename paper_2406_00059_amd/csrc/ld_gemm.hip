@@ -684,12 +684,6 @@ static void launch_tiles(const uint16_t *W, const bf16_t *hi, const bf16_t *lo, 
     launch_reduce(partial, T, N, p.ks, epi, y, out, {}, s);
 }
 
-static void launch_rope_rows(const float *partial, int T, int ks, float *y, const RopeKvArgs &rk, int row0, hipStream_t s) {
-    const dim3 grid(rk.H + rk.Hkv, (T + 15) / 16);
-    if (rk.hd == 128) LD_LAUNCH((k_rope_rows<128, bf16_t>), grid, dim3(256), 0, s, partial, T, ks, y, rk, rk.pool, row0, rk.store_kv && ks > 0);
-    else LD_LAUNCH((k_rope_rows<64, bf16_t>), grid, dim3(128), 0, s, partial, T, ks, y, rk, rk.pool, row0, rk.store_kv && ks > 0);
-}
-
 // Where the rows of a product go next.
 struct RowsNext { const float *g; float eps; OperandImage out; const RopeKvArgs *rope; int row0; };
 
@@ -713,7 +707,7 @@ static void gemm_rows(const uint16_t *W, const bf16_t *hi, const bf16_t *lo, int
     const OperandImage out = nx && epi == GEMM_SWIGLU ? nx->out : OperandImage{};
     auto finish = [&](int ks) {      // ks: slabs whose partial sums the finishing kernel still has to add
         if (chain_rope) {
-            launch_rope_rows(partial, T, ks, y, *nx->rope, nx->row0, s);
+            launch_rope(partial, T, ks, y, *nx->rope, nx->rope->pool, nx->row0, s);
         } else if (N <= 5 * 1024) {
             LD_LAUNCH((k_reduce_add_norm_split<5>), dim3(T), dim3(256), 0, s, partial, T, N, ks, y, nx->g, nx->eps, nx->out);
         } else {

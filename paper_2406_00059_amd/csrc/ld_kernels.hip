@@ -668,14 +668,10 @@ ld_status ldk_rope_kv_write(float *qkv, const float *cos_sin, const int32_t *pos
         return ld::fail(LD_E_INVAL, "ldk_rope_kv_write: bad argument");
     if (T == 0) return LD_OK;
     if (dtype != LD_BF16 && dtype != LD_F32) return ld::fail(LD_E_INVAL, "ldk_rope_kv_write: bad dtype");
-    const dim3 grid(H + Hkv, (T + 15) / 16), block(2 * hd);
     hipStream_t s = (hipStream_t)stream;
     const ld::RopeKvArgs rk{(const float2 *)cos_sin, pos, seq_slot, table, table_stride, nullptr, H, Hkv, hd};
-#define LD_ROPE(HD_, KVT_) LD_LAUNCH((k_rope_rows<HD_, KVT_>), grid, block, 0, s, nullptr, T, 0, qkv, rk, (KVT_ *)pool_layer, 0, false)
-    if (dtype == LD_BF16) { if (hd == 128) LD_ROPE(128, bf16_t); else LD_ROPE(64, bf16_t); }
-    else if (hd == 128) LD_ROPE(128, float);
-    else LD_ROPE(64, float);
-#undef LD_ROPE
+    if (dtype == LD_BF16) launch_rope(nullptr, T, 0, qkv, rk, (bf16_t *)pool_layer, 0, s);
+    else launch_rope(nullptr, T, 0, qkv, rk, (float *)pool_layer, 0, s);
     return launched("k_rope_rows");
 }
 

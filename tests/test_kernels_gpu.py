@@ -127,6 +127,31 @@ def test_rope_and_cache_append_values_and_block_indexing(dtype, hd):
     assert touched.sum() == T * 2 * Hkv
 
 
+@pytest.mark.parametrize("dtype,hd", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("H,Hkv,T", [(3, 1, 95), (3, 1, 96), (3, 1, 97), (2, 2, 104), (20, 4, 64), (20, 4, 65), (32, 32, 24), (32, 32, 25), (16, 16, 67), (16, 4, 128), (16, 4, 129)])
+def test_rope_rows_together_equal_rows_alone(dtype, hd, H, Hkv, T):
+    """Many rows of one call (one wave a row up to 96 rows and 1536 rows times heads, four or eight rows a wave up to 128, sixteen a workgroup beyond) against a call
+    for each row: the same bits in the rotated rows, and in the pool, which holds nothing else.  Rows of two sequences that start
+    inside a block, and single rows of others."""
+    N, n0 = (H + 2 * Hkv) * hd, T - T // 3
+    qkv = gen.normal(71, hd, (T, N), device=DEV)
+    pos = torch.tensor([13 + i for i in range(n0 // 2)] + [47 + i for i in range(n0 - n0 // 2)] + [(37 * i) % 200 for i in range(T - n0)], dtype=torch.int32, device=DEV)
+    slot = torch.tensor([0] * (n0 // 2) + [1] * (n0 - n0 // 2) + [2 + i for i in range(T - n0)], dtype=torch.int32, device=DEV)
+    n_seq, per = 2 + T - n0, 13
+    table = torch.randperm(n_seq * per, generator=torch.Generator().manual_seed(T)).to(torch.int32).view(n_seq, per).to(DEV)
+    cs = torch.empty(T, hd, device=DEV)
+    ld.ldk_rope_table(pos, hd, 10000.0, cs)
+    pools = [torch.full((n_seq * per, 2, Hkv, 16, hd), 3.0, dtype=torch.bfloat16 if dtype == "bf16" else torch.float32, device=DEV) for _ in range(2)]
+    a, b = qkv.clone(), qkv.clone()
+    assert int(pos.max()) < per * 16
+    ld.ldk_rope_kv_write(a, cs, pos, slot, table, pools[0], H, Hkv, hd)
+    for t in range(T):
+        ld.ldk_rope_kv_write(b[t:t + 1], cs[t:t + 1], pos[t:t + 1], slot[t:t + 1], table, pools[1], H, Hkv, hd)
+    assert torch.equal(a, b) and torch.equal(*pools)
+    assert not torch.equal(a[:, :H * hd], qkv[:, :H * hd]) and torch.equal(a[:, H * hd:], qkv[:, H * hd:])
+    assert int((pools[0] != 3.0).any(-1).sum()) > 0
+
+
 def _attention_case(seed, lens, H, Hkv, hd, dtype, spare=5):
     B = len(lens)
     nb = [(n + 15) // 16 for n in lens]
