@@ -198,9 +198,12 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16_t *__restrict__
 
     // accumulator (a, j) of lane (l16, kg): row t0 + (wm AT + a) 16 + l16, four columns from n0 + (wn WOUT + j) 16 + 4 kg on
     const int ncols = SWI ? 2 * N : N;            // row length of the partial-sum buffer
-    auto put = [&](float *dst, const f32x4 &v, int left) {      // quads: rows are multiples of four floats, 16-byte aligned
-        if (quads) {
-            *reinterpret_cast<f32x4 *>(dst) = v;
+    // Four columns at once at any float's address: one at a time, a store touches four bytes of each of 64 sectors, which rows that
+    // are no multiple of four floats paid for
+    typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+    auto put = [&](float *dst, const f32x4 &v, int left) {
+        if (left >= 4) {
+            *reinterpret_cast<f32x4_any *>(dst) = v;
         } else {
 #pragma unroll
             for (int e = 0; e < 4; e++)
@@ -222,8 +225,8 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16_t *__restrict__
             float *dst = y + (int64_t)t * N + col;
             f32x4 v = tile_result(acc[a][j]);
             if constexpr (EPI == ld::GEMM_ADD) {
-                if (quads) {
-                    v += *reinterpret_cast<const f32x4 *>(dst);
+                if (left >= 4) {
+                    v += *reinterpret_cast<const f32x4_any *>(dst);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; e++)
@@ -235,7 +238,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16_t *__restrict__
 #pragma unroll
                 for (int e = 0; e < 4; e++) v[e] = swiglu(v[e], up[e]);
                 if (out.hi) {
-                    if (quads) {
+                    if (quads) {      // rows a multiple of four columns, 16-byte aligned
                         store_operand4(out, t, (int64_t)t * N + col, make_float4(v[0], v[1], v[2], v[3]));
                     } else {
 #pragma unroll
