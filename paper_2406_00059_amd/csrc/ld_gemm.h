@@ -55,8 +55,8 @@ void launch_weight_range_check(const uint16_t *W, int64_t n, int *flag, hipStrea
 void launch_weight_to_f16(const uint16_t *W, int64_t n, uint16_t *out, int *flag, hipStream_t s);
 
 // y = epilogue(x W^T) for up to 64 rows straight from the float rows, normalised where g is not null;
-// scratch as for the image form.  gemm_takes_floats: where that is the faster form (norm: g is not null).
-bool gemm_takes_floats(int T, int K, bool norm);
+// scratch as for the image form.  gemm_takes_floats: where that is the faster form (N: rows of the matrix; norm: g is not null).
+bool gemm_takes_floats(int T, int N, int K, bool norm);
 void launch_gemm_floats(const uint16_t *W, const float *x, const float *g, float eps, int T, int N, int K, int epi, float *y, void *scratch,
                         hipStream_t s);
 

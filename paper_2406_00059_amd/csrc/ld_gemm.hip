@@ -645,21 +645,27 @@ static void launch_reduce(const float *partial, int T, int N, int ks, int epi, f
 // The float rows take longer to arrive than octets do (rows a multiple of 4 KB apart come out of a few channels of the cache; with
 // 64 bytes of a row in a run and an exchange between lanes they take as long), the more the more 16-row tiles of them a workgroup
 // holds, and with a norm the kernel that adds the slabs has their squares to add.  Ahead of the pass they replace, therefore, where
-// that pass is long or the rows are few.  Every row count from 2 to 64 on 19 shapes, matrices out of HBM, images -> floats, us:
-//  one tile: 4096 x 4096 at 2 rows 14.4 -> 12.8, at 16 15.3 -> 15.0; with a norm 22016 x 4096 36.9 -> 35.5, 39.1 -> 38.9 (slower only
-//   where a short row meets many outputs: 8192 x 2048 from 10 rows on, at 16 15.3 -> 16.1);
-//  two tiles: with a norm behind everywhere up to 8192 columns (12288 x 4096 at 17 rows 27.2 -> 27.9, at 20 27.4 -> 28.3; 22016 x 4096
-//   at 20 41.1 -> 41.9); without one 4096 x 4096 at 17 16.7 -> 17.4, 5120 x 5120 at 17 20.3 -> 19.9, at 20 20.6 -> 20.5, at 24
-//   20.9 -> 21.3;
-//  three: without a norm 4096 x 4096 at 33 18.6 -> 17.6, at 40 18.6 -> 18.3, level at 48; with one 12288 x 4096 at 33 30.6 -> 31.3,
-//   at 40 31.6 -> 33.2, 27648 x 5120 level;
-//  rows of more than 8192 columns everywhere: 4096 x 11008 at 2 25.4 -> 21.4, at 20 28.8 -> 26.6, at 32 30.3 -> 29.0, at 33
-//   33.6 -> 29.1, at 64 38.9 -> 36.2; 5120 x 13824 at 20 37.7 -> 33.5, at 64 48.6 -> 46.3.
-bool gemm_takes_floats(int T, int K, bool norm) {
+// that pass is long or the rows are few.  GPU time at 2 .. 64 rows on 21 shapes with and without a norm, matrices out of HBM, images ->
+// floats, us (the width of the output hardly matters):
+//  one tile, no norm: 4096 x 4096 at 2 rows 13.9 -> 12.5, at 16 15.2 -> 15.0; 2048 x 2048 at 12 10.1 -> 10.0, at 16 10.4 -> 10.8;
+//   768 x 768 at 10 8.8 -> 8.6, at 16 8.8 -> 9.6;
+//  one tile, norm: 12288 x 4096 at 2 24.1 -> 22.9, at 16 25.8 -> 25.5; 8192 x 2048 at 8 level, at 16 15.2 -> 16.1; 9216 x 3072 at 12
+//   level, at 16 19.8 -> 20.2; 4096 x 1024 at 6 level, at 16 10.1 -> 11.5;
+//  two tiles: 12288 x 4096 with a norm at 17 27.3 -> 27.7, at 20 27.9 -> 28.4; without one 4096 x 4096 at 17 16.9 -> 17.2, 5120 x 5120 at
+//   17 20.3 -> 20.1, at 20 level, at 24 21.2 -> 21.4;
+//  three, no norm: 4096 x 4096 at 33 18.8 -> 17.8, at 40 18.9 -> 18.4, at 48 level; 2048 x 2048 at 40 11.4 -> 12.2; norm: 12288 x 4096 at
+//   33 30.9 -> 31.8;
+//  rows of more than 8192 columns everywhere: 4096 x 11008 at 2 25.1 -> 21.3, at 20 29.1 -> 26.7, at 33 33.5 -> 29.3, at 64
+//   39.2 -> 36.6.
+// A matrix of up to 8 MB takes the GPU less time than three launches take the caller: one launch fewer counts (3072 x 1024 at 16
+// rows, calls one after the other 13.2 -> 11.4, on the GPU 9.7 -> 11.3).
+bool gemm_takes_floats(int T, int N, int K, bool norm) {
     if (!gemm_takes_octets(T)) return false;
     const int forced = env_flag("LD_GEMM_FLOATS", -1);      // tuning knob: 1 float rows, 0 images
     if (forced >= 0) return forced != 0;
-    return K > 8192 || T <= 16 || (!norm && (T <= 32 ? K >= 5120 && T <= 20 : T <= 40));
+    if (K > 8192) return true;
+    if (T <= 16) return (int64_t)N * K <= 1 << 22 || (norm ? T <= 6 || T * 256 <= K : T <= 10 || K >= 2048);
+    return !norm && (T <= 32 ? T <= 20 && K >= 5120 : T <= 40 && K >= 3072);
 }
 
 void launch_gemm_floats(const uint16_t *W, const float *x, const float *g, float eps, int T, int N, int K, int epi, float *y, void *scratch,

@@ -629,7 +629,7 @@ ld_status ld::linear_pass(const void *W, int32_t dtype, const float *x, const fl
         return launched("k_gemv1");
     }
     if (dtype == LD_BF16 && scratch && ld::gemm_supported(T, N, K) && scratch_bytes >= ld::gemm_scratch_bytes(T, N, K, epilogue)) {
-        if ((!g || own_norm) && ld::gemm_takes_floats(T, K, g != nullptr)) {
+        if ((!g || own_norm) && ld::gemm_takes_floats(T, N * (epilogue == LDK_SWIGLU ? 2 : 1), K, g != nullptr)) {
             ld::launch_gemm_floats((const bf16_t *)W, x, g, eps, T, N, K, epilogue, y, scratch, s);
             return launched("the small-batch product");
         }

@@ -389,19 +389,22 @@ def test_rows_that_keep_both_terms_in_the_one_term_form(N, K, epi, after):
 
 
 def test_small_batch_form(monkeypatch):
-    """Where a product of up to 64 rows takes float rows instead of images: one 16-row tile, long rows, and without a norm a little further.
-    LD_GEMM_FLOATS forces either form, for these row counts only."""
-    takes = C.CFUNCTYPE(C.c_bool, C.c_int, C.c_int, C.c_bool)(("_ZN2ld17gemm_takes_floatsEiib", ld.lib()))
+    """Where a product of up to 64 rows takes float rows instead of images: up to 16 rows unless the rows are short, a little further
+    without a norm, and always where they are long.  LD_GEMM_FLOATS forces either form, for these row counts only."""
+    takes = C.CFUNCTYPE(C.c_bool, C.c_int, C.c_int, C.c_int, C.c_bool)(("_ZN2ld17gemm_takes_floatsEiiib", ld.lib()))
     monkeypatch.delenv("LD_GEMM_FLOATS", raising=False)
-    rows = lambda K, norm: [T for T in range(0, 70) if takes(T, K, norm)]
-    for K in (128, 4096, 5120, 8192):
-        assert rows(K, True) == list(range(2, 17))
-        assert rows(K, False) == list(range(2, 21 if K >= 5120 else 17)) + list(range(33, 41))
-    for K in (8320, 13824):
-        assert rows(K, True) == rows(K, False) == list(range(2, 65))
+    rows = lambda K, norm, N=40000: [T for T in range(0, 70) if takes(T, N, K, norm)]
+    upto = lambda n: list(range(2, n + 1))
+    for K, n in ((128, 6), (1536, 6), (2048, 8), (3072, 12), (4096, 16), (8192, 16)):
+        assert rows(K, True) == upto(n)
+    for K, tail in ((1024, upto(10)), (2048, upto(16)), (3072, upto(16) + list(range(33, 41))), (5120, upto(20) + list(range(33, 41)))):
+        assert rows(K, False) == tail
+    for norm in (False, True):
+        assert rows(1024, norm, 4096) == upto(16) and rows(1024, norm, 4097) == upto(6 if norm else 10)
+        assert rows(8320, norm) == rows(13824, norm) == upto(64)
     for form in ("0", "1"):
         monkeypatch.setenv("LD_GEMM_FLOATS", form)
-        assert rows(4096, True) == rows(13824, False) == (list(range(2, 65)) if form == "1" else [])
+        assert rows(4096, True) == rows(13824, False) == (upto(64) if form == "1" else [])
 
 
 def test_operands_of_4_gib_keep_both_terms():
