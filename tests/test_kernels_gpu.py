@@ -651,9 +651,9 @@ def test_linear_every_tile(form, rows, cols, K, ks, monkeypatch, capfd):
 @pytest.mark.parametrize("form", ["two", "f16"])
 @pytest.mark.parametrize("T,N,ks", [(65, 4, 1), (333, 300, 1), (333, 300, 3), (257, 1028, 2), (300, 302, 1)])
 def test_linear_tile_stores_of_four_columns(form, T, N, ks, monkeypatch):
-    """The big-tile kernel stores four columns at a time where rows are a multiple of four floats and 16-byte aligned, one at a
-    time elsewhere (302 columns; an output that starts 4 bytes past an aligned address): the same bits, nothing written beside
-    the output, and within 2^-16 sum_k |w x| of float64 on the inputs as the form rounds them (see test_linear_every_tile)."""
+    """The big-tile kernel stores four columns at a time at any float's address, and one at a time what is left of a row (302 columns;
+    an output that starts 4 bytes past an aligned address): the same bits, nothing written beside the output, and within
+    2^-16 sum_k |w x| of float64 on the inputs as the form rounds them (see test_linear_every_tile)."""
     monkeypatch.setenv("LD_GEMM_BIG", "128,256,%d" % ks)
     K = 1152
     W = _mat(43, N, 2 * N, K, "bf16").to(DEV); x = gen.normal(43, 2, (T, K), device=DEV); y0 = gen.normal(43, 4, (T, N), device=DEV)
