@@ -32,7 +32,8 @@ void launch_norm_split(const float *x, const float *g, float eps, int T, int K, 
 // would write.  With GEMM_SWIGLU (g unused): the result goes to next->xs as split(result) and y is not written.
 // With GEMM_STORE and rope != nullptr (the q-k-v projection; cos_sin, pos and seq_slot indexed by row): the kernel
 // that finishes y rotates the q heads in y and writes the rotated k heads and the v heads into the paged pool,
-// with the values the separate rotate-and-append pass would write (k and v are not stored to y).
+// with the values the separate rotate-and-append pass would write (k and v are stored to y only with rope->store_kv, and where
+// the product was split: elsewhere it has stored them).
 //
 // f16_flag != nullptr: the caller allows the rows of this pass to enter the product rounded to fp16 (11 significant
 // bits instead of the 16 of the two-term split) where that pays: more than 64 rows in the big-tile kernel, i.e. the rows

@@ -5,11 +5,11 @@
 // product carries ~16 significant bits of the activation instead of 8.  In the decode regime the
 // kernel is bound by the weight stream from HBM, where the second MFMA pass is free.
 //
-// Two kinds of kernel by row count, fed by the (hi, lo) bf16 images of the activations, which k_norm_split
-// writes in a pass of its own or a producer writes directly (k_reduce_add_norm_split and the SwiGLU epilogues
-// here, the attention kernels, the fused reducers of ld_batch.hip):
-//  - k_gemm_skinny (2..64 rows): weight-stream bound, see its comment.
-//  - k_gemm_tile (> 64 rows): MFMA-bound; both operands through LDS, see its comment.
+// Two kinds of kernel by row count, fed by images of the activations (two bf16 terms, or one fp16 term where the caller allows it),
+// which k_norm_split writes in a pass of its own or a producer writes directly (k_reduce_add_norm_split and the SwiGLU
+// epilogues, the attention kernels, the fused reducers of ld_batch.hip):
+//  - k_gemm_skinny (2..64 rows): weight-stream bound, see its comment.  It also takes the float rows themselves.
+//  - k_gemm_tile (> 64 rows, ld_gemm_tile_kernel.h): MFMA-bound; both operands through LDS, see its comment.
 // Workgroups that share a W panel (same columns, different token tiles) are mapped to the same XCD so
 // that the panel is fetched into one L2 only.  Split-K partial sums are added in fixed slab order.
 #include "ld_gemm.h"

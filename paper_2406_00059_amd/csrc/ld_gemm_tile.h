@@ -1,4 +1,5 @@
-// The big-tile kernel (products of more than 64 rows) and what its two translation units share with the planner.
+// The big-tile kernel (products of more than 64 rows): what its three translation units (two terms, one on the fp16 image, one on the
+// bf16 matrix) share with the planner.
 #pragma once
 #include "ld_gemm.h"
 #include "ld_device.h"
@@ -11,10 +12,8 @@ using ldd::bf16_t;
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;   // native 16-byte vector (keeps arrays of it in registers)
-
 
 // Tiles of the two forms, in units of 32 rows and 32 columns, and measured us per 64-wide chunk of K.  (Odd column units have
 // no SwiGLU form.)

@@ -1,4 +1,4 @@
-// k_gemm_tile, included by the two translation units that instantiate it.
+// k_gemm_tile, included by the three translation units that instantiate it.
 #pragma once
 #include "ld_gemm_tile.h"
 

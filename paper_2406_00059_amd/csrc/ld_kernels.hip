@@ -203,7 +203,8 @@ __global__ __launch_bounds__(256) void k_begin(const WT *__restrict__ E, const i
 __device__ __forceinline__ int band_first(int ctx, int window) { return (window > 0 && ctx > window) ? ctx - window : 0; }
 
 // FINISH: launches of one chunk a row (contexts of up to 64 positions, or many rows of up to 512), whose results need no merge:
-// a step of the two-layer fp32 decoder at 33 positions, a chain of 3 us kernels, 117 -> 109 us.
+// a step of the two-layer fp32 decoder at 33 positions, a chain of 3 us kernels, 117 -> 109 us.  (The grouped kernel, whose chunks are
+// twice as long, leaves its results to the merge in every launch.)
 template <int HD, typename KVT, int G, bool FINISH>
 __global__ __launch_bounds__(256) void k_attn_partial(const float *__restrict__ q, int q_stride,
                                                       const KVT *__restrict__ pool, int Hkv,
