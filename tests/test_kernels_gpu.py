@@ -501,10 +501,10 @@ def test_linear_small_batch_edges(T, N, K, floats, monkeypatch):
 
 
 @pytest.mark.parametrize("H,Hkv,hd", [(2, 1, 128), (3, 3, 64)])
-@pytest.mark.parametrize("T", [64, 65, 79, 257, 300])
+@pytest.mark.parametrize("T", [64, 65, 79, 97, 128, 129, 257, 300])
 def test_qkv_rope_equals_product_then_rotation(T, H, Hkv, hd):
-    """ldk_qkv_rope on many rows (rotation, cache append and the sum of the product's slabs in one kernel, 16 rows a workgroup, from 65
-    rows on) against ldk_linear followed by ldk_rope_kv_write: the same bits in the whole q-k-v buffer and in the whole pool.  Rows of
+    """ldk_qkv_rope on many rows (rotation, cache append and the sum of the product's slabs in one kernel from 65 rows on, in each of its
+    forms: a row, four or eight, sixteen at a time) against ldk_linear followed by ldk_rope_kv_write: the same bits in the whole q-k-v buffer and in the whole pool.  Rows of
     two sequences at consecutive positions that start inside a block, single rows of a third, and a ragged last group of rows.
     The rows of the pool also against float64: one rounding to bf16 of a sum within 2^-16 of its terms."""
     K, N = 1152, (H + 2 * Hkv) * hd
