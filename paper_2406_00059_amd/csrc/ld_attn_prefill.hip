@@ -13,15 +13,19 @@
 // behind block-table entries read another unit earlier, and shared by the four waves.  LDS is double buffered, with one
 // barrier per unit.  Two workgroups fit a CU, so that one wave's softmax overlaps another's MFMAs.
 //
-// What bounds it: the work per step at two waves per SIMD (a third of the cycles issue vector arithmetic, a fifth run MFMAs, the
-// rest waits for operands and barriers).  Hence two steps a barrier; in F16 one maximum, one exchange and one look at the
-// rescaling for both (scores start at -m, which saves the subtraction before the exponential); and as little as possible
-// around them: blocks are addressed in scalar registers, the range check of a widened pair is one instruction, a unit that
-// lies below the last position is staged without a look at each piece, the two halves of a query exchange maxima without LDS.
-// 12 tiles x 32 heads at contexts 2.2k .. 6.4k: 322 -> 214 -> 181 us with these (one step at a time, two, now); four segments
-// of 256 rows behind 0.5k .. 2.9k 98 -> 85 -> 76; one 256-row chunk behind 1500, in two terms, 33 -> 30 -> 30.
+// What bounds it: the work per step at two waves per SIMD, vector arithmetic and exponentials (which hold up the SIMD's MFMAs)
+// as much as the MFMAs themselves.  Hence two steps a barrier; in F16 both steps' scores at once; and as little as possible around
+// them: blocks are addressed in scalar registers, the range check of a widened pair is one instruction, a unit that lies below the
+// last position is staged without a look at each piece, scores start at -m, and a maximum is looked for only where the
+// exponentials against the last one have grown large.  The operands of the next MFMAs are read from LDS ahead of them, in an order that
+// is pinned: left alone, the compiler reads each right before its use and waits for it.  Queries come in whole rows and shares go out in
+// whole lanes: 16 bytes of each of 64 rows an instruction cost some 6000 and 2000 cycles a workgroup.
+// 12 tiles x 32 heads at contexts 2.2k .. 6.4k: 322 -> 214 -> 181 -> 171 us with these (one step at a time, two, no passes over
+// the queries, the last three); one 256-row chunk behind 1500, in two terms, 33 -> 31; one of 2048 behind 2048 151 -> 135; over 135 sets
+// of tiles (4 .. 40 heads, 1 .. 24 tiles, walks of 4 .. 250 steps) the last three give 12 % in the mean, 9 % in two terms.
 // Forming the next unit's scores between this one's exponentials, and staging between its value products, was level
-// (209 and 79 us: its second set of scores fills the registers).
+// (209 and 79 us: its second set of scores fills the registers).  Two halves of a workgroup that take the matrix cores in turn, on
+// pairs of tiles, reach 153 us in the first example but lose by up to three times where the work is small.
 //
 // Both products are computed transposed, so that the query index is the MFMA column (= lane % 32)
 // everywhere and the online-softmax statistics of a query live in the lanes that hold its scores:
@@ -94,6 +98,10 @@ __device__ __forceinline__ u32x4 load_in_block(const bf16_t *block, uint32_t off
 __device__ u32x4 load_in_block(const bf16_t *, uint32_t) { return u32x4{}; }
 #endif
 
+// Partial results: [tile][head][share][128 rows][HD] and (m, l) likewise.  Place of dimensions 8 d8 + 4 hi .. + 4 of a row among the 128: as
+// the lanes that have them store them, 1 KB in a row a wave.
+__device__ __forceinline__ int part_place(int row, int d8, int hi) { return (((row >> 5) * (HD / 8) + d8) * 64 + hi * 32 + (row & 31)) * 4; }
+
 // Steps of KVB positions that a tile walks: from the first position its first row sees (rounded down) to its last row's.
 __device__ __forceinline__ int tile_start(const int4 &tile, int window) { return window > 0 ? (max(tile.z - window + 1, 0) & ~(KVB - 1)) : 0; }
 __device__ __forceinline__ int tile_steps(const int4 &tile, int window) { return (tile.z + tile.y - 1 - tile_start(tile, window)) / KVB + 1; }
@@ -128,8 +136,11 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
                                                          float scale_log2e, float *__restrict__ out,
                                                          int per, float *__restrict__ part_o, float *__restrict__ part_ml,
                                                          ld::OperandImage image, int *__restrict__ f16_flag) {
-    __shared__ __attribute__((aligned(16))) bf16_t ks[2][2][KVB][KLD];      // [buffer][step of the unit]
-    __shared__ __attribute__((aligned(16))) bf16_t vt[2][2][HD][VLD];
+    struct Tiles { bf16_t ks[2][2][KVB][KLD], vt[2][2][HD][VLD]; };      // [buffer][step of the unit]
+    struct Queries { bf16_t part[4][F16 ? 1 : 2][32][KLD]; };              // [wave][term]: ahead of them
+    __shared__ __attribute__((aligned(16))) union Lds { Tiles tiles; Queries queries; } lds;
+    auto &ks = lds.tiles.ks;
+    auto &vt = lds.tiles.vt;
     // Work items longest first: shares in order, in each the tiles by their length, heads fastest.  Two workgroups share a
     // CU and run at each other's expense: in the tiles' own order long ones meet long ones.  Blocks b, b + 8, ... run on
     // one XCD: with the heads dealt out in eighths, the heads that read the same keys and values go through one L2.
@@ -147,11 +158,15 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
     const int64_t block_stride = kv_block_elems(Hkv, HD);
     const int32_t *trow = table + (int64_t)tile.w * table_stride;
 
+    const int wg_last_pos = tile.z + tile.y - 1;                       // last position any wave needs
+    const int kv_start = tile_start(tile, window);
+    const int kv_begin = kv_start + split * per * KVB;
+    const int kv_end = split + 1 == gridDim.z ? wg_last_pos + 1 : min(kv_begin + per * KVB, wg_last_pos + 1);      // exclusive; the last share takes what is left
+
     // this lane's query: row index inside the tile, validity, absolute position
     const int qi = wave * 32 + l32;
     const bool q_valid = qi < tile.y;
     const int q_pos = tile.z + min(qi, tile.y - 1);
-    const int wg_last_pos = tile.z + tile.y - 1;                       // last position any wave needs
     const int wave_last_pos = tile.z + min(wave * 32 + 31, tile.y - 1);
     const bool wave_active = wave * 32 < tile.y;
     // band: lowest position visible to this lane's query, to the wave's first query, to the tile's first query
@@ -159,35 +174,40 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
     const int wave_low = window > 0 ? max(tile.z + wave * 32 - window + 1, 0) : 0;
     const int wave_first_pos = tile.z + wave * 32;                      // position of the wave's first query
     const int wave_low_hi = window > 0 ? max(wave_last_pos - window + 1, 0) : 0;   // lowest position its last query sees
-    const int kv_start = tile_start(tile, window);
     // first position of the lowest block any row of the tile sees: block-table entries below it may belong
     // to blocks the sequence has given up (ld_kv_trim) and are never dereferenced
     const int first_held_pos = window > 0 ? (max(tile.z - window + 1, 0) & ~15) : 0;
 
     // Q operand: for k-step j the lane supplies dims half*64 + j*8 .. +8 of its query (hi and lo parts; F16: one
-    // fp16 term in qh)
+    // fp16 term in qh).  The rows come as they lie in memory, two a load, and take the operand's form through LDS: a load of each
+    // row's next 16 bytes touches 64 lines, sixteen times over
     u32x4 qh[8], ql[F16 ? 1 : 8];
-    bool out_of_range = false;      // F16: a value beyond the fp16 range was seen by this lane
-    float mag = 0.f;                // F16: largest magnitude among the keys and values this lane staged
+    float mag = 0.f;                // F16: largest magnitude among the queries, keys and values that this lane rounded
     {
-        const float *qp = q + (int64_t)(tile.x + min(qi, tile.y - 1)) * q_stride + h * HD + half * 64;
+        auto &mine = lds.queries.part[wave];
+        float4 raw[16];
+#pragma unroll
+        for (int i = 0; i < 16; i++)
+            raw[i] = *reinterpret_cast<const float4 *>(q + (int64_t)(tile.x + min(wave * 32 + 2 * i + half, tile.y - 1)) * q_stride + h * HD + 4 * l32);
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const float4 v = make_float4(raw[i].x * scale_log2e, raw[i].y * scale_log2e, raw[i].z * scale_log2e, raw[i].w * scale_log2e);
+            uint2 hi, lo;
+            if constexpr (F16) {
+                mag = __builtin_elementwise_maximum(__builtin_elementwise_maximum(mag, fabsf(v.x)), fabsf(v.y));
+                mag = __builtin_elementwise_maximum(__builtin_elementwise_maximum(mag, fabsf(v.z)), fabsf(v.w));
+                hi = make_uint2(pack2_f16(v.x, v.y), pack2_f16(v.z, v.w));
+            } else {
+                hi.x = split2_bf16(v.x, v.y, lo.x);
+                hi.y = split2_bf16(v.z, v.w, lo.y);
+                *reinterpret_cast<uint2 *>(&mine[F16 ? 0 : 1][2 * i + half][4 * l32]) = lo;
+            }
+            *reinterpret_cast<uint2 *>(&mine[0][2 * i + half][4 * l32]) = hi;
+        }
 #pragma unroll
         for (int j = 0; j < 8; j++) {
-            float v[8];
-            load8(qp + j * 8, v);
-            uint32_t hw[4], lw[4];
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                const float a = v[2 * e] * scale_log2e, b = v[2 * e + 1] * scale_log2e;
-                if constexpr (F16) {
-                    out_of_range = out_of_range || !(fabsf(a) <= 65504.f) || !(fabsf(b) <= 65504.f);
-                    hw[e] = pack2_f16(a, b);
-                } else {
-                    hw[e] = split2_bf16(a, b, lw[e]);
-                }
-            }
-            qh[j] = (u32x4){hw[0], hw[1], hw[2], hw[3]};
-            if constexpr (!F16) ql[j] = (u32x4){lw[0], lw[1], lw[2], lw[3]};
+            qh[j] = *reinterpret_cast<const u32x4 *>(&mine[0][l32][half * 64 + j * 8]);
+            if constexpr (!F16) ql[j] = *reinterpret_cast<const u32x4 *>(&mine[F16 ? 0 : 1][l32][half * 64 + j * 8]);
         }
     }
 
@@ -260,115 +280,121 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
         if (kv_unit + 2 * KVB - 1 <= wg_last_pos) stage_pieces(st, kv_unit, std::true_type{});
         else stage_pieces(st, kv_unit, std::false_type{});
     };
-    const int kv_begin = kv_start + split * per * KVB;
-    const int kv_end = split + 1 == gridDim.z ? wg_last_pos + 1 : min(kv_begin + per * KVB, wg_last_pos + 1);      // exclusive; the last share takes what is left
     // NT consecutive steps [u0, u0 + NT) of the unit at kv_unit: scores, softmax, output.  Two steps at a time (F16; the
     // two-term form has no registers left for that) give the matrix cores two independent chains of scores and the
     // softmax one maximum, one exchange and one look at the rescaling for 64 positions.
-    constexpr int NT = F16 ? 2 : 1;
+    constexpr int NT = F16 ? 2 : 1, RD = 4;      // RD: operands read ahead (3, 4 and 6 are level)
+    f32x16 less_m;      // sixteen times minus the exponents' reference
+#pragma unroll
+    for (int i = 0; i < 16; i++) less_m[i] = 0.f;
     auto compute = [&](int kv_unit, int st, int u0) {
         const int kv0 = kv_unit + KVB * u0;
         // ---- S^T = K Q^T for 32 kv positions x 32 queries a step; tile row l32 is position kv0 + tau(l32).  The sums start
         // at -m, so that the scores come out relative to the exponents' reference
-        const float m_in = m > -INFINITY ? m : 0.f;
         f32x16 sc_t[NT];
+        u32x4 f[RD];
+        auto key = [&](int i) __attribute__((always_inline)) {      // operand i: k-step i / NT of step i % NT
+            f[i % RD] = *reinterpret_cast<const u32x4 *>(&ks[st][u0 + i % NT][tau(l32)][half * 64 + i / NT * 8]);
+        };
 #pragma unroll
-        for (int n = 0; n < NT; n++)
-#pragma unroll
-            for (int i = 0; i < 16; i++) sc_t[n][i] = -m_in;
+        for (int i = 0; i < RD; i++) key(i);
+        __builtin_amdgcn_sched_barrier(0);
         // The matrix-core phases run at a raised wave priority: the other workgroup's wave on this SIMD then
         // fills the issue slots between the MFMAs with its softmax arithmetic instead of competing for them.
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-        for (int j = 0; j < 8; j++)
-#pragma unroll
-            for (int n = 0; n < NT; n++) {
-                const u32x4 ka = *reinterpret_cast<const u32x4 *>(&ks[st][u0 + n][tau(l32)][half * 64 + j * 8]);
-                if constexpr (F16) {
-                    sc_t[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, ka), __builtin_bit_cast(f16x8, qh[j]), sc_t[n], 0, 0, 0);
-                } else {
-                    sc_t[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka), __builtin_bit_cast(bf16x8, qh[j]), sc_t[n], 0, 0, 0);
-                    sc_t[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka), __builtin_bit_cast(bf16x8, ql[j]), sc_t[n], 0, 0, 0);
-                }
+        for (int i = 0; i < 8 * NT; i++) {
+            const int j = i / NT, n = i % NT;
+            const u32x4 ka = f[i % RD];
+            if constexpr (F16) {
+                sc_t[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, ka), __builtin_bit_cast(f16x8, qh[j]), j ? sc_t[n] : less_m, 0, 0, 0);
+            } else {
+                sc_t[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka), __builtin_bit_cast(bf16x8, qh[j]), j ? sc_t[n] : less_m, 0, 0, 0);
+                sc_t[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka), __builtin_bit_cast(bf16x8, ql[j]), sc_t[n], 0, 0, 0);
             }
+            if (i + RD < 8 * NT) key(i + RD);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         __builtin_amdgcn_s_setprio(0);
         // ---- online softmax; accumulator element i is row 8*(i/4) + 4*half + i%4 of the tile, which holds
         // position kv0 + 16*(i/8) + 8*half + i%8
-        float mb = -INFINITY;
-        if (kv0 + NT * KVB - 1 <= wave_first_pos && kv0 >= wave_low_hi) {
-            // every position of the steps is visible to every query of the wave (the common case away from
-            // the diagonal and the band edge): no masks; rows past the tile compute on a copy of the last row
+        if (!(kv0 + NT * KVB - 1 <= wave_first_pos && kv0 >= wave_low_hi)) {
+            // Not every position of the steps is visible to every query of the wave (at the diagonal and the band's edge): position
+            // p is where p - q_low, unsigned, is at most q_pos - q_low.  Rows past the tile compute on a copy of the last row
+            const uint32_t at0 = kv0 + 8 * half - q_low, most = q_pos - q_low;
+#pragma unroll
+            for (int n = 0; n < NT; n++)
+#pragma unroll
+                for (int i = 0; i < 16; i++) sc_t[n][i] = at0 + (uint32_t)(KVB * n + 16 * (i / 8) + i % 8) <= most ? sc_t[n][i] : -INFINITY;
+        }
+        uint32_t ph[NT][8], pl[NT][F16 ? 1 : 8];
+        auto exponentials = [&]() __attribute__((always_inline)) {
+            float sum = 0.f;
+#pragma unroll
+            for (int n = 0; n < NT; n++)
+#pragma unroll
+                for (int i = 0; i < 16; i += 2) {
+                    const float p0 = fast_exp2(sc_t[n][i]), p1 = fast_exp2(sc_t[n][i + 1]);      // masked: exp2(-inf) = 0
+                    sum += p0 + p1;
+                    if constexpr (F16) ph[n][i / 2] = pack2_f16(p0, p1);
+                    else ph[n][i / 2] = split2_bf16(p0, p1, pl[n][i / 2]);
+                }
+            return sum;
+        };
+        float psum = exponentials();
+        // m is the reference the exponents are taken against, not necessarily the running maximum: the maximum is looked for, and
+        // m moved up to it, only where a lane's sum has grown past what fp16 surely holds (a sum of 256 over 32 positions has a term
+        // of at least 2^3), or where a row has seen nothing yet.  o, l and m stay consistent, which is all the final division and
+        // the split merge need.
+        if (__any(!(psum <= 256.f) || !(m > -INFINITY))) {
+            float mb = -INFINITY;      // relative to m
 #pragma unroll
             for (int n = 0; n < NT; n++)
 #pragma unroll
                 for (int i = 0; i < 16; i++) mb = fmaxf(mb, sc_t[n][i]);
-        } else {
-#pragma unroll
-            for (int n = 0; n < NT; n++)
-#pragma unroll
-                for (int i = 0; i < 16; i++) {
-                    const int kv_pos = kv0 + KVB * n + 16 * (i / 8) + 8 * half + (i % 8);
-                    const bool ok = q_valid && kv_pos <= q_pos && kv_pos >= q_low;
-                    sc_t[n][i] = ok ? sc_t[n][i] : -INFINITY;
-                    mb = fmaxf(mb, sc_t[n][i]);
-                }
-        }
-        {      // the other half of the wave holds the query's other scores
+            // the other half of the wave holds the query's other scores
             const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(mb), __float_as_uint(mb), false, false);
             mb = fmaxf(__uint_as_float(both[0]), __uint_as_float(both[1]));
-        }
-        // m is the reference the exponents are taken against, not necessarily the running maximum: it moves up
-        // only when the maximum has outgrown it by more than 2^8, so p stays below 256 and the accumulators
-        // are rescaled on few steps instead of most.  o, l and m stay consistent, which is all the final
-        // division and the split merge need.  (mb is relative to m_in.)
-        const bool first = !(m > -INFINITY), move = first ? mb > -INFINITY : mb > 8.f;
-        float sc = 1.f;
-        const bool any_move = __any(move);
-        if (any_move) {
-            const float up = move ? mb : 0.f;
-            sc = first ? (move ? 0.f : 1.f) : fast_exp2(-up);
-            if (move) m = m_in + up;
+            const bool first = !(m > -INFINITY), move = first ? mb > -INFINITY : mb > 3.f;
+            const float up = move ? mb : 0.f, sc = first ? (move ? 0.f : 1.f) : fast_exp2(-up);
+            if (move) m = (first ? 0.f : m) + up;
+#pragma unroll
+            for (int i = 0; i < 16; i++) less_m[i] = m > -INFINITY ? -m : 0.f;
 #pragma unroll
             for (int n = 0; n < NT; n++)
 #pragma unroll
                 for (int i = 0; i < 16; i++) sc_t[n][i] -= up;
             l *= sc;
-        }
-        uint32_t ph[NT][8], pl[NT][F16 ? 1 : 8];
-        float psum = 0.f;
 #pragma unroll
-        for (int n = 0; n < NT; n++)
-#pragma unroll
-            for (int i = 0; i < 16; i += 2) {
-                const float p0 = fast_exp2(sc_t[n][i]), p1 = fast_exp2(sc_t[n][i + 1]);      // masked: exp2(-inf) = 0
-                psum += p0 + p1;
-                if constexpr (F16) ph[n][i / 2] = pack2_f16(p0, p1);      // p <= 2^8: well inside fp16
-                else ph[n][i / 2] = split2_bf16(p0, p1, pl[n][i / 2]);
-            }
-        l += psum;
-        // ---- O^T = O^T * sc + V^T P^T; the rescale is skipped when no query of the wave moved its reference
-        __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-        for (int nt = 0; nt < 4; nt++) {
-            if (any_move) {
+            for (int nt = 0; nt < 4; nt++)
 #pragma unroll
                 for (int i = 0; i < 16; i++) o[nt][i] *= sc;
+            psum = exponentials();
+        }
+        l += psum;
+        // ---- O^T += V^T P^T
+        // slot e of this lane <-> position kv0 + 32*n + 16*mm + 8*half + e; operand i: step i / 8, half i / 4 % 2 of it, dimensions 32 (i % 4) + l32
+        auto value = [&](int i) __attribute__((always_inline)) {
+            f[i % RD] = *reinterpret_cast<const u32x4 *>(&vt[st][u0 + i / 8][i % 4 * 32 + l32][16 * (i / 4 % 2) + 8 * half]);
+        };
+#pragma unroll
+        for (int i = 0; i < RD; i++) value(i);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int i = 0; i < 8 * NT; i++) {
+            const int n = i / 8, mm = i / 4 % 2, nt = i % 4;
+            const u32x4 va = f[i % RD];
+            const u32x4 pbh = (u32x4){ph[n][4 * mm], ph[n][4 * mm + 1], ph[n][4 * mm + 2], ph[n][4 * mm + 3]};
+            if constexpr (F16) {
+                o[nt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, va), __builtin_bit_cast(f16x8, pbh), o[nt], 0, 0, 0);
+            } else {
+                const u32x4 pbl = (u32x4){pl[n][4 * mm], pl[n][4 * mm + 1], pl[n][4 * mm + 2], pl[n][4 * mm + 3]};
+                o[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, va), __builtin_bit_cast(bf16x8, pbh), o[nt], 0, 0, 0);
+                o[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, va), __builtin_bit_cast(bf16x8, pbl), o[nt], 0, 0, 0);
             }
-#pragma unroll
-            for (int n = 0; n < NT; n++)
-#pragma unroll
-                for (int mm = 0; mm < 2; mm++) {
-                    // slot e of this lane <-> position kv0 + 32*n + 16*mm + 8*half + e
-                    const u32x4 va = *reinterpret_cast<const u32x4 *>(&vt[st][u0 + n][nt * 32 + l32][16 * mm + 8 * half]);
-                    const u32x4 pbh = (u32x4){ph[n][4 * mm], ph[n][4 * mm + 1], ph[n][4 * mm + 2], ph[n][4 * mm + 3]};
-                    if constexpr (F16) {
-                        o[nt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, va), __builtin_bit_cast(f16x8, pbh), o[nt], 0, 0, 0);
-                    } else {
-                        const u32x4 pbl = (u32x4){pl[n][4 * mm], pl[n][4 * mm + 1], pl[n][4 * mm + 2], pl[n][4 * mm + 3]};
-                        o[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, va), __builtin_bit_cast(bf16x8, pbh), o[nt], 0, 0, 0);
-                        o[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, va), __builtin_bit_cast(bf16x8, pbl), o[nt], 0, 0, 0);
-                    }
-                }
+            if (i + RD < 8 * NT) value(i + RD);
+            __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_s_setprio(0);
     };
@@ -379,6 +405,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
     // last, its unwritten slots pass for visible positions: neither as values nor for the range check.
     if (kv_begin < first_held_pos) kreg[0][0] = vreg[0][0] = (u32x4){0u, 0u, 0u, 0u};
     look_up(kv_begin + 2 * KVB);
+    lds_barrier();      // the tiles take the queries' place
     int st = 0;
     for (int kv0 = kv_begin; kv0 < kv_end; kv0 += 2 * KVB) {
         // Stage this unit, then fetch the next.  One barrier per unit: a wave that writes buffer st for unit n has passed
@@ -402,19 +429,19 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
     // the two halves of a query's scores were summed separately
     l += __shfl_xor(l, 32, WAVE);
     if constexpr (F16) {
-        if (out_of_range || !(mag <= 65504.f)) *f16_flag = 1;      // a magnitude that fp16 cannot hold, or a NaN
+        if (!(mag <= 65504.f)) *f16_flag = 1;      // a magnitude that fp16 cannot hold, or a NaN
     }
-    if (!whole) {      // unnormalised share: [tile][row in tile][head][split][HD] and (m, l)
+    if (!whole) {      // unnormalised share
         if (q_valid) {
-            const int64_t item = (((int64_t)tile_idx * 128 + qi) * H + h) * gridDim.z + split;
-            float *op = part_o + item * HD;
+            const int64_t item = ((int64_t)tile_idx * H + h) * gridDim.z + split;
+            float *op = part_o + item * 128 * HD;
 #pragma unroll
             for (int nt = 0; nt < 4; nt++)
 #pragma unroll
                 for (int a = 0; a < 4; a++)
-                    *reinterpret_cast<float4 *>(op + nt * 32 + 8 * a + 4 * half) =
+                    *reinterpret_cast<float4 *>(op + part_place(qi, 4 * nt + a, half)) =
                         make_float4(o[nt][4 * a], o[nt][4 * a + 1], o[nt][4 * a + 2], o[nt][4 * a + 3]);
-            if (half == 0) { part_ml[item * 2] = m; part_ml[item * 2 + 1] = l; }
+            if (half == 0) *reinterpret_cast<float2 *>(part_ml + (item * 128 + qi) * 2) = make_float2(m, l);
         }
         return;
     }
@@ -449,8 +476,8 @@ __global__ __launch_bounds__(256) void k_attn_prefill_merge(const int4 *__restri
     const int n = min((tile_steps(tile, window) + per - 1) / per, ns);
     const int r = blockIdx.z * 8 + (threadIdx.x >> 5), h = blockIdx.x, sub = threadIdx.x & 31;
     if (n <= 1 || r >= tile.y) return;
-    const int64_t base = (((int64_t)blockIdx.y * 128 + r) * H + h) * ns;
-    const float2 ml = sub < n ? *reinterpret_cast<const float2 *>(part_ml + (base + sub) * 2) : make_float2(-INFINITY, 0.f);
+    const int64_t base = ((int64_t)blockIdx.y * H + h) * ns;
+    const float2 ml = sub < n ? *reinterpret_cast<const float2 *>(part_ml + ((base + sub) * 128 + r) * 2) : make_float2(-INFINITY, 0.f);
     float M = ml.x;
 #pragma unroll
     for (int off = 1; off < MAX_SPLITS; off <<= 1) M = fmaxf(M, __shfl_xor(M, off, WAVE));
@@ -459,7 +486,7 @@ __global__ __launch_bounds__(256) void k_attn_prefill_merge(const int4 *__restri
     float L = 0.f;
     for (int z = 0; z < n; z++) {
         const float a = __shfl(weight, z, 32);
-        const float4 v = *reinterpret_cast<const float4 *>(part_o + (base + z) * HD + sub * 4);
+        const float4 v = *reinterpret_cast<const float4 *>(part_o + (base + z) * 128 * HD + part_place(r, sub >> 1, sub & 1));
         o.x += a * v.x; o.y += a * v.y; o.z += a * v.z; o.w += a * v.w;
         L += a * __shfl(ml.y, z, 32);
     }
