@@ -60,12 +60,16 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+typedef __attribute__((ext_vector_type(2))) uint16_t u16x2;
 
 constexpr int HD = 128;
 constexpr int KVB = 32;          // kv positions per step
 constexpr int KLD = HD + 8;      // LDS row stride of the key tile (elements): 272 bytes, conflict-free 16-byte reads
 constexpr int MAX_SPLITS = 16;   // shares of a tile's KV steps, at most
+constexpr int FEW_ROWS = 16;     // tiles of up to so many rows take few_rows()
 constexpr int VLD = KVB + 8;     // LDS row stride of the transposed value tile (elements): 80 bytes
 
 __device__ __forceinline__ int tau(int r) { return (r & 19) | ((r & 4) << 1) | ((r & 8) >> 1); }
@@ -106,14 +110,14 @@ __device__ __forceinline__ int part_place(int row, int d8, int hi) { return (((r
 __device__ __forceinline__ int tile_start(const int4 &tile, int window) { return window > 0 ? (max(tile.z - window + 1, 0) & ~(KVB - 1)) : 0; }
 __device__ __forceinline__ int tile_steps(const int4 &tile, int window) { return (tile.z + tile.y - 1 - tile_start(tile, window)) / KVB + 1; }
 
-// The tile that comes rank-th when they are sorted by their steps (longest first, ties by index), and its index; more than a
-// wave's lanes of them stay in their own order.
+// The tile that comes rank-th when they are sorted by their steps (longest first, those of few rows, which take a fraction of the time, last;
+// ties by index), and its index; more than a wave's lanes of them stay in their own order.
 __device__ __forceinline__ int4 nth_longest(const int4 *__restrict__ tiles, int n_tiles, int window, int rank, int &index) {
     index = rank;
     if (n_tiles == 1 || n_tiles > WAVE) return tiles[rank];
     const int lane = threadIdx.x & 63;
     const int4 t = tiles[min(lane, n_tiles - 1)];
-    const int own = tile_steps(t, window);
+    const int own = t.y <= FEW_ROWS ? 0 : tile_steps(t, window);
     int before = 0;
     for (int i = 0; i < n_tiles; i++) {
         const int other = __builtin_amdgcn_readlane(own, i);
@@ -122,6 +126,214 @@ __device__ __forceinline__ int4 nth_longest(const int4 *__restrict__ tiles, int 
     index = __ffsll(__ballot(lane < n_tiles && before == rank)) - 1;
     return make_int4(__builtin_amdgcn_readlane(t.x, index), __builtin_amdgcn_readlane(t.y, index), __builtin_amdgcn_readlane(t.z, index),
                      __builtin_amdgcn_readlane(t.w, index));
+}
+
+// Tiles of up to FEW_ROWS rows, which are not worth the staging (a 257-row segment ends in a tile of one row, whose walk took as long as
+// half a full tile's): each wave walks every fourth step of the share by itself.  Four segments of 257 rows behind 2.2k .. 6.4k, GQA 4:1:
+// 126 -> 119 us; eight lone 5-row tiles of 32 heads 50 -> 26 in two terms; 135 sets of tiles 4 % faster in the mean in two terms.  Arithmetic and operands as in the decode kernel for
+// grouped heads, a row of the tile in place of a head (two bf16 terms in both forms; in F16 the range is checked all the same).
+union FewLds {
+    char keys[4][4096];      // a block's keys on their way to operands, of each wave
+    struct { float o[4][FEW_ROWS][HD + 4], ml[4][FEW_ROWS][2]; } waves;
+};
+template <bool F16>
+__device__ __forceinline__ void few_rows(const float *__restrict__ q, int q_stride, const bf16_t *__restrict__ pool, int Hkv, const int32_t *__restrict__ trow,
+                                         const int4 &tile, int h, int H, int kvh, int window, float scale_log2e, int kv_begin, int kv_end,
+                                         FewLds &lds, float *__restrict__ part_o, float *__restrict__ part_ml, float *__restrict__ out,
+                                         const ld::OperandImage &image, int *__restrict__ f16_flag) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = lane & 15, rg = lane >> 4;      // column of the 16 x 16 tiles: row of the tile
+    const int last = tile.z + tile.y - 1, first_held = window > 0 ? (max(tile.z - window + 1, 0) & ~15) : 0;
+    const int row = min(c, tile.y - 1), pos = tile.z + row, low = window > 0 ? max(pos - window + 1, 0) : 0;
+    const int low_last = window > 0 ? max(last - window + 1, 0) : 0;      // all rows see [low_last, tile.z]
+    const int64_t block_stride = kv_block_elems(Hkv, HD);
+    float mag = 0.f;
+    u16x2 most = {0, 0};      // F16: largest magnitudes of the keys and values
+    bf16x8 qh[4], ql[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        float v[8];
+        load8(q + (int64_t)(tile.x + row) * q_stride + h * HD + 32 * j + 8 * rg, v);
+        u32x4 hw, lw;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const float a = v[2 * e] * scale_log2e, b = v[2 * e + 1] * scale_log2e;
+            mag = __builtin_elementwise_maximum(__builtin_elementwise_maximum(mag, fabsf(a)), fabsf(b));
+            uint32_t lo;
+            hw[e] = split2_bf16(a, b, lo);
+            lw[e] = lo;
+        }
+        qh[j] = __builtin_bit_cast(bf16x8, hw);
+        ql[j] = __builtin_bit_cast(bf16x8, lw);
+    }
+    f32x4 o[8];      // O^T: dims 16 nt + 4 rg + i of column c
+#pragma unroll
+    for (int nt = 0; nt < 8; nt++) o[nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;
+    // piece p (8 dims) of slot s sits in slot p ^ s of its 256-byte row
+    char *tk = lds.keys[wave], *tk_st[4];
+    const char *tk_ld[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        const int sl = 4 * j + rg;
+        tk_st[j] = tk + sl * 256 + ((c ^ sl) & 15) * 16;
+        tk_ld[j] = tk + c * 256 + ((sl ^ c) & 15) * 16;
+    }
+    const int steps = (kv_end - kv_begin + KVB - 1) / KVB, mine = (steps - wave + 3) / 4;      // of the share, of this wave
+    u32x4 kf[2][4];
+    u32x2 vf[8][2];
+    for (int s0 = 0; s0 < mine; s0 += 32) {      // a lane has the table's entry of one of the next 64 blocks
+        const int entry = trow[max(min((kv_begin >> 4) + 2 * (wave + 4 * (s0 + (lane >> 1))) + (lane & 1), last >> 4), first_held >> 4)];
+        const int k = min(mine - s0, 32);
+        auto block = [&](int t, int u) __attribute__((always_inline)) { return pool + (int64_t)__builtin_amdgcn_readlane(entry, 2 * t + u) * block_stride; };
+        auto load_keys = [&](int t, int u) __attribute__((always_inline)) {
+            const bf16_t *kp = block(t, u) + kv_k_offset(HD, kvh, 0, 0) + 8 * lane;
+#pragma unroll
+            for (int j = 0; j < 4; j++) kf[u][j] = *reinterpret_cast<const u32x4 *>(kp + 512 * j);
+        };
+        auto load_values = [&](int t, int u) __attribute__((always_inline)) {
+            const bf16_t *vp = block(t, u) + kv_v_offset(Hkv, HD, kvh, 4 * rg, c);
+#pragma unroll
+            for (int nt = 0; nt < 8; nt++) vf[nt][u] = *reinterpret_cast<const u32x2 *>(vp + nt * 256);
+        };
+#pragma unroll
+        for (int u = 0; u < 2; u++) { load_keys(0, u); load_values(0, u); }
+        for (int t = 0; t < k; t++) {
+            // the next step's keys are asked for when this one's are in LDS, its values when this one's are multiplied (the last step's
+            // again behind it: without a condition)
+            const int kv0 = kv_begin + KVB * (wave + 4 * (s0 + t)), next = min(t + 1, k - 1);
+            if (kv0 + KVB - 1 > last || kv0 < first_held) {      // what was never written, or stands for a block that is not there
+#pragma unroll
+                for (int u = 0; u < 2; u++) {
+#pragma unroll
+                    for (int j = 0; j < 4; j++) {
+                        const int p = kv0 + 16 * u + 4 * j + rg;
+                        if (p > last || p < first_held) kf[u][j] = (u32x4){0u, 0u, 0u, 0u};
+                    }
+#pragma unroll
+                    for (int nt = 0; nt < 8; nt++)
+#pragma unroll
+                        for (int e = 0; e < 4; e++) {
+                            const int p = kv0 + 16 * u + 4 * rg + e;
+                            if (p > last || p < first_held) vf[nt][u][e / 2] &= e % 2 ? 0x0000ffffu : 0xffff0000u;
+                        }
+                }
+            }
+            if constexpr (F16) {      // as whole numbers: a NaN is the largest
+                auto look = [&](uint32_t w) { most = __builtin_elementwise_max(most, __builtin_bit_cast(u16x2, w & 0x7fff7fffu)); };
+#pragma unroll
+                for (int u = 0; u < 2; u++) {
+#pragma unroll
+                    for (int j = 0; j < 4; j++)
+#pragma unroll
+                        for (int e = 0; e < 4; e++) look(kf[u][j][e]);
+#pragma unroll
+                    for (int nt = 0; nt < 8; nt++) { look(vf[nt][u][0]); look(vf[nt][u][1]); }
+                }
+            }
+            f32x4 sc[2];
+#pragma unroll
+            for (int u = 0; u < 2; u++) {
+                sc[u] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int j = 0; j < 4; j++) *reinterpret_cast<u32x4 *>(tk_st[j]) = kf[u][j];
+                load_keys(next, u);
+                __builtin_amdgcn_wave_barrier();
+                u32x4 kt[4];
+#pragma unroll
+                for (int j = 0; j < 4; j++) kt[j] = *reinterpret_cast<const u32x4 *>(tk_ld[j]);
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    const bf16x8 ka = __builtin_bit_cast(bf16x8, kt[j]);
+                    sc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qh[j], sc[u], 0, 0, 0);
+                    sc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, ql[j], sc[u], 0, 0, 0);
+                }
+            }
+            if (kv0 + KVB - 1 > tile.z || kv0 < low_last) {      // element i of block u is position kv0 + 16 u + 4 rg + i
+#pragma unroll
+                for (int u = 0; u < 2; u++)
+#pragma unroll
+                    for (int i = 0; i < 4; i++) sc[u][i] = (uint32_t)(kv0 + 16 * u + 4 * rg + i - low) <= (uint32_t)(pos - low) ? sc[u][i] : -INFINITY;
+            }
+            float mb = -INFINITY;
+#pragma unroll
+            for (int u = 0; u < 2; u++)
+#pragma unroll
+                for (int i = 0; i < 4; i++) mb = fmaxf(mb, sc[u][i]);
+            mb = fmaxf(mb, __shfl_xor(mb, 16, WAVE));
+            mb = fmaxf(mb, __shfl_xor(mb, 32, WAVE));
+            const float m_new = fmaxf(m, mb), ref = m_new > -INFINITY ? m_new : 0.f;
+            const float scale = m > -INFINITY ? fast_exp2(m - ref) : 0.f;      // (o and l are zero with m)
+            m = m_new;
+            float p[8], psum = 0.f;
+#pragma unroll
+            for (int u = 0; u < 2; u++)
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    p[4 * u + i] = fast_exp2(sc[u][i] - ref);
+                    psum += p[4 * u + i];
+                }
+            l = l * scale + psum;
+            u32x4 ph, pl;
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                uint32_t lo;
+                ph[e] = split2_bf16(p[2 * e], p[2 * e + 1], lo);
+                pl[e] = lo;
+            }
+            const bool rescale = __any(scale != 1.f);
+#pragma unroll
+            for (int nt = 0; nt < 8; nt++) {
+                if (rescale) {
+#pragma unroll
+                    for (int i = 0; i < 4; i++) o[nt][i] *= scale;
+                }
+                const bf16x8 va = __builtin_bit_cast(bf16x8, (u32x4){vf[nt][0][0], vf[nt][0][1], vf[nt][1][0], vf[nt][1][1]});
+                o[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, __builtin_bit_cast(bf16x8, ph), o[nt], 0, 0, 0);
+                o[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, __builtin_bit_cast(bf16x8, pl), o[nt], 0, 0, 0);
+            }
+#pragma unroll
+            for (int u = 0; u < 2; u++) load_values(next, u);
+        }
+    }
+    if constexpr (F16) {
+        mag = __builtin_elementwise_maximum(__builtin_elementwise_maximum(mag, bf16_to_f32(most[0])), bf16_to_f32(most[1]));
+        if (!(mag <= 65504.f)) *f16_flag = 1;
+    }
+    l += __shfl_xor(l, 16, WAVE);
+    l += __shfl_xor(l, 32, WAVE);
+    lds_barrier();      // every wave is done with its keys
+    if (c < tile.y) {
+#pragma unroll
+        for (int nt = 0; nt < 8; nt++) *reinterpret_cast<float4 *>(&lds.waves.o[wave][c][16 * nt + 4 * rg]) = make_float4(o[nt][0], o[nt][1], o[nt][2], o[nt][3]);
+        if (rg == 0) *reinterpret_cast<float2 *>(lds.waves.ml[wave][c]) = make_float2(m, l);
+    }
+    lds_barrier();
+    for (int idx = threadIdx.x; idx < tile.y * (HD / 4); idx += 256) {
+        const int r = idx / (HD / 4), d = idx % (HD / 4) * 4;
+        float M = -INFINITY, L = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; w++) M = fmaxf(M, lds.waves.ml[w][r][0]);
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int w = 0; w < 4; w++) {      // a wave that saw no visible position has weight 0
+            const float mw = lds.waves.ml[w][r][0], a = mw > -INFINITY ? fast_exp2(mw - M) : 0.f;
+            const float4 x = *reinterpret_cast<const float4 *>(&lds.waves.o[w][r][d]);
+            v.x += a * x.x; v.y += a * x.y; v.z += a * x.z; v.w += a * x.w;
+            L += a * lds.waves.ml[w][r][1];
+        }
+        if (part_o) {
+            *reinterpret_cast<float4 *>(part_o + part_place(r, d >> 3, (d >> 2) & 1)) = v;
+            if (d == 0) *reinterpret_cast<float2 *>(part_ml + r * 2) = make_float2(M, L);
+        } else {
+            const float inv = 1.0f / L;
+            v = make_float4(mul_rounded(v.x, inv), mul_rounded(v.y, inv), mul_rounded(v.z, inv), mul_rounded(v.w, inv));
+            const int64_t e = ((int64_t)(tile.x + r) * H + h) * HD + d;
+            if (image.hi) store_operand4(image, tile.x + r, e, v);
+            else *reinterpret_cast<float4 *>(out + e) = v;
+        }
+    }
 }
 
 // F16 (the long passes whose rows the engine lets enter the products rounded to fp16): queries and probabilities as
@@ -138,7 +350,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
                                                          ld::OperandImage image, int *__restrict__ f16_flag) {
     struct Tiles { bf16_t ks[2][2][KVB][KLD], vt[2][2][HD][VLD]; };      // [buffer][step of the unit]
     struct Queries { bf16_t part[4][F16 ? 1 : 2][32][KLD]; };              // [wave][term]: ahead of them
-    __shared__ __attribute__((aligned(16))) union Lds { Tiles tiles; Queries queries; } lds;
+    __shared__ __attribute__((aligned(16))) union Lds { Tiles tiles; Queries queries; FewLds few; } lds;
     auto &ks = lds.tiles.ks;
     auto &vt = lds.tiles.vt;
     // Work items longest first: shares in order, in each the tiles by their length, heads fastest.  Two workgroups share a
@@ -162,6 +374,12 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
     const int kv_start = tile_start(tile, window);
     const int kv_begin = kv_start + split * per * KVB;
     const int kv_end = split + 1 == gridDim.z ? wg_last_pos + 1 : min(kv_begin + per * KVB, wg_last_pos + 1);      // exclusive; the last share takes what is left
+    if (tile.y <= FEW_ROWS) {
+        const int64_t item = ((int64_t)tile_idx * H + h) * gridDim.z + split;
+        few_rows<F16>(q, q_stride, pool, Hkv, trow, tile, h, H, kvh, window, scale_log2e, kv_begin, kv_end, lds.few, whole ? nullptr : part_o + item * 128 * HD,
+                      part_ml + item * 256, out, image, f16_flag);
+        return;
+    }
 
     // this lane's query: row index inside the tile, validity, absolute position
     const int qi = wave * 32 + l32;

@@ -1061,6 +1061,58 @@ def test_prefill_attention_moving_maximum(growth, rows, window):
 
 
 @pytest.mark.parametrize("split", [False, True], ids=["whole", "kv-split"])
+@pytest.mark.parametrize("window", [0, 1, 50, 4500])
+@pytest.mark.parametrize("H,Hkv", [(3, 3), (8, 1)])
+def test_prefill_attention_few_rows(H, Hkv, window, split):
+    """Tiles of up to 16 rows, whose waves walk every fourth step of a share by themselves, and the first beyond them: 1, 2, 15, 16 and 17
+    rows alone and behind a full tile; last positions just before, at and behind a block's and a step's end; walks of fewer steps
+    than waves and, at 4200 and 8300 positions, of more than the 32 that a wave looks up at a time.  What was never written
+    is NaN.  Both forms against the oracle: the tiles of up to 16 rows take two terms in both, so the bound of the two-term form holds for them."""
+    hd = 128
+    segs = [(0, 1), (14, 1), (15, 2), (30, 1), (31, 15), (97, 15), (112, 16), (113, 16), (90, 17), (0, 16), (200, 129), (75, 144), (60, 145), (4200, 16), (8300, 3)]
+    lens = [p + n for p, n in segs]
+    table, pool, _ = _attention_case(61, lens, H, Hkv, hd, "bf16")
+    T = sum(n for _, n in segs)
+    q = gen.normal(61, 9, (T, H, hd), device=DEV)
+    tiles, row_seq, row_pos, few, r = [], [], [], [], 0
+    for s, (p0, n) in enumerate(segs):
+        for off in range(0, n, 128):
+            tiles.append([r + off, min(128, n - off), p0 + off, s])
+            few += [tiles[-1][1] <= 16] * tiles[-1][1]
+        row_seq += [s] * n; row_pos += list(range(p0, p0 + n)); r += n
+    tiles_d, flag = torch.tensor(tiles, dtype=torch.int32, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
+    scratch = torch.empty(ld.ldk_prefill_attention_scratch_bytes(), dtype=torch.uint8, device=DEV) if split else None
+    out, out16 = torch.zeros(T, H, hd, device=DEV), torch.zeros(T, H, hd, device=DEV)
+    args = (H * hd, device_pool(pool), table.to(DEV), tiles_d, H, Hkv, hd)
+    ld.ldk_prefill_attention(q, *args, out, max(row_pos), window=window, scratch=scratch)
+    ld.ldk_prefill_attention_f16(q, *args, out16, max(row_pos), flag, window=window, scratch=scratch)
+    assert int(flag.item()) == 0
+    ph = oracle.to_host_matrix(pool.reshape(pool.shape[0], -1)).reshape(-1)
+    ref = oracle.paged_attention(q.cpu().numpy(), ph, ph[Hkv * 16 * hd:], (2 * Hkv * 16 * hd, 16 * hd, hd),
+                                 table.numpy()[row_seq], [p + 1 for p in row_pos], Hkv, window=window)
+    for got, bound in ((out, 3e-5), (out16, np.where(few, 3e-5, 1e-3))):
+        err = np.max(np.abs(got.cpu().numpy() - ref), axis=(1, 2)) / np.abs(ref).max()
+        assert np.all(err <= bound), (err.max(), int(err.argmax()), row_pos[int(err.argmax())])
+
+
+@pytest.mark.parametrize("what", [float("nan"), -float("inf"), 65536.0, 65280.0])
+@pytest.mark.parametrize("part", [0, 1], ids=["key", "value"])
+@pytest.mark.parametrize("pos", [95, 96, 111, 127, 128, 157, 171, 172, 175])
+def test_prefill_attention_few_rows_fp16_range_check(what, part, pos):
+    """The flag of the fp16 form in a tile of 11 rows at 161 .. 171 with a band of 61: raised by what the walk touches, from the first
+    block that the band holds (position 96) to the last row's position, as in the larger tiles; not by the rest of the last block."""
+    H, hd, lens = 2, 128, [172]
+    table, pool, _ = _attention_case(53, lens, H, H, hd, "bf16")
+    q = gen.normal(53, 9, (11, H, hd), device=DEV)
+    tiles = torch.tensor([[0, 11, 161, 0]], dtype=torch.int32, device=DEV)
+    pool = pool.clone()
+    pool[int(table[0, pos // 16]), part, 1, pos % 16, 17] = what
+    flag, out = torch.zeros(1, dtype=torch.int32, device=DEV), torch.zeros(11, H, hd, device=DEV)
+    ld.ldk_prefill_attention_f16(q, H * hd, device_pool(pool), table.to(DEV), tiles, H, H, hd, out, 171, flag, window=61)
+    assert int(flag.item()) == (what != 65280.0 and 96 <= pos <= 171)
+
+
+@pytest.mark.parametrize("split", [False, True], ids=["whole", "kv-split"])
 @pytest.mark.parametrize("window", [0, 1, 40, 128, 200, 5000])
 @pytest.mark.parametrize("H,Hkv", [(4, 4), (8, 2)])
 def test_prefill_attention_segments(H, Hkv, window, split):
