@@ -431,23 +431,29 @@ int cu_count() {
 }
 // Tile, workgroup count and split-K factor of the big-tile kernel for a row count: the candidate with the smallest
 // estimated time.  Workgroups run in rounds of one per CU (256 of them); a round takes the tile's time per 64-wide chunk of K
-// times its chunks, a last round that leaves CUs idle a little less (the others draw less power and run faster: 0.27 of the idle
-// share in two terms, 0.31 in one); split-K adds the write and the ordered re-read of its partial sums.  The constants are
-// fitted to every tile and split of the 7B, grouped-KV and 13B layer shapes, 8192 x 8192 and 3000 x 3072 at 72 - 500 rows (two
-// terms) and 512 - 2111 (one): the choice is 1.0 % (1.4 %) slower than the best pair in the mean, 11 % (17 %) at worst.  With
-// six and four tiles instead of ten and eight the best pair would be 2.5 % (3.1 %) slower in the mean, 21 % (16 %) at worst.
+// times its chunks, a last round that leaves CUs idle a little less (the others draw less power and run faster: 0.16 of the idle
+// share in two terms, 0.27 in one); split-K adds the write and the ordered re-read of its partial sums.  The constants are
+// fitted to the tiles and splits of the 7B, grouped-KV and 13B layer shapes at 80 - 480 rows (two terms) and 512 - 2048 (one): the
+// choice is 1.2 % (1.0 %) slower than the best pair in the mean, 12 % (7 %) at worst; that of the constants before tiles had three stages is
+// 2.2 % (1.8 %) slower.  With six and four tiles instead of ten and eight the best pair would be some 3 % slower in the mean.
 struct BigPlan { int bm, bn, n_ttiles, n_nblocks, ks; double est_us; };
 struct Tile { int bm, bn; bool swiglu; double chunk_us; };
 #define LD_TILE_ROW(AT_, BT_, US_) {32 * AT_, 32 * BT_, BT_ % 2 == 0, US_},
 const Tile tiles_two[] = {LD_TILES_TWO(LD_TILE_ROW)};
 const Tile tiles_f16[] = {LD_TILES_F16(LD_TILE_ROW)};
+// the times that a rule on results (which rows keep both terms, see tail_rows) stays with
+const Tile tiles_f16_rule[] = {{128, 192, true, 0.74}, {128, 256, true, 0.99}, {192, 192, true, 1.05}, {192, 256, true, 1.23},
+                               {224, 256, true, 1.40}, {256, 160, false, 1.14}, {256, 192, true, 1.23}, {256, 256, true, 1.54}};
 #undef LD_TILE_ROW
-BigPlan plan_big(int T, int N, int K, int epi, bool f16 = false, bool *ignored = nullptr) {
+struct Costs { const Tile *first, *end; double idle, us_per_mb; };
+const Costs costs_two{std::begin(tiles_two), std::end(tiles_two), 0.16, 0.53};
+const Costs costs_f16{std::begin(tiles_f16), std::end(tiles_f16), 0.27, 0.46};
+const Costs costs_f16_rule{std::begin(tiles_f16_rule), std::end(tiles_f16_rule), 0.31, 0.44};
+BigPlan plan_big(int T, int N, int K, int epi, const Costs &costs, bool *ignored = nullptr) {
     const bool swi = epi == ld::GEMM_SWIGLU;
-    const double idle = f16 ? 0.31 : 0.27, us_per_mb = 0.44;
     BigPlan best{};
     double best_t = 1e30;
-    const Tile *first = f16 ? std::begin(tiles_f16) : std::begin(tiles_two), *end = f16 ? std::end(tiles_f16) : std::end(tiles_two);
+    const Tile *first = costs.first, *end = costs.end;
     // tuning knob: "rows,columns,ks" of a tile (rows 2, 4: 128, 256); what is no plan of this form is ignored (see gemm_rows)
     const char *forced = getenv("LD_GEMM_BIG");
     int f_bm = 0, f_bn = 0, f_ks = 0;
@@ -464,13 +470,16 @@ BigPlan plan_big(int T, int N, int K, int epi, bool f16 = false, bool *ignored =
         for (int ks = 1; ks <= max_ks; ks++) {
             if (known && ks != std::min(f_ks, max_ks)) continue;
             const int64_t wgs = (int64_t)n_tt * n_nb * ks;
-            const double rounds = (double)(wgs / 256) + (wgs % 256 ? 1.0 - idle * (1.0 - (wgs % 256) / 256.0) : 0.0);
+            const double rounds = (double)(wgs / 256) + (wgs % 256 ? 1.0 - costs.idle * (1.0 - (wgs % 256) / 256.0) : 0.0);
             double t = rounds * tl->chunk_us * ((K / 64 + ks - 1) / ks);
-            if (ks > 1) t += 2.0 + us_per_mb * 4e-6 * T * N * (swi ? 2 : 1) * ks;
+            if (ks > 1) t += 2.0 + costs.us_per_mb * 4e-6 * T * N * (swi ? 2 : 1) * ks;
             if (t < best_t) { best_t = t; best = {tl->bm, tl->bn, n_tt, n_nb, ks, t}; }
         }
     }
     return best;
+}
+BigPlan plan_big(int T, int N, int K, int epi, bool f16 = false, bool *ignored = nullptr) {
+    return plan_big(T, N, K, epi, f16 ? costs_f16 : costs_two, ignored);
 }
 
 // Most rows the small-batch kernel takes: four 16-row tiles of X fit a wave's registers beside its fragments.  Feed-
@@ -551,14 +560,15 @@ static bool tail_keeps_both_terms(int T, int r, int N, int K, int epi) {
 
 // Rows that would only start one more, nearly empty 256-row tile (a mixed step's 4 x 257 + 28 rows, a 2048-row
 // chunk beside 63 decode rows) are cut off and go through the small-batch kernels where that costs less by the cost model
-// that picks the tile (the weights are streamed once more), and in the one-term form also where the rule above wants them
-// there.  Returns the number of such tail rows (0: no cut).
+// that picks the tile (the weights are streamed once more; in the one-term form the costs of the rule on terms), and in the one-term
+// form also where the rule above wants them there.  Returns the number of such tail rows (0: no cut).
 int tail_rows(int T, int N, int K, int epi, bool f16) {
     const int r = T % 256;
     static const int enabled = env_int("LD_GEMM_TAIL", 1);   // tuning knob: 0 keeps every row in the tiled kernel
     if (!enabled || T <= 256 || r == 0 || r > 64 || getenv("LD_GEMM_BIG")) return 0;
     if (f16 && tail_keeps_both_terms(T, r, N, K, epi)) return r;
-    const double whole = plan_big(T, N, K, epi, f16).est_us, main_part = plan_big(T - r, N, K, epi, f16).est_us;
+    const Costs &costs = f16 ? costs_f16_rule : costs_two;
+    const double whole = plan_big(T, N, K, epi, costs).est_us, main_part = plan_big(T - r, N, K, epi, costs).est_us;
     const double tail = (double)N * (epi == GEMM_SWIGLU ? 2 : 1) * K * 2.0 / 5.2e6 + 10.0;   // ~5.2 TB/s + two launches
     return main_part + tail < whole ? r : 0;
 }

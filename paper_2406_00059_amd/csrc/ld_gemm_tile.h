@@ -18,11 +18,16 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;   // native 16-byte 
 // Tiles of the two forms, in units of 32 rows and 32 columns, and measured us per 64-wide chunk of K.  (Odd column units have
 // no SwiGLU form.)
 #define LD_TILES_TWO(X) \
-    X(3, 4, 0.73) X(3, 6, 1.03) X(3, 8, 1.23) X(4, 4, 0.96) X(4, 6, 1.21) X(4, 8, 1.50) X(5, 6, 1.42) X(5, 8, 1.77) X(6, 6, 1.61) X(6, 8, 2.04)
-#define LD_TILES_F16(X) X(4, 6, 0.74) X(4, 8, 0.99) X(6, 6, 1.05) X(6, 8, 1.23) X(7, 8, 1.40) X(8, 5, 1.14) X(8, 6, 1.23) X(8, 8, 1.54)
+    X(3, 4, 0.66) X(3, 6, 0.79) X(3, 8, 1.00) X(4, 4, 0.74) X(4, 6, 0.98) X(4, 8, 1.18) X(5, 6, 1.13) X(5, 8, 1.35) X(6, 6, 1.27) X(6, 8, 1.56)
+#define LD_TILES_F16(X) X(4, 6, 0.73) X(4, 8, 0.91) X(6, 6, 0.92) X(6, 8, 1.16) X(7, 8, 1.30) X(8, 5, 0.99) X(8, 6, 1.15) X(8, 8, 1.42)
 
 constexpr int TILE_MAX_K = 1 << 23;      // the lane offsets of the copies reach over 256 rows in 32 bits
-constexpr int tile_lds(int terms, int bm, int bn) { return 2 * (terms * bm + bn) * 128; }
+// Stages of K chunks in LDS: three where they fit, else two.  The smallest tiles, two workgroups of which fit a CU with two stages
+// each, keep two where a launch has more than one workgroup a CU (12288 x 4096 at 480 rows in 96 x 128 tiles: 98 us so, 104 with three).
+constexpr int tile_lds(int terms, int bm, int bn, int stages) { return stages * (terms * bm + bn) * 128; }
+constexpr int LDS_BYTES = 160 * 1024;
+constexpr int tile_stages(int terms, int bm, int bn) { return tile_lds(terms, bm, bn, 3) <= LDS_BYTES ? 3 : 2; }
+constexpr bool tile_twice(int terms, int bm, int bn) { return 2 * tile_lds(terms, bm, bn, 2) <= LDS_BYTES; }
 
 // One launch: grid workgroups for n_ttiles row tiles, all column blocks and ks slabs of K.
 struct TileLaunch {

@@ -9,7 +9,7 @@ namespace {
 
 // The big-tile kernel.  Four waves, one per SIMD (512 registers each), two by two, a wave owning AT x BT accumulator
 // tiles of 16 x 16: the fewest operand bytes out of LDS per MFMA that the registers allow.  K advances in chunks of 64
-// (rows of 128 bytes: whole cache lines), two stages, copied straight into LDS (buffer loads with the lds bit: a
+// (rows of 128 bytes: whole cache lines), two or three stages, copied straight into LDS (buffer loads with the lds bit: a
 // scalar base, a lane offset that never changes and a scalar step along K, so that a copy costs no vector
 // arithmetic).
 // What bounds it with real numbers in the operands is the power the matrix cores draw: on zeros 2048 x 8192 x 13824 takes
@@ -17,12 +17,16 @@ namespace {
 // in bf16 with 32 x 32 x 16, 1968 and 2105 with 16 x 16 x 32 (2440 - 2470 both on zeros): half as many accumulator bytes go in
 // and out per product.  Hence the small MFMA: products with their operand passes 2048 x 8192 x 13824 430 -> 401 us,
 // 2048 x 5120 x 13824 339 -> 281, 2111 x 27648 x 5120 568 -> 527, in two terms 152 x 4096 x 11008 54 -> 50.
-// Beside that it is how the copies are issued.  A copy whose turn comes while the CU's address
+// Beside that it is how the copies are issued and how long they have to arrive.  A copy whose turn comes while the CU's address
 // unit is busy holds up the MFMAs behind it, and two stages leave a copy less than a chunk's time to arrive; so
 //  - the operands of a chunk are all in registers before its second half (112 - 128 registers), its stage is free
 //    from then on, and
 //  - the copies of the chunk after next are spread over a whole chunk's MFMAs, a few per k-step, none in a row
 //    (1118 -> 1245 TFLOP/s with the larger MFMA; 1454 without any copies).
+// Where three stages fit (up to 53 KB each) a copy has two chunks' time and a chunk one barrier instead of two: with up to one
+// workgroup a CU 5 - 13 % off the smaller tiles' launches (4096 x 4096 at 1028 rows in fp16, 128 x 192 tiles: 67 -> 58 us; at 300
+// rows in two terms, 96 x 128: 40 -> 35), 0 - 7 % beyond.  Four stages are level with three; reading the operands eight MFMAs
+// ahead of the barrier gives 0.3 % to the larger tiles.
 // The matrix instructions are assembly, issued exactly in the order written here (see tile_mfma_bf16).
 // One copy instruction covers 8 rows x 128 bytes; piece p (16 bytes) of row r sits in slot p ^ ((r >> 1) & 7) of its row:
 // 16 consecutive rows at one p lie in 16 bank groups.
@@ -74,7 +78,7 @@ __device__ __forceinline__ void each_of(std::integer_sequence<int, I...>, F &&f)
 template <int N, typename F>
 __device__ __forceinline__ void each(F &&f) { each_of(std::make_integer_sequence<int, N>{}, f); }
 
-template <int TERMS, int WF, int AT, int BT, int EPI>
+template <int TERMS, int WF, int AT, int BT, int EPI, int S>
 __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16_t *__restrict__ W, const bf16_t *__restrict__ xhi,
                                                       const bf16_t *__restrict__ xlo, int T, int N, int K,
                                                       float *__restrict__ y, int n_ttiles, int ks,
@@ -86,8 +90,9 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16_t *__restrict__
     constexpr int WOUT = SWI ? BT / 2 : BT;           // output column tiles per wave
     constexpr int P = ROWS / 32;                      // copies per wave and chunk: copy j of wave w covers rows (4 j + w) 8 .. + 8
     constexpr int NA = TERMS * AT, NM = NA * BT, NR = NA + BT;      // A tiles, MFMAs and operand reads of a k-step
-    // copies (for the chunk after next) issued in the second half of a chunk; the rest in the first half of the chunk that follows
-    constexpr int PRE = (P * 12 + 15) / 16;
+    // two stages: copies (for the chunk after next) issued in the second half of a chunk; the rest in the first half of the chunk that
+    // follows.  Three: all in the chunk that follows
+    constexpr int PRE = S == 2 ? (P * 12 + 15) / 16 : 0, YOUNGER = (S - 2) * P + PRE;      // copies of the chunks behind the next
     // A tiles of the first k-step that are multiplied after its stage is given up, and of the last one that are multiplied
     // while the next chunk's operands are read
     constexpr int NL = NA >= 4 ? NA / 4 : 1, NF = NA >= 4 ? NA / 4 : 1;
@@ -120,8 +125,8 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16_t *__restrict__
     const BufferCopy from_hi(xhi + (int64_t)t0 * K), from_lo((TERMS == 2 ? xlo : xhi) + (int64_t)t0 * K), from_w(W + (int64_t)n0 * K),
         from_up(W + (int64_t)(SWI ? N + n0 : n0) * K);
     const int c_begin = (int)((int64_t)kz * (K / 64) / ks), n = (int)((int64_t)(kz + 1) * (K / 64) / ks) - c_begin;      // >= 2 chunks
-    auto copy = [&](int c, int j) {      // copy j of chunk c into its stage
-        char *dst = lds + (c & 1) * STAGE + (4 * j + wave) * 1024;
+    auto copy = [&](int c, int st, int j) {      // copy j of chunk c into stage st
+        char *dst = lds + st * STAGE + (4 * j + wave) * 1024;
         const uint32_t off = (uint32_t)(c_begin + min(c, n - 1)) * 128u;
         if (32 * j < BM) from_hi(dst, coff[j], off);
         else if (32 * j < TERMS * BM) from_lo(dst, coff[j], off);
@@ -166,30 +171,38 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16_t *__restrict__
     };
 
 #pragma unroll
-    for (int j = 0; j < P; j++) copy(0, j);
-    // the count below lets the last PRE copies be outstanding: they have to be chunk 1's (arithmetic may cross)
-    __builtin_amdgcn_sched_barrier(7);
+    for (int c = 0; c < S; c++) {
 #pragma unroll
-    for (int j = 0; j < PRE; j++) copy(1, j);
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PRE) : "memory");
+        for (int j = 0; j < (c < S - 1 ? P : PRE); j++) copy(c, c, j);
+        // the count below lets all copies but chunk 0's be outstanding (arithmetic may cross)
+        __builtin_amdgcn_sched_barrier(7);
+    }
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(YOUNGER) : "memory");
     asm volatile("s_barrier" ::: "memory");
     Frags f0, f1;
 #pragma unroll
     for (int r = 0; r < NR; r++) read(f0, 0, 0, r);
     auto none = [](int) {};
     // One loop for all chunks.  Past the last one the copies fetch it again, into the stage that nobody reads any more
-    int i = 0;
+    int i = 0, st = 0;
     do {
-        const int st = i & 1;
+        const int next = st + 1 == S ? 0 : st + 1, last = st == 0 ? S - 1 : st - 1;
         asm volatile("s_nop 1" ::: "memory");      // before the first pass: the cleared accumulators
-        mix(f0, f0, 0, NM - NL * BT, NR, [&](int r) { read(f1, st, 1, r); }, P - PRE, [&](int c) { copy(i + 1, PRE + c); });
-        // every wave has this chunk's operands in registers: its stage is requested again, for chunk i + 2
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-        mix(f0, f1, NM - NL * BT, (NL + NA - NF) * BT, 0, none, PRE, [&](int c) { copy(i + 2, c); });
-        // the own copies of chunk i + 1 have landed (only those of chunk i + 2 are younger), and after the barrier everyone's
-        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(PRE) : "memory");
-        mix(f1, f1, NM - NF * BT, NF * BT, NR, [&](int r) { read(f0, st ^ 1, 0, r); }, 0, none);
+        if constexpr (S == 2) {
+            mix(f0, f0, 0, NM - NL * BT, NR, [&](int r) { read(f1, st, 1, r); }, P - PRE, [&](int c) { copy(i + 1, last, PRE + c); });
+            // every wave has this chunk's operands in registers: its stage is requested again, for chunk i + 2
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            mix(f0, f1, NM - NL * BT, (NL + NA - NF) * BT, 0, none, PRE, [&](int c) { copy(i + 2, st, c); });
+        } else {      // the stage of the chunk before is free: every wave has passed the barrier below with its operands in registers
+            constexpr int M1 = NM, M2 = (NA - NF) * BT, P1 = (P * M1 + M1 + M2 - 1) / (M1 + M2);
+            mix(f0, f0, 0, M1, NR, [&](int r) { read(f1, st, 1, r); }, P1, [&](int c) { copy(i + S - 1, last, c); });
+            mix(f1, f1, 0, M2, 0, none, P - P1, [&](int c) { copy(i + S - 1, last, P1 + c); });
+        }
+        // the own copies of chunk i + 1 have landed (only those of later chunks are younger), and after the barrier everyone's
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(YOUNGER) : "memory");
+        mix(f1, f1, NM - NF * BT, NF * BT, NR, [&](int r) { read(f0, next, 0, r); }, 0, none);
+        st = next;
     } while (++i < n);
     // the copies have left, and the last results are in their registers before anything reads them (the compiler does not
     // see into the assembly)
@@ -253,16 +266,23 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16_t *__restrict__
     });
 }
 
-template <int TERMS, int WF, int AT, int BT, int EPI>
-void launch_tile(const TileLaunch &l) {
-    constexpr int lds_bytes = tile_lds(TERMS, AT * 32, BT * 32);
+template <int TERMS, int WF, int AT, int BT, int EPI, int S>
+void launch_tile_stages(const TileLaunch &l) {
+    constexpr int lds_bytes = tile_lds(TERMS, AT * 32, BT * 32, S);
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void *)k_gemm_tile<TERMS, WF, AT, BT, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        (void)hipFuncSetAttribute((const void *)k_gemm_tile<TERMS, WF, AT, BT, EPI, S>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
         attr_set = true;
     }
-    LD_LAUNCH((k_gemm_tile<TERMS, WF, AT, BT, EPI>), dim3(l.grid), dim3(256), lds_bytes, l.s, l.W, l.hi, l.lo, l.T, l.N, l.K, l.y,
+    LD_LAUNCH((k_gemm_tile<TERMS, WF, AT, BT, EPI, S>), dim3(l.grid), dim3(256), lds_bytes, l.s, l.W, l.hi, l.lo, l.T, l.N, l.K, l.y,
               l.n_ttiles, l.ks, l.partial, l.out, l.quads);
+}
+template <int TERMS, int WF, int AT, int BT, int EPI>
+void launch_tile(const TileLaunch &l) {
+    if constexpr (tile_twice(TERMS, AT * 32, BT * 32)) {
+        if (l.grid > 256) return launch_tile_stages<TERMS, WF, AT, BT, EPI, 2>(l);
+    }
+    launch_tile_stages<TERMS, WF, AT, BT, EPI, tile_stages(TERMS, AT * 32, BT * 32)>(l);
 }
 template <int TERMS, int WF, int AT, int BT>
 void launch_tile_epilogue(const TileLaunch &l) {

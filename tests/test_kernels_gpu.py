@@ -648,6 +648,34 @@ def test_linear_every_tile(form, rows, cols, K, ks, monkeypatch, capfd):
     assert "LD_GEMM_BIG" not in capfd.readouterr().err
 
 
+@pytest.mark.parametrize("form,rows,cols", [("two", 96, 128), ("f16", 128, 192), ("two", 128, 128), ("f16", 256, 160)])
+@pytest.mark.parametrize("K,ks", [(128, 1), (256, 1), (384, 1), (896, 3), (1408, 3)])
+def test_linear_tile_stages(form, rows, cols, K, ks, monkeypatch):
+    """The smallest tile of each form keeps two stages in a launch of more than 256 workgroups (here 3 x 100 x ks of them) and has three in
+    a smaller one (the first columns alone), as the tiles beside them have in both: 2, 4 and 6 chunks of K, and split K with
+    uneven slabs (14 and 22 chunks over 3).  The same bits for the columns that both compute, and within
+    2^-16 sum_k |w x| of float64 on the inputs as the form rounds them (see test_linear_every_tile)."""
+    monkeypatch.setenv("LD_GEMM_BIG", "%d,%d,%d" % (rows, cols, ks))
+    T, N, part = 2 * rows + 5, 99 * cols + 7, 20 * cols + 40
+    W = _mat(47, K, N, K, "bf16").to(DEV); x = gen.normal(47, 2, (T, K), device=DEV)
+    flag = torch.zeros(1, dtype=torch.int32, device=DEV)
+    Wh = torch.empty_like(W, dtype=torch.float16); ld.ldk_weights_to_f16(W, Wh, flag)
+    scratch = torch.empty(2 * T * K * 2 + 256 + ks * T * N * 4, dtype=torch.uint8, device=DEV)
+    hi = x.bfloat16().float()
+    xr = ((hi + (x - hi).bfloat16().float()).half() if form == "f16" else x).double()
+    ref, mag = xr @ W.double().t(), xr.abs() @ W.double().abs().t()
+    for image in ((None, Wh) if form == "f16" else (None,)):
+        ys = []
+        for n in (N, part):
+            ys.append(torch.full((T, n), float("nan"), device=DEV))
+            if form == "f16":
+                ld.ldk_linear_f16(W[:n], x, ys[-1], flag, ld.LDK_STORE, scratch=scratch, W_f16=None if image is None else image[:n])
+            else:
+                ld.ldk_linear(W[:n], x, ys[-1], ld.LDK_STORE, scratch=scratch)
+        assert torch.equal(ys[0][:, :part], ys[1])
+        assert ((ys[0].double() - ref).abs() <= 2.0 ** -16 * mag + 1e-6).all()
+
+
 @pytest.mark.parametrize("form", ["two", "f16"])
 @pytest.mark.parametrize("T,N,ks", [(65, 4, 1), (333, 300, 1), (333, 300, 3), (257, 1028, 2), (300, 302, 1)])
 def test_linear_tile_stores_of_four_columns(form, T, N, ks, monkeypatch):
