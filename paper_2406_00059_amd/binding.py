@@ -163,6 +163,10 @@ def _ptr(t):
 
 def _stream(stream):
     if stream is None:
+        # the handle itself: the Stream object that current_stream() builds around it takes 2.7 us a call, 120 of the 165 us in which
+        # a caller forks, feeds and frees the 32 sequences of a step
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 

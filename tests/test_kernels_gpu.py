@@ -9,6 +9,7 @@ import torch
 
 import oracle
 import paper_2406_00059_amd as ld
+from paper_2406_00059_amd import binding
 from workloads import gen
 from helpers import device_pool, logical_pool
 
@@ -1138,6 +1139,24 @@ def test_prefill_attention_few_rows_fp16_range_check(what, part, pos):
     flag, out = torch.zeros(1, dtype=torch.int32, device=DEV), torch.zeros(11, H, hd, device=DEV)
     ld.ldk_prefill_attention_f16(q, H * hd, device_pool(pool), table.to(DEV), tiles, H, H, hd, out, 171, flag, window=61)
     assert int(flag.item()) == (what != 65280.0 and 96 <= pos <= 171)
+
+
+def test_calls_without_a_stream_run_on_the_current_one():
+    """The stream of a call that names none: torch's current stream of the calling thread, also inside a stream context and a capture."""
+    import threading
+    same = lambda: binding._stream(None) == torch.cuda.current_stream().cuda_stream
+    assert same()
+    s = torch.cuda.Stream()
+    seen = []
+    with torch.cuda.stream(s):
+        assert same() and binding._stream(None) == s.cuda_stream
+        t = threading.Thread(target=lambda: seen.append(same() and binding._stream(None) != s.cuda_stream)); t.start(); t.join()
+    assert same() and seen == [True]
+    x, y = torch.ones(64, device=DEV), torch.zeros(64, device=DEV)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(torch.cuda.CUDAGraph(), stream=s):
+        y.copy_(x)
+        assert same() and binding._stream(None) == s.cuda_stream
 
 
 @pytest.mark.parametrize("split", [False, True], ids=["whole", "kv-split"])
