@@ -130,8 +130,9 @@ __device__ __forceinline__ int4 nth_longest(const int4 *__restrict__ tiles, int 
 
 // Tiles of up to FEW_ROWS rows, which are not worth the staging (a 257-row segment ends in a tile of one row, whose walk took as long as
 // half a full tile's): each wave walks every fourth step of the share by itself.  Four segments of 257 rows behind 2.2k .. 6.4k, GQA 4:1:
-// 126 -> 119 us; eight lone 5-row tiles of 32 heads 50 -> 26 in two terms; 135 sets of tiles 4 % faster in the mean in two terms.  Arithmetic and operands as in the decode kernel for
-// grouped heads, a row of the tile in place of a head (two bf16 terms in both forms; in F16 the range is checked all the same).
+// 126 -> 119 us; four lone 5-row tiles of 32 heads over 8 50 -> 26 in two terms; 135 sets of tiles 4 % faster in the mean in two
+// terms, 1 % in fp16 (33 rows upwards pay 0 - 3 % for the second path in the kernel).  Arithmetic and operands as in the decode kernel
+// for grouped heads, a row of the tile in place of a head (two bf16 terms in both forms; in F16 the range is checked all the same).
 union FewLds {
     char keys[4][4096];      // a block's keys on their way to operands, of each wave
     struct { float o[4][FEW_ROWS][HD + 4], ml[4][FEW_ROWS][2]; } waves;
@@ -685,7 +686,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
 
 // Adds the shares of a tile's rows in order: half a wave per row (four dimensions a lane), eight rows of one head at a
 // time.  A share that saw no visible position of the row has m = -inf and weight 0; some share always saw one.  Tiles
-// that one workgroup walked whole are finished already.
+// that one workgroup walked whole are finished already.  What bounds it is the chain of its loads and, with many shares, their bytes:
+// 8 full tiles of 32 heads 17.3 -> 16.0 us with four shares asked for at once, two of them 7.6 -> 7.0.
 __global__ __launch_bounds__(256) void k_attn_prefill_merge(const int4 *__restrict__ tiles, int H, int window, int per, int ns,
                                                             const float *__restrict__ part_o,
                                                             const float *__restrict__ part_ml,
@@ -696,22 +698,34 @@ __global__ __launch_bounds__(256) void k_attn_prefill_merge(const int4 *__restri
     if (n <= 1 || r >= tile.y) return;
     const int64_t base = ((int64_t)blockIdx.y * H + h) * ns;
     const float2 ml = sub < n ? *reinterpret_cast<const float2 *>(part_ml + ((base + sub) * 128 + r) * 2) : make_float2(-INFINITY, 0.f);
+    const float *po = part_o + base * 128 * HD + part_place(r, sub >> 1, sub & 1);
+    // four shares at a time, the first of them asked for with the statistics: what is past the last one is read again and not used
+    constexpr int AHEAD = 4;
+    float4 v[AHEAD];
+#pragma unroll
+    for (int u = 0; u < AHEAD; u++) v[u] = *reinterpret_cast<const float4 *>(po + (int64_t)min(u, n - 1) * 128 * HD);
     float M = ml.x;
 #pragma unroll
     for (int off = 1; off < MAX_SPLITS; off <<= 1) M = fmaxf(M, __shfl_xor(M, off, WAVE));
     const float weight = fast_exp2(ml.x - M);
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
     float L = 0.f;
-    for (int z = 0; z < n; z++) {
-        const float a = __shfl(weight, z, 32);
-        const float4 v = *reinterpret_cast<const float4 *>(part_o + (base + z) * 128 * HD + part_place(r, sub >> 1, sub & 1));
-        o.x += a * v.x; o.y += a * v.y; o.z += a * v.z; o.w += a * v.w;
-        L += a * __shfl(ml.y, z, 32);
+    for (int z0 = 0; z0 < n; z0 += AHEAD) {
+        if (z0)
+#pragma unroll
+            for (int u = 0; u < AHEAD; u++) v[u] = *reinterpret_cast<const float4 *>(po + (int64_t)min(z0 + u, n - 1) * 128 * HD);
+#pragma unroll
+        for (int u = 0; u < AHEAD; u++) {
+            if (z0 + u >= n) break;
+            const float a = __shfl(weight, z0 + u, 32);
+            o.x += a * v[u].x; o.y += a * v[u].y; o.z += a * v[u].z; o.w += a * v[u].w;
+            L += a * __shfl(ml.y, z0 + u, 32);
+        }
     }
-    const float4 v = make_float4(o.x / L, o.y / L, o.z / L, o.w / L);
+    const float4 r4 = make_float4(o.x / L, o.y / L, o.z / L, o.w / L);
     const int64_t e = ((int64_t)(tile.x + r) * H + h) * HD + sub * 4;
-    if (image.hi) store_operand4(image, tile.x + r, e, v);
-    else *reinterpret_cast<float4 *>(out + e) = v;
+    if (image.hi) store_operand4(image, tile.x + r, e, r4);
+    else *reinterpret_cast<float4 *>(out + e) = r4;
 }
 
 }  // namespace
@@ -724,8 +738,8 @@ bool prefill_attention_supported(int dtype_is_bf16, int hd) { return dtype_is_bf
 // steps of a workgroup: a share costs its steps and ten more (launch, queries, first loads, result), a round of up to 256
 // workgroups that, of up to 512 (two per CU) 1.15 times as much, and the merge two steps and 1 / 60 for each partial result of
 // 64 KB.  At least 4 steps a share, and only as many shares as the scratch holds.  Fitted to every number of shares for 243 sets of
-// tiles (4 .. 40 heads, 1 .. 16 tiles, walks of 4 .. 250 steps): the choice is 2 % slower than the best in the mean, 39 % at worst,
-// where tiles differ most in length.  A model that made the merge cheaper chose two shares for narrow bands over short
+// tiles (4 .. 40 heads, 1 .. 16 tiles, walks of 4 .. 250 steps) and looked at again for 135 with the kernels as they are: the choice is
+// 2.5 % (two terms 3.2 %) slower than the best in the mean, 29 % at worst, where tiles differ most in length.  A model that made the merge cheaper chose two shares for narrow bands over short
 // segments: 22 -> 29 us for eight 64-row tiles of 32 heads with a band of 256, 22 so.
 static int prefill_shares(int n_tiles, int H, int max_pos, int window, size_t scratch_bytes, int *per) {
     const int span = window > 0 ? std::min<int64_t>(max_pos + 1, (int64_t)window + 128 + KVB) : max_pos + 1;   // positions a tile walks
