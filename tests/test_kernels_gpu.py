@@ -649,6 +649,24 @@ def test_linear_every_tile(form, rows, cols, K, ks, monkeypatch, capfd):
     assert "LD_GEMM_BIG" not in capfd.readouterr().err
 
 
+@pytest.mark.parametrize("N,K", [(301, 4224), (640, 5120), (96, 6144), (130, 10368), (513, 11008), (37, 14336), (77, 2816), (77, 11392), (12, 24704)])
+@pytest.mark.parametrize("T", [2, 20, 33, 64])
+def test_linear_small_batch_slabs(T, N, K):
+    """The small-batch product where its K slabs (2048 columns at most, 1024 beyond 32 rows) go up to a power of two (3 to 4, 6 and 7 to
+    8, 12 to 16) and where they stay (2, 5, 11, 13): uneven slabs, fewer columns than workgroups.  Against float64: two terms are off by
+    at most 2^-16 of a product, the float32 sums by 2^-20 of the sum of magnitudes."""
+    W = _mat(71, K, N, K, "bf16").to(DEV); x = gen.normal(71, 2, (T, K), device=DEV); g = 1 + 0.1 * gen.normal(71, 3, (K,), device=DEV)
+    y = torch.full((T, N), float("nan"), device=DEV)
+    scratch = torch.empty(ld.ldk_linear_scratch_bytes(T, N, K, ld.LDK_STORE), dtype=torch.uint8, device=DEV)
+    for norm in (False, True):
+        ld.ldk_linear(W, x, y, ld.LDK_STORE, g if norm else None, 1e-5, scratch)
+        xd = x.double()
+        if norm:
+            xd = xd * g.double() / torch.sqrt((xd * xd).mean(1, keepdim=True) + 1e-5)
+        ref, mag = xd @ W.double().t(), xd.abs() @ W.double().abs().t()
+        assert ((y.double() - ref).abs() <= (2.0 ** -16 + 2.0 ** -20) * mag).all()
+
+
 @pytest.mark.parametrize("form,rows,cols", [("two", 96, 128), ("f16", 128, 192), ("two", 128, 128), ("f16", 256, 160)])
 @pytest.mark.parametrize("K,ks", [(128, 1), (256, 1), (384, 1), (896, 3), (1408, 3)])
 def test_linear_tile_stages(form, rows, cols, K, ks, monkeypatch):
