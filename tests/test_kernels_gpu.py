@@ -75,6 +75,20 @@ def test_linear_full_7b_shapes_on_sampled_outputs():
             assert abs(y[0, n].item() - a) <= 1e-5 * max(1.0, abs(a)) + 2e-6 * math.sqrt(K) * 0.02
 
 
+@pytest.mark.parametrize("off", [0, 1], ids=["aligned", "4-bytes-off"])
+@pytest.mark.parametrize("d", [1, 3, 4, 255, 260, 1024, 1028, 4096, 8188, 8192, 8196])
+def test_rmsnorm_lengths_and_alignments(d, off):
+    """Rows that are read four floats at a time and kept (a multiple of four, up to 8192, 16-byte aligned) and all others, gathered and in
+    order, against float64.  Bound: at most 33 + 6 + 3 roundings of 2^-24 in the sum of squares, which count half, and a few behind it."""
+    x = gen.normal(91, 1, (7 * d + off,), device=DEV)[off:].view(7, d); g = 1 + 0.1 * gen.normal(91, 2, (d,), device=DEV)
+    out = torch.full((5 * d + off,), float("nan"), device=DEV)[off:].view(5, d)
+    for idx in (None, [6, 0, 3, 3, 1]):
+        ld.ldk_rmsnorm(x, g, out, 1e-5, row_idx=None if idx is None else torch.tensor(idx, dtype=torch.int32, device=DEV))
+        v = x[:5].double() if idx is None else x[idx].double()
+        ref = v / torch.sqrt((v * v).mean(1, keepdim=True) + 1e-5) * g.double()
+        assert ((out.double() - ref).abs() <= 32 * 2.0 ** -24 * ref.abs()).all()
+
+
 def test_embed_and_rmsnorm_gather():
     E = _mat(4, 1, 50, 256, "bf16"); tok = torch.tensor([3, 49, 0, 3], dtype=torch.int32)
     x = torch.empty(4, 256, device=DEV)
