@@ -431,11 +431,16 @@ int cu_count() {
 }
 // Tile, workgroup count and split-K factor of the big-tile kernel for a row count: the candidate with the smallest
 // estimated time.  Workgroups run in rounds of one per CU (256 of them); a round takes the tile's time per 64-wide chunk of K
-// times its chunks, a last round that leaves CUs idle a little less (the others draw less power and run faster: 0.16 of the idle
-// share in two terms, 0.27 in one); split-K adds the write and the ordered re-read of its partial sums.  The constants are
-// fitted to the tiles and splits of the 7B, grouped-KV and 13B layer shapes at 80 - 480 rows (two terms) and 512 - 2048 (one): the
-// choice is 1.2 % (1.0 %) slower than the best pair in the mean, 12 % (7 %) at worst; that of the constants before tiles had three stages is
-// 2.2 % (1.8 %) slower.  With six and four tiles instead of ten and eight the best pair would be some 3 % slower in the mean.
+// times its chunks, a last round that leaves CUs idle a little less (the others draw less power and run faster: 0.27 of the idle
+// share in both forms); split-K adds the write and the ordered re-read of its partial sums.  The constants are fitted to the tiles
+// and splits of the 7B, grouped-KV and 13B layer shapes.  One term, 512 - 2048 rows: the choice is 0.8 % slower than the best pair in
+// the mean, 9 % at worst.  Two terms, 80 - 480 rows: 1.4 % and 9 %, with the times of tiles of two stages, though three take 5 - 13 %
+// off the smaller ones.  Fitted anew the choice was 0.8 % slower than the best, but K was cut in fewer slabs at 942 of 4917 sizes (65 .. 511
+// rows of these shapes) and in more at 222, and longer sums are less exact: rms error over rms of the result against float64 in one, two, four and eight slabs
+// 2.520, 2.487, 2.470, 2.463e-6 (256 x 12288 x 4096), 3.636, 3.579, 3.554, 3.543e-6 (152 x 11008 x 4096 SwiGLU).  Nor is the plain
+// product's time all there is: with the rotation that adds the slabs (ldk_qkv_rope) 256 x 12288 x 4096 takes 58.6 us in the two slabs
+// of this model, 64.1 in the one of that, 256 x 15360 x 5120 80.2 and 85.3, while plain products gained up to 8 % (480 x 4096 x 11008 in
+// five and four slabs 93.4 -> 87.3).  With six and four tiles instead of ten and eight the best pair would be some 3 % slower in the mean.
 struct BigPlan { int bm, bn, n_ttiles, n_nblocks, ks; double est_us; };
 struct Tile { int bm, bn; bool swiglu; double chunk_us; };
 #define LD_TILE_ROW(AT_, BT_, US_) {32 * AT_, 32 * BT_, BT_ % 2 == 0, US_},
@@ -446,7 +451,7 @@ const Tile tiles_f16_rule[] = {{128, 192, true, 0.74}, {128, 256, true, 0.99}, {
                                {224, 256, true, 1.40}, {256, 160, false, 1.14}, {256, 192, true, 1.23}, {256, 256, true, 1.54}};
 #undef LD_TILE_ROW
 struct Costs { const Tile *first, *end; double idle, us_per_mb; };
-const Costs costs_two{std::begin(tiles_two), std::end(tiles_two), 0.16, 0.53};
+const Costs costs_two{std::begin(tiles_two), std::end(tiles_two), 0.27, 0.44};
 const Costs costs_f16{std::begin(tiles_f16), std::end(tiles_f16), 0.27, 0.46};
 const Costs costs_f16_rule{std::begin(tiles_f16_rule), std::end(tiles_f16_rule), 0.31, 0.44};
 BigPlan plan_big(int T, int N, int K, int epi, const Costs &costs, bool *ignored = nullptr) {

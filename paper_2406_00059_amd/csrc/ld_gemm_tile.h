@@ -15,10 +15,11 @@ typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;   // native 16-byte vector (keeps arrays of it in registers)
 
-// Tiles of the two forms, in units of 32 rows and 32 columns, and measured us per 64-wide chunk of K.  (Odd column units have
-// no SwiGLU form.)
+// Tiles of the two forms, in units of 32 rows and 32 columns, and measured us per 64-wide chunk of K: of the two-term form with two
+// stages in LDS (see plan_big), of the one-term form as it runs, whose smallest tile has one time for two and three stages (the
+// latter, in launches of up to one workgroup a CU, 11 % faster).  (Odd column units have no SwiGLU form.)
 #define LD_TILES_TWO(X) \
-    X(3, 4, 0.66) X(3, 6, 0.79) X(3, 8, 1.00) X(4, 4, 0.74) X(4, 6, 0.98) X(4, 8, 1.18) X(5, 6, 1.13) X(5, 8, 1.35) X(6, 6, 1.27) X(6, 8, 1.56)
+    X(3, 4, 0.73) X(3, 6, 1.03) X(3, 8, 1.23) X(4, 4, 0.96) X(4, 6, 1.21) X(4, 8, 1.50) X(5, 6, 1.42) X(5, 8, 1.77) X(6, 6, 1.61) X(6, 8, 2.04)
 #define LD_TILES_F16(X) X(4, 6, 0.73) X(4, 8, 0.91) X(6, 6, 0.92) X(6, 8, 1.16) X(7, 8, 1.30) X(8, 5, 0.99) X(8, 6, 1.15) X(8, 8, 1.42)
 
 constexpr int TILE_MAX_K = 1 << 23;      // the lane offsets of the copies reach over 256 rows in 32 bits

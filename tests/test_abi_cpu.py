@@ -407,6 +407,13 @@ def test_small_batch_form(monkeypatch):
         assert rows(4096, True) == rows(13824, False) == (upto(64) if form == "1" else [])
 
 
+def test_two_term_products_keep_their_slabs():
+    """Slabs that K is cut in where tiles take a product of 65 .. 511 rows, seen in the scratch that it asks for: longer sums are less exact, so
+    faster tiles are no reason to cut K in fewer.  (Sizes at which the one-term form, whose scratch is counted too, asks for no more.)"""
+    for T, N, K, epi, slabs in ((128, 4096, 4096, ld.LDK_ADD, 8), (128, 5120, 5120, ld.LDK_ADD, 6), (152, 14336, 4096, ld.LDK_SWIGLU, 2), (256, 4096, 11008, ld.LDK_ADD, 8)):
+        assert ld.ldk_linear_scratch_bytes(T, N, K, epi) == 4 * T * K + slabs * T * N * (2 if epi == ld.LDK_SWIGLU else 1) * 4
+
+
 def test_operands_of_4_gib_keep_both_terms():
     """Rows enter as one fp16 term only while the matrix (gate and up rows together) and the rows' image stay below 4 GiB."""
     for N, K, epi in ((1 << 19, 4096, ld.LDK_STORE), (1 << 18, 4096, ld.LDK_SWIGLU), (1 << 17, 16384, ld.LDK_ADD)):

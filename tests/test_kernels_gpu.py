@@ -681,6 +681,20 @@ def test_linear_small_batch_slabs(T, N, K):
         assert ((y.double() - ref).abs() <= (2.0 ** -16 + 2.0 ** -20) * mag).all()
 
 
+@pytest.mark.parametrize("T,N,K,epi,slabs", [(256, 12288, 4096, "STORE", 2), (152, 12288, 4096, "STORE", 4), (300, 12288, 4096, "STORE", 2),
+                                             (152, 11008, 4096, "SWIGLU", 2), (200, 4096, 11008, "ADD", 8), (256, 15360, 5120, "STORE", 2)])
+def test_linear_two_term_slabs(T, N, K, epi, slabs):
+    """K is cut in as many slabs as ever where tiles take a two-term product (longer sums are less exact): the slabs whose partial sums the call
+    leaves in its scratch.  The sums are finite, so what is still NaN was not written."""
+    code = getattr(ld, "LDK_" + epi); R = N * (2 if epi == "SWIGLU" else 1)
+    W = torch.full((R, K), 0.01, dtype=torch.bfloat16, device=DEV); x = torch.ones(T, K, device=DEV); y = torch.zeros(T, N, device=DEV)
+    scratch = torch.full((T * K + 8 * T * R,), float("nan"), device=DEV)
+    assert scratch.numel() * 4 >= ld.ldk_linear_scratch_bytes(T, N, K, code)
+    ld.ldk_linear(W, x, y, code, scratch=scratch)
+    written = scratch[T * K:].isfinite()
+    assert int(written.sum()) == slabs * T * R and written[:slabs * T * R].all()
+
+
 @pytest.mark.parametrize("form,rows,cols", [("two", 96, 128), ("f16", 128, 192), ("two", 128, 128), ("f16", 256, 160)])
 @pytest.mark.parametrize("K,ks", [(128, 1), (256, 1), (384, 1), (896, 3), (1408, 3)])
 def test_linear_tile_stages(form, rows, cols, K, ks, monkeypatch):
