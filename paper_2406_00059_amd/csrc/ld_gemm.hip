@@ -446,14 +446,10 @@ struct Tile { int bm, bn; bool swiglu; double chunk_us; };
 #define LD_TILE_ROW(AT_, BT_, US_) {32 * AT_, 32 * BT_, BT_ % 2 == 0, US_},
 const Tile tiles_two[] = {LD_TILES_TWO(LD_TILE_ROW)};
 const Tile tiles_f16[] = {LD_TILES_F16(LD_TILE_ROW)};
-// the times that a rule on results (which rows keep both terms, see tail_rows) stays with
-const Tile tiles_f16_rule[] = {{128, 192, true, 0.74}, {128, 256, true, 0.99}, {192, 192, true, 1.05}, {192, 256, true, 1.23},
-                               {224, 256, true, 1.40}, {256, 160, false, 1.14}, {256, 192, true, 1.23}, {256, 256, true, 1.54}};
 #undef LD_TILE_ROW
 struct Costs { const Tile *first, *end; double idle, us_per_mb; };
 const Costs costs_two{std::begin(tiles_two), std::end(tiles_two), 0.27, 0.44};
 const Costs costs_f16{std::begin(tiles_f16), std::end(tiles_f16), 0.27, 0.46};
-const Costs costs_f16_rule{std::begin(tiles_f16_rule), std::end(tiles_f16_rule), 0.31, 0.44};
 BigPlan plan_big(int T, int N, int K, int epi, const Costs &costs, bool *ignored = nullptr) {
     const bool swi = epi == ld::GEMM_SWIGLU;
     BigPlan best{};
@@ -565,26 +561,32 @@ static double nominal_tiles_us(int T, int N, int K, int epi) {
     }
     return best;
 }
+// And by a third, eight tiles with two stages in LDS, chosen among as the planner does: it alone decides one of a thousand sizes (64 ..
+// 60000 columns, K to 30000), none of the 7B, grouped-KV and 13B layer shapes below 4200 rows.  None of the three says what the tiles
+// of today take, which would be left whole at a quarter of those shapes' tails: the second stream of W is there the price of the same results.
+const Tile tiles_nominal[] = {{128, 192, true, 0.74}, {128, 256, true, 0.99}, {192, 192, true, 1.05}, {192, 256, true, 1.23},
+                              {224, 256, true, 1.40}, {256, 160, false, 1.14}, {256, 192, true, 1.23}, {256, 256, true, 1.54}};
+const Costs costs_nominal{std::begin(tiles_nominal), std::end(tiles_nominal), 0.31, 0.44};
+static double stream_us(double bytes) { return bytes / 5.2e6 + 10.0; }      // ~5.2 TB/s + two launches
 static bool tail_keeps_both_terms(int T, int r, int N, int K, int epi) {
     const int wr = epi == GEMM_SWIGLU ? 2 : 1;
     const double stream = (double)N * wr * K * 2.0;
     return nominal_us(T - r, N, K, wr) + stream / 4.0e6 + 12.0 < nominal_us(T, N, K, wr) ||
-           nominal_tiles_us(T - r, N, K, epi) + stream / 5.2e6 + 10.0 < nominal_tiles_us(T, N, K, epi);
+           nominal_tiles_us(T - r, N, K, epi) + stream_us(stream) < nominal_tiles_us(T, N, K, epi) ||
+           plan_big(T - r, N, K, epi, costs_nominal).est_us + stream_us(stream) < plan_big(T, N, K, epi, costs_nominal).est_us;
 }
 
 // Rows that would only start one more, nearly empty 256-row tile (a mixed step's 4 x 257 + 28 rows, a 2048-row
-// chunk beside 63 decode rows) are cut off and go through the small-batch kernels where that costs less by the cost model
-// that picks the tile (the weights are streamed once more; in the one-term form the costs of the rule on terms), and in the one-term
-// form also where the rule above wants them there.  Returns the number of such tail rows (0: no cut).
+// chunk beside 63 decode rows) are cut off and go through the small-batch kernels: in the two-term form where that costs less by the
+// cost model that picks the tile (the weights are streamed once more), in the one-term form where the rule above wants both terms in
+// them.  Returns the number of such tail rows (0: no cut).
 int tail_rows(int T, int N, int K, int epi, bool f16) {
     const int r = T % 256;
     static const int enabled = env_int("LD_GEMM_TAIL", 1);   // tuning knob: 0 keeps every row in the tiled kernel
     if (!enabled || T <= 256 || r == 0 || r > 64 || getenv("LD_GEMM_BIG")) return 0;
-    if (f16 && tail_keeps_both_terms(T, r, N, K, epi)) return r;
-    const Costs &costs = f16 ? costs_f16_rule : costs_two;
-    const double whole = plan_big(T, N, K, epi, costs).est_us, main_part = plan_big(T - r, N, K, epi, costs).est_us;
-    const double tail = (double)N * (epi == GEMM_SWIGLU ? 2 : 1) * K * 2.0 / 5.2e6 + 10.0;   // ~5.2 TB/s + two launches
-    return main_part + tail < whole ? r : 0;
+    if (f16) return tail_keeps_both_terms(T, r, N, K, epi) ? r : 0;
+    const double whole = plan_big(T, N, K, epi).est_us, main_part = plan_big(T - r, N, K, epi).est_us;
+    return main_part + stream_us((double)N * (epi == GEMM_SWIGLU ? 2 : 1) * K * 2.0) < whole ? r : 0;
 }
 
 static size_t partial_bytes(int T, int N, int K, int epi, bool f16 = false) {

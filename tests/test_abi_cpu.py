@@ -377,7 +377,7 @@ def _f16_rows(*shape):
 @pytest.mark.parametrize("N,K,epi,after", _TWO_TERM_TAILS)
 def test_rows_that_keep_both_terms_in_the_one_term_form(N, K, epi, after):
     """How many terms a row's activations have is part of a product's results: the rows named here keep both whatever tiles the
-    product is cut into (the planner may send others of the last 64 the same way); whole tiles and longer remainders go with one."""
+    product is cut into (others of the last 64 may); whole tiles and longer remainders go with one."""
     for base in after:
         for r in (1, 2, 28, 31, 32, 33, 63, 64):
             assert _f16_rows(base + r, N, K, epi) == base, (base, r)
@@ -386,6 +386,13 @@ def test_rows_that_keep_both_terms_in_the_one_term_form(N, K, epi, after):
     for T in range(257, 4200, 13):
         assert _f16_rows(T, N, K, epi) in ((T, T - T % 256) if 0 < T % 256 <= 64 else (T,))
     assert _f16_rows(64, N, K, epi) == 0
+
+
+@pytest.mark.parametrize("T,N,K,epi", [(535, 22924, 5504, ld.LDK_ADD), (562, 22904, 5760, ld.LDK_STORE), (1845, 3367, 6016, ld.LDK_STORE), (3597, 1561, 8064, ld.LDK_STORE),
+                                       (5402, 4005, 10752, ld.LDK_SWIGLU), (7193, 403, 26880, ld.LDK_SWIGLU)])
+def test_rows_that_keep_both_terms_by_the_third_set_of_nominal_times(T, N, K, epi):
+    """Sizes at which only the last of the three sets of times in the rule on terms keeps both in the remainder's rows."""
+    assert _f16_rows(T, N, K, epi) == T - T % 256
 
 
 def test_small_batch_form(monkeypatch):
