@@ -423,6 +423,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_prefill(const float *__restrict
             }
             *reinterpret_cast<uint2 *>(&mine[0][2 * i + half][4 * l32]) = hi;
         }
+        __builtin_amdgcn_wave_barrier();      // a lane reads what others of its wave wrote
 #pragma unroll
         for (int j = 0; j < 8; j++) {
             qh[j] = *reinterpret_cast<const u32x4 *>(&mine[0][l32][half * 64 + j * 8]);
