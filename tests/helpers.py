@@ -110,3 +110,42 @@ class NearTies:
         print("near-tie:", case)
         assert 0.0 <= gap <= bound, f"token mismatch beyond a near-tie: {case}"
         return case
+
+
+MOVING_CTX, MOVING_HEADS = 900, 2      # moving_maximum_inputs(): rows at positions MOVING_CTX on
+
+
+def moving_maximum_inputs(growth, rows, device="cpu"):
+    """Queries [rows, H, 128] and bf16 keys and values [MOVING_CTX + rows, H, 128] whose scores fall or rise along the walk, by up to 50 in the
+    exponent, differently in each row and head."""
+    H, hd, n = MOVING_HEADS, 128, MOVING_CTX + rows
+    q = gen.normal(67, 9, (rows, H, hd), device=device)
+    q[:, :, 0] = torch.linspace(0.2, 1.0, rows * H, device=device).reshape(rows, H) * hd ** 0.5
+    k, v = (gen.normal(67, s, (n, H, hd), device=device).bfloat16() for s in (11, 12))
+    k[:, :, 0] = (growth * torch.arange(n, device=device))[:, None].bfloat16()
+    return q, k, v
+
+
+def rounded_queries(q, form):
+    """Queries times 1/sqrt(hd) log2(e) as the chunk-attention kernels hold them: one fp16 term ("f16") or the sum of two bf16 terms ("two")."""
+    s = q.float() * torch.tensor(np.float32(np.float32(1.0 / np.sqrt(q.shape[-1])) * np.float32(np.log2(np.e))), device=q.device)
+    return s.half().double() if form == "f16" else s.bfloat16().double() + (s - s.bfloat16().float()).bfloat16().double()
+
+
+def attention_and_bound(q, k, v, first, window, form):
+    """Attention of rows at positions first, first + 1, ... in float64 on the operands as the form rounds them, and how far from it a correct
+    kernel can be, element by element.  A score is off by a rounding of 2^-24 for each of its products (128, in two terms 256), the
+    subtraction of the exponents' reference and the exponential, of at most twice the sum of its products' magnitudes: a relative
+    error r of its probability, which counts in the sums above and below.  A probability is rounded to fp16 (2^-11, or 2^-25 of the reference's
+    below 2^-14) or to two bf16 terms (2^-17); the sums over the positions and their rescaling add 2^-12."""
+    qr, k, v = rounded_queries(q, form).transpose(0, 1), k.double().transpose(0, 1), v.double().transpose(0, 1)
+    pos, at = first + torch.arange(q.shape[0], device=q.device)[:, None], torch.arange(k.shape[1], device=q.device)[None]
+    seen = (at <= pos) & (at > pos - window if window else at >= 0)
+    s = (qr @ k.transpose(1, 2)).masked_fill(~seen, -np.inf)
+    mag = (qr.abs() @ k.abs().transpose(1, 2)).masked_fill(~seen, 0).amax(2, keepdim=True)
+    p = torch.softmax(s * np.log(2.0), 2)
+    r = torch.expm1(np.log(2.0) * ((130 if form == "f16" else 258) * 2.0 ** -24 * 2 * mag)) + 2.0 ** -22
+    bound = (2 * r + (2.0 ** -11 if form == "f16" else 2.0 ** -17) + 2.0 ** -12) * (p @ v.abs())
+    if form == "f16":
+        bound += 2.0 ** -25 * k.shape[1] * v.abs().amax()
+    return (p @ v).transpose(0, 1), bound.transpose(0, 1)

@@ -11,7 +11,7 @@ import oracle
 import paper_2406_00059_amd as ld
 from paper_2406_00059_amd import binding
 from workloads import gen
-from helpers import device_pool, logical_pool
+from helpers import MOVING_CTX, MOVING_HEADS, attention_and_bound, device_pool, logical_pool, moving_maximum_inputs
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -1109,15 +1109,15 @@ def test_prefill_attention_uneven_tiles(H, Hkv, many, window, shares):
 @pytest.mark.parametrize("growth", [-0.03, 0.01, 0.03])
 def test_prefill_attention_moving_maximum(growth, rows, window):
     """Scores that fall or rise along the walk, by up to 50 in the exponent, so that the reference of the exponentials stays where the first
-    positions put it, is moved now and then, differently in each row and half of a wave.  Both forms against the
-    oracle.  Bound: a row's exponents are off by at most the rounding of its query (2^-11, in two terms 2^-16) and of 128 sums
-    (2^-17) of the sum of magnitudes behind its scores, which changes its output by that much, twice, of the largest value; then the forms' own bounds."""
-    hd, H, ctx = 128, 2, 900
+    positions put it, is moved now and then, differently in each row and half of a wave.  Both forms against float64 on the operands as
+    they round them (tiles of up to 16 rows take two terms in both), bound beside it; a wrong rescaling lies far
+    outside (test_moving_maximum_bound_sees_wrong_rescaling)."""
+    hd, H, ctx = 128, MOVING_HEADS, MOVING_CTX
     table, pool, _ = _attention_case(67, [ctx + rows], H, H, hd, "bf16")
-    q = gen.normal(67, 9, (rows, H, hd), device=DEV)
-    q[:, :, 0] = torch.linspace(0.2, 1.0, rows * H, device=DEV).reshape(rows, H) * hd ** 0.5
-    for pos in range(ctx + rows):
-        pool[int(table[0, pos // 16]), 0, :, pos % 16, 0] = growth * pos
+    q, k, v = moving_maximum_inputs(growth, rows, DEV)
+    pos = torch.arange(ctx + rows)
+    for part, x in ((0, k), (1, v)):
+        pool[table[0, pos // 16].long().to(DEV), part, :, (pos % 16).to(DEV), :] = x
     tiles = [[off, min(128, rows - off), ctx + off, 0] for off in range(0, rows, 128)]
     tiles_d, flag = torch.tensor(tiles, dtype=torch.int32, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
     out, out16 = torch.zeros(rows, H, hd, device=DEV), torch.zeros(rows, H, hd, device=DEV)
@@ -1125,14 +1125,9 @@ def test_prefill_attention_moving_maximum(growth, rows, window):
     ld.ldk_prefill_attention(q, *args, out, ctx + rows - 1, window=window)
     ld.ldk_prefill_attention_f16(q, *args, out16, ctx + rows - 1, flag, window=window)
     assert int(flag.item()) == 0
-    ph = oracle.to_host_matrix(pool.reshape(pool.shape[0], -1)).reshape(-1)
-    ref = oracle.paged_attention(q.cpu().numpy(), ph, ph[H * 16 * hd:], (2 * H * 16 * hd, 16 * hd, hd), table.numpy()[[0] * rows],
-                                 [ctx + i + 1 for i in range(rows)], H, window=window)
-    mag = float((q.abs().double().cpu().amax((0, 1)) * pool[:, 0].nan_to_num(0).abs().double().cpu().amax((0, 1, 2))).sum()) / hd ** 0.5
-    top = float(pool[:, 1].nan_to_num(0).abs().max())
-    for got, form, base in ((out, 2.0 ** -16 + 2.0 ** -17, 3e-5), (out16, 2.0 ** -11 + 2.0 ** -17, 1e-3)):
-        err = np.max(np.abs(got.cpu().numpy() - ref))
-        assert err <= 2 * np.expm1(form * mag) * top + base * np.abs(ref).max(), (err, mag, top)
+    for got, form in ((out, "two"), (out16, "f16" if rows > 16 else "two")):
+        ref, bound = attention_and_bound(q, k, v, ctx, window, form)
+        assert ((got.double() - ref).abs() <= bound).all(), (form, float(((got.double() - ref).abs() / bound).max()))
 
 
 @pytest.mark.parametrize("split", [False, True], ids=["whole", "kv-split"])

@@ -14,6 +14,7 @@ import torch
 import torch.nn.functional as F
 
 import oracle
+from helpers import MOVING_CTX, attention_and_bound, moving_maximum_inputs, rounded_queries
 from workloads import gen, TINY, make_weights, SEED_BASE
 
 RNG = np.random.default_rng(7)
@@ -723,3 +724,53 @@ def test_golden_tiny_tokens_are_reproduced_by_the_oracle():
     assert fresh["tokens"] == stored["tokens"] and fresh["prompt"] == stored["prompt"]
     assert fresh["block_table"] == stored["block_table"] == [0, 1, 2, 3, 4, 5]
     assert len(set(stored["tokens"])) >= 4         # not a constant sequence
+
+
+# ------------------------------------------------------------------ what a test's bound sees
+
+def _walk(q, k, v, first, window, form, mistake=""):
+    """Chunk attention as a walk in steps of 64 (two terms 32) positions against a reference of the exponents that is moved only where half a
+    step's sum passes 256, in groups of 32 rows; optionally with a mistake in moving it."""
+    rows, H, hd = q.shape
+    qr, out, step = rounded_queries(q, form), torch.empty(rows, H, hd, dtype=torch.float64), 64 if form == "f16" else 32
+    for g in range(0, rows, 32):
+        n = min(32, rows - g)
+        pos = first + g + torch.arange(n)[:, None]
+        for h in range(H):
+            m, l, o = torch.full((n, 1), -np.inf, dtype=torch.float64), torch.zeros(n, 1, dtype=torch.float64), torch.zeros(n, hd, dtype=torch.float64)
+            for kv0 in range(max(first + g - window + 1, 0) // 32 * 32 if window else 0, int(pos[-1]) + 1, step):
+                at = kv0 + torch.arange(min(step, k.shape[0] - kv0))
+                ok = (at[None] <= pos) & (at[None] > pos - window if window else at[None] >= 0)
+                s = (qr[g:g + n, h] @ k[at, h].double().t() - torch.where(m > -np.inf, m, 0.0)).masked_fill(~ok, -np.inf)
+                half = (at // 8 % 2 == 0)[None]      # the lanes of a query
+                sums = [torch.exp2(s).masked_fill(~x, 0).sum(1, keepdim=True) for x in (half, ~half)]
+                if any(((x > 256) | ~(m > -np.inf)).any() for x in sums):
+                    mb = s.amax(1, keepdim=True)
+                    new = ~(m > -np.inf)
+                    move = torch.where(new, mb > -np.inf, mb > 3)
+                    up = torch.where(move, mb, 0.0)
+                    sc = torch.where(new, torch.where(move, 0.0, 1.0), torch.exp2(-up))
+                    m = torch.where(move, torch.where(new, 0.0, m) + up, m)
+                    s = s - up
+                    wrong = {"half the exponent": sc.sqrt(), "one too little": torch.where(sc < 1, 2 * sc, sc)}.get(mistake, sc)
+                    l, o = l * (1.0 if mistake == "sum as it was" else wrong), o * (1.0 if mistake == "output as it was" else wrong)
+                p = torch.exp2(s)
+                l, o = l + p.sum(1, keepdim=True), o + (p.half().double() if form == "f16" else p) @ v[at, h].double()
+            out[g:g + n, h] = o / l
+    return out
+
+
+@pytest.mark.parametrize("window", [0, 300])
+@pytest.mark.parametrize("growth", [-0.03, 0.01, 0.03])
+@pytest.mark.parametrize("form", ["two", "f16"])
+def test_moving_maximum_bound_sees_wrong_rescaling(form, growth, window):
+    """The bound that chunk attention is held to on scores that rise along the walk: the walk itself is inside it, and outside, by a factor
+    of twenty at least, is one whose sum or output keeps its size when the reference moves, or is scaled by a wrong factor.  (With scores
+    that fall the reference stays where the first positions put it.)"""
+    q, k, v = moving_maximum_inputs(growth, 200)
+    ref, bound = attention_and_bound(q, k, v, MOVING_CTX, window, form)
+    off = lambda mistake: float(((_walk(q, k, v, MOVING_CTX, window, form, mistake) - ref).abs() / bound).max())
+    assert off("") <= 1
+    if growth > 0:
+        for mistake in ("sum as it was", "output as it was", "half the exponent", "one too little"):
+            assert off(mistake) > 20, mistake
