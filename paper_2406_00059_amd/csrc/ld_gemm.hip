@@ -696,7 +696,8 @@ bool gemm_takes_floats(int T, int N, int K, bool norm) {
 
 void launch_gemm_floats(const uint16_t *W, const float *x, const float *g, float eps, int T, int N, int K, int epi, float *y, void *scratch,
                         hipStream_t s) {
-    // the scratch of the image form: its images' place holds the sums of squares (at most K / 128 a row)
+    // the scratch of the image form: its images' place (K floats a row) holds the sums of squares, one of each wave of each slab: with
+    // at most one slab per 128 columns at most K / 16 a row
     float *ss = (float *)scratch, *partial = (float *)((char *)scratch + gemm_split_bytes(T, K));
     const int ks = skinny_split(T, K);
     launch_skinny(W, nullptr, nullptr, T, N * (epi == GEMM_SWIGLU ? 2 : 1), K, partial, s, SK_FLOATS, {x, g, ss});

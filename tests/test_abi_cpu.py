@@ -421,6 +421,22 @@ def test_two_term_products_keep_their_slabs():
         assert ld.ldk_linear_scratch_bytes(T, N, K, epi) == 4 * T * K + slabs * T * N * (2 if epi == ld.LDK_SWIGLU else 1) * 4
 
 
+def test_small_batch_slabs():
+    """K slabs of the small-batch product: a slab has 128 columns at least, so that the sums of squares of its eight waves (8 floats a row and
+    slab, which lie where the images of K floats a row would) take K / 16 floats a row at most; as many as the rows' registers ask for (2048
+    columns each, 1024 beyond 32 rows) or, up to a third more, a power of two; no fewer for more rows; each with its partial sums in the
+    scratch that the product asks for."""
+    slabs = C.CFUNCTYPE(C.c_int, C.c_int, C.c_int)(("_ZN2ld12skinny_slabsEii", ld.lib()))
+    for K in list(range(128, 16384, 128)) + [19456, 24704, 32896, 65664, (1 << 20) + 128]:
+        last = 0
+        for T in (2, 16, 17, 32, 33, 48, 49, 64):
+            n, fewest = slabs(T, K), -(-K // (2048 if T <= 32 else 1024))
+            assert last <= n <= K // 128 and 8 * n <= K // 16
+            assert n == fewest or fewest < n <= fewest * 4 / 3 and n & (n - 1) == 0
+            assert ld.ldk_linear_scratch_bytes(T, 9, K, ld.LDK_ADD) == -(-4 * T * K // 256) * 256 + n * T * 9 * 4
+            last = n
+
+
 def test_operands_of_4_gib_keep_both_terms():
     """Rows enter as one fp16 term only while the matrix (gate and up rows together) and the rows' image stay below 4 GiB."""
     for N, K, epi in ((1 << 19, 4096, ld.LDK_STORE), (1 << 18, 4096, ld.LDK_SWIGLU), (1 << 17, 16384, ld.LDK_ADD)):
