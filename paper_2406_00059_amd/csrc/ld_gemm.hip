@@ -489,16 +489,18 @@ BigPlan plan_big(int T, int N, int K, int epi, bool f16 = false, bool *ignored =
 // 128 -> 91 us; at 2 / 16 / 32 rows 68 -> 64, 76 -> 68, 84 -> 74 us.
 constexpr int SKINNY_MAX_ROWS = 64;
 int skinny_tiles(int T) { return T <= 16 ? 1 : T <= 32 ? 2 : T <= 48 ? 3 : 4; }      // 16-row tiles of X
-// K slabs: what the eight waves of a workgroup hold of X in registers; as many as a power of two where that is up to a third more:
-// the CUs divide into as many groups for each slab, an XCD reads the X of fewer slabs, and a workgroup starts with less of it.  us at 2 / 20
-// rows, fewest slabs -> power of two: 4096 x 11008 (6, 8) 21.7 / 27.4 -> 20.9 / 26.8, 4096 x 14336 (7, 8) 26.1 / 31.2 -> 25.1 /
-// 30.2, 13824 x 5120 SwiGLU (3, 4) 54.7 / 62.6 -> 51.8 / 59.6; 1024 x 2816 at 64 rows (3, 4) 13.4 -> 12.1.  More is slower: 15360 x 5120
-// at 64 rows (5, 8) 52.1 -> 59.4, 12288 x 4096 at 20 (2, 4) 27.9 -> 30.8.
+// K slabs: what the eight waves of a workgroup hold of X in registers; as many as a power of two where that is up to a third more, or
+// beyond eight slabs up to a seventh (14 and 15 to 16): the CUs divide into as many groups for each slab, an XCD reads the X of fewer
+// slabs, and a workgroup starts with less of it.  us at 2 / 20 rows, fewest slabs -> power of two: 4096 x 11008 (6, 8) 21.7 / 27.4 ->
+// 20.9 / 26.8, 4096 x 14336 (7, 8) 26.1 / 31.2 -> 25.1 / 30.2, 13824 x 5120 SwiGLU (3, 4) 54.7 / 62.6 -> 51.8 / 59.6; 1024 x 2816 at
+// 64 rows (3, 4) 13.4 -> 12.1; 14 to 16 1.5 % faster in the mean of 19 sizes.  More is slower: 15360 x 5120 at 64 rows (5, 8) 52.1 ->
+// 59.4, 12288 x 4096 at 20 (2, 4) 27.9 -> 30.8; and so is the same share of many: 6144 x 12288 at 64 rows (12, 16) 49.2 -> 51.8,
+// 64 x 24576 at 33 (24, 32) 17.3 -> 19.3, 8192 x 28672 at 48 (28, 32) 110.7 -> 114.3.
 int skinny_split(int T, int K) {
     const int fewest = (K + sk_slab(skinny_tiles(T)) - 1) / sk_slab(skinny_tiles(T));
     int p = 1;
     while (p < fewest) p *= 2;
-    return 3 * p <= 4 * fewest ? p : fewest;
+    return p <= 8 ? (3 * p <= 4 * fewest ? p : fewest) : p == 16 && 7 * p <= 8 * fewest ? p : fewest;
 }
 
 int split_factor(int T, int N, int K, int epi, bool f16 = false) {
