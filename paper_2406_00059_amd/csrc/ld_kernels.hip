@@ -35,7 +35,9 @@ __global__ void k_embed(const WT *__restrict__ E, const int32_t *__restrict__ to
 // ---------------------------------------------------------------- RMSNorm (stand-alone, with row gather)
 
 // One workgroup per row.  REGS > 0: rows of a multiple of four floats, 16-byte aligned, at most 1024 * REGS long, are read once, all
-// loads in flight together: a step has one of these in its chain of kernels (32 rows of 4096 9.5 -> 4.8 us).
+// loads in flight together: a step has one of these in its chain of kernels (32 rows of 4096 5.7 -> 2.8 us on the GPU).  REGS as the rows
+// need: what a short one does not use costs registers, of which many rows' workgroups then wait for each other (8000 rows of 64, of
+// 260 and of 1024: 5.2, 8.5, 16.3 us read twice, 8.9, 9.8, 12.5 with eight, 5.2, 6.6, 11.7 with one).
 template <int REGS>
 __global__ __launch_bounds__(256) void k_rmsnorm(const float *__restrict__ x, const float *__restrict__ g,
                                                  const int32_t *__restrict__ row_idx, int d, float eps,
@@ -609,10 +611,12 @@ ld_status ldk_rmsnorm(const float *x, const float *g, const int32_t *row_idx, in
                       float *out, void *stream) {
     if (!x || !g || !out || R < 0 || d <= 0) return ld::fail(LD_E_INVAL, "ldk_rmsnorm: bad argument");
     if (R == 0) return LD_OK;
-    if (d % 4 == 0 && d <= 8 * 1024 && (((uintptr_t)x | (uintptr_t)g | (uintptr_t)out) & 15) == 0)
-        LD_LAUNCH(k_rmsnorm<8>, dim3(R), dim3(256), 0, (hipStream_t)stream, x, g, row_idx, d, eps, out);
-    else
-        LD_LAUNCH(k_rmsnorm<0>, dim3(R), dim3(256), 0, (hipStream_t)stream, x, g, row_idx, d, eps, out);
+    const bool quads = d % 4 == 0 && (((uintptr_t)x | (uintptr_t)g | (uintptr_t)out) & 15) == 0;
+    const dim3 grid(R), block(256);
+    if (quads && d <= 1024) LD_LAUNCH(k_rmsnorm<1>, grid, block, 0, (hipStream_t)stream, x, g, row_idx, d, eps, out);
+    else if (quads && d <= 4 * 1024) LD_LAUNCH(k_rmsnorm<4>, grid, block, 0, (hipStream_t)stream, x, g, row_idx, d, eps, out);
+    else if (quads && d <= 8 * 1024) LD_LAUNCH(k_rmsnorm<8>, grid, block, 0, (hipStream_t)stream, x, g, row_idx, d, eps, out);
+    else LD_LAUNCH(k_rmsnorm<0>, grid, block, 0, (hipStream_t)stream, x, g, row_idx, d, eps, out);
     return launched("k_rmsnorm");
 }
 

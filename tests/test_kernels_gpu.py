@@ -76,7 +76,7 @@ def test_linear_full_7b_shapes_on_sampled_outputs():
 
 
 @pytest.mark.parametrize("off", [0, 1], ids=["aligned", "4-bytes-off"])
-@pytest.mark.parametrize("d", [1, 3, 4, 255, 260, 1024, 1028, 4096, 8188, 8192, 8196])
+@pytest.mark.parametrize("d", [1, 3, 4, 255, 260, 1024, 1028, 4096, 4100, 8188, 8192, 8196])
 def test_rmsnorm_lengths_and_alignments(d, off):
     """Rows that are read four floats at a time and kept (a multiple of four, up to 8192, 16-byte aligned) and all others, gathered and in
     order, against float64.  Bound: at most 33 + 6 + 3 roundings of 2^-24 in the sum of squares, which count half, and a few behind it."""
