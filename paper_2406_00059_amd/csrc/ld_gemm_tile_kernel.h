@@ -183,10 +183,12 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16_t *__restrict__
 #pragma unroll
     for (int r = 0; r < NR; r++) read(f0, 0, 0, r);
     auto none = [](int) {};
-    // One loop for all chunks.  Past the last one the copies fetch it again, into the stage that nobody reads any more
-    int i = 0, st = 0;
+    // One loop for all chunks.  Past the last one the copies fetch it again, into the stage that nobody reads any more.  Two stages are told
+    // apart by the parity of i, and their second barrier has no reads to wait for: with the general form's few scalar instructions more a chunk
+    // the fp16 products of 14336 x 4096 pairs took 106.6 instead of 105.1 us at 512 rows, 213.6 instead of 209.3 at 1024 (96 products 0.2 %)
+    int i = 0, at = 0;
     do {
-        const int next = st + 1 == S ? 0 : st + 1, last = st == 0 ? S - 1 : st - 1;
+        const int st = S == 2 ? i & 1 : at, next = S == 2 ? st ^ 1 : st + 1 == S ? 0 : st + 1, last = S == 2 ? st ^ 1 : st == 0 ? S - 1 : st - 1;
         asm volatile("s_nop 1" ::: "memory");      // before the first pass: the cleared accumulators
         if constexpr (S == 2) {
             mix(f0, f0, 0, NM - NL * BT, NR, [&](int r) { read(f1, st, 1, r); }, P - PRE, [&](int c) { copy(i + 1, last, PRE + c); });
@@ -194,15 +196,16 @@ __global__ __launch_bounds__(256, 1) void k_gemm_tile(const bf16_t *__restrict__
             asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
             __builtin_amdgcn_sched_barrier(0);
             mix(f0, f1, NM - NL * BT, (NL + NA - NF) * BT, 0, none, PRE, [&](int c) { copy(i + 2, st, c); });
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(YOUNGER) : "memory");
         } else {      // the stage of the chunk before is free: every wave has passed the barrier below with its operands in registers
             constexpr int M1 = NM, M2 = (NA - NF) * BT, P1 = (P * M1 + M1 + M2 - 1) / (M1 + M2);
             mix(f0, f0, 0, M1, NR, [&](int r) { read(f1, st, 1, r); }, P1, [&](int c) { copy(i + S - 1, last, c); });
             mix(f1, f1, 0, M2, 0, none, P - P1, [&](int c) { copy(i + S - 1, last, P1 + c); });
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(YOUNGER) : "memory");
         }
         // the own copies of chunk i + 1 have landed (only those of later chunks are younger), and after the barrier everyone's
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(YOUNGER) : "memory");
         mix(f1, f1, NM - NF * BT, NF * BT, NR, [&](int r) { read(f0, next, 0, r); }, 0, none);
-        st = next;
+        at = next;
     } while (++i < n);
     // the copies have left, and the last results are in their registers before anything reads them (the compiler does not
     // see into the assembly)
