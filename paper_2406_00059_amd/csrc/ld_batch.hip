@@ -136,10 +136,10 @@ size_t batch_layer_xs_bytes(int T, int d, int H, int hd, int ffn) {
 }
 size_t batch_layer_partial_bytes(int T, int d, int H, int Hkv, int hd, int ffn) {
     const size_t nqkv = (size_t)(H + 2 * Hkv) * hd, nq = (size_t)H * hd;
-    size_t m = skinny_slabs(T, d) * nqkv;                       // q/k/v: K = d
-    m = std::max(m, (size_t)skinny_slabs(T, (int)nq) * d);      // wo: K = nq
-    m = std::max(m, (size_t)skinny_slabs(T, d) * 2 * ffn);      // gate/up: K = d
-    m = std::max(m, (size_t)skinny_slabs(T, ffn) * d);          // down: K = ffn
+    size_t m = skinny_slabs(T, nqkv, d) * nqkv;                                     // q/k/v: K = d
+    m = std::max(m, (size_t)skinny_slabs(T, d, (int)nq) * d);                       // wo: K = nq
+    m = std::max(m, (size_t)skinny_slabs(T, (int64_t)2 * ffn, d) * 2 * ffn);        // gate/up: K = d
+    m = std::max(m, (size_t)skinny_slabs(T, d, ffn) * d);                           // down: K = ffn
     return m * T * sizeof(float);
 }
 size_t batch_layer_ss_bytes(int T, int d) { return (size_t)2 * T * (d / RB) * sizeof(float); }
@@ -153,7 +153,7 @@ void launch_batch_qkv(const BatchLayerArgs &a, hipStream_t s) {
     const int nqkv = (a.H + 2 * a.Hkv) * a.hd, nssp = a.d / RB;
     launch_gemm_skinny(a.wqkv, a.xs, a.xs + (size_t)a.T * a.d, a.T, nqkv, a.d, a.partial, s, true);
     const int n = a.T * (a.H + 2 * a.Hkv) * 64;
-    LD_LAUNCH(k_red_rope, dim3((n + 255) / 256), dim3(256), 0, s, a.partial, skinny_slabs(a.T, a.d), a.ss_part, nssp,
+    LD_LAUNCH(k_red_rope, dim3((n + 255) / 256), dim3(256), 0, s, a.partial, skinny_slabs(a.T, nqkv, a.d), a.ss_part, nssp,
                        a.eps, a.d, a.T, a.H, a.Hkv, (const float2 *)a.cos_sin, a.pos, a.seq_slot, a.table, a.table_stride,
                        a.q, a.q_stride, a.pool);
 }
@@ -162,7 +162,7 @@ void launch_batch_wo(const BatchLayerArgs &a, hipStream_t s) {
     // output projection; residual; operand + statistics of the FFN norm
     const int nq = a.H * a.hd, nssp = a.d / RB;
     launch_gemm_skinny(a.wo, a.xs, a.xs + (size_t)a.T * nq, a.T, a.d, nq, a.partial, s, true);
-    LD_LAUNCH(k_red_add_split, dim3(nssp, a.T), dim3(256), 0, s, a.partial, skinny_slabs(a.T, nq), a.x, a.ffn_norm, a.T,
+    LD_LAUNCH(k_red_add_split, dim3(nssp, a.T), dim3(256), 0, s, a.partial, skinny_slabs(a.T, a.d, nq), a.x, a.ffn_norm, a.T,
                        a.d, a.xs, a.ss_part + (size_t)a.T * nssp);
 }
 
@@ -171,7 +171,7 @@ void launch_batch_gate_up(const BatchLayerArgs &a, hipStream_t s) {
     const int nssp = a.d / RB;
     launch_gemm_skinny(a.wgate_up, a.xs, a.xs + (size_t)a.T * a.d, a.T, 2 * a.ffn, a.d, a.partial, s, true);
     const int64_t n = (int64_t)a.T * (a.ffn / 4);
-    LD_LAUNCH(k_red_swiglu_split, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.partial, skinny_slabs(a.T, a.d),
+    LD_LAUNCH(k_red_swiglu_split, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.partial, skinny_slabs(a.T, (int64_t)2 * a.ffn, a.d),
                        a.ss_part + (size_t)a.T * nssp, nssp, a.eps, a.d, a.T, a.ffn, a.xs);
 }
 
@@ -179,7 +179,7 @@ void launch_batch_down(const BatchLayerArgs &a, hipStream_t s) {
     // down; residual; operand + statistics of the next layer's attention norm
     const int nssp = a.d / RB;
     launch_gemm_skinny(a.wdown, a.xs, a.xs + (size_t)a.T * a.ffn, a.T, a.d, a.ffn, a.partial, s, true);
-    LD_LAUNCH(k_red_add_split, dim3(nssp, a.T), dim3(256), 0, s, a.partial, skinny_slabs(a.T, a.ffn), a.x, a.next_norm,
+    LD_LAUNCH(k_red_add_split, dim3(nssp, a.T), dim3(256), 0, s, a.partial, skinny_slabs(a.T, a.d, a.ffn), a.x, a.next_norm,
                        a.T, a.d, a.xs, a.ss_part);
 }
 

@@ -61,9 +61,9 @@ bool gemm_takes_floats(int T, int N, int K, bool norm);
 void launch_gemm_floats(const uint16_t *W, const float *x, const float *g, float eps, int T, int N, int K, int epi, float *y, void *scratch,
                         hipStream_t s);
 
-// Skinny product alone (T <= 64 rows, K a multiple of 128): partial[z][t][row] for the skinny_slabs(T, K) K slabs z;
+// Skinny product alone (T <= 64 rows, K a multiple of 128): partial[z][t][row] for the skinny_slabs(T, n_rows, K) K slabs z;
 // the caller adds the slabs in order.  octets: the layout of the images, see launch_norm_split.
-int skinny_slabs(int T, int K);
+int skinny_slabs(int T, int64_t n_rows, int K);
 void launch_gemm_skinny(const uint16_t *W, const uint16_t *xhi, const uint16_t *xlo, int T, int n_rows, int K,
                         float *partial, hipStream_t s, bool octets);
 

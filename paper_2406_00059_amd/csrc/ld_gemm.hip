@@ -489,22 +489,29 @@ BigPlan plan_big(int T, int N, int K, int epi, bool f16 = false, bool *ignored =
 // 128 -> 91 us; at 2 / 16 / 32 rows 68 -> 64, 76 -> 68, 84 -> 74 us.
 constexpr int SKINNY_MAX_ROWS = 64;
 int skinny_tiles(int T) { return T <= 16 ? 1 : T <= 32 ? 2 : T <= 48 ? 3 : 4; }      // 16-row tiles of X
-// K slabs: what the eight waves of a workgroup hold of X in registers; as many as a power of two where that is up to a third more, or
-// beyond eight slabs up to a seventh (14 and 15 to 16): the CUs divide into as many groups for each slab, an XCD reads the X of fewer
-// slabs, and a workgroup starts with less of it.  us at 2 / 20 rows, fewest slabs -> power of two: 4096 x 11008 (6, 8) 21.7 / 27.4 ->
-// 20.9 / 26.8, 4096 x 14336 (7, 8) 26.1 / 31.2 -> 25.1 / 30.2, 13824 x 5120 SwiGLU (3, 4) 54.7 / 62.6 -> 51.8 / 59.6; 1024 x 2816 at
-// 64 rows (3, 4) 13.4 -> 12.1; 14 to 16 1.5 % faster in the mean of 19 sizes.  More is slower: 15360 x 5120 at 64 rows (5, 8) 52.1 ->
-// 59.4, 12288 x 4096 at 20 (2, 4) 27.9 -> 30.8; and so is the same share of many: 6144 x 12288 at 64 rows (12, 16) 49.2 -> 51.8,
-// 64 x 24576 at 33 (24, 32) 17.3 -> 19.3, 8192 x 28672 at 48 (28, 32) 110.7 -> 114.3.
-int skinny_split(int T, int K) {
-    const int fewest = (K + sk_slab(skinny_tiles(T)) - 1) / sk_slab(skinny_tiles(T));
-    int p = 1;
-    while (p < fewest) p *= 2;
-    return p <= 8 ? (3 * p <= 4 * fewest ? p : fewest) : p == 16 && 7 * p <= 8 * fewest ? p : fewest;
+// K slabs: what the eight waves of a workgroup hold of X in registers, or a power of two of up to eight where that is up to a third more and
+// saves work: the CUs divide into even groups, and a workgroup starts with less of X.  What it saves shows in the steps of the workgroup
+// that has most of them, its 16-row tiles times its slab's columns; what it costs is the partial sums of the slabs added.  Hence: 3 to 4
+// and 6 to 8 where the steps go down to 0.85 or less (0.925 for 3 to 4 of up to 32 rows and tiles enough, eight, to level out what is
+// particular to the last one), 7 to 8 to 0.975.  us, fewest slabs -> power of two, by that ratio: 3 to 4, 0.71: 2048 x 5120 at 24 rows 15.1 ->
+// 13.3; 0.86: 8192 x 6144 at 24 29.5 -> 27.0; 0.89: 15360 x 5120 at 20 39.4 -> 36.3, but 5120 x 5120 at 2 (five tiles) 13.1 -> 13.9; 0.95:
+// 13824 x 3072 at 48 30.3 -> 31.8; 1.06: 13824 x 2304 at 48 27.8 -> 31.0.  6 to 8, 0.84: 4096 x 11008 at 8 20.9 -> 20.5; 0.88: 6144 x 11008
+// at 24 34.0 -> 35.7.  7 to 8, 0.88: 3072 x 13824 at 16 23.3 -> 20.5; 0.98: 13824 x 13824 at 24 75.8 -> 77.2.  Over the 519 sizes that the
+// limits were drawn from 3.6 % off, 1.5 % more at worst (with the power of two wherever it is up to a third more 3.6 % off, 11 % more); over
+// 260 others 2.4 % off, 3 % more at worst.  Others are slower: 15360 x 5120 at 64 rows (5, 8) 52.1 -> 59.4, 12288 x 4096 at 20 (2, 4)
+// 27.9 -> 30.8, 13824 x 13824 at 64 (14, 16) 99.9 -> 102.7.
+int skinny_split(int T, int64_t n_rows, int K) {
+    const int slab = sk_slab(skinny_tiles(T)), fewest = (K + slab - 1) / slab, p = fewest == 3 ? 4 : fewest == 6 || fewest == 7 ? 8 : fewest;
+    if (p == fewest) return fewest;
+    const int64_t units = (n_rows + 3) / 4;      // of the row groups, see the kernel
+    auto tiles = [&](int ks) { const int64_t groups = std::min<int64_t>(256 / ks, (n_rows + 15) / 16); return ((units + groups - 1) / groups + 3) / 4; };
+    auto steps = [&](int ks) { return tiles(ks) * ((K / 128 + ks - 1) / ks); };
+    const int limit = fewest == 7 ? 975 : fewest == 3 && T <= 32 && tiles(p) >= 8 ? 925 : 850;      // thousandths
+    return 1000 * steps(p) <= limit * steps(fewest) ? p : fewest;
 }
 
 int split_factor(int T, int N, int K, int epi, bool f16 = false) {
-    if (T <= SKINNY_MAX_ROWS) return skinny_split(T, K);
+    if (T <= SKINNY_MAX_ROWS) return skinny_split(T, (int64_t)N * (epi == ld::GEMM_SWIGLU ? 2 : 1), K);
     return plan_big(T, N, K, epi, f16).ks;
 }
 
@@ -624,11 +631,11 @@ void launch_norm_split(const float *x, const float *g, float eps, int T, int K, 
 #undef LD_NS
 }
 
-int skinny_slabs(int T, int K) { return skinny_split(T, K); }
+int skinny_slabs(int T, int64_t n_rows, int K) { return skinny_split(T, n_rows, K); }
 
 static void launch_skinny(const uint16_t *W, const uint16_t *xhi, const uint16_t *xlo, int T, int n_rows, int K, float *partial, hipStream_t s,
                           SkinnySource src, const FloatRows &fr) {
-    const int ks = skinny_split(T, K);
+    const int ks = skinny_split(T, n_rows, K);
     static const int n_cu = cu_count();
     // one workgroup per CU; fewer where a row group would get less than a tile
     const int n_grp = std::max(1, std::min(n_cu / ks, (n_rows + 15) / 16));
@@ -701,8 +708,8 @@ void launch_gemm_floats(const uint16_t *W, const float *x, const float *g, float
     // the scratch of the image form: its images' place (K floats a row) holds the sums of squares, one of each wave of each slab: with
     // at most one slab per 128 columns at most K / 16 a row
     float *ss = (float *)scratch, *partial = (float *)((char *)scratch + gemm_split_bytes(T, K));
-    const int ks = skinny_split(T, K);
-    launch_skinny(W, nullptr, nullptr, T, N * (epi == GEMM_SWIGLU ? 2 : 1), K, partial, s, SK_FLOATS, {x, g, ss});
+    const int n_rows = N * (epi == GEMM_SWIGLU ? 2 : 1), ks = skinny_split(T, n_rows, K);
+    launch_skinny(W, nullptr, nullptr, T, n_rows, K, partial, s, SK_FLOATS, {x, g, ss});
     launch_reduce(partial, T, N, ks, epi, y, {}, {g ? ss : nullptr, ks * SK_WAVES, K, eps}, s);
 }
 

@@ -421,20 +421,35 @@ def test_two_term_products_keep_their_slabs():
         assert ld.ldk_linear_scratch_bytes(T, N, K, epi) == 4 * T * K + slabs * T * N * (2 if epi == ld.LDK_SWIGLU else 1) * 4
 
 
+def _small_batch_slabs():
+    return C.CFUNCTYPE(C.c_int, C.c_int, C.c_int64, C.c_int)(("_ZN2ld12skinny_slabsEili", ld.lib()))
+
+
 def test_small_batch_slabs():
     """K slabs of the small-batch product: a slab has 128 columns at least, so that the sums of squares of its eight waves (8 floats a row and
     slab, which lie where the images of K floats a row would) take K / 16 floats a row at most; as many as the rows' registers ask for (2048
-    columns each, 1024 beyond 32 rows) or, up to a third more, 4 or 8, from 14 on 16; no fewer for more rows; each with its partial sums in
+    columns each, 1024 beyond 32 rows) or, for 3, 6 and 7, the next power of two; no fewer for more rows; each with its partial sums in
     the scratch that the product asks for."""
-    slabs = C.CFUNCTYPE(C.c_int, C.c_int, C.c_int)(("_ZN2ld12skinny_slabsEii", ld.lib()))
-    for K in list(range(128, 16384, 128)) + [19456, 24704, 32896, 65664, (1 << 20) + 128]:
-        last = 0
-        for T in (2, 16, 17, 32, 33, 48, 49, 64):
-            n, fewest = slabs(T, K), -(-K // (2048 if T <= 32 else 1024))
-            assert last <= n <= K // 128 and 8 * n <= K // 16
-            assert n == {3: 4, 6: 8, 7: 8, 14: 16, 15: 16}.get(fewest, fewest)
-            assert ld.ldk_linear_scratch_bytes(T, 9, K, ld.LDK_ADD) == -(-4 * T * K // 256) * 256 + n * T * 9 * 4
-            last = n
+    slabs = _small_batch_slabs()
+    for N in (1, 9, 300, 4100, 5120, 13824, 1 << 20):
+        for K in list(range(128, 16384, 128)) + [19456, 24704, 32896, 65664, (1 << 20) + 128]:
+            last = 0
+            for T in (2, 16, 17, 32, 33, 48, 49, 64):
+                n, fewest = slabs(T, N, K), -(-K // (2048 if T <= 32 else 1024))
+                assert last <= n <= K // 128 and 8 * n <= K // 16
+                assert n in (fewest, {3: 4, 6: 8, 7: 8}.get(fewest))
+                assert ld.ldk_linear_scratch_bytes(T, N, K, ld.LDK_ADD) == -(-4 * T * K // 256) * 256 + n * T * N * 4
+                last = n
+
+
+@pytest.mark.parametrize("N,K,slabs", [(4096, 11008, (8, 11)), (15360, 5120, (4, 5)), (2 * 13824, 5120, (4, 5)), (4096, 14336, (8, 14)), (5120, 5120, (3, 5)), (6144, 11008, (6, 11)),
+                                       (5120, 4224, (3, 5)), (13824, 4224, (3, 5)), (8192, 3072, (2, 3)), (13824, 2304, (2, 3)), (3072, 2304, (2, 4)), (13824, 13824, (7, 14)), (512, 14336, (8, 14))])
+def test_small_batch_slabs_only_where_they_pay(N, K, slabs):
+    """More slabs than the rows need are slower where they leave the workgroups as much to do (by up to 11 %): both sides of the rule, at up to 32
+    rows and beyond."""
+    of = _small_batch_slabs()
+    assert (of(20, N, K), of(48, N, K)) == slabs
+    assert of(20, (1 << 32) + 2, K) == -(-K // 2048)      # pairs of 2^31 rows: no overflow
 
 
 def test_operands_of_4_gib_keep_both_terms():

@@ -663,11 +663,12 @@ def test_linear_every_tile(form, rows, cols, K, ks, monkeypatch, capfd):
     assert "LD_GEMM_BIG" not in capfd.readouterr().err
 
 
-@pytest.mark.parametrize("N,K", [(301, 4224), (640, 5120), (96, 6144), (130, 10368), (513, 11008), (37, 14336), (77, 2816), (77, 11392), (12, 24704)])
+@pytest.mark.parametrize("N,K", [(301, 4224), (640, 5120), (96, 6144), (130, 10368), (513, 11008), (37, 14336), (77, 2816), (77, 11392), (12, 24704),
+                                 (5120, 4224), (8200, 5120), (8200, 2304)])
 @pytest.mark.parametrize("T", [2, 20, 33, 64])
 def test_linear_small_batch_slabs(T, N, K):
     """The small-batch product where its K slabs (2048 columns at most, 1024 beyond 32 rows) go up to a power of two (3 to 4, 6 and 7 to
-    8, 14 to 16) and where they stay (2, 5, 11, 12, 13, 25): uneven slabs, fewer columns than workgroups.  Against float64: two terms are off by
+    8) and where they stay (2, 3, 5, 11, 12, 13, 14, 25): uneven slabs, fewer columns than workgroups.  Against float64: two terms are off by
     at most 2^-16 of a product, the float32 sums by 2^-20 of the sum of magnitudes."""
     W = _mat(71, K, N, K, "bf16").to(DEV); x = gen.normal(71, 2, (T, K), device=DEV); g = 1 + 0.1 * gen.normal(71, 3, (K,), device=DEV)
     y = torch.full((T, N), float("nan"), device=DEV)
