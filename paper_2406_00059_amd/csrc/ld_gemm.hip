@@ -433,14 +433,16 @@ int cu_count() {
 // estimated time.  Workgroups run in rounds of one per CU (256 of them); a round takes the tile's time per 64-wide chunk of K
 // times its chunks, a last round that leaves CUs idle a little less (the others draw less power and run faster: 0.27 of the idle
 // share in both forms); split-K adds the write and the ordered re-read of its partial sums.  The constants are fitted to the tiles
-// and splits of the 7B, grouped-KV and 13B layer shapes.  One term, 512 - 2048 rows: the choice is 0.8 % slower than the best pair in
-// the mean, 9 % at worst.  Two terms, 80 - 480 rows: 1.4 % and 9 %, with the times of tiles of two stages, though three take 5 - 13 %
-// off the smaller ones.  Fitted anew the choice was 0.8 % slower than the best, but K was cut in fewer slabs at 942 of 4917 sizes (65 .. 511
-// rows of these shapes) and in more at 222, and longer sums are less exact: rms error over rms of the result against float64 in one, two, four and eight slabs
-// 2.520, 2.487, 2.470, 2.463e-6 (256 x 12288 x 4096), 3.636, 3.579, 3.554, 3.543e-6 (152 x 11008 x 4096 SwiGLU).  Nor is the plain
-// product's time all there is: with the rotation that adds the slabs (ldk_qkv_rope) 256 x 12288 x 4096 takes 58.6 us in the two slabs
-// of this model, 64.1 in the one of that, 256 x 15360 x 5120 80.2 and 85.3, while plain products gained up to 8 % (480 x 4096 x 11008 in
-// five and four slabs 93.4 -> 87.3).  With six and four tiles instead of ten and eight the best pair would be some 3 % slower in the mean.
+// and splits of the 7B, grouped-KV and 13B layer shapes.  One term, 512 - 3072 rows, on the image (widened): the choice is 0.6 % (1.1 %)
+// slower than the best pair in the mean, 11 % (19 %) at worst, and nowhere slower than that of the times of two stages (0.9 % and 12 %, 2.0 %
+// and 29 %).  192 x 192 at the 0.92 us that larger products show took 4096 x 4096 at 2048 rows from 128 x 256: 77.3 -> 81.6 us; at 1536 68.2
+// -> 73.4. Two terms, 80 - 480 rows: 1.4 % and 9 %, with the times of tiles of two stages, though three take 5 - 13 % off the smaller ones.
+// Fitted anew the choice was 0.8 % slower than the best, but K was cut in fewer slabs at 942 of 4917 sizes (65 .. 511 rows of these shapes)
+// and in more at 222, and longer sums are less exact: rms error over rms of the result against float64 in one, two, four and eight slabs
+// 2.520, 2.487, 2.470, 2.463e-6 (256 x 12288 x 4096), 3.636, 3.579, 3.554, 3.543e-6 (152 x 11008 x 4096 SwiGLU).  Nor is the plain product's
+// time all there is: with the rotation that adds the slabs (ldk_qkv_rope) 256 x 12288 x 4096 takes 58.6 us in the two slabs of this model,
+// 64.1 in the one of that, 256 x 15360 x 5120 80.2 and 85.3, while plain products gained up to 8 % (480 x 4096 x 11008 in five and four slabs
+// 93.4 -> 87.3).  With six and four tiles instead of ten and eight the best pair would be some 3 % slower in the mean.
 struct BigPlan { int bm, bn, n_ttiles, n_nblocks, ks; double est_us; };
 struct Tile { int bm, bn; bool swiglu; double chunk_us; };
 #define LD_TILE_ROW(AT_, BT_, US_) {32 * AT_, 32 * BT_, BT_ % 2 == 0, US_},

@@ -20,7 +20,7 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;   // native 16-byte 
 // latter, in launches of up to one workgroup a CU, 11 % faster).  (Odd column units have no SwiGLU form.)
 #define LD_TILES_TWO(X) \
     X(3, 4, 0.73) X(3, 6, 1.03) X(3, 8, 1.23) X(4, 4, 0.96) X(4, 6, 1.21) X(4, 8, 1.50) X(5, 6, 1.42) X(5, 8, 1.77) X(6, 6, 1.61) X(6, 8, 2.04)
-#define LD_TILES_F16(X) X(4, 6, 0.73) X(4, 8, 0.91) X(6, 6, 0.92) X(6, 8, 1.16) X(7, 8, 1.30) X(8, 5, 0.99) X(8, 6, 1.15) X(8, 8, 1.42)
+#define LD_TILES_F16(X) X(4, 6, 0.74) X(4, 8, 0.91) X(6, 6, 0.95) X(6, 8, 1.16) X(7, 8, 1.30) X(8, 5, 0.99) X(8, 6, 1.15) X(8, 8, 1.42)
 
 constexpr int TILE_MAX_K = 1 << 23;      // the lane offsets of the copies reach over 256 rows in 32 bits
 // Stages of K chunks in LDS: three where they fit, else two.  The smallest tiles, two workgroups of which fit a CU with two stages
