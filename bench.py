@@ -30,7 +30,7 @@ HBM_PEAK = 8.0e12          # bytes/s, MI355X HBM3E
 TRAFFIC_BYTES = 180_820_000
 TRAFFIC_KERNEL_MD5 = "3cc22b0a375e"
 ATTN_TRAFFIC_RATIO = 1.008
-ATTN_TRAFFIC_MD5 = "44080b043743"
+ATTN_TRAFFIC_MD5 = "7e8868eb2d83"
 ROUND_TOKENS = 256         # tokens emitted per round (1 by the preceding prefill + 255 decode steps)
 CHUNK = 256
 

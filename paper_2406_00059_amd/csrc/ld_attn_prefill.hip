@@ -20,9 +20,10 @@
 // exponentials against the last one have grown large.  The operands of the next MFMAs are read from LDS ahead of them, in an order that
 // is pinned: left alone, the compiler reads each right before its use and waits for it.  Queries come in whole rows and shares go out in
 // whole lanes: 16 bytes of each of 64 rows an instruction cost some 6000 and 2000 cycles a workgroup.
-// 12 tiles x 32 heads at contexts 2.2k .. 6.4k: 322 -> 214 -> 181 -> 171 us with these (one step at a time, two, no passes over
-// the queries, the last three); one 256-row chunk behind 1500, in two terms, 33 -> 31; one of 2048 behind 2048 151 -> 135; over 135 sets
-// of tiles (4 .. 40 heads, 1 .. 24 tiles, walks of 4 .. 250 steps) the last three give 12 % in the mean, 9 % in two terms.
+// 12 tiles x 32 heads (four segments of 257 rows) at contexts 2.2k .. 6.4k: 322 -> 214 -> 181 -> 171 us with these (one step at a time,
+// two, no passes over the queries, the last three), 167 with the path for few rows; one 256-row chunk behind 1500, in two terms, 33 -> 31; one
+// of 2048 behind 2048 151 -> 135; over 135 sets of tiles (4 .. 40 heads, 1 .. 24 tiles, walks of 4 .. 250 steps) the last three give 12 % in
+// the mean, 9 % in two terms.
 // Forming the next unit's scores between this one's exponentials, and staging between its value products, was level
 // (209 and 79 us: its second set of scores fills the registers).  Two halves of a workgroup that take the matrix cores in turn, on
 // pairs of tiles, reach 153 us in the first example but lose by up to three times where the work is small.
